@@ -1,9 +1,9 @@
-// Comparison of two partitions with at most 65,535 labels each (Section II-A): the
+// Comparison of two partitions (Section II-A): the
 // contingency table n_ij = |c_i ∩ c'_j| built by label bands, and its reduction to the
 // per-row quantities the final pass combines into VI, NMI, F, NVD, RI, ARI and JI
 // (Eqs. (1)-(7)).
 //
-// The ground-truth labels are cut into bands: runs of consecutive label ids holding about
+// At most 65,535 labels on each side: the ground-truth labels are cut into bands: runs of consecutive label ids holding about
 // T nodes (and at most CB_ROWS labels); the band sizes and their places follow from the
 // label sizes alone.  A pass over chunks of nodes writes every node as one 32-bit word
 // (label - first label of its band) << 16 | detected label into its band's range: a
@@ -29,11 +29,19 @@ constexpr int CC_THREADS = 512;       // k_cmp_cells workgroup
 constexpr int CC_LOG2_SLOTS = 13;
 constexpr u32 CC_SLOTS = 1u << CC_LOG2_SLOTS;  // LDS hash slots (key and count words)
 constexpr u32 CC_PROBE = 64;          // a key that finds no place within this many slots splits its class
-constexpr int CC_SUB = 8;             // counters per row for the row's dominant detected label
 constexpr u32 CC_JUMP = 2;            // a class that overflows is split into up to 2^CC_JUMP classes
 constexpr int CC_STACK = 64;          // pending residue classes (depth first)
 constexpr int CC_BATCH = 8;           // band words each thread loads at once
 constexpr u32 CMP_BAD_B = 0xFFFFu;    // detected label outside [0, Lb)
+// Shapes of k_cmp_cells' words (row << BBITS | detected label) and tables: rows per band and
+// counters per row for the row's dominant detected label.  Both keep two workgroups per CU
+// (at most 80 KB of LDS each).
+struct CellsNarrow {  // 16-bit label spaces
+  static constexpr int ROWS = CB_ROWS, SUB = 8, BBITS = 16;
+};
+struct CellsWide {  // label spaces beyond 16 bits: small communities, so more and shorter rows
+  static constexpr int ROWS = 256, SUB = 2, BBITS = 24;
+};
 
 // A flag in LDS that other threads of the workgroup may set: read as a workgroup-scope
 // atomic, which stays an LDS read (a volatile access through a generic pointer would
@@ -387,12 +395,252 @@ __global__ __launch_bounds__(CP_THREADS) void k_cmp_part(int n, const int32_t* _
   }
 }
 
+// ---- label spaces beyond 16 bits ------------------------------------------------
+// Here communities are small and numerous, and a histogram of the labels no longer fits LDS
+// (global atomics, one per node, take 130 us per side at 3M nodes: they top out near 23 G/s
+// on this chip).  The bands are therefore fixed runs of 2^ra ground-truth labels ("bins"),
+// whose sizes fit an LDS histogram; the nodes are written bin by bin as in the band path
+// (words (label - first label of the bin) << 24 | detected label), and the label sizes are
+// counted in LDS afterwards, one workgroup per bin.  The detected labels' sizes come from a
+// second partition of the nodes into bins of 2^rb detected labels (16-bit words).  3M nodes
+// with 135,540 labels on both sides: 3.86 ms per call on the segment path (its group pass,
+// one workgroup per community of 22 nodes, took 3.2 ms), 0.225 ms here.
+constexpr int BH_THREADS = 1024;
+constexpr int BH_NPT = 8;             // nodes per thread and round in k_bin_hist
+constexpr int BIN_A_MAX = 4096;       // ground-truth bins (block_excl_scan4, 16-bit bin numbers)
+constexpr int BIN_B_MAX = 512;        // detected bins
+constexpr int BIN_RB_MIN = 10, BIN_RB_MAX = 14;  // log2 of the detected labels per bin (LDS counters)
+
+// Adds one to s[bin] for every lane with `on`; returns the counter's value before this lane's
+// own addition.  When at least four lanes share the first lane's bin (nodes stored by
+// community), those lanes add through one of them: atomics on one LDS address are performed
+// one after another.
+__device__ __forceinline__ u32 bin_add(u32* s, u32 bin, bool on) {
+  const u64 act = __ballot(on);
+  if (act == 0) return 0;
+  const int leader = __ffsll((long long)act) - 1;
+  const u32 lead_bin = __shfl(bin, leader, 64);
+  const u64 grp = __ballot(on && bin == lead_bin);
+  const int lane = threadIdx.x & 63;
+  u32 old = 0;
+  if (__popcll(grp) >= 4) {
+    if (lane == leader) old = atomicAdd(&s[lead_bin], (u32)__popcll(grp));
+    old = __shfl(old, leader, 64) + (u32)__popcll(grp & ((1ull << lane) - 1ull));
+    if (on && bin != lead_bin) old = atomicAdd(&s[bin], 1u);
+  } else if (on) {
+    old = atomicAdd(&s[bin], 1u);
+  }
+  return old;
+}
+
+// Nodes per bin: row blockIdx.x of H (nbA ground-truth bins, then nbB detected bins; nbB = 0
+// leaves the detected labels out).  Labels out of range are flagged and not counted.
+__global__ __launch_bounds__(BH_THREADS) void k_bin_hist(int n, const int32_t* __restrict__ la, int La, int ra, int nbA,
+                                                         const int32_t* __restrict__ lb, int Lb, int rb, int nbB,
+                                                         u32* __restrict__ H, Ctl* __restrict__ ctl) {
+  extern __shared__ u32 s_bin[];
+  __shared__ u32 s_bad;
+  const int nb = nbA + nbB;
+  for (int i = threadIdx.x; i < nb; i += BH_THREADS) s_bin[i] = 0;
+  if (threadIdx.x == 0) s_bad = 0;
+  __syncthreads();
+  u32 bad = 0;
+  for (long long base = (long long)blockIdx.x * BH_THREADS * BH_NPT; base < n; base += (long long)gridDim.x * BH_THREADS * BH_NPT) {
+    int a[BH_NPT], b[BH_NPT];
+#pragma unroll
+    for (int k = 0; k < BH_NPT; ++k) {
+      const long long u = base + threadIdx.x + (long long)k * BH_THREADS;
+      a[k] = u < n ? la[u] : -1;
+      b[k] = u < n && nbB ? lb[u] : -1;
+      if (u < n) bad |= ((u32)a[k] >= (u32)La) | (nbB && (u32)b[k] >= (u32)Lb);
+    }
+#pragma unroll
+    for (int k = 0; k < BH_NPT; ++k) {
+      (void)bin_add(s_bin, (u32)a[k] >> ra, (u32)a[k] < (u32)La);
+      if (nbB) (void)bin_add(s_bin + nbA, (u32)b[k] >> rb, (u32)b[k] < (u32)Lb);
+    }
+  }
+  if (bad) s_bad = 1;
+  __syncthreads();
+  for (int i = threadIdx.x; i < nb; i += BH_THREADS) H[(size_t)blockIdx.x * nb + i] = s_bin[i];
+  if (threadIdx.x == 0 && s_bad) atomicOr(&ctl->flags, F_LABEL);
+}
+
+// Bin sizes SZ (nbA + nbB) from the W rows of H; the last workgroup to finish (*done counts
+// them; it must be zero at launch) turns them into places: SA[0..nbA] for the ground-truth
+// bins, SB[0..nbB] for the detected ones, CUR (nbA + nbB) the claim cursors, BORD the
+// non-empty ground-truth bins by decreasing floor(log2 size), ctl->K their number.
+__global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_bin_totals(int W, int nbA, int nbB, const u32* __restrict__ H,
+                                                                      u32* __restrict__ SZ, u32* __restrict__ SA,
+                                                                      u32* __restrict__ SB, u32* __restrict__ CUR,
+                                                                      u32* __restrict__ BORD, u32* __restrict__ done,
+                                                                      Ctl* __restrict__ ctl) {
+  static_assert(CS_LABELS * CS_GROUPS == CP_THREADS, "block_excl_scan4");
+  __shared__ u32 s_n[CS_GROUPS][CS_LABELS];
+  __shared__ u32 s_v[BIN_A_MAX];
+  __shared__ u32 s_w[CP_THREADS / 64];
+  __shared__ u32 s_bcnt[33], s_boff[33];
+  __shared__ u32 s_last;
+  const int nb = nbA + nbB, tid = threadIdx.x;
+  const int lane = tid % CS_LABELS, grp = tid / CS_LABELS;
+  const int c = (int)blockIdx.x * CS_LABELS + lane;
+  const int per = (W + CS_GROUPS - 1) / CS_GROUPS;
+  const int w0 = min(W, grp * per), w1 = min(W, w0 + per);
+  u32 sn = 0;
+  if (c < nb)
+    for (int w = w0; w < w1; ++w) sn += H[(size_t)w * nb + c];
+  s_n[grp][lane] = sn;
+  __syncthreads();
+  if (c < nb && grp == 0) {
+    u32 t = 0;
+    for (int i = 0; i < CS_GROUPS; ++i) t += s_n[i][lane];
+    SZ[c] = t;
+  }
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) s_last = atomicAdd(done, 1u) == gridDim.x - 1 ? 1u : 0u;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  if (tid < 33) s_bcnt[tid] = 0;
+  for (int i = tid; i < nbA; i += CP_THREADS) s_v[i] = SZ[i];
+  __syncthreads();
+  for (int i = tid; i < nbA; i += CP_THREADS) {
+    const u32 sz = s_v[i];
+    if (sz) atomicAdd(&s_bcnt[size_bucket(sz)], 1u);
+  }
+  u32 total = block_excl_scan4(s_v, nbA, s_w);
+  for (int i = tid; i < nbA; i += CP_THREADS) {
+    SA[i] = s_v[i];
+    CUR[i] = s_v[i];
+  }
+  if (tid == 0) {
+    SA[nbA] = total;
+    u32 off = 0;
+    for (int b = 32; b >= 0; --b) {
+      s_boff[b] = off;
+      off += s_bcnt[b];
+    }
+    ctl->K = off;
+  }
+  __syncthreads();
+  for (int i = tid; i < nbA; i += CP_THREADS) {
+    const u32 sz = (i + 1 < nbA ? s_v[i + 1] : total) - s_v[i];
+    if (sz) BORD[atomicAdd(&s_boff[size_bucket(sz)], 1u)] = (u32)i;
+  }
+  __syncthreads();
+  for (int i = tid; i < nbB; i += CP_THREADS) s_v[i] = SZ[nbA + i];
+  __syncthreads();
+  total = block_excl_scan4(s_v, nbB, s_w);
+  for (int i = tid; i < nbB; i += CP_THREADS) {
+    SB[i] = s_v[i];
+    CUR[nbA + i] = s_v[i];
+  }
+  if (tid == 0) SB[nbB] = total;
+}
+
+// Writes the nodes of one chunk (NPT * 1024 nodes) into their bins, as k_cmp_part does:
+// workgroups [0, chunks) write ground-truth words to E, the others (nbB > 0) the detected
+// labels' places in their bins to EB.  Dynamic LDS: two words per bin.
+template <int NPT>
+__global__ __launch_bounds__(CP_THREADS) void k_bin_part(int n, int chunks, const int32_t* __restrict__ la, int La, int ra,
+                                                         int nbA, const int32_t* __restrict__ lb, int Lb, int rb, int nbB,
+                                                         u32* __restrict__ CUR, u32* __restrict__ E,
+                                                         uint16_t* __restrict__ EB) {
+  constexpr int CHUNK = CP_THREADS * NPT;
+  __shared__ u32 s_buf[CHUNK];
+  __shared__ uint16_t s_bid[CHUNK];
+  __shared__ u32 s_w[CP_THREADS / 64];
+  extern __shared__ u32 s_dyn[];
+  const bool side_a = (int)blockIdx.x < chunks;
+  const int nb = side_a ? nbA : nbB;
+  u32* s_run = s_dyn;      // first global place of the chunk's run in each bin
+  u32* s_rc = s_dyn + nb;  // the chunk's nodes per bin, then their first place in s_buf
+  const int tid = threadIdx.x;
+  for (int i = tid; i < nb; i += CP_THREADS) s_rc[i] = 0;
+  __syncthreads();
+  const long long u0 = (long long)(side_a ? blockIdx.x : blockIdx.x - chunks) * CHUNK;
+  u32 word[NPT], bin[NPT], rank[NPT];  // bin 0xFFFFFFFF: not written
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    const long long u = u0 + tid + (long long)k * CP_THREADS;
+    int a = -1, b = -1;
+    if (u < n) {
+      if (side_a) a = la[u];
+      b = lb[u];
+    }
+    if (side_a) {
+      bin[k] = (u32)a < (u32)La ? (u32)a >> ra : 0xFFFFFFFFu;
+      word[k] = (((u32)a & ((1u << ra) - 1u)) << CellsWide::BBITS) | ((u32)b < (u32)Lb ? (u32)b : (1u << CellsWide::BBITS) - 1u);
+    } else {
+      bin[k] = (u32)b < (u32)Lb ? (u32)b >> rb : 0xFFFFFFFFu;
+      word[k] = (u32)b & ((1u << rb) - 1u);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) rank[k] = bin_add(s_rc, bin[k], bin[k] != 0xFFFFFFFFu);
+  __syncthreads();
+  for (int i = tid; i < nb; i += CP_THREADS) {
+    const u32 c = s_rc[i];
+    s_run[i] = c ? atomicAdd(&CUR[(side_a ? 0 : nbA) + i], c) : 0u;  // one claim per bin the chunk has nodes of
+  }
+  const u32 total = block_excl_scan4(s_rc, nb, s_w);
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    if (bin[k] != 0xFFFFFFFFu) {
+      const u32 p = s_rc[bin[k]] + rank[k];
+      s_buf[p] = word[k];
+      s_bid[p] = (uint16_t)bin[k];
+    }
+  }
+  __syncthreads();
+  for (u32 p = tid; p < total; p += CP_THREADS) {
+    const u32 i = s_bid[p];
+    const u32 to = s_run[i] + (p - s_rc[i]);
+    if (side_a) E[to] = s_buf[p];
+    else EB[to] = (uint16_t)s_buf[p];
+  }
+}
+
+// Label sizes from the partitioned words, one workgroup per bin: blocks [0, nbA) write A,
+// the others B.  Dynamic LDS: one counter per label of a bin.
+constexpr int BC_THREADS = 512;
+constexpr int BC_UNROLL = 4;
+__global__ __launch_bounds__(BC_THREADS) void k_bin_count(int La, int ra, int nbA, int Lb, int rb, const u32* __restrict__ SA,
+                                                          const u32* __restrict__ SB, const u32* __restrict__ E,
+                                                          const uint16_t* __restrict__ EB, u32* __restrict__ A,
+                                                          u32* __restrict__ B) {
+  extern __shared__ u32 s_cnt[];
+  const bool side_a = (int)blockIdx.x < nbA;
+  const int bin = side_a ? (int)blockIdx.x : (int)blockIdx.x - nbA;
+  const int r = side_a ? ra : rb;
+  const int L = side_a ? La : Lb;
+  const u32 s0 = side_a ? SA[bin] : SB[bin], s1 = side_a ? SA[bin + 1] : SB[bin + 1];
+  for (int i = threadIdx.x; i < (1 << r); i += BC_THREADS) s_cnt[i] = 0;
+  __syncthreads();
+  for (u32 e0 = s0; e0 < s1; e0 += BC_THREADS * BC_UNROLL) {  // uniform trip count
+    u32 v[BC_UNROLL];
+#pragma unroll
+    for (int k = 0; k < BC_UNROLL; ++k) {
+      const u32 e = e0 + threadIdx.x + (u32)k * BC_THREADS;
+      v[k] = e < s1 ? (side_a ? E[e] >> CellsWide::BBITS : (u32)EB[e]) : 0xFFFFFFFFu;
+    }
+#pragma unroll
+    for (int k = 0; k < BC_UNROLL; ++k) (void)bin_add(s_cnt, v[k], v[k] != 0xFFFFFFFFu);
+  }
+  __syncthreads();
+  const int c0 = bin << r, c1 = min(L, c0 + (1 << r));
+  u32* N = side_a ? A : B;
+  for (int c = c0 + threadIdx.x; c < c1; c += BC_THREADS) N[c] = s_cnt[c - c0];
+}
+
 // One band at a time per workgroup (bands by decreasing size from the work queues).
 // A = |c_i|, B = |c'_j|; outputs per ground-truth label i: RA11 = Σ_j C(n_ij, 2),
 // RMAX = max_j n_ij, RF = max_j 2 n_ij / (|c_i| + |c'_j|) (Eq. (3)), RXL = Σ_j fix96 of
 // (n_ij / N) log n_ij; per detected label: COLMAX = max_i n_ij (cells of one node are left
 // to the final pass, which counts 1 for every non-empty column); non-zero cells are
 // summed per work queue; optional export of (i, j, n_ij).
+template <class S>
 __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restrict__ E, const u32* __restrict__ SBS,
                                                           const u32* __restrict__ SZB, const u32* __restrict__ SBA,
                                                           const u32* __restrict__ BORD, Ctl* __restrict__ ctl,
@@ -401,13 +649,16 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
                                                           u32* __restrict__ RMAX, double* __restrict__ RF,
                                                           u64* __restrict__ RXL, int32_t* __restrict__ eci,
                                                           int32_t* __restrict__ ecj, int64_t* __restrict__ ecnt,
-                                                          long long ecap, u32* __restrict__ wq) {
+                                                          long long ecap, u32* __restrict__ wq, int La, int ra) {
+  constexpr int CC_SUB = S::SUB;
+  constexpr u32 BMASK = (1u << S::BBITS) - 1u;
+  constexpr u32 BAD_B = BMASK;
   __shared__ u32 s_key[CC_SLOTS];
   __shared__ u32 s_cnt[CC_SLOTS];
-  __shared__ u32 s_hot[CB_ROWS];            // per row: the first detected label the class met in it
-  __shared__ u32 s_hcnt[CB_ROWS * CC_SUB];  // its count, spread over CC_SUB counters
-  __shared__ u64 r_a11[CB_ROWS], r_f[CB_ROWS], r_xlo[CB_ROWS], r_xhi[CB_ROWS];
-  __shared__ u32 r_max[CB_ROWS], r_ai[CB_ROWS];
+  __shared__ u32 s_hot[S::ROWS];            // per row: the first detected label the class met in it
+  __shared__ u32 s_hcnt[S::ROWS * CC_SUB];  // its count, spread over CC_SUB counters
+  __shared__ u64 r_a11[S::ROWS], r_f[S::ROWS], r_xlo[S::ROWS], r_xhi[S::ROWS];
+  __shared__ u32 r_max[S::ROWS], r_ai[S::ROWS];
   __shared__ u32 s_item, s_over, s_sp, s_new, s_seen, s_est;
   __shared__ u32 s_stack[CC_STACK];  // pending classes: residue << 5 | log2 of the modulus
   const int tid = threadIdx.x;
@@ -420,8 +671,10 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
     const u32 item = s_item;
     if (item == 0xFFFFFFFFu) break;
     const u32 band = BORD[item];
-    const u32 base = SBS[band], len = SZB[band], a0 = SBA[band];
-    const u32 rows = SBA[band + 1] - a0;
+    const u32 base = SBS[band], len = SZB[band];
+    // a band's labels: the listed ones, or (SBA null) the 2^ra labels of its number
+    const u32 a0 = SBA ? SBA[band] : band << ra;
+    const u32 rows = (SBA ? SBA[band + 1] : min((u32)La, a0 + (1u << ra))) - a0;
     for (u32 r = tid; r < rows; r += CC_THREADS) {
       r_a11[r] = 0;
       r_f[r] = 0;
@@ -455,8 +708,8 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
       // counting threads would all meet it unset at once
       if ((u32)tid < len) {
         const u32 w = E[base + (u32)tid];
-        const u32 b = w & 0xFFFFu;
-        if (b != CMP_BAD_B && (b & mask) == res && s_hot[w >> 16] == EMPTY) atomicCAS(&s_hot[w >> 16], EMPTY, b);
+        const u32 b = w & BMASK;
+        if (b != BAD_B && (b & mask) == res && s_hot[w >> S::BBITS] == EMPTY) atomicCAS(&s_hot[w >> S::BBITS], EMPTY, b);
       }
       __syncthreads();
       // a cell (row, detected label) is counted in the hash table, except the row's first
@@ -490,15 +743,15 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
 #pragma unroll
         for (int k = 0; k < CC_BATCH; ++k) {
           const u32 e = e0 + (u32)tid + (u32)k * CC_THREADS;
-          wv[k] = e < len ? E[base + e] : 0xFFFFFFFFu;  // b = CMP_BAD_B: skipped
+          wv[k] = e < len ? E[base + e] : 0xFFFFFFFFu;  // b = BAD_B: skipped
         }
 #pragma unroll
         for (int k = 0; k < CC_BATCH; ++k) {
           const u32 w = wv[k];
-          const u32 b = w & 0xFFFFu;
-          if (b == CMP_BAD_B || (b & mask) != res) continue;
+          const u32 b = w & BMASK;
+          if (b == BAD_B || (b & mask) != res) continue;
           ++nseen;
-          const u32 r = w >> 16;
+          const u32 r = w >> S::BBITS;
           u32 hb = s_hot[r];
           if (hb == EMPTY) {
             const u32 old = atomicCAS(&s_hot[r], EMPTY, b);
@@ -537,7 +790,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
           u32 c = 0;
 #pragma unroll
           for (int k = 0; k < CC_SUB; ++k) c += s_hcnt[r * CC_SUB + k];
-          insert((r << 16) | hb, c);  // a new key: no entry with this label of the row went to the table
+          insert((r << S::BBITS) | hb, c);  // a new key: no entry with this label of the row went to the table
         }
       }
       __syncthreads();
@@ -548,10 +801,10 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
           // split to about 5,000 expected cells per class (the first batch's estimate, else
           // the class's node count), at least one and at most CC_JUMP levels further
           u32 want = lg + 1u;
-          while (want < lg + CC_JUMP && want < 16u && (s_est >> (want - lg)) > CC_SLOTS * 5u / 8u) ++want;
+          while (want < lg + CC_JUMP && want < (u32)S::BBITS && (s_est >> (want - lg)) > CC_SLOTS * 5u / 8u) ++want;
           const u32 nchild = 1u << (want - lg);
-          if (want > 16u || s_sp - 1u + nchild > (u32)CC_STACK) {
-            atomicOr(&ctl->flags, F_STACK);  // never expected: 2^16 classes hold one label each
+          if (want > (u32)S::BBITS || s_sp - 1u + nchild > (u32)CC_STACK) {
+            atomicOr(&ctl->flags, F_STACK);  // never expected: 2^BBITS classes hold one label each
             s_sp = 0;
           } else {
             for (u32 c = 0; c < nchild; ++c) s_stack[s_sp - 1u + c] = ((res | (c << lg)) << 5) | want;
@@ -569,13 +822,13 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
 #pragma unroll
       for (int k = 0; k < VPT; ++k) vkey[k] = s_key[i0 + (u32)tid + (u32)k * CC_THREADS];
 #pragma unroll
-      for (int k = 0; k < VPT; ++k) vbj[k] = vkey[k] != EMPTY ? B[vkey[k] & 0xFFFFu] : 0u;
+      for (int k = 0; k < VPT; ++k) vbj[k] = vkey[k] != EMPTY ? B[vkey[k] & BMASK] : 0u;
 #pragma unroll
       for (int k = 0; k < VPT; ++k) {
         const u32 key = vkey[k];
         if (key == EMPTY) continue;
         const u32 x = s_cnt[i0 + (u32)tid + (u32)k * CC_THREADS];
-        const u32 r = key >> 16, j = key & 0xFFFFu;
+        const u32 r = key >> S::BBITS, j = key & BMASK;
         const u32 bj = vbj[k];
         // row maxima: a plain read first, since most cells do not raise them
         if (x > r_max[r]) atomicMax(&r_max[r], x);

@@ -325,6 +325,11 @@ struct CmpLayout {
   u32 T;                      // band path: nodes per band aimed at
   size_t ctl, wq, A, B, start, order, COLMAX, RA11, RMAX, RF, RXL, SZ, loc, HN, HB, CB, parts, res, total;
   size_t HA, sbk, SBA, SZB, SBS, CUR, BORD, E;
+  // wide path (a label space beyond 16 bits): log2 labels per bin, bins, histogram grid,
+  // nodes per thread and chunks of the partition
+  bool wide, binsB;  // binsB: the detected labels' sizes come from bins too
+  int ra, rb, nbA, nbB, Wh, npt, chunks;
+  size_t SBB, EB;
 };
 
 // Band path sizes: bands of about T nodes, at least 8,192 (a band's cells then mostly fit
@@ -334,6 +339,26 @@ struct CmpLayout {
 constexpr int64_t CB_MIN_T = 8192;
 constexpr int64_t CB_MAX_BANDS_BY_SIZE = 1024;
 constexpr int64_t CP_MAX_CHUNKS = 1024;
+
+// Wide path (k_bin_*): ground-truth bins of about CB_MIN_T nodes and at most 256 labels, at
+// most BIN_A_MAX of them; detected bins of at least 1,024 and at most 16,384 labels, at most
+// BIN_B_MAX of them.  Communities of more than CB_MIN_T nodes on average stay on the segment
+// path, whose workgroups take one community each either way (a bin of one such community
+// would be no better), as do label spaces too wide for the bins or for 24-bit words.
+bool wide_bins(int64_t n, int64_t La, int64_t Lb, CmpLayout* s) {
+  if ((La <= 65535 && Lb <= 65535) || n / La > CB_MIN_T || Lb >= (1 << CellsWide::BBITS) - 1) return false;
+  int ra = 0;
+  while (ra < 8 && (n << (ra + 1)) / La <= CB_MIN_T) ++ra;
+  while (ra < 8 && (La + (1 << ra) - 1) >> ra > BIN_A_MAX) ++ra;
+  int rb = BIN_RB_MIN;
+  while (rb < BIN_RB_MAX && (Lb + (1 << rb) - 1) >> rb > BIN_B_MAX) ++rb;
+  s->ra = ra;
+  s->rb = rb;
+  s->binsB = Lb > 65535;
+  s->nbA = (int)((La + (1 << ra) - 1) >> ra);
+  s->nbB = s->binsB ? (int)((Lb + (1 << rb) - 1) >> rb) : 0;
+  return s->nbA <= BIN_A_MAX && s->nbB <= BIN_B_MAX;
+}
 
 CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
   CmpLayout s{};
@@ -369,6 +394,37 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
     s.CUR = c.take(4 * (size_t)s.nbmax);
     s.BORD = c.take(4 * (size_t)s.nbmax);
     s.E = c.take(4 * (size_t)n);
+    s.parts = c.take(sizeof(CmpPart) * (s.Ga + s.Gb));
+    s.res = c.take(sizeof(CmpResultDev));
+    s.total = c.off;
+    return s;
+  }
+  s.wide = wide_bins(n, La, Lb, &s);
+  if (s.wide) {
+    const int nb = s.nbA + s.nbB;
+    s.Wh = (int)std::min<int64_t>(256, (n + BH_THREADS * BH_NPT - 1) / (BH_THREADS * BH_NPT));
+    // chunks of 10 nodes per thread (two workgroups per CU) until 20 (one per CU) fill two
+    // waves of workgroups: longer runs per bin and half the claims
+    s.npt = n >= (int64_t)512 * 20 * CP_THREADS ? 20 : 10;
+    s.chunks = (int)((n + (int64_t)s.npt * CP_THREADS - 1) / ((int64_t)s.npt * CP_THREADS));
+    s.ctl = c.take(sizeof(Ctl));
+    s.wq = c.take(WQ_BYTES);
+    s.A = c.take(4 * La);
+    s.B = c.take(4 * Lb);
+    s.COLMAX = c.take(4 * Lb);
+    s.RA11 = c.take(8 * La);
+    s.RMAX = c.take(4 * La);
+    s.RF = c.take(8 * La);
+    s.RXL = c.take(16 * La);
+    s.HA = c.take(4 * (size_t)s.Wh * nb);
+    s.HB = s.binsB ? 0 : c.take(4 * (size_t)s.Wb * Lb);
+    s.SZB = c.take(4 * (size_t)nb);
+    s.SBS = c.take(4 * ((size_t)s.nbA + 1));
+    s.SBB = c.take(4 * ((size_t)s.nbB + 1));
+    s.CUR = c.take(4 * (size_t)nb);
+    s.BORD = c.take(4 * (size_t)s.nbA);
+    s.E = c.take(4 * (size_t)n);
+    s.EB = s.binsB ? c.take(2 * (size_t)n) : 0;
     s.parts = c.take(sizeof(CmpPart) * (s.Ga + s.Gb));
     s.res = c.take(sizeof(CmpResultDev));
     s.total = c.off;
@@ -848,11 +904,77 @@ void label_totals(int n, const int32_t* labels, int L, int W, u32* H, u32* N, Ct
   k_colscan<false, false><<<colscan_grid(L), CS_LABELS * CS_GROUPS, 0, s>>>(W, L, H, H, N, nullptr);
 }
 
+template <class S>
 unsigned cells_grid(cq_context* ctx) {
-  static int nb = 0;
-  if (nb == 0 && (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_cmp_cells, CC_THREADS, 0) != hipSuccess || nb < 1))
-    nb = 1;
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_cmp_cells<S>, CC_THREADS, 0) != hipSuccess || nb < 1) nb = 1;
   return (unsigned)(ctx->num_cus * nb);
+}
+
+// A label space beyond 16 bits: contingency cells counted per bin of ground-truth labels.
+void compare_launch_wide(cq_context* ctx, int32_t n, const int32_t* la, int32_t La, const int32_t* lb, int32_t Lb, void* ws,
+                         const CmpLayout& lay, CmpResultDev* d_out, const cq_cell_table* cells, bool timed) {
+  hipStream_t s = ctx->stream;
+  Ctl* ctl = at<Ctl>(ws, lay.ctl);
+  u32* A = at<u32>(ws, lay.A);
+  u32* B = at<u32>(ws, lay.B);
+  u32* COLMAX = at<u32>(ws, lay.COLMAX);
+  u32* wq = at<u32>(ws, lay.wq);
+  u32* SZ = at<u32>(ws, lay.SZB);
+  u32* SA = at<u32>(ws, lay.SBS);
+  u32* SB = at<u32>(ws, lay.SBB);
+  u32* CUR = at<u32>(ws, lay.CUR);
+  u32* BORD = at<u32>(ws, lay.BORD);
+  u32* E = at<u32>(ws, lay.E);
+  uint16_t* EB = lay.binsB ? at<uint16_t>(ws, lay.EB) : nullptr;
+  u64* RA11 = at<u64>(ws, lay.RA11);
+  u32* RMAX = at<u32>(ws, lay.RMAX);
+  double* RF = at<double>(ws, lay.RF);
+  u64* RXL = at<u64>(ws, lay.RXL);
+  const int nb = lay.nbA + lay.nbB;
+  {
+    StageMark mk(ctx, ST_SETUP, timed);
+    const int words = (int)(sizeof(Ctl) / 4) + (int)WQ_WORDS + Lb;
+    k_cmp_clear<<<grid_for(words, 256, 1024), 256, 0, s>>>(reinterpret_cast<u32*>(ctl), (int)(sizeof(Ctl) / 4), wq, COLMAX, Lb);
+  }
+  {
+    StageMark mk(ctx, ST_NODE, timed);
+    u32* H = at<u32>(ws, lay.HA);
+    k_bin_hist<<<lay.Wh, BH_THREADS, (size_t)nb * 4, s>>>(n, la, La, lay.ra, lay.nbA, lb, Lb, lay.rb, lay.nbB, H, ctl);
+    k_bin_totals<<<(nb + CS_LABELS - 1) / CS_LABELS, CS_LABELS * CS_GROUPS, 0, s>>>(lay.Wh, lay.nbA, lay.nbB, H, SZ, SA, SB,
+                                                                                 CUR, BORD, &ctl->done, ctl);
+  }
+  {
+    StageMark mk(ctx, ST_SCATTER, timed);
+    const unsigned grid = (unsigned)lay.chunks * (lay.binsB ? 2u : 1u);
+    const size_t shm = 8 * (size_t)std::max(lay.nbA, lay.nbB);
+    if (lay.npt == 20) {
+      (void)hipFuncSetAttribute((const void*)k_bin_part<20>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+      k_bin_part<20><<<grid, CP_THREADS, shm, s>>>(n, lay.chunks, la, La, lay.ra, lay.nbA, lb, Lb, lay.rb, lay.nbB, CUR, E, EB);
+    } else {
+      (void)hipFuncSetAttribute((const void*)k_bin_part<10>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+      k_bin_part<10><<<grid, CP_THREADS, shm, s>>>(n, lay.chunks, la, La, lay.ra, lay.nbA, lb, Lb, lay.rb, lay.nbB, CUR, E, EB);
+    }
+  }
+  {
+    StageMark mk(ctx, ST_HIST_B, timed);
+    if (!lay.binsB) label_totals(n, lb, Lb, lay.Wb, at<u32>(ws, lay.HB), B, ctl, s);
+    const size_t shm = (size_t)4 << (lay.binsB ? std::max(lay.ra, lay.rb) : lay.ra);
+    k_bin_count<<<nb, BC_THREADS, shm, s>>>(La, lay.ra, lay.nbA, Lb, lay.rb, SA, SB, E, EB, A, B);
+  }
+  const long long ecap = cells ? cells->capacity : 0;
+  {
+    StageMark mk(ctx, ST_GROUPS, timed);
+    k_cmp_cells<CellsWide><<<cells_grid<CellsWide>(ctx), CC_THREADS, 0, s>>>(
+        E, SA, SZ, nullptr, BORD, ctl, A, B, (double)n, COLMAX, RA11, RMAX, RF, RXL, cells ? cells->ci : nullptr,
+        cells ? cells->cj : nullptr, cells ? cells->count : nullptr, ecap, wq, La, lay.ra);
+  }
+  CmpPart* parts = at<CmpPart>(ws, lay.parts);
+  {
+    StageMark mk(ctx, ST_FINAL, timed);
+    k_cmp_final1<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, RA11, RMAX, RF, RXL, (double)n, parts);
+    k_cmp_final2<<<1, 64, 0, s>>>(lay.Ga + lay.Gb, parts, n, ecap, ctl, d_out, wq);
+  }
 }
 
 // Both label spaces fit 16 bits: contingency cells counted per band of ground-truth labels.
@@ -910,9 +1032,9 @@ void compare_launch_bands(cq_context* ctx, int32_t n, const int32_t* la, int32_t
   const long long ecap = cells ? cells->capacity : 0;
   {
     StageMark mk(ctx, ST_GROUPS, timed);
-    k_cmp_cells<<<cells_grid(ctx), CC_THREADS, 0, s>>>(E, SBS, SZB, SBA, BORD, ctl, A, B, (double)n, COLMAX, RA11, RMAX, RF,
-                                                       RXL, cells ? cells->ci : nullptr, cells ? cells->cj : nullptr,
-                                                       cells ? cells->count : nullptr, ecap, wq);
+    k_cmp_cells<CellsNarrow><<<cells_grid<CellsNarrow>(ctx), CC_THREADS, 0, s>>>(
+        E, SBS, SZB, SBA, BORD, ctl, A, B, (double)n, COLMAX, RA11, RMAX, RF, RXL, cells ? cells->ci : nullptr,
+        cells ? cells->cj : nullptr, cells ? cells->count : nullptr, ecap, wq, La, 0);
   }
   CmpPart* parts = at<CmpPart>(ws, lay.parts);
   {
@@ -937,6 +1059,8 @@ cq_status compare_enqueue(cq_context* ctx, int32_t n, const int32_t* la, int32_t
   if (reinterpret_cast<uintptr_t>(ws) % WS_ALIGN) return fail(ctx, CQ_E_INVALID_ARG, "workspace not 16-byte aligned");
   if (lay.bands)
     compare_launch_bands(ctx, n, la, La, lb, Lb, ws, lay, d_out, cells, timed);
+  else if (lay.wide)
+    compare_launch_wide(ctx, n, la, La, lb, Lb, ws, lay, d_out, cells, timed);
   else if (lay.small)
     compare_launch<uint16_t>(ctx, n, la, La, lb, Lb, ws, lay, d_out, cells, timed);
   else

@@ -198,3 +198,44 @@ def test_band_path_edges(cq, ctx):
     r, _ = cq.compare_partitions(ctx, a4, 50, b4, 60, cells_capacity=int(o.result["nnz"]) - 1,
                                  allow=(cq.CQ_E_CAPACITY,))
     assert r["status"] == cq.CQ_E_CAPACITY
+
+
+def _wide_case(kind, n, La, Lb):
+    rng = np.random.default_rng(n + La + Lb)
+    if kind == "close":  # a perturbed copy
+        a = rng.integers(0, La, n)
+        b = np.where(rng.random(n) < 0.2, rng.integers(0, Lb, n), a % Lb)
+    elif kind == "stored":  # nodes stored by community: whole waves carry one label
+        a = np.sort(rng.integers(0, La, n))
+        b = np.minimum(a // 2 * 2, Lb - 1)
+    elif kind == "giant":  # one community of half the nodes beside small ones, on both sides
+        a = np.where(rng.random(n) < 0.5, La - 1, rng.integers(0, La, n))
+        b = np.where(rng.random(n) < 0.5, 3, rng.integers(0, Lb, n))
+    else:  # random: nearly every cell holds one node, so bins split into classes
+        a, b = rng.integers(0, La, n), rng.integers(0, Lb, n)
+    a[0], b[0], a[-1], b[-1] = La - 1, Lb - 1, 0, 0
+    return a.astype(np.int32), b.astype(np.int32)
+
+
+# label spaces beyond 16 bits: bins of one label and of 256, the last bin partly filled, one
+# side narrow (its sizes counted directly), empty bins, bins that split into classes
+@pytest.mark.parametrize("kind,n,La,Lb", [
+    ("close", 100_003, 65_536, 65_536), ("close", 20_480, 70_001, 5), ("close", 20_481, 5, 70_001),
+    ("stored", 300_007, 65_537, 100_000), ("giant", 200_000, 80_000, 66_000), ("random", 4_000_000, 66_000, 70_000),
+    ("random", 50_000, 300_000, 65_535), ("close", 11_000_000, 520_000, 520_000), ("random", 2, 65_536, 1),
+    ("random", 300_000, 1_048_576, 1_000_000), ("random", 60_000, 5, 70_000),
+])
+def test_wide_label_spaces(cq, ctx, kind, n, La, Lb):
+    a, b = _wide_case(kind, n, La, Lb)
+    run_cmp(cq, ctx, a, La, b, Lb, f"wide {kind} n={n} La={La} Lb={Lb}", cells=n < 1_000_000)
+
+
+def test_wide_label_out_of_range(cq, ctx):
+    a, b = _wide_case("close", 30_000, 70_000, 70_000)
+    for side in (0, 1):
+        x = [a.copy(), b.copy()]
+        for bad in (-1, 70_000):
+            x[side][777] = bad
+            with pytest.raises(cq.CQError) as e:
+                cq.compare_partitions(ctx, torch.as_tensor(x[0]).cuda(), 70_000, torch.as_tensor(x[1]).cuda(), 70_000)
+            assert e.value.status == cq.CQ_E_LABEL_RANGE
