@@ -411,28 +411,6 @@ constexpr int BIN_A_MAX = 4096;       // ground-truth bins (block_excl_scan4, 16
 constexpr int BIN_B_MAX = 512;        // detected bins
 constexpr int BIN_RB_MIN = 10, BIN_RB_MAX = 14;  // log2 of the detected labels per bin (LDS counters)
 
-// Adds one to s[bin] for every lane with `on`; returns the counter's value before this lane's
-// own addition.  When at least four lanes share the first lane's bin (nodes stored by
-// community), those lanes add through one of them: atomics on one LDS address are performed
-// one after another.
-__device__ __forceinline__ u32 bin_add(u32* s, u32 bin, bool on) {
-  const u64 act = __ballot(on);
-  if (act == 0) return 0;
-  const int leader = __ffsll((long long)act) - 1;
-  const u32 lead_bin = __shfl(bin, leader, 64);
-  const u64 grp = __ballot(on && bin == lead_bin);
-  const int lane = threadIdx.x & 63;
-  u32 old = 0;
-  if (__popcll(grp) >= 4) {
-    if (lane == leader) old = atomicAdd(&s[lead_bin], (u32)__popcll(grp));
-    old = __shfl(old, leader, 64) + (u32)__popcll(grp & ((1ull << lane) - 1ull));
-    if (on && bin != lead_bin) old = atomicAdd(&s[bin], 1u);
-  } else if (on) {
-    old = atomicAdd(&s[bin], 1u);
-  }
-  return old;
-}
-
 // Nodes per bin: row blockIdx.x of H (nbA ground-truth bins, then nbB detected bins; nbB = 0
 // leaves the detected labels out).  Labels out of range are flagged and not counted.
 __global__ __launch_bounds__(BH_THREADS) void k_bin_hist(int n, const int32_t* __restrict__ la, int La, int ra, int nbA,
@@ -456,8 +434,8 @@ __global__ __launch_bounds__(BH_THREADS) void k_bin_hist(int n, const int32_t* _
     }
 #pragma unroll
     for (int k = 0; k < BH_NPT; ++k) {
-      (void)bin_add(s_bin, (u32)a[k] >> ra, (u32)a[k] < (u32)La);
-      if (nbB) (void)bin_add(s_bin + nbA, (u32)b[k] >> rb, (u32)b[k] < (u32)Lb);
+      (void)wave_count<1>(s_bin, (u32)a[k] >> ra, (u32)a[k] < (u32)La);
+      if (nbB) (void)wave_count<1>(s_bin + nbA, (u32)b[k] >> rb, (u32)b[k] < (u32)Lb);
     }
   }
   if (bad) s_bad = 1;
@@ -480,7 +458,6 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_bin_totals(int W, int
   __shared__ u32 s_v[BIN_A_MAX];
   __shared__ u32 s_w[CP_THREADS / 64];
   __shared__ u32 s_bcnt[33], s_boff[33];
-  __shared__ u32 s_last;
   const int nb = nbA + nbB, tid = threadIdx.x;
   const int lane = tid % CS_LABELS, grp = tid / CS_LABELS;
   const int c = (int)blockIdx.x * CS_LABELS + lane;
@@ -496,12 +473,7 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_bin_totals(int W, int
     for (int i = 0; i < CS_GROUPS; ++i) t += s_n[i][lane];
     SZ[c] = t;
   }
-  __threadfence();
-  __syncthreads();
-  if (tid == 0) s_last = atomicAdd(done, 1u) == gridDim.x - 1 ? 1u : 0u;
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
+  if (!last_workgroup(done, gridDim.x)) return;
   if (tid < 33) s_bcnt[tid] = 0;
   for (int i = tid; i < nbA; i += CP_THREADS) s_v[i] = SZ[i];
   __syncthreads();
@@ -578,7 +550,7 @@ __global__ __launch_bounds__(CP_THREADS) void k_bin_part(int n, int chunks, cons
     }
   }
 #pragma unroll
-  for (int k = 0; k < NPT; ++k) rank[k] = bin_add(s_rc, bin[k], bin[k] != 0xFFFFFFFFu);
+  for (int k = 0; k < NPT; ++k) rank[k] = wave_count<1>(s_rc, bin[k], bin[k] != 0xFFFFFFFFu);
   __syncthreads();
   for (int i = tid; i < nb; i += CP_THREADS) {
     const u32 c = s_rc[i];
@@ -626,7 +598,7 @@ __global__ __launch_bounds__(BC_THREADS) void k_bin_count(int La, int ra, int nb
       v[k] = e < s1 ? (side_a ? E[e] >> CellsWide::BBITS : (u32)EB[e]) : 0xFFFFFFFFu;
     }
 #pragma unroll
-    for (int k = 0; k < BC_UNROLL; ++k) (void)bin_add(s_cnt, v[k], v[k] != 0xFFFFFFFFu);
+    for (int k = 0; k < BC_UNROLL; ++k) (void)wave_count<1>(s_cnt, v[k], v[k] != 0xFFFFFFFFu);
   }
   __syncthreads();
   const int c0 = bin << r, c1 = min(L, c0 + (1 << r));

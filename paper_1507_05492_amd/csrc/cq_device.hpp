@@ -53,13 +53,24 @@ constexpr u32 WQ_WAVE = 2 * WQ_QUEUES * WQ_LINE;  // word offset of the wave pas
 
 // Next item for the calling workgroup (thread 0 only), or 0xFFFFFFFF when every queue is
 // empty.  q and left are thread 0's own state: start with q = blockIdx.x % 8, left = 8.
+// When its queue is empty, the other counters are read together (counters only grow, so a
+// queue seen empty stays empty) and the next queue that may hold work is tried: one round
+// trip instead of one atomic per queue at the end of every persistent kernel.
 __device__ __forceinline__ u32 wq_next(u32* __restrict__ wq, u32 K, u32& q, u32& left) {
   while (left) {
     const u32 i = atomicAdd(&wq[q * WQ_LINE], 1u);
     const u64 item = (u64)q + (u64)WQ_QUEUES * i;
     if (item < K) return (u32)item;
-    q = (q + 1u) % WQ_QUEUES;
-    --left;
+    u32 c[WQ_QUEUES];
+#pragma unroll
+    for (u32 k = 1; k < WQ_QUEUES; ++k)
+      c[k] = __hip_atomic_load(&wq[((q + k) % WQ_QUEUES) * WQ_LINE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    u32 step = left;  // no queue left
+#pragma unroll
+    for (u32 k = WQ_QUEUES - 1; k > 0; --k)
+      if (k < left && (u64)((q + k) % WQ_QUEUES) + (u64)WQ_QUEUES * c[k] < K) step = k;
+    q = (q + step) % WQ_QUEUES;
+    left -= step;
   }
   return 0xFFFFFFFFu;
 }
@@ -228,6 +239,51 @@ __device__ __forceinline__ u32 wave_incl_scan(u32 x) {
     if (lane >= o) x += y;
   }
   return x;
+}
+
+// Adds one to the LDS counter s[bin] for every lane with `on`; returns the counter's value
+// before this lane's own addition.  Atomics on one LDS address are performed one after
+// another, so up to ROUNDS times the lanes that share the first pending lane's bin (nodes
+// stored by community), when there are at least four of them, add through one lane.  The
+// calling wave must be converged.
+template <int ROUNDS>
+__device__ __forceinline__ u32 wave_count(u32* s, u32 bin, bool on) {
+  const u32 lane = threadIdx.x & 63u;
+  u32 old = 0;
+  for (int i = 0; i < ROUNDS; ++i) {
+    const u64 act = __ballot(on);
+    if (act == 0) break;
+    const int leader = __ffsll((long long)act) - 1;
+    const u32 lead_bin = __shfl(bin, leader, 64);
+    const u64 grp = __ballot(on && bin == lead_bin);
+    if (__popcll(grp) < 4) break;  // mixed bins: plain atomics below
+    u32 b = 0;
+    if (lane == (u32)leader) b = atomicAdd(&s[lead_bin], (u32)__popcll(grp));
+    b = __shfl(b, leader, 64);
+    if (on && bin == lead_bin) {
+      old = b + (u32)__popcll(grp & ((1ull << lane) - 1ull));
+      on = false;
+    }
+  }
+  if (on) old = atomicAdd(&s[bin], 1u);
+  return old;
+}
+
+// Whether the calling workgroup is the last of `total` to get here (*done starts at zero); if
+// so, everything the others wrote to global memory before is visible to it.  One thread
+// fences for its workgroup: a fence at device scope writes back the XCD's whole L2, and with
+// one per wave the label scan of a 1M-node graph took 27 us instead of 16.
+__device__ __forceinline__ bool last_workgroup(u32* done, u32 total) {
+  __shared__ u32 s_last;
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have reached L2
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    s_last = atomicAdd(done, 1u) == total - 1u ? 1u : 0u;
+    __threadfence();
+  }
+  __syncthreads();
+  return s_last != 0;
 }
 
 __device__ __forceinline__ u32 hash_slot(u32 key, u32 log2cap) {

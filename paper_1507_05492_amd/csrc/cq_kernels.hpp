@@ -1083,15 +1083,11 @@ constexpr int CS_LABELS = 64;
 constexpr int CS_GROUPS = 16;
 // zero64 (optional): one 64-bit word per label cleared on the way (the run cursors).
 template <bool WEIGHTED, bool SCAN>
-__global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_colscan(int W, int L, u32* __restrict__ HN,
-                                                                   u32* __restrict__ HD, u32* __restrict__ N,
-                                                                   u32* __restrict__ D,
-                                                                   unsigned long long* __restrict__ zero64 = nullptr,
-                                                                   const Ctl* __restrict__ gate = nullptr, u32 run_if = 0) {
-  if (gate && gate->mode != run_if) return;  // see k_node_priv
+__device__ __forceinline__ void colscan_tile(int W, int L, u32* __restrict__ HN, u32* __restrict__ HD, u32* __restrict__ N,
+                                             u32* __restrict__ D, unsigned long long* __restrict__ zero64, int blk) {
   __shared__ u32 s_n[CS_GROUPS][CS_LABELS], s_d[CS_GROUPS][CS_LABELS];
   const int lane = threadIdx.x % CS_LABELS, grp = threadIdx.x / CS_LABELS;
-  const int c = blockIdx.x * CS_LABELS + lane;
+  const int c = blk * CS_LABELS + lane;
   const int per = (W + CS_GROUPS - 1) / CS_GROUPS;
   const int w0 = min(W, grp * per), w1 = min(W, w0 + per);
   u32* PM = WEIGHTED ? HD : HN;
@@ -1127,6 +1123,16 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_colscan(int W, int L,
     if (D) D[c] = td;
     if (zero64) zero64[c] = 0ull;
   }
+}
+
+template <bool WEIGHTED, bool SCAN>
+__global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_colscan(int W, int L, u32* __restrict__ HN,
+                                                                   u32* __restrict__ HD, u32* __restrict__ N,
+                                                                   u32* __restrict__ D,
+                                                                   unsigned long long* __restrict__ zero64 = nullptr,
+                                                                   const Ctl* __restrict__ gate = nullptr, u32 run_if = 0) {
+  if (gate && gate->mode != run_if) return;  // see k_node_priv
+  colscan_tile<WEIGHTED, SCAN>(W, L, HN, HD, N, D, zero64, blockIdx.x);
 }
 
 // Column-blocked node pass: adds the histogram rows of the dense buckets (rows[0,
@@ -1207,26 +1213,43 @@ __device__ __forceinline__ void load_labels16(int c0, int L, const u32* __restri
   }
 }
 
-// One workgroup of 1024 threads; thread t takes SO_PER consecutive labels of each pass
-// of 1024 * SO_PER, with all of their loads issued before the first use.
-constexpr int SO_PER = 16;  // load_labels16
-__device__ void scan_order_body(int L, const u32* __restrict__ N, const u32* __restrict__ D, u32* __restrict__ start,
-                                u32* __restrict__ order, Ctl* __restrict__ ctl) {
+// One workgroup of 1024 threads; thread t takes PER consecutive labels of each pass of
+// 1024 * PER, with all of their loads issued before the first use.  Few labels are spread
+// over more threads (PER = 1 up to 1,024 labels, 4 up to 4,096): a thread's LDS adds are
+// performed one after another (399 labels: 6.2 us with 16 labels per thread).
+template <int PER>
+__device__ __forceinline__ void load_labels(int c0, int L, const u32* __restrict__ N, const u32* __restrict__ D, u32 (&d)[PER],
+                                            u32 (&nn)[PER]) {
+  if constexpr (PER == 16) {
+    load_labels16(c0, L, N, D, d, nn);
+  } else {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int c = c0 + k;
+      d[k] = c < L ? D[c] : 0u;
+      nn[k] = c < L ? N[c] : 0u;
+    }
+  }
+}
+
+template <int PER>
+__device__ void scan_order_per(int L, const u32* __restrict__ N, const u32* __restrict__ D, u32* __restrict__ start,
+                               u32* __restrict__ order, Ctl* __restrict__ ctl) {
   __shared__ u32 s_wtot[16];
   __shared__ u32 s_carry;
-  __shared__ u32 s_bcnt[33];
-  __shared__ u32 s_boff[33];
+  __shared__ u32 s_bcnt[64];
+  __shared__ u32 s_boff[64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (tid < 33) s_bcnt[tid] = 0;
+  if (tid < 64) s_bcnt[tid] = 0;
   if (tid == 0) s_carry = 0;
   __syncthreads();
-  for (int base = 0; base < L; base += 1024 * SO_PER) {
-    const int c0 = base + tid * SO_PER;
-    u32 d[SO_PER], nn[SO_PER];
-    load_labels16(c0, L, N, D, d, nn);
+  for (int base = 0; base < L; base += 1024 * PER) {
+    const int c0 = base + tid * PER;
+    u32 d[PER], nn[PER];
+    load_labels<PER>(c0, L, N, D, d, nn);
     u32 sum = 0;
 #pragma unroll
-    for (int k = 0; k < SO_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
       sum += d[k];
       if (nn[k] > 0) atomicAdd(&s_bcnt[size_bucket(d[k])], 1u);
     }
@@ -1236,34 +1259,39 @@ __device__ void scan_order_body(int L, const u32* __restrict__ N, const u32* __r
     u32 run = s_carry + incl - sum;
     for (int i = 0; i < wv; ++i) run += s_wtot[i];
 #pragma unroll
-    for (int k = 0; k < SO_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
       if (c0 + k < L) start[c0 + k] = run;
       run += d[k];
     }
     __syncthreads();
-    if (tid == 0) {
-      u32 t = s_carry;
-      for (int i = 0; i < 16; ++i) t += s_wtot[i];
-      s_carry = t;
-    }
+    if (tid == 1023) s_carry = run;  // the last thread's run ends at the pass's total
     __syncthreads();
   }
-  if (tid == 0) {
-    u32 off = 0;
-    for (int b = 32; b >= 0; --b) { s_boff[b] = off; off += s_bcnt[b]; }
-    ctl->K = off;
-    ctl->kbig = s_boff[GW_SPLIT_BUCKET - 1];  // groups in buckets >= GW_SPLIT_BUCKET
+  if (tid < 64) {
+    // places of the size buckets, largest first: lane i takes bucket 32 - i
+    const u32 cnt = tid <= 32 ? s_bcnt[32 - tid] : 0u;
+    const u32 incl = wave_incl_scan(cnt);
+    if (tid <= 32) s_boff[32 - tid] = incl - cnt;
+    if (tid == 32) ctl->K = incl;
+    if (tid == 32 - (GW_SPLIT_BUCKET - 1)) ctl->kbig = incl - cnt;  // groups in buckets >= GW_SPLIT_BUCKET
   }
   __syncthreads();
-  for (int base = 0; base < L; base += 1024 * SO_PER) {
-    const int c0 = base + tid * SO_PER;
-    u32 d[SO_PER], nn[SO_PER];
-    load_labels16(c0, L, N, D, d, nn);
+  for (int base = 0; base < L; base += 1024 * PER) {
+    const int c0 = base + tid * PER;
+    u32 d[PER], nn[PER];
+    load_labels<PER>(c0, L, N, D, d, nn);
 #pragma unroll
-    for (int k = 0; k < SO_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
       if (nn[k] > 0) order[atomicAdd(&s_boff[size_bucket(d[k])], 1u)] = (u32)(c0 + k);
     }
   }
+}
+
+__device__ __forceinline__ void scan_order_body(int L, const u32* __restrict__ N, const u32* __restrict__ D,
+                                                u32* __restrict__ start, u32* __restrict__ order, Ctl* __restrict__ ctl) {
+  if (L <= 1024) scan_order_per<1>(L, N, D, start, order, ctl);
+  else if (L <= 4096) scan_order_per<4>(L, N, D, start, order, ctl);
+  else scan_order_per<16>(L, N, D, start, order, ctl);
 }
 
 __global__ __launch_bounds__(1024) void k_scan_order(int L, const u32* __restrict__ N, const u32* __restrict__ D,
@@ -1895,6 +1923,30 @@ __device__ __forceinline__ void for_each_in_segment(const LT* __restrict__ seg, 
   for (u32 e = head + nvec * PER + threadIdx.x; e < len; e += NT) f((u32)seg[e]);
 }
 
+// Visits every counter of a direct table (nq 16-byte words) with the first NT threads of the
+// workgroup, each in increasing order.  The sizes |j| of two table words' labels are loaded
+// before their visits, so that the loads overlap; N is read as 16-byte words up to the
+// table's padding (workspace arrays are 16-byte aligned and padded to 256 bytes).
+template <int NT, class V>
+__device__ __forceinline__ void visit_direct(const uint4* tab4, const u32 nq, typename V::State& st, V& vis) {
+  const uint4* N4 = reinterpret_cast<const uint4*>(vis.N);
+  for (u32 q0 = threadIdx.x; q0 < nq; q0 += 2u * NT) {
+    const u32 q1 = q0 + NT;
+    const uint4 n0 = N4[q0];
+    uint4 n1 = make_uint4(0u, 0u, 0u, 0u);
+    if (q1 < nq) n1 = N4[q1];
+    auto visit4 = [&](u32 q, const uint4& nv) {
+      const uint4 x = tab4[q];
+      if (x.x) vis.visit_n(st, 4u * q, x.x, nv.x);
+      if (x.y) vis.visit_n(st, 4u * q + 1u, x.y, nv.y);
+      if (x.z) vis.visit_n(st, 4u * q + 2u, x.z, nv.z);
+      if (x.w) vis.visit_n(st, 4u * q + 3u, x.w, nv.w);
+    };
+    visit4(q0, n0);
+    if (q1 < nq) visit4(q1, n1);
+  }
+}
+
 // Counts one group's segment CB[base, base+len) (values in [0, Lv) or the sentinel)
 // in LDS and hands every (label, count) with count > 0 to the visitor.  hot0 entries of
 // the hot label were counted elsewhere (compact staging leaves them out of the segment).
@@ -2007,25 +2059,7 @@ __device__ void group_one(const LT* __restrict__ CB, const u32 base, const u32 l
     __syncthreads();
     if (tid == 0 && s_hot && hot < Lv) vis.visit(st, hot, s_hot);
     if constexpr (V::kSizesAhead) {
-      // the sizes |j| of two table words' labels are loaded before their visits, so
-      // that the loads overlap; N is read as 16-byte words up to the table's padding
-      // (workspace arrays are 16-byte aligned and padded to 256 bytes)
-      const uint4* N4 = reinterpret_cast<const uint4*>(vis.N);
-      for (u32 q0 = tid; q0 < nq; q0 += 2u * NT) {
-        const u32 q1 = q0 + NT;
-        const uint4 n0 = N4[q0];
-        uint4 n1 = make_uint4(0u, 0u, 0u, 0u);
-        if (q1 < nq) n1 = N4[q1];
-        auto visit4 = [&](u32 q, const uint4& nv) {
-          const uint4 x = tab4[q];
-          if (x.x) vis.visit_n(st, 4u * q, x.x, nv.x);
-          if (x.y) vis.visit_n(st, 4u * q + 1u, x.y, nv.y);
-          if (x.z) vis.visit_n(st, 4u * q + 2u, x.z, nv.z);
-          if (x.w) vis.visit_n(st, 4u * q + 3u, x.w, nv.w);
-        };
-        visit4(q0, n0);
-        if (q1 < nq) visit4(q1, n1);
-      }
+      visit_direct<NT>(tab4, nq, st, vis);
     } else {
       for (u32 q = tid; q < nq; q += NT) {
         const uint4 x = tab4[q];

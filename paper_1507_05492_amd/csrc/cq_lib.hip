@@ -21,6 +21,7 @@
 #include "cq.h"
 #include "cq_kernels.hpp"
 #include "cq_compare.hpp"
+#include "cq_rows.hpp"
 #include "srv_core.hpp"
 
 using namespace cq;
@@ -260,6 +261,8 @@ struct ScoreLayout {
   int chunk, W, G;
   size_t ctl, wq, N, D, start, order, I, NP, PEN, SZ, cursor, loc, HN, HD, RL, labx, CB, parts, res, total;
   size_t CW, SW, IW, PENW, INVN;  // weighted graphs only (0 otherwise)
+  bool rows;  // scored by member rows (cq_rows.hpp): rec and bad in place of the staged entries
+  size_t rec, bad;
 };
 
 ScoreLayout score_layout(int64_t n, int64_t nnz, int64_t L, bool weighted = false, int64_t max_chunk = 65536,
@@ -311,10 +314,37 @@ ScoreLayout score_layout(int64_t n, int64_t nnz, int64_t L, bool weighted = fals
 // histogram rows (W x L per task) few.  Never larger than the single-call layout.
 ScoreLayout batch_task_layout(int64_t n, int64_t nnz, int64_t L) { return score_layout(n, nnz, L, false, 65536, 4096); }
 
+// Nodes up to which a graph without column blocks is scored by member rows: their 16-bit
+// labels fill one XCD's 4 MB L2.
+constexpr int64_t ROWS_MAX_N = 2 << 20;
+
 // The layout of one scoring call on graph g (the node pass it takes decides the chunk).
+// Member rows take the workspace of the staged path (which they fit unless the graph has
+// hardly any edges).
 ScoreLayout graph_score_layout(const cq_graph* g, int64_t L) {
   const bool perm = g->rpb && g->pos1 && L <= PRIV_MAX;
-  return score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
+  const ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
+  if (g->rpb || g->w || L > DIRECT_MAX || g->n > ROWS_MAX_N) return s;
+  ScoreLayout r = s;
+  Carve c;
+  r.rows = true;
+  r.ctl = c.take(sizeof(Ctl));
+  r.wq = c.take(WQ_BYTES);
+  r.N = c.take(4 * L);
+  r.D = c.take(4 * L);
+  r.start = c.take(4 * L);
+  r.order = c.take(4 * L);
+  r.I = c.take(4 * L);
+  r.NP = c.take(4 * L);
+  r.PEN = c.take(16 * L);
+  r.loc = c.take(4 * (size_t)g->n);
+  r.HN = c.take(4 * (size_t)r.W * L);
+  r.bad = c.take(4 * (size_t)r.W);
+  r.labx = c.take(2 * (size_t)g->n);
+  r.rec = c.take(8 * (size_t)g->n);
+  r.parts = c.take(sizeof(ScorePart) * r.G);
+  r.res = c.take(sizeof(ScoreResultDev));
+  return c.off <= s.total ? r : s;
 }
 
 struct CmpLayout {
@@ -399,37 +429,6 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
     s.total = c.off;
     return s;
   }
-  s.wide = wide_bins(n, La, Lb, &s);
-  if (s.wide) {
-    const int nb = s.nbA + s.nbB;
-    s.Wh = (int)std::min<int64_t>(256, (n + BH_THREADS * BH_NPT - 1) / (BH_THREADS * BH_NPT));
-    // chunks of 10 nodes per thread (two workgroups per CU) until 20 (one per CU) fill two
-    // waves of workgroups: longer runs per bin and half the claims
-    s.npt = n >= (int64_t)512 * 20 * CP_THREADS ? 20 : 10;
-    s.chunks = (int)((n + (int64_t)s.npt * CP_THREADS - 1) / ((int64_t)s.npt * CP_THREADS));
-    s.ctl = c.take(sizeof(Ctl));
-    s.wq = c.take(WQ_BYTES);
-    s.A = c.take(4 * La);
-    s.B = c.take(4 * Lb);
-    s.COLMAX = c.take(4 * Lb);
-    s.RA11 = c.take(8 * La);
-    s.RMAX = c.take(4 * La);
-    s.RF = c.take(8 * La);
-    s.RXL = c.take(16 * La);
-    s.HA = c.take(4 * (size_t)s.Wh * nb);
-    s.HB = s.binsB ? 0 : c.take(4 * (size_t)s.Wb * Lb);
-    s.SZB = c.take(4 * (size_t)nb);
-    s.SBS = c.take(4 * ((size_t)s.nbA + 1));
-    s.SBB = c.take(4 * ((size_t)s.nbB + 1));
-    s.CUR = c.take(4 * (size_t)nb);
-    s.BORD = c.take(4 * (size_t)s.nbA);
-    s.E = c.take(4 * (size_t)n);
-    s.EB = s.binsB ? c.take(2 * (size_t)n) : 0;
-    s.parts = c.take(sizeof(CmpPart) * (s.Ga + s.Gb));
-    s.res = c.take(sizeof(CmpResultDev));
-    s.total = c.off;
-    return s;
-  }
   s.chunk = pick_chunk(n, La > PRIV_MAX ? RANGE_CHUNK_MAX : 65536);
   s.W = (int)((n + s.chunk - 1) / s.chunk);
   s.ctl = c.take(sizeof(Ctl));
@@ -451,7 +450,38 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
   s.parts = c.take(sizeof(CmpPart) * (s.Ga + s.Gb));
   s.res = c.take(sizeof(CmpResultDev));
   s.total = c.off;
-  return s;
+  // the wide path takes the same workspace (one that would need more stays on segments)
+  CmpLayout w = s;
+  if (!wide_bins(n, La, Lb, &w)) return s;
+  w.wide = true;
+  Carve k;
+  const int nb = w.nbA + w.nbB;
+  w.Wh = (int)std::min<int64_t>(256, (n + BH_THREADS * BH_NPT - 1) / (BH_THREADS * BH_NPT));
+  // chunks of 10 nodes per thread (two workgroups per CU) until 20 (one per CU) fill two
+  // waves of workgroups: longer runs per bin and half the claims
+  w.npt = n >= (int64_t)512 * 20 * CP_THREADS ? 20 : 10;
+  w.chunks = (int)((n + (int64_t)w.npt * CP_THREADS - 1) / ((int64_t)w.npt * CP_THREADS));
+  w.ctl = k.take(sizeof(Ctl));
+  w.wq = k.take(WQ_BYTES);
+  w.A = k.take(4 * La);
+  w.B = k.take(4 * Lb);
+  w.COLMAX = k.take(4 * Lb);
+  w.RA11 = k.take(8 * La);
+  w.RMAX = k.take(4 * La);
+  w.RF = k.take(8 * La);
+  w.RXL = k.take(16 * La);
+  w.HA = k.take(4 * (size_t)w.Wh * nb);
+  w.HB = w.binsB ? 0 : k.take(4 * (size_t)w.Wb * Lb);
+  w.SZB = k.take(4 * (size_t)nb);
+  w.SBS = k.take(4 * ((size_t)w.nbA + 1));
+  w.SBB = k.take(4 * ((size_t)w.nbB + 1));
+  w.CUR = k.take(4 * (size_t)nb);
+  w.BORD = k.take(4 * (size_t)w.nbA);
+  w.E = k.take(4 * (size_t)n);
+  w.EB = w.binsB ? k.take(2 * (size_t)n) : 0;
+  w.parts = k.take(sizeof(CmpPart) * (w.Ga + w.Gb));
+  w.res = k.take(sizeof(CmpResultDev));
+  return k.off <= s.total ? w : s;
 }
 
 template <class T>
@@ -763,6 +793,99 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   }
 }
 
+// Threads per workgroup of the member-row group pass: enough that the workgroups a CU holds
+// beside their tables fill its 2,048 threads, and that few communities spread over the chip
+// (399 communities: 1,024 threads each).
+int rows_threads(cq_context* ctx, int32_t L) {
+  const int64_t tables = std::min<int64_t>(16, (int64_t)(150 << 10) / (4 * (int64_t)L + 2048));  // workgroups per CU by LDS
+  const int64_t want = std::max<int64_t>(2048 / std::max<int64_t>(tables, 1), (int64_t)ctx->num_cus * 2048 / L);
+  int nt = L <= (int32_t)SMALL_L_MAX ? 128 : 256;
+  while (nt < 1024 && nt < want) nt *= 2;
+  return nt;
+}
+
+template <int NT_, int NTV_>
+struct RowsTag {  // one shape of k_rows_groups
+  static constexpr int NT = NT_, NTV = NTV_;
+  static unsigned grid(cq_context* ctx, int32_t L, size_t lds) {
+    int nb = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rows_groups<uint16_t, NT, NTV>, NT, lds) != hipSuccess || nb < 1) nb = 1;
+    const int64_t cap = ((int64_t)L + 7) / 8 * 8;  // a multiple of the queues (static first items)
+    return (unsigned)std::min<int64_t>((int64_t)ctx->num_cus * nb / 8 * 8, cap);
+  }
+};
+
+// A graph scored by member rows (cq_rows.hpp).
+void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels, int32_t L, void* ws, const ScoreLayout& lay,
+                       ScoreResultDev* d_out, const cq_per_community* per_comm, const cq_pair_table* pairs, bool timed) {
+  const int n = g->n;
+  hipStream_t s = ctx->stream;
+  Ctl* ctl = at<Ctl>(ws, lay.ctl);
+  u32* wq = at<u32>(ws, lay.wq);
+  u32* N = at<u32>(ws, lay.N);
+  u32* D = at<u32>(ws, lay.D);
+  u32* start = at<u32>(ws, lay.start);
+  u32* order = at<u32>(ws, lay.order);
+  u32* loc = at<u32>(ws, lay.loc);
+  u32* HN = at<u32>(ws, lay.HN);
+  u32* bad = at<u32>(ws, lay.bad);
+  uint16_t* labx = at<uint16_t>(ws, lay.labx);
+  uint2* rec = at<uint2>(ws, lay.rec);
+  ScoreVis vis;
+  vis.N = N;
+  vis.twom = (double)g->nnz;
+  vis.I = at<u32>(ws, lay.I);
+  vis.NP = at<u32>(ws, lay.NP);
+  vis.PEN = at<u64>(ws, lay.PEN);
+  vis.eci = pairs ? pairs->ci : nullptr;
+  vis.ecj = pairs ? pairs->cj : nullptr;
+  vis.ecnt = pairs ? pairs->count : nullptr;
+  vis.ecap = pairs ? pairs->capacity : 0;
+  vis.ctl = ctl;
+  const size_t lds = (size_t)std::max<u32>(((u32)L + 3u) & ~3u, 128u) * 4;
+  const int nt = rows_threads(ctx, L);
+  const bool small = L <= (int32_t)SMALL_L_MAX;
+  auto groups = [&](auto tag, bool launch) -> unsigned {
+    using T = decltype(tag);
+    const unsigned grid = T::grid(ctx, L, lds);
+    if (launch)
+      k_rows_groups<uint16_t, T::NT, T::NTV><<<grid, T::NT, lds, s>>>(rec, g->col, labx, start, order, D, ctl, (u32)L, vis, wq);
+    return grid;
+  };
+  auto pick = [&](bool launch) -> unsigned {
+    if (small) return nt == 128 ? groups(RowsTag<128, GBLOCK_SMALL>{}, launch) : nt == 256 ? groups(RowsTag<256, GBLOCK_SMALL>{}, launch)
+                    : nt == 512 ? groups(RowsTag<512, GBLOCK_SMALL>{}, launch) : groups(RowsTag<1024, GBLOCK_SMALL>{}, launch);
+    return nt == 256 ? groups(RowsTag<256, GBLOCK_DIRECT>{}, launch) : nt == 512 ? groups(RowsTag<512, GBLOCK_DIRECT>{}, launch)
+                     : groups(RowsTag<1024, GBLOCK_DIRECT>{}, launch);
+  };
+  {
+    StageMark mk(ctx, ST_NODE, timed);
+    k_rows_node<uint16_t><<<lay.W, 1024, (size_t)L * 4, s>>>(n, labels, g->perm, L, lay.chunk, HN, loc, labx, bad, ctl, wq,
+                                                             pick(false) / WQ_QUEUES);
+  }
+  {
+    StageMark mk(ctx, ST_ORDER, timed);
+    k_rows_scan<<<colscan_grid(L), CS_LABELS * CS_GROUPS, 0, s>>>(lay.W, L, HN, N, start, order, bad, ctl);
+  }
+  {
+    StageMark mk(ctx, ST_SCATTER, timed);
+    k_rows_place<uint16_t><<<grid_for(n, 256, 8192), 256, 0, s>>>(n, g->rp, L, lay.chunk, HN, start, loc, labx, rec);
+  }
+  {
+    StageMark mk(ctx, ST_GROUPS, timed);
+    (void)pick(true);
+  }
+  PerComm pc;
+  std::memset(&pc, 0, sizeof(pc));
+  if (per_comm) std::memcpy(&pc, per_comm, sizeof(pc));
+  ScorePart* parts = at<ScorePart>(ws, lay.parts);
+  {
+    StageMark mk(ctx, ST_FINAL, timed);
+    k_score_final1<<<lay.G, FBLOCK, 0, s>>>(L, N, D, vis.I, vis.NP, vis.PEN, (double)g->nnz, pc, parts);
+    k_score_final2<<<1, 64, 0, s>>>(lay.G, parts, n, g->nnz, vis.ecap, ctl, d_out, 0u);
+  }
+}
+
 cq_status score_enqueue(cq_context* ctx, const cq_graph* g, const int32_t* labels, int32_t L, void* ws, size_t ws_bytes,
                         ScoreResultDev* d_out, const cq_per_community* per_comm, const cq_pair_table* pairs, bool timed) {
   if (!ctx) return CQ_E_INVALID_ARG;
@@ -778,7 +901,9 @@ cq_status score_enqueue(cq_context* ctx, const cq_graph* g, const int32_t* label
   if (!ws || ws_bytes < lay.total)
     return fail(ctx, CQ_E_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, lay.total);
   if (reinterpret_cast<uintptr_t>(ws) % WS_ALIGN) return fail(ctx, CQ_E_INVALID_ARG, "workspace not 16-byte aligned");
-  if (lay.small)
+  if (lay.rows)
+    score_launch_rows(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
+  else if (lay.small)
     score_launch<uint16_t>(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
   else
     score_launch<uint32_t>(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
@@ -1825,6 +1950,10 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_groups<ScoreVis, uint32_t, GBLOCK_WIDE>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<CmpVis, uint16_t>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<CmpVis, uint32_t>), gl);
+  set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 1024, GBLOCK_DIRECT>), DIRECT_MAX * 4);
+  set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 512, GBLOCK_DIRECT>), DIRECT_MAX * 4);
+  set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 256, GBLOCK_DIRECT>), DIRECT_MAX * 4);
+  set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_b_node), 2 * PRIV_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_b_groups<GBLOCK_DIRECT>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_b_groups<GBLOCK_SMALL>), gl);
