@@ -28,8 +28,7 @@ struct Ctl {
   u32 kbig;       // groups whose segment holds at least GW_SPLIT entries (they come first in the order)
   u32 dense_rows;  // node pass of column-blocked graphs: buckets that wrote histogram rows
   unsigned long long export_count;
-  u32 done;       // workgroups that have finished a pass whose last workgroup goes on alone
-  u32 reserved1;
+  u32 done, done2;  // workgroups that have finished a pass whose last workgroup goes on alone
   u32 changes;    // column-blocked node pass: label changes between consecutive stored ids
   u32 mode;       // column-blocked graphs: STAGE_BLOCKS or STAGE_ROWS, chosen from `changes`
   unsigned long long pad1[3];

@@ -2872,13 +2872,6 @@ __device__ void score_final1_body(int L, const u32* __restrict__ N, const u32* _
   }
 }
 
-__global__ __launch_bounds__(FBLOCK) void k_score_final1(int L, const u32* __restrict__ N, const u32* __restrict__ D,
-                                                         const u32* __restrict__ I, const u32* __restrict__ NP,
-                                                         const u64* __restrict__ PEN, double twom, PerComm pc,
-                                                         ScorePart* __restrict__ parts) {
-  score_final1_body(L, N, D, I, NP, PEN, twom, pc, parts, blockIdx.x, gridDim.x);
-}
-
 // device mirror of the public cq_score_result (same layout)
 struct ScoreResultDev {
   int64_t n, m, K, num_pairs, sum_ein, sum_eout;
@@ -2897,17 +2890,39 @@ __device__ __forceinline__ u32 staging_of(const Ctl* ctl, u32 blocked) {
   return ctl->mode ? ctl->mode : (blocked ? STAGE_BLOCKS : STAGE_ROWS_ONLY);
 }
 
+// Sums the doubles f[k][0..G) of NF fields in order, one field per lane (G <= FINAL_PARTS);
+// lane k ends with field k's sum.  Called by one converged wave.
+constexpr int FINAL_PARTS = 128;
+template <int NF>
+__device__ __forceinline__ double sum_fields_in_order(const double (&f)[NF][FINAL_PARTS], int G) {
+  const int lane = threadIdx.x & 63;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the wave's own LDS writes
+  double t = 0.0;
+  if (lane < NF)
+    for (int b = 0; b < G; ++b) t += f[lane][b];
+  return t;
+}
+
+// Stage 2 of the final reduction, by one wave: each lane takes every 64th part; integers are
+// summed across the wave, doubles in the order of the parts.
 __device__ void score_final2_body(int G, const ScorePart* __restrict__ parts, long long n, long long twom, long long ecap,
                                   Ctl* __restrict__ ctl, ScoreResultDev* __restrict__ out, u32 blocked) {
+  __shared__ double s_f[5][FINAL_PARTS];
+  const int lane = threadIdx.x & 63;
   u64 K = 0, sein = 0, seout = 0, sD2 = 0, np = 0;
   u128 pen = 0;
-  double qds_a = 0, s_dens = 0, s_contr = 0, s_exp = 0, s_cond = 0;
-  for (int b = 0; b < G; ++b) {
+  for (int b = lane; b < G; b += 64) {
     const ScorePart p = parts[b];
     K += p.K; sein += p.sein; seout += p.seout; sD2 += p.sD2; np += p.np;
     pen += ((u128)p.pen_hi << 64) | p.pen_lo;
-    qds_a += p.qds_a; s_dens += p.s_dens; s_contr += p.s_contr; s_exp += p.s_exp; s_cond += p.s_cond;
+    s_f[0][b] = p.qds_a; s_f[1][b] = p.s_dens; s_f[2][b] = p.s_contr; s_f[3][b] = p.s_exp; s_f[4][b] = p.s_cond;
   }
+  K = wave_sum_u64(K); sein = wave_sum_u64(sein); seout = wave_sum_u64(seout); sD2 = wave_sum_u64(sD2); np = wave_sum_u64(np);
+  pen = wave_sum_u128(pen);
+  const double sum = sum_fields_in_order(s_f, G);
+  const double qds_a = __shfl(sum, 0, 64), s_dens = __shfl(sum, 1, 64), s_contr = __shfl(sum, 2, 64);
+  const double s_exp = __shfl(sum, 3, 64), s_cond = __shfl(sum, 4, 64);
+  if (lane != 0) return;
   const long long m = twom / 2;
   ScoreResultDev r;
   r.n = n; r.m = m; r.K = (int64_t)K; r.num_pairs = (int64_t)np;
@@ -2943,11 +2958,59 @@ struct WScorePart {
   double q, qds_a, s_dens, s_contr, s_exp, s_cond, pad2[2];
 };
 
-__global__ __launch_bounds__(FBLOCK) void k_score_final1_w(int L, const u32* __restrict__ N, const u32* __restrict__ D,
+// Stage 2, by one wave (see score_final2_body).
+__device__ void score_final2_w_body(int G, const WScorePart* __restrict__ parts, long long n, long long twom, double W,
+                                    long long ecap, Ctl* __restrict__ ctl, ScoreResultDev* __restrict__ out, u32 blocked) {
+  __shared__ double s_f[6][FINAL_PARTS];
+  const int lane = threadIdx.x & 63;
+  u64 K = 0, sein = 0, seout = 0, sD2 = 0, np = 0;
+  u128 penw = 0, swi2 = 0, swo = 0;
+  for (int b = lane; b < G; b += 64) {
+    const WScorePart p = parts[b];
+    K += p.K; sein += p.sein; seout += p.seout; sD2 += p.sD2; np += p.np;
+    penw += ((u128)p.penw_hi << 64) | p.penw_lo;
+    swi2 += ((u128)p.wi_hi << 64) | p.wi_lo;
+    swo += ((u128)p.wo_hi << 64) | p.wo_lo;
+    s_f[0][b] = p.q; s_f[1][b] = p.qds_a; s_f[2][b] = p.s_dens; s_f[3][b] = p.s_contr; s_f[4][b] = p.s_exp; s_f[5][b] = p.s_cond;
+  }
+  K = wave_sum_u64(K); sein = wave_sum_u64(sein); seout = wave_sum_u64(seout); sD2 = wave_sum_u64(sD2); np = wave_sum_u64(np);
+  penw = wave_sum_u128(penw); swi2 = wave_sum_u128(swi2); swo = wave_sum_u128(swo);
+  const double sum = sum_fields_in_order(s_f, G);
+  const double q = __shfl(sum, 0, 64), qds_a = __shfl(sum, 1, 64), s_dens = __shfl(sum, 2, 64), s_contr = __shfl(sum, 3, 64);
+  const double s_exp = __shfl(sum, 4, 64), s_cond = __shfl(sum, 5, 64);
+  if (lane != 0) return;
+  ScoreResultDev r;
+  r.n = n; r.m = twom / 2; r.K = (int64_t)K; r.num_pairs = (int64_t)np;
+  r.sum_ein = (int64_t)sein; r.sum_eout = (int64_t)seout; r.sum_degsum_sq = sD2;
+  const double pen = unfix96(penw);
+  r.Q = q;
+  r.split_penalty = pen;
+  r.Qds = qds_a - pen;
+  const double Kd = (double)K;
+  const double wi = 0.5 * unfixw(swi2), wout = unfixw(swo);
+  r.mean_intra_edges = wi / Kd;
+  r.mean_intra_density = s_dens / Kd;
+  r.mean_contraction = s_contr / Kd;
+  r.mean_inter_edges = wout / Kd;
+  r.mean_expansion = s_exp / Kd;
+  r.mean_conductance = s_cond / Kd;
+  r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
+  r.weighted = 1;
+  r.total_weight = W;
+  r.sum_w_in = wi;
+  r.sum_w_out = wout;
+  r.staging = staging_of(ctl, blocked);
+  r.reserved = 0;
+  *out = r;
+}
+
+__global__ __launch_bounds__(FBLOCK) void k_score_final_w(int L, const u32* __restrict__ N, const u32* __restrict__ D,
                                                            const u32* __restrict__ I, const u32* __restrict__ NP,
                                                            const u64* __restrict__ SW, const u64* __restrict__ IW,
                                                            const u64* __restrict__ PENW, double W, PerComm pc,
-                                                           WScorePart* __restrict__ parts) {
+                                                           WScorePart* __restrict__ parts, long long n, long long twom,
+                                                           long long ecap, Ctl* __restrict__ ctl,
+                                                           ScoreResultDev* __restrict__ out, u32 blocked) {
   const int G = gridDim.x, blk = blockIdx.x;
   const int R = (L + G - 1) / G;
   const int c0 = blk * R, c1 = min(L, c0 + R);
@@ -3024,51 +3087,22 @@ __global__ __launch_bounds__(FBLOCK) void k_score_final1_w(int L, const u32* __r
     p.pad2[0] = p.pad2[1] = 0;
     parts[blk] = p;
   }
-}
-
-__global__ void k_score_final2_w(int G, const WScorePart* __restrict__ parts, long long n, long long twom, double W,
-                                 long long ecap, Ctl* __restrict__ ctl, ScoreResultDev* __restrict__ out, u32 blocked) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  u64 K = 0, sein = 0, seout = 0, sD2 = 0, np = 0;
-  u128 penw = 0, swi2 = 0, swo = 0;
-  double q = 0, qds_a = 0, s_dens = 0, s_contr = 0, s_exp = 0, s_cond = 0;
-  for (int b = 0; b < G; ++b) {
-    const WScorePart p = parts[b];
-    K += p.K; sein += p.sein; seout += p.seout; sD2 += p.sD2; np += p.np;
-    penw += ((u128)p.penw_hi << 64) | p.penw_lo;
-    swi2 += ((u128)p.wi_hi << 64) | p.wi_lo;
-    swo += ((u128)p.wo_hi << 64) | p.wo_lo;
-    q += p.q; qds_a += p.qds_a; s_dens += p.s_dens; s_contr += p.s_contr; s_exp += p.s_exp; s_cond += p.s_cond;
-  }
-  ScoreResultDev r;
-  r.n = n; r.m = twom / 2; r.K = (int64_t)K; r.num_pairs = (int64_t)np;
-  r.sum_ein = (int64_t)sein; r.sum_eout = (int64_t)seout; r.sum_degsum_sq = sD2;
-  const double pen = unfix96(penw);
-  r.Q = q;
-  r.split_penalty = pen;
-  r.Qds = qds_a - pen;
-  const double Kd = (double)K;
-  const double wi = 0.5 * unfixw(swi2), wout = unfixw(swo);
-  r.mean_intra_edges = wi / Kd;
-  r.mean_intra_density = s_dens / Kd;
-  r.mean_contraction = s_contr / Kd;
-  r.mean_inter_edges = wout / Kd;
-  r.mean_expansion = s_exp / Kd;
-  r.mean_conductance = s_cond / Kd;
-  r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
-  r.weighted = 1;
-  r.total_weight = W;
-  r.sum_w_in = wi;
-  r.sum_w_out = wout;
-  r.staging = staging_of(ctl, blocked);
-  r.reserved = 0;
-  *out = r;
+  if (!last_workgroup(&ctl->done2, gridDim.x)) return;
+  if (threadIdx.x < 64) score_final2_w_body(G, parts, n, twom, W, ecap, ctl, out, blocked);
 }
 
 
-__global__ void k_score_final2(int G, const ScorePart* __restrict__ parts, long long n, long long twom, long long ecap,
-                               Ctl* __restrict__ ctl, ScoreResultDev* __restrict__ out, u32 blocked) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) score_final2_body(G, parts, n, twom, ecap, ctl, out, blocked);
+
+// Both stages in one launch: the last workgroup to finish its labels combines the parts.
+// `out` may be host memory that the device can write.
+__global__ __launch_bounds__(FBLOCK) void k_score_final(int L, const u32* __restrict__ N, const u32* __restrict__ D,
+                                                        const u32* __restrict__ I, const u32* __restrict__ NP,
+                                                        const u64* __restrict__ PEN, long long n, long long twom, PerComm pc,
+                                                        ScorePart* __restrict__ parts, long long ecap, Ctl* __restrict__ ctl,
+                                                        ScoreResultDev* __restrict__ out, u32 blocked) {
+  score_final1_body(L, N, D, I, NP, PEN, (double)twom, pc, parts, blockIdx.x, gridDim.x);
+  if (!last_workgroup(&ctl->done2, gridDim.x)) return;
+  if (threadIdx.x < 64) score_final2_body(gridDim.x, parts, n, twom, ecap, ctl, out, blocked);
 }
 
 // comparison final reduction ------------------------------------------------
@@ -3077,10 +3111,82 @@ struct CmpPart {
   double fsum, pad[3];
 };
 
-__global__ __launch_bounds__(FBLOCK) void k_cmp_final1(int La, int Lb, int Ga, const u32* __restrict__ A, const u32* __restrict__ B,
+struct CmpResultDev {
+  int64_t n, Ka, Kb, nnz, a11, a10, a01, a00, A;
+  double VI, NMI, F, NVD, RI, ARI, JI;
+  uint32_t device_flags, reserved;
+};
+
+__device__ __forceinline__ double i128_to_f64(__int128 v) {
+  bool neg = v < 0;
+  u128 a = neg ? (u128)(-v) : (u128)v;
+  double d = ldexp((double)(u64)(a >> 64), 64) + (double)(u64)a;
+  return neg ? -d : d;
+}
+
+// Stage 2, by one wave (see score_final2_body).
+__device__ void cmp_final2_body(int G, const CmpPart* __restrict__ parts, long long n, long long ecap, Ctl* __restrict__ ctl,
+                                CmpResultDev* __restrict__ out, u32* __restrict__ wq) {
+  __shared__ double s_f[1][FINAL_PARTS];
+  const int lane = threadIdx.x & 63;
+  u64 cells = lane < (int)WQ_QUEUES ? *wq_sum(wq, (u32)lane) : 0;
+  u64 Ka = 0, Kb = 0, a11 = 0, X = 0, Y = 0, smax = 0;
+  u128 xl = 0, sa = 0, sb = 0;
+  for (int b = lane; b < G; b += 64) {
+    const CmpPart p = parts[b];
+    Ka += p.Ka; Kb += p.Kb; a11 += p.a11; X += p.X; Y += p.Y; smax += p.smax;
+    xl += ((u128)p.xl_hi << 64) | p.xl_lo;
+    sa += ((u128)p.sa_hi << 64) | p.sa_lo;
+    sb += ((u128)p.sb_hi << 64) | p.sb_lo;
+    s_f[0][b] = p.fsum;
+  }
+  cells = wave_sum_u64(cells);
+  Ka = wave_sum_u64(Ka); Kb = wave_sum_u64(Kb); a11 = wave_sum_u64(a11); X = wave_sum_u64(X); Y = wave_sum_u64(Y);
+  smax = wave_sum_u64(smax);
+  xl = wave_sum_u128(xl); sa = wave_sum_u128(sa); sb = wave_sum_u128(sb);
+  const double fsum = sum_fields_in_order(s_f, G);  // lane 0 holds the one field
+  if (lane != 0) return;
+  const double Nd = (double)n;
+  const u64 A = (u64)n * (u64)(n - 1) / 2u;
+  CmpResultDev r;
+  r.n = n; r.Ka = (int64_t)Ka; r.Kb = (int64_t)Kb; r.nnz = (int64_t)cells;
+  r.a11 = (int64_t)a11;
+  r.a10 = (int64_t)(X - a11);
+  r.a01 = (int64_t)(Y - a11);
+  r.a00 = (int64_t)(A - X - Y + a11);
+  r.A = (int64_t)A;
+  // combined in fixed point before the one conversion (see CmpVis).  A side with one
+  // community has entropy 0 and shares no information: exactly, from the counts.
+  const double logN = log(Nd);
+  r.VI = -unfix96(2 * xl - sa - sb);
+  const double ha = Ka == 1 ? 0.0 : logN - unfix96(sa);  // H(C)
+  const double hb = Kb == 1 ? 0.0 : logN - unfix96(sb);  // H(C')
+  const double mi = (Ka == 1 || Kb == 1) ? 0.0 : unfix96(xl - sa - sb) + logN;
+  const double den = ha + hb;
+  r.NMI = den != 0.0 ? 2.0 * mi / den : 1.0;
+  r.F = fsum / Nd;
+  r.NVD = 1.0 - (double)smax / (2.0 * Nd);
+  r.RI = (double)(a11 + (A - X - Y + a11)) / (double)A;
+  // Eq. 6 with M = (a11+a10)(a11+a01)/A, numerator and denominator scaled by 2A:
+  // ARI = (2 A a11 - 2 X Y) / (A (X + Y) - 2 X Y), exact in 128-bit integers.
+  const __int128 XY = (__int128)X * (__int128)Y;
+  const __int128 anum = 2 * (__int128)A * (__int128)a11 - 2 * XY;
+  const __int128 aden = (__int128)A * (__int128)(X + Y) - 2 * XY;
+  r.ARI = aden != 0 ? i128_to_f64(anum) / i128_to_f64(aden) : 1.0;
+  const u64 jden = a11 + (X - a11) + (Y - a11);
+  r.JI = jden != 0 ? (double)a11 / (double)jden : 1.0;
+  r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
+  r.reserved = 0;
+  *out = r;
+}
+
+__global__ __launch_bounds__(FBLOCK) void k_cmp_final(int La, int Lb, int Ga, const u32* __restrict__ A, const u32* __restrict__ B,
                                                        const u32* __restrict__ COLMAX, const u64* __restrict__ RA11,
                                                        const u32* __restrict__ RMAX, const double* __restrict__ RF,
-                                                       const u64* __restrict__ RXL, double Nd, CmpPart* __restrict__ parts) {
+                                                       const u64* __restrict__ RXL, long long n, CmpPart* __restrict__ parts,
+                                                       long long ecap, Ctl* __restrict__ ctl,
+                                                       CmpResultDev* __restrict__ out, u32* __restrict__ wq) {
+  const double Nd = (double)n;
   u64 Ka = 0, Kb = 0, a11 = 0, X = 0, Y = 0, smax = 0;
   u128 xl = 0, sa = 0, sb = 0;  // S, S_a, S_b (see CmpVis)
   double fsum = 0;
@@ -3130,70 +3236,10 @@ __global__ __launch_bounds__(FBLOCK) void k_cmp_final1(int La, int Lb, int Ga, c
     p.pad[0] = p.pad[1] = p.pad[2] = 0;
     parts[blockIdx.x] = p;
   }
+  if (!last_workgroup(&ctl->done2, gridDim.x)) return;
+  if (threadIdx.x < 64) cmp_final2_body(gridDim.x, parts, n, ecap, ctl, out, wq);
 }
 
-struct CmpResultDev {
-  int64_t n, Ka, Kb, nnz, a11, a10, a01, a00, A;
-  double VI, NMI, F, NVD, RI, ARI, JI;
-  uint32_t device_flags, reserved;
-};
-
-__device__ __forceinline__ double i128_to_f64(__int128 v) {
-  bool neg = v < 0;
-  u128 a = neg ? (u128)(-v) : (u128)v;
-  double d = ldexp((double)(u64)(a >> 64), 64) + (double)(u64)a;
-  return neg ? -d : d;
-}
-
-__global__ void k_cmp_final2(int G, const CmpPart* __restrict__ parts, long long n, long long ecap, Ctl* __restrict__ ctl,
-                             CmpResultDev* __restrict__ out, u32* __restrict__ wq) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  unsigned long long cells = 0;
-  for (u32 q = 0; q < WQ_QUEUES; ++q) cells += *wq_sum(wq, q);
-  u64 Ka = 0, Kb = 0, a11 = 0, X = 0, Y = 0, smax = 0;
-  u128 xl = 0, sa = 0, sb = 0;
-  double fsum = 0;
-  for (int b = 0; b < G; ++b) {
-    const CmpPart p = parts[b];
-    Ka += p.Ka; Kb += p.Kb; a11 += p.a11; X += p.X; Y += p.Y; smax += p.smax;
-    xl += ((u128)p.xl_hi << 64) | p.xl_lo;
-    sa += ((u128)p.sa_hi << 64) | p.sa_lo;
-    sb += ((u128)p.sb_hi << 64) | p.sb_lo;
-    fsum += p.fsum;
-  }
-  const double Nd = (double)n;
-  const u64 A = (u64)n * (u64)(n - 1) / 2u;
-  CmpResultDev r;
-  r.n = n; r.Ka = (int64_t)Ka; r.Kb = (int64_t)Kb; r.nnz = (int64_t)cells;
-  r.a11 = (int64_t)a11;
-  r.a10 = (int64_t)(X - a11);
-  r.a01 = (int64_t)(Y - a11);
-  r.a00 = (int64_t)(A - X - Y + a11);
-  r.A = (int64_t)A;
-  // combined in fixed point before the one conversion (see CmpVis).  A side with one
-  // community has entropy 0 and shares no information: exactly, from the counts.
-  const double logN = log(Nd);
-  r.VI = -unfix96(2 * xl - sa - sb);
-  const double ha = Ka == 1 ? 0.0 : logN - unfix96(sa);  // H(C)
-  const double hb = Kb == 1 ? 0.0 : logN - unfix96(sb);  // H(C')
-  const double mi = (Ka == 1 || Kb == 1) ? 0.0 : unfix96(xl - sa - sb) + logN;
-  const double den = ha + hb;
-  r.NMI = den != 0.0 ? 2.0 * mi / den : 1.0;
-  r.F = fsum / Nd;
-  r.NVD = 1.0 - (double)smax / (2.0 * Nd);
-  r.RI = (double)(a11 + (A - X - Y + a11)) / (double)A;
-  // Eq. 6 with M = (a11+a10)(a11+a01)/A, numerator and denominator scaled by 2A:
-  // ARI = (2 A a11 - 2 X Y) / (A (X + Y) - 2 X Y), exact in 128-bit integers.
-  const __int128 XY = (__int128)X * (__int128)Y;
-  const __int128 anum = 2 * (__int128)A * (__int128)a11 - 2 * XY;
-  const __int128 aden = (__int128)A * (__int128)(X + Y) - 2 * XY;
-  r.ARI = aden != 0 ? i128_to_f64(anum) / i128_to_f64(aden) : 1.0;
-  const u64 jden = a11 + (X - a11) + (Y - a11);
-  r.JI = jden != 0 ? (double)a11 / (double)jden : 1.0;
-  r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
-  r.reserved = 0;
-  *out = r;
-}
 
 // ---------------------------------------------------------------------------
 // Batched scoring: many (graph, partition) tasks per launch.  Every stage of the
@@ -3455,10 +3501,8 @@ __global__ __launch_bounds__(FBLOCK) void k_b_final1(const TaskDev* __restrict__
   score_final1_body(d.L, d.N, d.D, d.I, d.NP, d.PEN, (double)d.nnz, pc, d.parts, (int)(blockIdx.x - Gpre[t]), d.G);
 }
 
-__global__ void k_b_final2(const TaskDev* __restrict__ td, int T) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T) return;
-  const TaskDev& d = td[t];
+__global__ __launch_bounds__(64) void k_b_final2(const TaskDev* __restrict__ td) {
+  const TaskDev& d = td[blockIdx.x];
   score_final2_body(d.G, d.parts, d.n, d.nnz, 0, d.ctl, d.out, 0u);
 }
 

@@ -34,7 +34,8 @@ struct cq_context {
   void* scratch = nullptr;  // device address of the library's scratch array on this device
   hipStream_t stream = nullptr;
   int num_cus = 256;
-  void* pinned = nullptr;  // host staging for result structs (hipHostMalloc)
+  void* pinned = nullptr;  // host memory the synchronous calls' results are written to (hipHostMalloc)
+  void* pinned_dev = nullptr;  // its device address
   u32* dscratch = nullptr; // 2 words used by graph checks
   char err[512] = {0};
   // stage timing
@@ -744,8 +745,8 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
     WScorePart* wparts = reinterpret_cast<WScorePart*>(parts);
     {
       StageMark mk(ctx, ST_FINAL, timed);
-      k_score_final1_w<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, wo.SW, wo.IW, wo.PENW, g->total_w, pc, wparts);
-      k_score_final2_w<<<1, 64, 0, s>>>(lay.G, wparts, n, nnz, g->total_w, vis.ecap, ctl, d_out, g->rpb ? 1u : 0u);
+      k_score_final_w<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, wo.SW, wo.IW, wo.PENW, g->total_w, pc, wparts, n, nnz, vis.ecap,
+                                               ctl, d_out, g->rpb ? 1u : 0u);
     }
     return;
   }
@@ -788,8 +789,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   }
   {
     StageMark mk(ctx, ST_FINAL, timed);
-    k_score_final1<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, PEN, (double)nnz, pc, parts);
-    k_score_final2<<<1, 64, 0, s>>>(lay.G, parts, n, nnz, vis.ecap, ctl, d_out, g->rpb ? 1u : 0u);
+    k_score_final<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, PEN, n, nnz, pc, parts, vis.ecap, ctl, d_out, g->rpb ? 1u : 0u);
   }
 }
 
@@ -881,8 +881,7 @@ void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels
   ScorePart* parts = at<ScorePart>(ws, lay.parts);
   {
     StageMark mk(ctx, ST_FINAL, timed);
-    k_score_final1<<<lay.G, FBLOCK, 0, s>>>(L, N, D, vis.I, vis.NP, vis.PEN, (double)g->nnz, pc, parts);
-    k_score_final2<<<1, 64, 0, s>>>(lay.G, parts, n, g->nnz, vis.ecap, ctl, d_out, 0u);
+    k_score_final<<<lay.G, FBLOCK, 0, s>>>(L, N, D, vis.I, vis.NP, vis.PEN, n, g->nnz, pc, parts, vis.ecap, ctl, d_out, 0u);
   }
 }
 
@@ -1014,9 +1013,8 @@ void compare_launch(cq_context* ctx, int32_t n, const int32_t* la, int32_t La, c
   CmpPart* parts = at<CmpPart>(ws, lay.parts);
   {
     StageMark mk(ctx, ST_FINAL, timed);
-    k_cmp_final1<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, vis.RA11, vis.RMAX, vis.RF, vis.RXL,
-                                                   (double)n, parts);
-    k_cmp_final2<<<1, 64, 0, s>>>(lay.Ga + lay.Gb, parts, n, vis.ecap, ctl, d_out, vis.wq);
+    k_cmp_final<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, vis.RA11, vis.RMAX, vis.RF, vis.RXL, n, parts,
+                                                   vis.ecap, ctl, d_out, vis.wq);
   }
 }
 
@@ -1097,8 +1095,8 @@ void compare_launch_wide(cq_context* ctx, int32_t n, const int32_t* la, int32_t 
   CmpPart* parts = at<CmpPart>(ws, lay.parts);
   {
     StageMark mk(ctx, ST_FINAL, timed);
-    k_cmp_final1<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, RA11, RMAX, RF, RXL, (double)n, parts);
-    k_cmp_final2<<<1, 64, 0, s>>>(lay.Ga + lay.Gb, parts, n, ecap, ctl, d_out, wq);
+    k_cmp_final<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, RA11, RMAX, RF, RXL, n, parts,
+                                                   ecap, ctl, d_out, wq);
   }
 }
 
@@ -1164,8 +1162,8 @@ void compare_launch_bands(cq_context* ctx, int32_t n, const int32_t* la, int32_t
   CmpPart* parts = at<CmpPart>(ws, lay.parts);
   {
     StageMark mk(ctx, ST_FINAL, timed);
-    k_cmp_final1<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, RA11, RMAX, RF, RXL, (double)n, parts);
-    k_cmp_final2<<<1, 64, 0, s>>>(lay.Ga + lay.Gb, parts, n, ecap, ctl, d_out, wq);
+    k_cmp_final<<<lay.Ga + lay.Gb, FBLOCK, 0, s>>>(La, Lb, lay.Ga, A, B, COLMAX, RA11, RMAX, RF, RXL, n, parts,
+                                                   ecap, ctl, d_out, wq);
   }
 }
 
@@ -1193,11 +1191,12 @@ cq_status compare_enqueue(cq_context* ctx, int32_t n, const int32_t* la, int32_t
   return launch_status(ctx, "compare launch");
 }
 
+// Waits for a synchronous call, whose last kernel wrote the result into the context's pinned
+// host memory (a copy of its own cost a launch: 10 us of a 50 us call).
 template <class R>
-cq_status fetch(cq_context* ctx, const void* d_res, R* h_out) {
-  hipError_t e = hipMemcpyAsync(ctx->pinned, d_res, sizeof(R), hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  if (e != hipSuccess) return fail(ctx, CQ_E_DEVICE, "result copy: %s", hipGetErrorString(e));
+cq_status fetch(cq_context* ctx, R* h_out) {
+  const hipError_t e = hipStreamSynchronize(ctx->stream);
+  if (e != hipSuccess) return fail(ctx, CQ_E_DEVICE, "waiting for the result: %s", hipGetErrorString(e));
   std::memcpy(h_out, ctx->pinned, sizeof(R));
   if (ctx->timing) collect_stage_times(ctx);
   return CQ_OK;
@@ -1470,7 +1469,7 @@ void batch_launch(cq_batch_plan* p, hipStream_t s, int rsel, int occ) {
     k_b_groups<GBLOCK_DIRECT><<<(unsigned)(p->ctx->num_cus * occ), GBLOCK_DIRECT, (size_t)lds_words * 4, s>>>(
         td, p->Kpre, T, p->wq + WQ_WORDS, lds_words, p->items, 0);
   k_b_final1<<<p->Gsum, FBLOCK, 0, s>>>(td, p->Gpre, T);
-  k_b_final2<<<grid_for(T, 64, 1u << 20), 64, 0, s>>>(td, T);
+  k_b_final2<<<T, 64, 0, s>>>(td);
 }
 
 
@@ -1920,6 +1919,7 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) == hipSuccess) ctx->num_cus = prop.multiProcessorCount;
   if (hipHostMalloc(&ctx->pinned, 4096, hipHostMallocDefault) != hipSuccess ||
+      hipHostGetDevicePointer(&ctx->pinned_dev, ctx->pinned, 0) != hipSuccess ||
       hipMalloc(&ctx->dscratch, 256) != hipSuccess) {
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
@@ -2176,12 +2176,10 @@ cq_status cq_score_partition(cq_context* ctx, const cq_graph* g, const int32_t* 
   if (!ctx) return CQ_E_INVALID_ARG;
   if (!h_out) return fail(ctx, CQ_E_INVALID_ARG, "null result pointer");
   if (!g) return fail(ctx, CQ_E_INVALID_ARG, "null graph");
-  const ScoreLayout lay = graph_score_layout(g, std::max(num_labels, 1));
-  ScoreResultDev* d_res = (d_ws && ws_bytes >= lay.total) ? at<ScoreResultDev>(d_ws, lay.res) : nullptr;
-  cq_status st = score_enqueue(ctx, g, d_labels, num_labels, d_ws, ws_bytes, d_res ? d_res : reinterpret_cast<ScoreResultDev*>(1),
+  cq_status st = score_enqueue(ctx, g, d_labels, num_labels, d_ws, ws_bytes, static_cast<ScoreResultDev*>(ctx->pinned_dev),
                                per_comm, pairs, true);
   if (st != CQ_OK) return st;
-  st = fetch(ctx, d_res, h_out);
+  st = fetch(ctx, h_out);
   if (st != CQ_OK) return st;
   return map_flags(ctx, h_out->device_flags);
 }
@@ -2212,12 +2210,10 @@ cq_status cq_compare_partitions(cq_context* ctx, int32_t n, const int32_t* d_lab
                                 cq_compare_result* h_out, const cq_cell_table* cells) {
   if (!ctx) return CQ_E_INVALID_ARG;
   if (!h_out) return fail(ctx, CQ_E_INVALID_ARG, "null result pointer");
-  const CmpLayout lay = cmp_layout(std::max(n, 2), std::max(num_labels_a, 1), std::max(num_labels_b, 1));
-  CmpResultDev* d_res = (d_ws && ws_bytes >= lay.total) ? at<CmpResultDev>(d_ws, lay.res) : nullptr;
   cq_status st = compare_enqueue(ctx, n, d_labels_a, num_labels_a, d_labels_b, num_labels_b, d_ws, ws_bytes,
-                                 d_res ? d_res : reinterpret_cast<CmpResultDev*>(1), cells, true);
+                                 static_cast<CmpResultDev*>(ctx->pinned_dev), cells, true);
   if (st != CQ_OK) return st;
-  st = fetch(ctx, d_res, h_out);
+  st = fetch(ctx, h_out);
   if (st != CQ_OK) return st;
   return map_flags(ctx, h_out->device_flags);
 }
