@@ -2736,8 +2736,8 @@ struct CmpVis {
 // result is bitwise reproducible.
 constexpr int FBLOCK = 256;
 
-// Block sums of NU u64, NX u128 and NF binary64 fields of an FBLOCK-thread block with one
-// barrier: a fixed butterfly in each wave, then thread 0 adds the waves in order, which
+// Block sums of NU u64, NX u128 and NF binary64 fields of the first FBLOCK threads of a
+// workgroup (all of its threads call) with one barrier: a fixed butterfly in each wave, then thread 0 adds the waves in order, which
 // gives each field the value a block sum of that field alone would.  The totals replace
 // the inputs in thread 0 only.
 template <int NU, int NX, int NF>
@@ -2754,7 +2754,7 @@ __device__ __forceinline__ void block_sum_fields(u64 (&u)[NU], u128 (&x)[NX], do
   for (int k = 0; k < NF; ++k)
     for (int o = 32; o > 0; o >>= 1) f[k] += __shfl_xor(f[k], o, 64);
   const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
+  if ((threadIdx.x & 63) == 0 && w < NW) {
 #pragma unroll
     for (int k = 0; k < NU; ++k) s_u[k][w] = u[k];
 #pragma unroll
@@ -2814,7 +2814,7 @@ __device__ void score_final1_body(int L, const u32* __restrict__ N, const u32* _
   u64 K = 0, sein = 0, seout = 0, sD2 = 0, np = 0;
   u128 pen = 0;
   double qds_a = 0, s_dens = 0, s_contr = 0, s_exp = 0, s_cond = 0;
-  for (int c = c0 + threadIdx.x; c < c1; c += FBLOCK) {
+  for (int c = threadIdx.x < FBLOCK ? c0 + (int)threadIdx.x : c1; c < c1; c += FBLOCK) {
     const u32 nc = N[c];
     int64_t o_size = 0, o_deg = 0, o_ein = 0, o_eout = 0;
     double o_d = 0, o_contr = 0, o_exp = 0, o_cond = 0, o_q = 0, o_qds = 0;
@@ -3126,10 +3126,9 @@ __device__ __forceinline__ double i128_to_f64(__int128 v) {
 
 // Stage 2, by one wave (see score_final2_body).
 __device__ void cmp_final2_body(int G, const CmpPart* __restrict__ parts, long long n, long long ecap, Ctl* __restrict__ ctl,
-                                CmpResultDev* __restrict__ out, u32* __restrict__ wq) {
+                                CmpResultDev* __restrict__ out, u64 cells) {
   __shared__ double s_f[1][FINAL_PARTS];
   const int lane = threadIdx.x & 63;
-  u64 cells = lane < (int)WQ_QUEUES ? *wq_sum(wq, (u32)lane) : 0;
   u64 Ka = 0, Kb = 0, a11 = 0, X = 0, Y = 0, smax = 0;
   u128 xl = 0, sa = 0, sb = 0;
   for (int b = lane; b < G; b += 64) {
@@ -3140,7 +3139,6 @@ __device__ void cmp_final2_body(int G, const CmpPart* __restrict__ parts, long l
     sb += ((u128)p.sb_hi << 64) | p.sb_lo;
     s_f[0][b] = p.fsum;
   }
-  cells = wave_sum_u64(cells);
   Ka = wave_sum_u64(Ka); Kb = wave_sum_u64(Kb); a11 = wave_sum_u64(a11); X = wave_sum_u64(X); Y = wave_sum_u64(Y);
   smax = wave_sum_u64(smax);
   xl = wave_sum_u128(xl); sa = wave_sum_u128(sa); sb = wave_sum_u128(sb);
@@ -3237,7 +3235,10 @@ __global__ __launch_bounds__(FBLOCK) void k_cmp_final(int La, int Lb, int Ga, co
     parts[blockIdx.x] = p;
   }
   if (!last_workgroup(&ctl->done2, gridDim.x)) return;
-  if (threadIdx.x < 64) cmp_final2_body(gridDim.x, parts, n, ecap, ctl, out, wq);
+  if (threadIdx.x < 64) {
+    const u64 cells = wave_sum_u64(threadIdx.x < WQ_QUEUES ? *wq_sum(wq, threadIdx.x) : 0ull);  // non-zero cells, per queue
+    cmp_final2_body(gridDim.x, parts, n, ecap, ctl, out, cells);
+  }
 }
 
 

@@ -22,6 +22,7 @@
 #include "cq_kernels.hpp"
 #include "cq_compare.hpp"
 #include "cq_rows.hpp"
+#include "cq_small.hpp"
 #include "srv_core.hpp"
 
 using namespace cq;
@@ -264,6 +265,8 @@ struct ScoreLayout {
   size_t CW, SW, IW, PENW, INVN;  // weighted graphs only (0 otherwise)
   bool rows;  // scored by member rows (cq_rows.hpp): rec and bad in place of the staged entries
   size_t rec, bad;
+  int small_wgs;  // > 0: scored in two launches (cq_small.hpp) by that many counting workgroups
+  size_t slots;
 };
 
 ScoreLayout score_layout(int64_t n, int64_t nnz, int64_t L, bool weighted = false, int64_t max_chunk = 65536,
@@ -319,6 +322,12 @@ ScoreLayout batch_task_layout(int64_t n, int64_t nnz, int64_t L) { return score_
 // labels fill one XCD's 4 MB L2.
 constexpr int64_t ROWS_MAX_N = 2 << 20;
 
+// Small graphs (cq_small.hpp): entries, entries per counting workgroup, and table cells that
+// the finishing workgroup adds up.
+constexpr int64_t SMALL_MAX_NNZ = 400000;
+constexpr int64_t SMALL_WG_NNZ = 2048;
+constexpr int64_t SMALL_MAX_CELLS = 256 << 10;
+
 // The layout of one scoring call on graph g (the node pass it takes decides the chunk).
 // Member rows take the workspace of the staged path (which they fit unless the graph has
 // hardly any edges).
@@ -328,6 +337,14 @@ ScoreLayout graph_score_layout(const cq_graph* g, int64_t L) {
   if (g->rpb || g->w || L > DIRECT_MAX || g->n > ROWS_MAX_N) return s;
   ScoreLayout r = s;
   Carve c;
+  if (g->n <= SS_MAX_N && L <= SS_MAX_L && g->nnz <= SMALL_MAX_NNZ) {
+    const int64_t cap = std::min<int64_t>(SMALL_MAX_CELLS / ss_words((int)L), (int64_t)(s.total / (4 * (size_t)ss_words((int)L))));
+    r.small_wgs = (int)std::min<int64_t>(std::min<int64_t>(cap, SS_MAX_WG), (g->nnz + SMALL_WG_NNZ - 1) / SMALL_WG_NNZ);
+    if (r.small_wgs > 0) {
+      r.slots = 0;
+      return r;
+    }
+  }
   r.rows = true;
   r.ctl = c.take(sizeof(Ctl));
   r.wq = c.take(WQ_BYTES);
@@ -815,6 +832,31 @@ struct RowsTag {  // one shape of k_rows_groups
   }
 };
 
+// A small graph scored in two launches (cq_small.hpp).
+void score_launch_small(cq_context* ctx, const cq_graph* g, const int32_t* labels, int32_t L, void* ws, const ScoreLayout& lay,
+                        ScoreResultDev* d_out, const cq_per_community* per_comm, const cq_pair_table* pairs, bool timed) {
+  hipStream_t s = ctx->stream;
+  u32* slots = at<u32>(ws, lay.slots);
+  {
+    StageMark mk(ctx, ST_NODE, timed);
+    k_small_count<<<lay.small_wgs, SS_THREADS, ss_lds(g->n, L), s>>>(g->n, labels, g->perm, g->rp, g->col, L, slots);
+  }
+  ScoreVis vis;
+  std::memset(&vis, 0, sizeof(vis));
+  vis.twom = (double)g->nnz;
+  vis.eci = pairs ? pairs->ci : nullptr;
+  vis.ecj = pairs ? pairs->cj : nullptr;
+  vis.ecnt = pairs ? pairs->count : nullptr;
+  vis.ecap = pairs ? pairs->capacity : 0;
+  PerComm pc;
+  std::memset(&pc, 0, sizeof(pc));
+  if (per_comm) std::memcpy(&pc, per_comm, sizeof(pc));
+  {
+    StageMark mk(ctx, ST_FINAL, timed);
+    k_small_final<<<1, SF_THREADS, 4 * (size_t)ss_cells(L), s>>>(L, lay.small_wgs, slots, vis, g->n, g->nnz, pc, d_out);
+  }
+}
+
 // A graph scored by member rows (cq_rows.hpp).
 void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels, int32_t L, void* ws, const ScoreLayout& lay,
                        ScoreResultDev* d_out, const cq_per_community* per_comm, const cq_pair_table* pairs, bool timed) {
@@ -900,7 +942,9 @@ cq_status score_enqueue(cq_context* ctx, const cq_graph* g, const int32_t* label
   if (!ws || ws_bytes < lay.total)
     return fail(ctx, CQ_E_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, lay.total);
   if (reinterpret_cast<uintptr_t>(ws) % WS_ALIGN) return fail(ctx, CQ_E_INVALID_ARG, "workspace not 16-byte aligned");
-  if (lay.rows)
+  if (lay.small_wgs > 0)
+    score_launch_small(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
+  else if (lay.rows)
     score_launch_rows(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
   else if (lay.small)
     score_launch<uint16_t>(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
@@ -1180,7 +1224,12 @@ cq_status compare_enqueue(cq_context* ctx, int32_t n, const int32_t* la, int32_t
   if (!ws || ws_bytes < lay.total)
     return fail(ctx, CQ_E_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, lay.total);
   if (reinterpret_cast<uintptr_t>(ws) % WS_ALIGN) return fail(ctx, CQ_E_INVALID_ARG, "workspace not 16-byte aligned");
-  if (lay.bands)
+  if (n <= SC_MAX_N && La <= SC_MAX_L && Lb <= SC_MAX_L && (int64_t)La * Lb <= SC_MAX_CELLS) {
+    StageMark mk(ctx, ST_GROUPS, timed);
+    k_small_compare<<<1, SC_THREADS, sc_lds(La, Lb), ctx->stream>>>(n, la, La, lb, Lb, cells ? cells->ci : nullptr,
+                                                                    cells ? cells->cj : nullptr, cells ? cells->count : nullptr,
+                                                                    cells ? cells->capacity : 0, d_out);
+  } else if (lay.bands)
     compare_launch_bands(ctx, n, la, La, lb, Lb, ws, lay, d_out, cells, timed);
   else if (lay.wide)
     compare_launch_wide(ctx, n, la, La, lb, Lb, ws, lay, d_out, cells, timed);
@@ -1954,6 +2003,9 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 512, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 256, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
+  set_big_lds(reinterpret_cast<const void*>(k_small_count), ss_lds(SS_MAX_N, SS_MAX_L));
+  set_big_lds(reinterpret_cast<const void*>(k_small_final), 4 * (size_t)ss_cells(SS_MAX_L));
+  set_big_lds(reinterpret_cast<const void*>(k_small_compare), 4 * (size_t)SC_MAX_CELLS + 24 * (size_t)SC_MAX_L + 64);
   set_big_lds(reinterpret_cast<const void*>(k_b_node), 2 * PRIV_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_b_groups<GBLOCK_DIRECT>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_b_groups<GBLOCK_SMALL>), gl);
