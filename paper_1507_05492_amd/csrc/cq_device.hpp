@@ -187,56 +187,87 @@ __device__ __forceinline__ double unfixw(u128 v) {
 }
 
 // ---- wave / block reductions (wave64) ---------------------------------------
-__device__ __forceinline__ u64 wave_sum_u64(u64 x) {
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+// Every lane of the wave must be active.  A sum of 64 lanes is a butterfly: lanes 32, 16, 8,
+// 4, 2 and 1 apart exchange values.  The exchanges are lane swaps and DPP moves of a few
+// cycles; as LDS permutes (__shfl_xor) each step waited for the LDS (about 100 cycles), and
+// the reductions were most of the kernels that finish a small call.
+template <int CTRL>
+__device__ __forceinline__ u32 dpp_u32(u32 x) {
+  return (u32)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+}
+// the value of lane ^ M (M = 1, 2, 4, 8)
+template <int M>
+__device__ __forceinline__ u32 lane_xor(u32 x) {
+  if constexpr (M == 1) return dpp_u32<0xB1>(x);        // quad_perm [1,0,3,2]
+  else if constexpr (M == 2) return dpp_u32<0x4E>(x);   // quad_perm [2,3,0,1]
+  else if constexpr (M == 4) return dpp_u32<0x1B>(dpp_u32<0x141>(x));  // row_half_mirror, then quad_perm [3,2,1,0]
+  else return dpp_u32<0x128>(x);                        // row_ror:8
+}
+// the values of the lanes 32 (16) apart as an unordered pair, the same pair in both lanes
+__device__ __forceinline__ void pair32(u32 x, u32& a, u32& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void pair16(u32 x, u32& a, u32& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  a = r[0];
+  b = r[1];
+}
+// Butterfly over T (words of 32 bits) with a commutative operation f(T, T).
+template <class T, class F>
+__device__ __forceinline__ T wave_butterfly(T x, F f) {
+  constexpr int W = sizeof(T) / 4;
+  struct Words { u32 w[W]; };
+  auto step = [&](auto exchange) {
+    const Words v = __builtin_bit_cast(Words, x);
+    Words a, b;
+#pragma unroll
+    for (int i = 0; i < W; ++i) exchange(v.w[i], a.w[i], b.w[i]);
+    x = f(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
+  };
+  step([](u32 v, u32& a, u32& b) { pair32(v, a, b); });
+  step([](u32 v, u32& a, u32& b) { pair16(v, a, b); });
+  step([](u32 v, u32& a, u32& b) { a = v; b = lane_xor<8>(v); });
+  step([](u32 v, u32& a, u32& b) { a = v; b = lane_xor<4>(v); });
+  step([](u32 v, u32& a, u32& b) { a = v; b = lane_xor<2>(v); });
+  step([](u32 v, u32& a, u32& b) { a = v; b = lane_xor<1>(v); });
   return x;
+}
+__device__ __forceinline__ u64 wave_sum_u64(u64 x) {
+  return wave_butterfly(x, [](u64 a, u64 b) { return a + b; });
+}
+__device__ __forceinline__ u32 wave_sum_u32(u32 x) {
+  return wave_butterfly(x, [](u32 a, u32 b) { return a + b; });
 }
 __device__ __forceinline__ u64 wave_max_u64(u64 x) {
-  for (int o = 32; o > 0; o >>= 1) { u64 y = __shfl_xor(x, o, 64); x = y > x ? y : x; }
-  return x;
+  return wave_butterfly(x, [](u64 a, u64 b) { return a > b ? a : b; });
 }
 __device__ __forceinline__ u32 wave_max_u32(u32 x) {
-  for (int o = 32; o > 0; o >>= 1) { u32 y = __shfl_xor(x, o, 64); x = y > x ? y : x; }
-  return x;
+  return wave_butterfly(x, [](u32 a, u32 b) { return a > b ? a : b; });
 }
 __device__ __forceinline__ double wave_max_f64(double x) {
-  for (int o = 32; o > 0; o >>= 1) { double y = __shfl_xor(x, o, 64); x = y > x ? y : x; }
-  return x;
+  return wave_butterfly(x, [](double a, double b) { return a > b ? a : b; });
+}
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  return wave_butterfly(x, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ u128 wave_sum_u128(u128 x) {
-  u64 lo = (u64)x, hi = (u64)(x >> 64);
-  for (int o = 32; o > 0; o >>= 1) {
-    u64 lo2 = __shfl_xor(lo, o, 64), hi2 = __shfl_xor(hi, o, 64);
-    u64 s = lo + lo2;
-    hi = hi + hi2 + (s < lo ? 1ull : 0ull);
-    lo = s;
-  }
-  return ((u128)hi << 64) | lo;
+  struct P { u64 lo, hi; };
+  const P r = wave_butterfly(P{(u64)x, (u64)(x >> 64)}, [](P a, P b) {
+    const u64 lo = a.lo + b.lo;
+    return P{lo, a.hi + b.hi + (lo < a.lo ? 1ull : 0ull)};
+  });
+  return ((u128)r.hi << 64) | r.lo;
 }
-// Deterministic double sum over a block: a fixed butterfly inside each wave, then
-// wave totals combined in wave order by thread 0.  The result depends only on which
-// thread held which value, never on timing.
-template <int NW>
-__device__ __forceinline__ double block_sum_f64(double x, double* sh) {
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[w] = x;
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < NW; ++i) r += sh[i];
-  }
-  __syncthreads();
-  return r;  // valid in thread 0
-}
-
-// inclusive scan of u32 inside a wave
+// inclusive scan of u32 inside a wave (row shifts, then each row's last lane added to the rows after it)
 __device__ __forceinline__ u32 wave_incl_scan(u32 x) {
-  int lane = threadIdx.x & 63;
-  for (int o = 1; o < 64; o <<= 1) {
-    u32 y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  x += dpp_u32<0x111>(x);  // row_shr:1
+  x += dpp_u32<0x112>(x);
+  x += dpp_u32<0x114>(x);
+  x += dpp_u32<0x118>(x);
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15 to rows 1 and 3
+  x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31 to rows 2 and 3
   return x;
 }
 

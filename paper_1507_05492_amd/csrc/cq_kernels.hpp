@@ -2314,29 +2314,6 @@ __global__ __launch_bounds__(64 * GW_WAVES) void k_groups_wave(const uint16_t* _
   }
 }
 
-// block reduction helpers for the visitors (GBLOCK threads)
-__device__ __forceinline__ u128 block_sum_u128(u128 x, u64* sh_lo, u64* sh_hi) {
-  x = wave_sum_u128(x);
-  int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) { sh_lo[w] = (u64)x; sh_hi[w] = (u64)(x >> 64); }
-  __syncthreads();
-  u128 r = 0;
-  if (threadIdx.x == 0)
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r += ((u128)sh_hi[i] << 64) | sh_lo[i];
-  __syncthreads();
-  return r;
-}
-__device__ __forceinline__ u64 block_sum_u64(u64 x, u64* sh) {
-  x = wave_sum_u64(x);
-  int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[w] = x;
-  __syncthreads();
-  u64 r = 0;
-  if (threadIdx.x == 0)
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r += sh[i];
-  __syncthreads();
-  return r;
-}
 // Score visitor: for community g, label j with count x in g's segment:
 //   j == g  ->  x = 2|E_g^in|
 //   j != g  ->  x = |E_{g,j}|; contributes |E_gj|/(2|E|) * |E_gj|/(|g||j|) to g's
@@ -2751,8 +2728,7 @@ __device__ __forceinline__ void block_sum_fields(u64 (&u)[NU], u128 (&x)[NX], do
 #pragma unroll
   for (int k = 0; k < NX; ++k) x[k] = wave_sum_u128(x[k]);
 #pragma unroll
-  for (int k = 0; k < NF; ++k)
-    for (int o = 32; o > 0; o >>= 1) f[k] += __shfl_xor(f[k], o, 64);
+  for (int k = 0; k < NF; ++k) f[k] = wave_sum_f64(f[k]);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0 && w < NW) {
 #pragma unroll
@@ -2903,6 +2879,37 @@ __device__ __forceinline__ double sum_fields_in_order(const double (&f)[NF][FINA
   return t;
 }
 
+// The metrics from the sums over all communities (one thread).
+__device__ void score_metrics(const ScorePart& t, long long n, long long twom, long long ecap, Ctl* __restrict__ ctl,
+                              ScoreResultDev* __restrict__ out, u32 blocked) {
+  const long long m = twom / 2;
+  ScoreResultDev r;
+  r.n = n; r.m = m; r.K = (int64_t)t.K; r.num_pairs = (int64_t)t.np;
+  r.sum_ein = (int64_t)t.sein; r.sum_eout = (int64_t)t.seout; r.sum_degsum_sq = t.sD2;
+  // Eq. 8 summed over communities: sum_c E_c/m - (D_c/2m)^2 = (4 m sum_c E_c - sum_c D_c^2) / (4 m^2),
+  // evaluated from exact integers with a single rounding of numerator and denominator.
+  const long long qnum = 4ll * m * (long long)t.sein - (long long)t.sD2;
+  r.Q = (double)qnum / (double)(4ull * (u64)m * (u64)m);
+  const double p = unfix96(((u128)t.pen_hi << 64) | t.pen_lo);
+  r.split_penalty = p;
+  r.Qds = t.qds_a - p;
+  const double Kd = (double)t.K;
+  r.mean_intra_edges = (double)t.sein / Kd;
+  r.mean_intra_density = t.s_dens / Kd;
+  r.mean_contraction = t.s_contr / Kd;
+  r.mean_inter_edges = (double)t.seout / Kd;
+  r.mean_expansion = t.s_exp / Kd;
+  r.mean_conductance = t.s_cond / Kd;
+  r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
+  r.weighted = 0;
+  r.total_weight = (double)m;
+  r.sum_w_in = (double)t.sein;
+  r.sum_w_out = (double)t.seout;
+  r.staging = staging_of(ctl, blocked);
+  r.reserved = 0;
+  *out = r;
+}
+
 // Stage 2 of the final reduction, by one wave: each lane takes every 64th part; integers are
 // summed across the wave, doubles in the order of the parts.
 __device__ void score_final2_body(int G, const ScorePart* __restrict__ parts, long long n, long long twom, long long ecap,
@@ -2923,32 +2930,11 @@ __device__ void score_final2_body(int G, const ScorePart* __restrict__ parts, lo
   const double qds_a = __shfl(sum, 0, 64), s_dens = __shfl(sum, 1, 64), s_contr = __shfl(sum, 2, 64);
   const double s_exp = __shfl(sum, 3, 64), s_cond = __shfl(sum, 4, 64);
   if (lane != 0) return;
-  const long long m = twom / 2;
-  ScoreResultDev r;
-  r.n = n; r.m = m; r.K = (int64_t)K; r.num_pairs = (int64_t)np;
-  r.sum_ein = (int64_t)sein; r.sum_eout = (int64_t)seout; r.sum_degsum_sq = sD2;
-  // Eq. 8 summed over communities: sum_c E_c/m - (D_c/2m)^2 = (4 m sum_c E_c - sum_c D_c^2) / (4 m^2),
-  // evaluated from exact integers with a single rounding of numerator and denominator.
-  const long long qnum = 4ll * m * (long long)sein - (long long)sD2;
-  r.Q = (double)qnum / (double)(4ull * (u64)m * (u64)m);
-  const double p = unfix96(pen);
-  r.split_penalty = p;
-  r.Qds = qds_a - p;
-  const double Kd = (double)K;
-  r.mean_intra_edges = (double)sein / Kd;
-  r.mean_intra_density = s_dens / Kd;
-  r.mean_contraction = s_contr / Kd;
-  r.mean_inter_edges = (double)seout / Kd;
-  r.mean_expansion = s_exp / Kd;
-  r.mean_conductance = s_cond / Kd;
-  r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
-  r.weighted = 0;
-  r.total_weight = (double)m;
-  r.sum_w_in = (double)sein;
-  r.sum_w_out = (double)seout;
-  r.staging = staging_of(ctl, blocked);
-  r.reserved = 0;
-  *out = r;
+  ScorePart t;
+  t.K = K; t.sein = sein; t.seout = seout; t.sD2 = sD2; t.np = np;
+  t.pen_lo = (u64)pen; t.pen_hi = (u64)(pen >> 64);
+  t.qds_a = qds_a; t.s_dens = s_dens; t.s_contr = s_contr; t.s_exp = s_exp; t.s_cond = s_cond;
+  score_metrics(t, n, twom, ecap, ctl, out, blocked);
 }
 
 // Weighted final reduction (see group_one_w): per community the Eq. 8 and Eq. 9
@@ -3124,26 +3110,9 @@ __device__ __forceinline__ double i128_to_f64(__int128 v) {
   return neg ? -d : d;
 }
 
-// Stage 2, by one wave (see score_final2_body).
-__device__ void cmp_final2_body(int G, const CmpPart* __restrict__ parts, long long n, long long ecap, Ctl* __restrict__ ctl,
-                                CmpResultDev* __restrict__ out, u64 cells) {
-  __shared__ double s_f[1][FINAL_PARTS];
-  const int lane = threadIdx.x & 63;
-  u64 Ka = 0, Kb = 0, a11 = 0, X = 0, Y = 0, smax = 0;
-  u128 xl = 0, sa = 0, sb = 0;
-  for (int b = lane; b < G; b += 64) {
-    const CmpPart p = parts[b];
-    Ka += p.Ka; Kb += p.Kb; a11 += p.a11; X += p.X; Y += p.Y; smax += p.smax;
-    xl += ((u128)p.xl_hi << 64) | p.xl_lo;
-    sa += ((u128)p.sa_hi << 64) | p.sa_lo;
-    sb += ((u128)p.sb_hi << 64) | p.sb_lo;
-    s_f[0][b] = p.fsum;
-  }
-  Ka = wave_sum_u64(Ka); Kb = wave_sum_u64(Kb); a11 = wave_sum_u64(a11); X = wave_sum_u64(X); Y = wave_sum_u64(Y);
-  smax = wave_sum_u64(smax);
-  xl = wave_sum_u128(xl); sa = wave_sum_u128(sa); sb = wave_sum_u128(sb);
-  const double fsum = sum_fields_in_order(s_f, G);  // lane 0 holds the one field
-  if (lane != 0) return;
+// The metrics from the sums over all communities of both sides (one thread).
+__device__ void cmp_metrics(u64 Ka, u64 Kb, u64 a11, u64 X, u64 Y, u64 smax, u128 xl, u128 sa, u128 sb, double fsum, u64 cells,
+                            long long n, long long ecap, Ctl* __restrict__ ctl, CmpResultDev* __restrict__ out) {
   const double Nd = (double)n;
   const u64 A = (u64)n * (u64)(n - 1) / 2u;
   CmpResultDev r;
@@ -3176,6 +3145,28 @@ __device__ void cmp_final2_body(int G, const CmpPart* __restrict__ parts, long l
   r.device_flags = ctl->flags | ((ecap > 0 && (long long)ctl->export_count > ecap) ? F_EXPORT : 0u);
   r.reserved = 0;
   *out = r;
+}
+
+// Stage 2, by one wave (see score_final2_body).
+__device__ void cmp_final2_body(int G, const CmpPart* __restrict__ parts, long long n, long long ecap, Ctl* __restrict__ ctl,
+                                CmpResultDev* __restrict__ out, u64 cells) {
+  __shared__ double s_f[1][FINAL_PARTS];
+  const int lane = threadIdx.x & 63;
+  u64 Ka = 0, Kb = 0, a11 = 0, X = 0, Y = 0, smax = 0;
+  u128 xl = 0, sa = 0, sb = 0;
+  for (int b = lane; b < G; b += 64) {
+    const CmpPart p = parts[b];
+    Ka += p.Ka; Kb += p.Kb; a11 += p.a11; X += p.X; Y += p.Y; smax += p.smax;
+    xl += ((u128)p.xl_hi << 64) | p.xl_lo;
+    sa += ((u128)p.sa_hi << 64) | p.sa_lo;
+    sb += ((u128)p.sb_hi << 64) | p.sb_lo;
+    s_f[0][b] = p.fsum;
+  }
+  Ka = wave_sum_u64(Ka); Kb = wave_sum_u64(Kb); a11 = wave_sum_u64(a11); X = wave_sum_u64(X); Y = wave_sum_u64(Y);
+  smax = wave_sum_u64(smax);
+  xl = wave_sum_u128(xl); sa = wave_sum_u128(sa); sb = wave_sum_u128(sb);
+  const double fsum = sum_fields_in_order(s_f, G);  // lane 0 holds the one field
+  if (lane == 0) cmp_metrics(Ka, Kb, a11, X, Y, smax, xl, sa, sb, fsum, cells, n, ecap, ctl, out);
 }
 
 __global__ __launch_bounds__(FBLOCK) void k_cmp_final(int La, int Lb, int Ga, const u32* __restrict__ A, const u32* __restrict__ B,

@@ -99,7 +99,7 @@ __global__ __launch_bounds__(SF_THREADS) void k_small_final(int L, int wgs, cons
                                                             ScoreResultDev* __restrict__ out) {
   static_assert(SS_MAX_L <= 4 * 64 && SS_MAX_L <= 512, "one table word per lane");
   extern __shared__ u32 s_tab[];
-  __shared__ u32 s_N[SS_MAX_L + 4], s_D[SS_MAX_L], s_I[SS_MAX_L], s_NP[SS_MAX_L];
+  __shared__ u32 s_N[SS_MAX_L], s_D[SS_MAX_L], s_I[SS_MAX_L], s_NP[SS_MAX_L];
   __shared__ u64 s_PEN[2 * SS_MAX_L];
   __shared__ Ctl s_ctl;
   __shared__ ScorePart s_part;
@@ -108,13 +108,18 @@ __global__ __launch_bounds__(SF_THREADS) void k_small_final(int L, int wgs, cons
   if (tid < (int)(sizeof(Ctl) / 4)) reinterpret_cast<u32*>(&s_ctl)[tid] = 0;
   __syncthreads();
   for (int i = tid; i < words; i += SF_THREADS) {
-    u32 t = 0;
-    for (int w = 0; w < wgs; ++w) t += slots[(size_t)w * words + i];
-    if (i < cells) s_tab[i] = t;
-    else if (t) s_ctl.flags = F_LABEL;
+    u32 x[SS_MAX_WG], t = 0;
+#pragma unroll
+    for (int w = 0; w < SS_MAX_WG; ++w) x[w] = w < wgs ? slots[(size_t)w * words + i] : 0u;  // all loads in flight
+#pragma unroll
+    for (int w = 0; w < SS_MAX_WG; ++w) t += x[w];
+    if (i < cells) {
+      s_tab[i] = t;
+      if (i % (L + 1) == L) s_N[i / (L + 1)] = t;
+    } else if (t) {
+      s_ctl.flags = F_LABEL;
+    }
   }
-  __syncthreads();
-  for (int c = tid; c < SS_MAX_L + 4; c += SF_THREADS) s_N[c] = c < L ? s_tab[c * (L + 1) + L] : 0u;
   __syncthreads();
   vis.N = s_N;
   vis.I = s_I;
@@ -134,7 +139,7 @@ __global__ __launch_bounds__(SF_THREADS) void k_small_final(int L, int wgs, cons
       if (x && j != g) vis.visit_n(st, (u32)j, x, s_N[j]);
     }
     vis.settle(st);
-    const u32 deg = (u32)wave_sum_u64(d);
+    const u32 deg = wave_sum_u32(d);
     if (lane == 0) {
       s_I[g] = row[g];
       s_D[g] = deg;
@@ -143,8 +148,7 @@ __global__ __launch_bounds__(SF_THREADS) void k_small_final(int L, int wgs, cons
   }
   __syncthreads();
   score_final1_body(L, s_N, s_D, s_I, s_NP, s_PEN, (double)twom, pc, &s_part, 0, 1);
-  __syncthreads();
-  if (tid < 64) score_final2_body(1, &s_part, n, twom, vis.ecap, &s_ctl, out, 0u);
+  if (tid == 0) score_metrics(s_part, n, twom, vis.ecap, &s_ctl, out, 0u);  // thread 0 wrote s_part
 }
 
 // ---- comparison ----------------------------------------------------------------
@@ -171,7 +175,6 @@ __global__ __launch_bounds__(SC_THREADS) void k_small_compare(int n, const int32
   u32* s_b = r_max + La;
   u32* c_max = s_b + Lb;
   __shared__ Ctl s_ctl;
-  __shared__ CmpPart s_part;
   __shared__ u64 s_u[8][SC_THREADS / 64], s_x[6][SC_THREADS / 64];
   __shared__ double s_fs[SC_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -195,22 +198,11 @@ __global__ __launch_bounds__(SC_THREADS) void k_small_compare(int n, const int32
       const bool ok = (u32)a[k] < (u32)La && (u32)b[k] < (u32)Lb;
       bad |= in && !ok;
       (void)wave_count<1>(s_cell, (u32)(a[k] * Lb + b[k]), in && ok);
+      (void)wave_count<1>(s_a, (u32)a[k], in && ok);
+      (void)wave_count<1>(s_b, (u32)b[k], in && ok);
     }
   }
   if (bad) s_ctl.flags = F_LABEL;
-  __syncthreads();
-  // row and column sums, one wave per row and one thread per column
-  for (int i = wv; i < La; i += SC_THREADS / 64) {
-    u32 t = 0;
-    for (int j = lane; j < Lb; j += 64) t += s_cell[i * Lb + j];
-    t = (u32)wave_sum_u64(t);
-    if (lane == 0) s_a[i] = t;
-  }
-  for (int j = tid; j < Lb; j += SC_THREADS) {
-    u32 t = 0;
-    for (int i = 0; i < La; ++i) t += s_cell[i * Lb + j];
-    s_b[j] = t;
-  }
   __syncthreads();
   const double Nd = (double)n;
   u64 nz = 0, a11 = 0;
@@ -235,34 +227,37 @@ __global__ __launch_bounds__(SC_THREADS) void k_small_compare(int n, const int32
       }
     }
   }
-  __syncthreads();
+  // entropy terms beside the cells: rows from the last thread down, columns from the first up
   u64 Ka = 0, Kb = 0, X = 0, Y = 0, smax = 0;
   u128 sa = 0, sb = 0;
-  double fsum = 0.0;
-  for (int i = tid; i < La; i += SC_THREADS) {
+  for (int i = SC_THREADS - 1 - tid; i < La; i += SC_THREADS) {
     const u32 ai = s_a[i];
     if (ai == 0) continue;
     Ka += 1;
-    smax += r_max[i];
     X += (u64)ai * (u64)(ai - 1u) / 2u;
-    fsum += (double)ai * __longlong_as_double((long long)r_f[i]);
     sa += fix96((double)ai / Nd * log((double)ai));
   }
   for (int j = tid; j < Lb; j += SC_THREADS) {
     const u32 bj = s_b[j];
     if (bj == 0) continue;
     Kb += 1;
-    smax += c_max[j];
     Y += (u64)bj * (u64)(bj - 1u) / 2u;
     sb += fix96((double)bj / Nd * log((double)bj));
   }
+  __syncthreads();
+  double fsum = 0.0;
+  for (int i = tid; i < La; i += SC_THREADS) {
+    smax += r_max[i];
+    fsum += (double)s_a[i] * __longlong_as_double((long long)r_f[i]);  // 0 for an empty row
+  }
+  for (int j = tid; j < Lb; j += SC_THREADS) smax += c_max[j];
   u64 u[8] = {Ka, Kb, a11, X, Y, smax, nz, 0};
   u128 x3[3] = {xl.value(), sa, sb};
 #pragma unroll
   for (int k = 0; k < 7; ++k) u[k] = wave_sum_u64(u[k]);
 #pragma unroll
   for (int k = 0; k < 3; ++k) x3[k] = wave_sum_u128(x3[k]);
-  for (int o = 32; o > 0; o >>= 1) fsum += __shfl_xor(fsum, o, 64);
+  fsum = wave_sum_f64(fsum);
   if (lane == 0) {
 #pragma unroll
     for (int k = 0; k < 7; ++k) s_u[k][wv] = u[k];
@@ -283,18 +278,10 @@ __global__ __launch_bounds__(SC_THREADS) void k_small_compare(int n, const int32
   for (int k = 0; k < 3; ++k) x3[k] = wave_sum_u128(lane < NW ? ((u128)s_x[2 * k + 1][lane] << 64) | s_x[2 * k][lane] : (u128)0);
   if (lane == 0) {
     double t = 0.0;
+#pragma unroll
     for (int i = 0; i < NW; ++i) t += s_fs[i];
-    CmpPart p;
-    p.Ka = u[0]; p.Kb = u[1]; p.a11 = u[2]; p.X = u[3]; p.Y = u[4]; p.smax = u[5];
-    p.xl_lo = (u64)x3[0]; p.xl_hi = (u64)(x3[0] >> 64);
-    p.sa_lo = (u64)x3[1]; p.sa_hi = (u64)(x3[1] >> 64);
-    p.sb_lo = (u64)x3[2]; p.sb_hi = (u64)(x3[2] >> 64);
-    p.fsum = t;
-    p.pad[0] = p.pad[1] = p.pad[2] = 0;
-    s_part = p;
+    cmp_metrics(u[0], u[1], u[2], u[3], u[4], u[5], x3[0], x3[1], x3[2], t, u[6], n, ecap, &s_ctl, out);
   }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  cmp_final2_body(1, &s_part, n, ecap, &s_ctl, out, u[6]);
 }
 
 }  // namespace cq
