@@ -52,24 +52,13 @@ constexpr u32 WQ_WAVE = 2 * WQ_QUEUES * WQ_LINE;  // word offset of the wave pas
 
 // Next item for the calling workgroup (thread 0 only), or 0xFFFFFFFF when every queue is
 // empty.  q and left are thread 0's own state: start with q = blockIdx.x % 8, left = 8.
-// When its queue is empty, the other counters are read together (counters only grow, so a
-// queue seen empty stays empty) and the next queue that may hold work is tried: one round
-// trip instead of one atomic per queue at the end of every persistent kernel.
 __device__ __forceinline__ u32 wq_next(u32* __restrict__ wq, u32 K, u32& q, u32& left) {
   while (left) {
     const u32 i = atomicAdd(&wq[q * WQ_LINE], 1u);
     const u64 item = (u64)q + (u64)WQ_QUEUES * i;
     if (item < K) return (u32)item;
-    u32 c[WQ_QUEUES];
-#pragma unroll
-    for (u32 k = 1; k < WQ_QUEUES; ++k)
-      c[k] = __hip_atomic_load(&wq[((q + k) % WQ_QUEUES) * WQ_LINE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    u32 step = left;  // no queue left
-#pragma unroll
-    for (u32 k = WQ_QUEUES - 1; k > 0; --k)
-      if (k < left && (u64)((q + k) % WQ_QUEUES) + (u64)WQ_QUEUES * c[k] < K) step = k;
-    q = (q + step) % WQ_QUEUES;
-    left -= step;
+    q = (q + 1u) % WQ_QUEUES;
+    --left;
   }
   return 0xFFFFFFFFu;
 }
