@@ -14,7 +14,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "csrc", "cq_lib.hip")
-DEPS = [os.path.join(HERE, "csrc", f) for f in ("cq_device.hpp", "cq_kernels.hpp", "cq_compare.hpp", "cq_rows.hpp", "cq_small.hpp", "srv_core.hpp")] + [os.path.join(ROOT, "include", "cq.h")]
+DEPS = [os.path.join(HERE, "csrc", f) for f in ("cq_device.hpp", "cq_kernels.hpp", "cq_compare.hpp", "cq_rows.hpp", "cq_small.hpp", "cq_tiles.hpp", "srv_core.hpp")] + [os.path.join(ROOT, "include", "cq.h")]
 OUT = os.path.join(HERE, "libcq.so")
 ARCH = "gfx950"
 

@@ -303,66 +303,6 @@ __global__ __launch_bounds__(256) void k_relabel_rows(int n, const int32_t* __re
   }
 }
 
-// Column blocks of the renumbered graph.  The id range is cut into COL_BLOCKS spans of
-// `span` ids; block y holds, row by row, the entries whose neighbour lies in span y, as
-// its own CSR whose row pointers RPB[y*(n+1) + u] index one array colb shared by all
-// blocks (block y's entries follow block y-1's); rowb holds the row of every entry.
-// One wave per row.
-constexpr int COL_BLOCKS = 8;
-
-__global__ __launch_bounds__(256) void k_blk_count(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                   int span, u32* __restrict__ cnt) {
-  const int lane = threadIdx.x & 63;
-  const size_t wave = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const size_t nwaves = ((size_t)gridDim.x * blockDim.x) >> 6;
-  for (size_t u = wave; u < (size_t)n; u += nwaves) {
-    const int a = rp[u], deg = rp[u + 1] - a;
-    u32 mine = 0;  // lane y < COL_BLOCKS counts block y
-    for (int k0 = 0; k0 < deg; k0 += 64) {
-      const int y = k0 + lane < deg ? col[a + k0 + lane] / span : -1;
-#pragma unroll
-      for (int b = 0; b < COL_BLOCKS; ++b) {
-        const u32 c = (u32)__popcll(__ballot(y == b));
-        if (lane == b) mine += c;
-      }
-    }
-    if (lane < COL_BLOCKS) cnt[(size_t)lane * ((size_t)n + 1) + u] = mine;
-    if (u == 0 && lane < COL_BLOCKS) cnt[(size_t)lane * ((size_t)n + 1) + n] = 0;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_blk_place(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                   int span, const u32* __restrict__ RPB, int32_t* __restrict__ colb,
-                                                   int32_t* __restrict__ rowb, const float* __restrict__ w,
-                                                   float* __restrict__ wb) {
-  const int lane = threadIdx.x & 63;
-  const u64 below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const size_t wave = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const size_t nwaves = ((size_t)gridDim.x * blockDim.x) >> 6;
-  for (size_t u = wave; u < (size_t)n; u += nwaves) {
-    const int a = rp[u], deg = rp[u + 1] - a;
-    u32 fill_b = lane < COL_BLOCKS ? RPB[(size_t)lane * ((size_t)n + 1) + u] : 0u;  // lane y: next slot of block y
-    for (int k0 = 0; k0 < deg; k0 += 64) {
-      const bool in = k0 + lane < deg;
-      const int v = in ? col[a + k0 + lane] : 0;
-      const int y = in ? v / span : -1;
-      u32 slot = 0;
-#pragma unroll
-      for (int b = 0; b < COL_BLOCKS; ++b) {
-        const u64 m = __ballot(y == b);
-        const u32 base = __shfl(fill_b, b, 64);
-        if (y == b) slot = base + (u32)__popcll(m & below);
-        if (lane == b) fill_b += (u32)__popcll(m);
-      }
-      if (in) {
-        colb[slot] = v;
-        rowb[slot] = (int32_t)u;
-        if (w) wb[slot] = w[a + k0 + lane];
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Node pass, LDS-private histograms (num_labels small enough for LDS).
 // Workgroup w owns nodes [w*chunk, (w+1)*chunk).  It counts, per label, the nodes
@@ -402,7 +342,7 @@ __global__ __launch_bounds__(256) void k_perm_count(int n, const int32_t* __rest
     if (h[i]) atomicAdd(&bcnt[i], h[i]);
 }
 
-// With lrank/spos (column-blocked graphs): the workgroup's slots in bucket order are
+// With lrank/spos (tiled graphs): the workgroup's slots in bucket order are
 // numbered 0 .. PERM_NODES-1 (its ranges of buckets 0, 1, ... one after the other);
 // lrank[u] is node u's number and spos[u0 + r] the slot numbered r, so a pass that puts
 // the chunk's labels in LDS by number writes them out to consecutive slots.
@@ -515,7 +455,7 @@ __global__ __launch_bounds__(1024) void k_node_perm(int n, const int32_t* __rest
   if (threadIdx.x == 0 && s_bad) atomicOr(&ctl->flags, F_LABEL);
 }
 
-// Node pass of a column-blocked graph, in two kernels.  k_node_scatter moves the labels
+// Node pass of a tiled graph, in two kernels.  k_node_scatter moves the labels
 // from the caller's order into the plan's buckets (tmp[pos1[u]]), one workgroup per
 // PERM_NODES nodes, which own one range of every bucket: the labels go to LDS by their
 // number in the plan (lrank) and leave in slot order (spos), so neighbouring lanes write
@@ -723,7 +663,7 @@ __global__ __launch_bounds__(256) void k_perm_scatter(int n, const int32_t* __re
   if (bad) atomicOr(&ctl->flags, F_LABEL);
 }
 
-// The same move in two streaming passes, for graphs without column blocks: caller-order
+// The same move in two streaming passes, for graphs without tiles: caller-order
 // labels scattered straight to their buckets land on random cache lines (one partial line
 // per 2-byte write over the whole label array).  Stored ids are cut into super-buckets of
 // 2^SB_SHIFT (2 MB of 16-bit labels, one XCD's L2).
@@ -1135,7 +1075,7 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_colscan(int W, int L,
   colscan_tile<WEIGHTED, SCAN>(W, L, HN, HD, N, D, zero64, blockIdx.x);
 }
 
-// Column-blocked node pass: adds the histogram rows of the dense buckets (rows[0,
+// Node pass of a tiled graph: adds the histogram rows of the dense buckets (rows[0,
 // ctl->dense_rows), written by k_perm_apply_count) to N and D, and clears the 64-bit run
 // cursors.  Integer sums, so the order of the row list does not matter.
 // It also chooses how the call stages neighbour labels (Ctl::mode): through the row-major
@@ -1345,18 +1285,14 @@ __device__ __forceinline__ void gather_rows(long long r0, int n, const int32_t* 
 // workgroup b runs on XCD b % 8 and takes tile (b % 8) * ceil(tiles / 8) + b / 8: each
 // XCD walks its own eighth of the rows in order, so the labels that neighbouring rows
 // share stay in its L2 (the 100M-node graph's edge pass: 7.63 -> 7.40 ms).  A smaller
-// grid takes the tiles in turn (grid-stride).  gate (optional): the launch does nothing
-// unless gate->mode == STAGE_ROWS (a column-blocked graph scored through its row-major
-// copy; see k_colscan_rows).
+// grid takes the tiles in turn (grid-stride).
 template <bool PRIV, class LT, bool WT>
 __global__ __launch_bounds__(GROWS) void k_gather(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                   const LT* __restrict__ labx, int L, int chunk, const u32* __restrict__ PM,
                                                   const u32* __restrict__ start, const u32* __restrict__ loc,
-                                                  LT* __restrict__ CB, const float* __restrict__ w, float* __restrict__ CW,
-                                                  const Ctl* __restrict__ gate = nullptr) {
+                                                  LT* __restrict__ CB, const float* __restrict__ w, float* __restrict__ CW) {
   __shared__ int s_rs[GROWS + 1];
   __shared__ u32 s_base[GROWS];
-  if (gate && gate->mode != STAGE_ROWS) return;
   const long long tiles = ((long long)n + GROWS - 1) / GROWS;
   const long long per = (tiles + 7) / 8;
   if (gridDim.x >= 8 * per) {
@@ -1368,481 +1304,6 @@ __global__ __launch_bounds__(GROWS) void k_gather(int n, const int32_t* __restri
     gather_rows<PRIV, LT, WT>(t * GROWS, n, rp, col, labx, L, chunk, PM, start, loc, CB, w, CW, s_rs, s_base);
     __syncthreads();  // the next tile's row starts replace this one's
   }
-}
-
-// Edge pass over a column-blocked graph.  Workgroup i runs on XCD i % 8 (workgroups
-// are handed to the XCDs in turn) and takes entries of column block y = i % 8, so every
-// neighbour label an XCD reads lies in the span of ids its own L2 holds.  Two kinds of
-// tile share the work of block y: own-span tiles take rows of span y itself (most
-// entries: a row's community mostly lies in its own span; the labels of ids near the
-// tile are staged in LDS), far tiles take the block's entries in the rows of the other
-// spans as a list of (row, neighbour) pairs (under one entry per row, so per-row
-// headers would cost more than the entries).  In a tile, rows with equal labels that
-// follow each other form a run; one atomic add on the community's cursor gives the run
-// consecutive places in the community's segment, and each entry goes to run start +
-// its index in the run.
-constexpr int BT_THREADS = 256;
-constexpr int BT_UNROLL = 8;     // entries in flight per thread
-constexpr int BT_HALO = 1024;    // OWN tiles keep labels of ids within this distance of their rows in LDS
-constexpr int BT_RPT = 2;                        // rows per thread in own-span tiles
-constexpr int BT_ROWS = BT_THREADS * BT_RPT;     // rows per own-span tile
-// Far entries per thread: few, since each is a random label read; weighted entries
-// carry a weight load as well and run best with fewer still.
-constexpr int FT_EPT = 4;
-constexpr int FT_EPT_W = 2;
-constexpr int FT_ENT = BT_THREADS * FT_EPT;      // far entries per tile
-constexpr int FT_ENT_W = BT_THREADS * FT_EPT_W;  // far entries per tile, weighted graphs
-constexpr int OWN_BUF = 1024;  // entries of another label an own-span tile keeps in LDS (compact staging)
-constexpr int OWN_BUF_W = 512;  // the same for weighted graphs (with weights and run sums: six workgroups per CU)
-
-// Far entries of column block y: colb/rowb ranges [b[y][0], b[y][1]) (rows before span y)
-// and [b[y][2], b[y][3]) (rows after it), row-major.
-struct FarTable {
-  u32 b[COL_BLOCKS][4];
-};
-
-template <class LT, bool WT = false>
-struct GatherLds {
-  static constexpr int PER = 16 / (int)sizeof(LT);             // labels per 16-byte word
-  static constexpr int WINV = (BT_ROWS + 2 * BT_HALO) / PER + 1;  // 16-byte words of the label window
-  static constexpr int RUN_WORDS = (4 * (BT_ROWS + 1) + 3) & ~3;  // four per-run arrays, padded to 16 bytes
-  static constexpr int BUF = sizeof(LT) == 2 ? (WT ? OWN_BUF_W : OWN_BUF) : 0;  // compact staging buffer (16-bit labels)
-  static constexpr int WBUF = WT ? BUF : 0;                        // the buffered entries' weights
-  static constexpr int ISUM = WT ? 4 * BT_ROWS : 0;                // per run: own-label weight sum, two u64
-  static constexpr int OWN = RUN_WORDS + 4 * WINV + BUF + WBUF + ISUM;
-  static constexpr int FAR = 3 * (FT_ENT + 1);
-  static constexpr int WORDS = OWN > FAR ? OWN : FAR;
-};
-
-// Block-wide run numbering: `heads` marks (bit j) the thread's items that start a run.
-// Returns the number of heads before this thread's items; *nruns gets the total.
-__device__ __forceinline__ u32 runs_before(u32 heads, u32* s_w, u32* nruns) {
-  const u32 nh = (u32)__popc(heads);
-  const u32 incl = wave_incl_scan(nh);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 63) s_w[w] = incl;
-  __syncthreads();
-  u32 q = incl - nh, tot = 0;
-  for (int i = 0; i < BT_THREADS / 64; ++i) {
-    if (i < w) q += s_w[i];
-    tot += s_w[i];
-  }
-  *nruns = tot;
-  return q;
-}
-
-// Gives every run (label c = s_lab[r], entries s_first[r] .. s_first[r+1]) consecutive
-// places in segment c: s_lab[r] becomes the place of its first entry, or SENT.
-template <class LT>
-__device__ __forceinline__ void claim_runs(u32 nruns, const u32* s_first, u32* s_lab, const u32* __restrict__ start,
-                                           const u32* __restrict__ D, u32* __restrict__ cursor, Ctl* __restrict__ ctl) {
-  for (u32 r = threadIdx.x; r < nruns; r += BT_THREADS) {
-    const u32 c = s_lab[r];
-    const u32 tot = s_first[r + 1] - s_first[r];
-    u32 base = SENT;
-    if (c != (u32)LabelT<LT>::SENTINEL && tot > 0) {
-      const u32 old = atomicAdd(&cursor[c], tot);
-      if (old + tot <= D[c]) base = start[c] + old;  // < 2^31, so never the SENT marker
-      else atomicOr(&ctl->flags, F_SEGMENT);  // never expected: the block counts disagree with the degrees
-    }
-    s_lab[r] = base;
-  }
-}
-
-// Compact staging (unweighted graphs): an entry whose neighbour carries the row's own label
-// adds only to 2|E_c^in| and is not staged.  Run r of label c (entries s_first[r] ..
-// s_first[r+1], s_cnt[r] of them with another label) adds (intra << 32) | inter to
-// cur64[c] with one atomic: the low word is the segment cursor, the high word the intra
-// count.  s_base[r] gets the place of the run's first staged entry, or SENT; s_cnt[r]
-// is reset so that it can hand out places inside the run.
-template <class LT>
-__device__ __forceinline__ void claim_runs_compact(u32 nruns, const u32* s_first, const u32* s_lab, u32* s_cnt,
-                                                   u32* s_base, const u32* __restrict__ start, const u32* __restrict__ D,
-                                                   unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl) {
-  for (u32 r = threadIdx.x; r < nruns; r += BT_THREADS) {
-    const u32 c = s_lab[r];
-    const u32 tot = s_first[r + 1] - s_first[r];
-    const u32 inter = s_cnt[r];
-    u32 base = SENT;
-    if (c != (u32)LabelT<LT>::SENTINEL && tot > 0) {
-      const unsigned long long old = atomicAdd(&cur64[c], ((unsigned long long)(tot - inter) << 32) | inter);
-      const u32 lo = (u32)old;
-      if (lo + inter <= D[c]) base = start[c] + lo;  // < 2^31, so never the SENT marker
-      else atomicOr(&ctl->flags, F_SEGMENT);  // never expected: the block counts disagree with the degrees
-    }
-    s_base[r] = base;
-    s_cnt[r] = 0;
-  }
-}
-
-// Own-span tile t of block y: rows [s0 + t*BT_ROWS, ...) of span y, their block-y entries.
-// Staging is compact (claim_runs_compact): a first pass over the tile's entries counts
-// each run's entries of another label, the runs claim their places, and those entries
-// are staged (from an LDS buffer, or by a second pass when it overflows).  WT: the graph
-// is weighted: a staged entry's weight goes to CW beside its label, and each run's
-// own-label weights are summed exactly (x 2^55, as WeightSum) and added to IWacc[c] (two
-// u64 words per community, low word first, the carry added to the high word).
-template <class LT, bool WT>
-__device__ void gather_own_tile(u32 y, u32 t, int n, int span, const u32* __restrict__ RPB,
-                                const int32_t* __restrict__ colb, const LT* __restrict__ labx,
-                                const u32* __restrict__ start, const u32* __restrict__ D, u32* __restrict__ cursor,
-                                Ctl* __restrict__ ctl, LT* __restrict__ CB, const float* __restrict__ wb,
-                                float* __restrict__ CW, unsigned long long* __restrict__ IWacc, u32* lds, u32* s_w) {
-  using LL = GatherLds<LT, WT>;
-  constexpr int PER = LL::PER;
-  constexpr int WIT = (LL::WINV + BT_THREADS - 1) / BT_THREADS;
-  u32* s_re = lds;                   // staged row starts, then first entry of run q (tile-relative)
-  u32* s_rl = lds + BT_ROWS + 1;     // staged row labels, then label of run q
-  u32* s_cnt = lds + 2 * (BT_ROWS + 1);   // entries of run q with another label
-  u32* s_base = lds + 3 * (BT_ROWS + 1);  // place of run q's first staged entry
-  uint4* s_win = reinterpret_cast<uint4*>(lds + LL::RUN_WORDS);  // labels of ids [w0, w1)
-  // WT: own-label weight sum of run q (low, high words)
-  unsigned long long* s_ilo =
-      reinterpret_cast<unsigned long long*>(lds + LL::RUN_WORDS + 4 * LL::WINV + LL::BUF + LL::WBUF);
-  unsigned long long* s_ihi = s_ilo + BT_ROWS;
-  const long long s0 = min((long long)n, (long long)y * span), s1 = min((long long)n, s0 + span);
-  const long long r0 = s0 + (long long)t * BT_ROWS, r1 = min(s1, r0 + BT_ROWS);
-  if (r0 >= r1) return;
-  const u32* rpb = RPB + (size_t)y * ((size_t)n + 1);
-  const int rows = (int)(r1 - r0);
-  const u32 e0 = rpb[r0], e1 = rpb[r1];
-  if (e0 == e1) return;
-  const int tid = threadIdx.x;
-  // Stage the tile's row starts and labels and the label window (coalesced; every load
-  // is issued before the first one is used), then each thread takes BT_RPT rows.
-  const long long w0 = (max(0ll, r0 - BT_HALO) / PER) * PER;
-  const long long w1 = max(w0, (min((long long)n, r1 + BT_HALO) / PER) * PER);
-  {
-    u32 ra[BT_RPT], rl[BT_RPT];
-#pragma unroll
-    for (int j = 0; j < BT_RPT; ++j) {
-      const int r = min(tid + j * BT_THREADS, rows - 1);
-      ra[j] = rpb[r0 + r];
-      rl[j] = (u32)labx[r0 + r];
-    }
-    // a native vector type: an array of HIP's uint4 class is kept in scratch memory
-    typedef u32 v4u __attribute__((ext_vector_type(4)));
-    const v4u* src = reinterpret_cast<const v4u*>(labx + w0);
-    v4u* s_winv = reinterpret_cast<v4u*>(s_win);
-    const int nv = (int)((w1 - w0) / PER);
-    v4u wv[WIT];
-    if (nv > 0) {  // uniform; every load unconditional (clamped)
-#pragma unroll
-      for (int j = 0; j < WIT; ++j) wv[j] = src[min(tid + j * BT_THREADS, nv - 1)];
-    }
-#pragma unroll
-    for (int j = 0; j < BT_RPT; ++j) {
-      const int r = tid + j * BT_THREADS;
-      if (r < rows) {
-        s_re[r] = ra[j] - e0;
-        s_rl[r] = rl[j];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < WIT; ++j) {
-      const int i = tid + j * BT_THREADS;
-      if (i < nv) s_winv[i] = wv[j];
-    }
-  }
-  __syncthreads();
-  u32 lab[BT_RPT], beg[BT_RPT];
-  u32 heads = 0;
-  const int rb = BT_RPT * tid;
-  u32 prev = rb > 0 && rb - 1 < rows ? s_rl[rb - 1] : 0xFFFFFFFFu;
-#pragma unroll
-  for (int j = 0; j < BT_RPT; ++j) {
-    const int r = rb + j;
-    lab[j] = r < rows ? s_rl[r] : 0u;
-    beg[j] = r < rows ? s_re[r] : 0u;
-    if (r < rows && (r == 0 || lab[j] != prev)) heads |= 1u << j;
-    prev = lab[j];
-  }
-  u32 nruns;
-  u32 q = runs_before(heads, s_w, &nruns);  // its barrier also ends the reads of staged rows
-#pragma unroll
-  for (int j = 0; j < BT_RPT; ++j) {
-    if (heads & (1u << j)) {
-      s_re[q] = beg[j];
-      s_rl[q] = lab[j];
-      ++q;
-    }
-  }
-  if (tid == 0) {
-    s_re[nruns] = e1 - e0;
-    s_base[BT_ROWS] = 0;  // compact: count of buffered entries
-  }
-  for (u32 r = tid; r < nruns; r += BT_THREADS) {
-    s_cnt[r] = 0;
-    if (WT) {
-      s_ilo[r] = 0ull;
-      s_ihi[r] = 0ull;
-    }
-  }
-  __syncthreads();
-  const int32_t* cb = colb + e0;
-  const u32 ne = e1 - e0;
-  // f(e, run, x, w) for the BT_UNROLL entries e = eb + u*BT_THREADS of each chunk (e < ne);
-  // w is the entry's weight (WT) or 0
-  auto for_entries = [&](auto&& f) {
-    for (u32 eb = tid; eb < ne; eb += BT_THREADS * BT_UNROLL) {
-      int v[BT_UNROLL];
-      float wt[BT_UNROLL];
-      u32 run[BT_UNROLL];
-#pragma unroll
-      for (int u = 0; u < BT_UNROLL; ++u) v[u] = cb[min(eb + (u32)(u * BT_THREADS), ne - 1u)];  // in bounds; masked below
-#pragma unroll
-      for (int u = 0; u < BT_UNROLL; ++u)  // loaded with the ids, so their latency overlaps the run search
-        wt[u] = WT ? wb[e0 + min(eb + (u32)(u * BT_THREADS), ne - 1u)] : 0.0f;
-#pragma unroll
-      for (int u = 0; u < BT_UNROLL; ++u) {
-        const u32 e = eb + (u32)(u * BT_THREADS);
-        u32 lo = 0, hi = nruns - 1;  // last run r with s_re[r] <= e
-        while (lo < hi) {
-          const u32 mid = (lo + hi + 1) >> 1;
-          if (s_re[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        run[u] = lo;
-      }
-      LT x[BT_UNROLL];
-#pragma unroll
-      for (int u = 0; u < BT_UNROLL; ++u) {
-        const u32 off = (u32)((long long)v[u] - w0);
-        x[u] = off < (u32)(w1 - w0) ? reinterpret_cast<const LT*>(s_win)[off] : labx[v[u]];
-      }
-#pragma unroll
-      for (int u = 0; u < BT_UNROLL; ++u) {
-        const u32 e = eb + (u32)(u * BT_THREADS);
-        if (e < ne) f(e, run[u], x[u], wt[u]);
-      }
-    }
-  };
-  // Pass 1: count each run's entries of another label and keep them, (run << 16) | label
-  // (and their weights, WT), in the LDS buffer; slots and counts are taken once per wave.
-  u32* s_buf = lds + LL::RUN_WORDS + 4 * LL::WINV;
-  float* s_wbuf = reinterpret_cast<float*>(s_buf + LL::BUF);
-  u32* s_nbuf = s_base + BT_ROWS;  // unused by runs (nruns <= BT_ROWS)
-  const int lane = tid & 63;
-  const u64 below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  // WT: a thread meets its entries in increasing order, so runs in increasing order: it
-  // sums the own-label weights of its current run and adds them to the run's LDS sum
-  // when the run changes (64-bit atomics, the low word's carry added to the high word)
-  u32 wrun = 0xFFFFFFFFu;
-  WeightSum wacc;
-  auto wflush = [&]() {
-    if (wrun != 0xFFFFFFFFu) {
-      const unsigned long long old = atomicAdd(&s_ilo[wrun], (unsigned long long)wacc.lo);
-      const unsigned long long hi = wacc.hi + (old + wacc.lo < old ? 1ull : 0ull);
-      if (hi) atomicAdd(&s_ihi[wrun], hi);
-    }
-  };
-  for_entries([&](u32, u32 r, LT x, float w) {
-    const bool inter = (u32)x != s_rl[r];
-    if (WT && !inter) {
-      if (r != wrun) {
-        wflush();
-        wrun = r;
-        wacc = WeightSum();
-      }
-      u64 vlo, vhi;
-      WeightSum::split(w, vlo, vhi);
-      wacc.add(vlo, vhi);
-    }
-    const u64 m = __ballot(inter);
-    if (m == 0) return;
-    const int lead = __ffsll((long long)m) - 1;
-    const u32 rl = __shfl(r, lead, 64);
-    const u64 ms = __ballot(inter && r == rl);
-    u32 slot0 = 0;
-    if (lane == lead) {
-      slot0 = atomicAdd(s_nbuf, (u32)__popcll(m));
-      atomicAdd(&s_cnt[rl], (u32)__popcll(ms));
-    }
-    slot0 = __shfl(slot0, lead, 64);
-    if (inter) {
-      const u32 slot = slot0 + (u32)__popcll(m & below);
-      if (slot < (u32)LL::BUF) {
-        s_buf[slot] = (r << 16) | (u32)x;
-        if (WT) s_wbuf[slot] = w;
-      }
-      if (r != rl) atomicAdd(&s_cnt[r], 1u);
-    }
-  });
-  if (WT) wflush();
-  __syncthreads();
-  claim_runs_compact<LT>(nruns, s_re, s_rl, s_cnt, s_base, start, D, reinterpret_cast<unsigned long long*>(cursor), ctl);
-  if (WT) {
-    // each run's own-label weights join its community's sum
-    for (u32 r = tid; r < nruns; r += BT_THREADS) {
-      const unsigned long long lo = s_ilo[r], hi = s_ihi[r];
-      const u32 c = s_rl[r];
-      if ((lo | hi) && c != (u32)LabelT<LT>::SENTINEL) {
-        const unsigned long long old = atomicAdd(&IWacc[2 * (size_t)c], lo);
-        const unsigned long long h = hi + (old + lo < old ? 1ull : 0ull);
-        if (h) atomicAdd(&IWacc[2 * (size_t)c + 1], h);
-      }
-    }
-  }
-  __syncthreads();
-  const u32 nb = *s_nbuf;
-  if (nb <= (u32)LL::BUF) {
-    // write the buffer out: each wave takes consecutive places per run (coalesced)
-    for (u32 k = tid; k < nb; k += BT_THREADS) {
-      const u32 ent = s_buf[k];
-      const u32 r = ent >> 16;
-      const u64 act = __ballot(true);
-      const int lead = __ffsll((long long)act) - 1;
-      const u32 rl = __shfl(r, lead, 64);
-      const u64 ms = __ballot(r == rl);
-      u32 p0 = 0;
-      if (lane == lead) p0 = atomicAdd(&s_cnt[rl], (u32)__popcll(ms));
-      p0 = __shfl(p0, lead, 64);
-      const u32 rank = r == rl ? p0 + (u32)__popcll(ms & below) : atomicAdd(&s_cnt[r], 1u);
-      const u32 base = s_base[r];
-      if (base != SENT) {
-        CB[base + rank] = (LT)(ent & 0xFFFFu);
-        if (WT) CW[base + rank] = s_wbuf[k];
-      }
-    }
-  } else {
-    // buffer overflow (or 32-bit labels): classify the tile's entries again
-    for_entries([&](u32, u32 r, LT x, float w) {
-      const u32 base = s_base[r];
-      if ((u32)x != s_rl[r] && base != SENT) {
-        const u32 rank = atomicAdd(&s_cnt[r], 1u);
-        CB[base + rank] = x;
-        if (WT) CW[base + rank] = w;
-      }
-    });
-  }
-}
-
-// Far tile t of block y: FT_ENT (weighted: FT_ENT_W) consecutive entries of the block's
-// far ranges.
-template <class LT, bool WT>
-__device__ void gather_far_tile(u32 y, u32 t, const FarTable& ft, const int32_t* __restrict__ colb,
-                                const int32_t* __restrict__ rowb, const LT* __restrict__ labx,
-                                const u32* __restrict__ start, const u32* __restrict__ D, u32* __restrict__ cursor,
-                                Ctl* __restrict__ ctl, LT* __restrict__ CB, const float* __restrict__ wb,
-                                float* __restrict__ CW, u32* lds, u32* s_w) {
-  constexpr int EPT = WT ? FT_EPT_W : FT_EPT;
-  constexpr u32 ENT = BT_THREADS * EPT;
-  u32* s_rf = lds;                     // first entry of run q (tile-relative); s_rf[nruns] = entry count
-  u32* s_rb = lds + ENT + 1;        // staged row labels, then label of run q, then its segment place
-  u32* s_cnt = lds + 2 * (ENT + 1);  // compact: entries of run q with another label
-  const u32 b0 = ft.b[y][0], b1 = ft.b[y][1], b2 = ft.b[y][2], b3 = ft.b[y][3];
-  const u32 t1 = (b1 - b0 + ENT - 1) / ENT;
-  u32 e0, e1;
-  if (t < t1) {
-    e0 = b0 + t * ENT;
-    e1 = min(b1, e0 + ENT);
-  } else {
-    e0 = b2 + (t - t1) * ENT;
-    if (e0 >= b3) return;
-    e1 = min(b3, e0 + ENT);
-  }
-  const u32 ne = e1 - e0;
-  const int tid = threadIdx.x;
-  const u32 i0 = (u32)tid * EPT;  // this thread's entries i0 .. i0+EPT-1 (tile-relative)
-  LT x[EPT];
-  u32 lab[EPT];
-  float wt[EPT];
-#pragma unroll
-  for (int j = 0; j < EPT; ++j) {
-    const u32 e = e0 + min(i0 + (u32)j, ne - 1u);  // in bounds; entries past ne are masked below
-    x[j] = labx[colb[e]];  // the neighbour labels are loaded now and used after the runs are placed
-    lab[j] = (u32)labx[rowb[e]];
-    if (WT) wt[j] = wb[e];
-  }
-#pragma unroll
-  for (int j = 0; j < EPT; ++j)
-    if (i0 + (u32)j < ne) s_rb[i0 + j] = lab[j];
-  __syncthreads();
-  u32 prev = (i0 > 0 && i0 - 1 < ne) ? s_rb[i0 - 1] : 0xFFFFFFFFu;
-  u32 heads = 0;
-#pragma unroll
-  for (int j = 0; j < EPT; ++j) {
-    const u32 i = i0 + (u32)j;
-    if (i < ne && (i == 0 || lab[j] != prev)) heads |= 1u << j;
-    prev = lab[j];
-  }
-  u32 nruns;
-  const u32 q0 = runs_before(heads, s_w, &nruns);  // its barrier also ends the reads of staged labels
-  {
-    u32 q = q0;
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      if (heads & (1u << j)) {
-        s_rf[q] = i0 + (u32)j;
-        s_rb[q] = lab[j];
-        ++q;
-      }
-    }
-  }
-  if (tid == 0) s_rf[nruns] = ne;
-  if (!WT)
-    for (u32 r = tid; r < nruns; r += BT_THREADS) s_cnt[r] = 0;
-  __syncthreads();
-  // f(j, i, run) for this thread's entries i = i0 + j < ne
-  auto for_entries = [&](auto&& f) {
-    u32 q = q0;  // runs started up to entry i0 + j
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      const u32 i = i0 + (u32)j;
-      if (heads & (1u << j)) ++q;
-      if (i < ne) f(j, i, q - 1u);  // entry i lies in the last run that starts at or before it
-    }
-  };
-  if (WT) {
-    // weighted: every far entry is staged on the compact cursor (its runs add no own-label
-    // count); the few of the row's own label are counted and weighed by the group pass.
-    // Each run's length is set by the thread that claims it.
-    for (u32 r = tid; r < nruns; r += BT_THREADS) s_cnt[r] = s_rf[r + 1] - s_rf[r];
-    claim_runs_compact<LT>(nruns, s_rf, s_rb, s_cnt, s_rb, start, D, reinterpret_cast<unsigned long long*>(cursor), ctl);
-    __syncthreads();
-    for_entries([&](int j, u32 i, u32 run) {
-      const u32 base = s_rb[run];
-      if (base != SENT) {
-        CB[base + (i - s_rf[run])] = x[j];
-        CW[base + (i - s_rf[run])] = wt[j];
-      }
-    });
-  } else {
-    for_entries([&](int j, u32, u32 run) {
-      if ((u32)x[j] != lab[j]) atomicAdd(&s_cnt[run], 1u);
-    });
-    __syncthreads();
-    // s_rb: the run's label, replaced by the place of its first staged entry
-    claim_runs_compact<LT>(nruns, s_rf, s_rb, s_cnt, s_rb, start, D, reinterpret_cast<unsigned long long*>(cursor), ctl);
-    __syncthreads();
-    for_entries([&](int j, u32, u32 run) {
-      const u32 base = s_rb[run];
-      if ((u32)x[j] != lab[j] && base != SENT) CB[base + atomicAdd(&s_cnt[run], 1u)] = x[j];
-    });
-  }
-}
-
-// One launch for both kinds of tile.  Groups of 8 consecutive workgroups (one per XCD,
-// so workgroup i serves block i % 8): the own-span groups first (they carry most
-// entries), then the far groups.
-template <class LT, bool WT>
-__global__ __launch_bounds__(BT_THREADS) void k_gather_blocked(int n, int span, const u32* __restrict__ RPB,
-                                                               const int32_t* __restrict__ colb,
-                                                               const int32_t* __restrict__ rowb, FarTable ft,
-                                                               u32 own_groups, u32 far_groups,
-                                                               const LT* __restrict__ labx, const u32* __restrict__ start,
-                                                               const u32* __restrict__ D, u32* __restrict__ cursor,
-                                                               Ctl* __restrict__ ctl, LT* __restrict__ CB,
-                                                               const float* __restrict__ wb, float* __restrict__ CW,
-                                                               unsigned long long* __restrict__ IWacc) {
-  __shared__ __align__(16) u32 lds[GatherLds<LT, WT>::WORDS];
-  __shared__ u32 s_w[BT_THREADS / 64];
-  if (ctl->mode == STAGE_ROWS) return;  // this call stages through the row-major copy (k_colscan_rows)
-  const u32 y = blockIdx.x % 8u, gi = blockIdx.x / 8u;
-  if (y >= (u32)COL_BLOCKS || gi >= own_groups + far_groups) return;
-  if (gi < own_groups)
-    gather_own_tile<LT, WT>(y, gi, n, span, RPB, colb, labx, start, D, cursor, ctl, CB, wb, CW, IWacc, lds, s_w);
-  else
-    gather_far_tile<LT, WT>(y, gi - own_groups, ft, colb, rowb, labx, start, D, cursor, ctl, CB, wb, CW, lds, s_w);
 }
 
 // Comparison: the segment of ground-truth community a_u receives b_u.
@@ -2290,7 +1751,7 @@ __device__ __forceinline__ void wave_group_one(u32* tab, const uint16_t* __restr
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the table's reads end before the next clears
 }
 
-// cur64 (compact staging of a column-blocked graph, else null): as in k_groups.
+// cur64 (compact staging of a tiled graph, else null): as in k_groups.
 template <class V>
 __global__ __launch_bounds__(64 * GW_WAVES) void k_groups_wave(const uint16_t* __restrict__ CB, const u32* __restrict__ seg_start,
                                                               const u32* __restrict__ seg_len, const u32* __restrict__ order,
@@ -2429,7 +1890,7 @@ struct ScoreVis {
 // once the table holds every count |E_gj|, reads labels and weights together: entry
 // (j, w) adds w to the weight sums and, for j != g, w |E_gj| / (2W |g| |j|) to the
 // penalty, truncated to a multiple of 2^-96 (term by term, so the sum is exact).  With
-// compact staging (column-blocked graphs) the segment holds only entries of other
+// compact staging (tiled graphs) the segment holds only entries of other
 // labels (and far entries): the edge pass has already counted the own-label entries
 // (high word of the cursor) and summed their weights into IW[g], which both sums add.
 struct WeightedOut {
@@ -2861,7 +2322,7 @@ struct ScoreResultDev {
 };
 
 // staging reported in the result: the choice made on the device (ctl->mode) when there
-// was one, else STAGE_BLOCKS for a column-blocked graph (blocked != 0), STAGE_ROWS_ONLY otherwise.
+// was one, else STAGE_BLOCKS for a tiled graph (blocked != 0), STAGE_ROWS_ONLY otherwise.
 __device__ __forceinline__ u32 staging_of(const Ctl* ctl, u32 blocked) {
   return ctl->mode ? ctl->mode : (blocked ? STAGE_BLOCKS : STAGE_ROWS_ONLY);
 }

@@ -22,6 +22,7 @@
 #include "cq_kernels.hpp"
 #include "cq_compare.hpp"
 #include "cq_rows.hpp"
+#include "cq_tiles.hpp"
 #include "cq_small.hpp"
 #include "srv_core.hpp"
 
@@ -61,9 +62,12 @@ struct cq_graph {
   int32_t* owned_rp = nullptr;    // device memory owned by the handle (CQ_GRAPH_REORDER)
   int32_t* owned_col = nullptr;
   int32_t* owned_perm = nullptr;
-  u32* rpb = nullptr;              // column blocks (owned; null when the graph is not blocked)
-  int32_t* colb = nullptr;
-  int32_t* rowb = nullptr;
+  u32* nrp = nullptr;              // tiles (cq_tiles.hpp; owned, null when the graph has none): near row starts,
+  u32* fpt = nullptr;              // far entries' first places per tile and slice,
+  uint16_t *ncol = nullptr, *fcol = nullptr, *frow = nullptr;  // near entries; far entries' columns and rows
+  float *nw = nullptr, *fw = nullptr;                          // their weights
+  int64_t far = 0;                 // far entries
+  int slices = 0;
   u32* deg_in = nullptr;           // label permutation plan (caller order -> stored order): degrees,
   u32* pos1 = nullptr;             // bucket slots and their stored ids; null when not built
   uint16_t* tgt = nullptr;         // offset of the slot's stored id in its bucket
@@ -74,26 +78,27 @@ struct cq_graph {
   int perm_buckets = 0;
   const float* w = nullptr;        // edge weights in the stored entry order (borrowed or owned_w); null: unweighted
   float* owned_w = nullptr;
-  float* wb = nullptr;             // weights in column-block order (with colb)
   double total_w = 0.0;            // W, summed exactly at load
-  FarTable far{};                  // per block: entry ranges of the rows outside its span
   int64_t clusters = 0, largest_cluster = 0;  // of the locality order
-  unsigned far_tiles = 0;          // most far-entry tiles of any block
   int64_t owned_bytes = 0;
   ~cq_graph() {
     if (owned_rp) (void)hipFree(owned_rp);
     if (owned_col) (void)hipFree(owned_col);
     if (owned_perm) (void)hipFree(owned_perm);
-    if (rpb) (void)hipFree(rpb);
-    if (colb) (void)hipFree(colb);
-    if (rowb) (void)hipFree(rowb);
+    free_tiles();
     for (u32* p : {deg_in, pos1, pbstart, sid})
       if (p) (void)hipFree(p);
     if (tgt) (void)hipFree(tgt);
     if (lrank) (void)hipFree(lrank);
     if (spos) (void)hipFree(spos);
     if (owned_w) (void)hipFree(owned_w);
-    if (wb) (void)hipFree(wb);
+  }
+  void free_tiles() {
+    for (void* p : {(void*)nrp, (void*)fpt, (void*)ncol, (void*)fcol, (void*)frow, (void*)nw, (void*)fw})
+      if (p) (void)hipFree(p);
+    nrp = fpt = nullptr;
+    ncol = fcol = frow = nullptr;
+    nw = fw = nullptr;
   }
 };
 
@@ -265,6 +270,8 @@ struct ScoreLayout {
   size_t CW, SW, IW, PENW, INVN;  // weighted graphs only (0 otherwise)
   bool rows;  // scored by member rows (cq_rows.hpp): rec and bad in place of the staged entries
   size_t rec, bad;
+  bool tiled;   // scored through the graph's tiles (cq_tiles.hpp); fl: its far entries' labels
+  size_t fl, min_total;
   int small_wgs;  // > 0: scored in two launches (cq_small.hpp) by that many counting workgroups
   size_t slots;
 };
@@ -328,13 +335,27 @@ constexpr int64_t SMALL_MAX_NNZ = 400000;
 constexpr int64_t SMALL_WG_NNZ = 2048;
 constexpr int64_t SMALL_MAX_CELLS = 256 << 10;
 
-// The layout of one scoring call on graph g (the node pass it takes decides the chunk).
-// Member rows take the workspace of the staged path (which they fit unless the graph has
-// hardly any edges).
-ScoreLayout graph_score_layout(const cq_graph* g, int64_t L) {
-  const bool perm = g->rpb && g->pos1 && L <= PRIV_MAX;
-  const ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
-  if (g->rpb || g->w || L > DIRECT_MAX || g->n > ROWS_MAX_N) return s;
+// The layout of one scoring call on graph g with `have` bytes of workspace.  min_total is the
+// least a call takes; a tiled graph uses its tiles when there is room for the far entries'
+// labels as well (total), else its row-major copy.  Member rows and small graphs take the
+// workspace of the staged path (which they fit unless the graph has hardly any edges).
+ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_MAX) {
+  const bool perm = g->nrp && g->pos1 && L <= PRIV_MAX;
+  ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
+  s.min_total = s.total;
+  if (g->nrp) {
+    ScoreLayout t = s;
+    Carve c;
+    c.off = s.total;
+    t.tiled = true;
+    t.fl = c.take((s.small ? 2 : 4) * (size_t)g->far);
+    t.total = c.off;
+    if (t.total <= have) return t;
+    s = score_layout(g->n, g->nnz, L, g->w != nullptr, 65536);
+    s.min_total = t.min_total;
+    return s;
+  }
+  if (g->w || L > DIRECT_MAX || g->n > ROWS_MAX_N) return s;
   ScoreLayout r = s;
   Carve c;
   if (g->n <= SS_MAX_N && L <= SS_MAX_L && g->nnz <= SMALL_MAX_NNZ) {
@@ -578,22 +599,22 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   float* CW = g->w ? at<float>(ws, lay.CW) : nullptr;  // weights staged beside the labels
   ScorePart* parts = at<ScorePart>(ws, lay.parts);
   const u32* PM = nullptr;
-  bool dual_rows = false;  // column-blocked graph whose staging is chosen on the device
+  const bool tiled = lay.tiled;
   {
     StageMark mk(ctx, ST_SETUP, timed);
     // the control block and the work queues in one launch
     k_cmp_clear<<<grid_for((int64_t)(sizeof(Ctl) / 4) + WQ_WORDS, 256, 64), 256, 0, s>>>(
         reinterpret_cast<u32*>(ctl), (int)(sizeof(Ctl) / 4), at<u32>(ws, lay.wq), nullptr, 0);
     if (!lay.priv) fill(at<u32>(ws, lay.SZ), 2 * (size_t)L, 0, s);
-    // run cursors of column-blocked graphs: cleared by the column scan on the
+    // run cursors of tiled graphs: cleared by the column scan on the
     // private-histogram path, here otherwise
-    if (g->rpb && !(L <= PRIV_MAX && g->pos1)) fill(at<u32>(ws, lay.cursor), 2 * (size_t)L, 0, s);
-    // weighted column-blocked graphs: the edge pass adds each community's own-label weights here
-    if (CW && g->rpb) fill(at<u32>(ws, lay.IW), 4 * (size_t)L, 0, s);
+    if (tiled && !(L <= PRIV_MAX && g->pos1)) fill(at<u32>(ws, lay.cursor), 2 * (size_t)L, 0, s);
+    // weighted tiled graphs: the edge pass adds each community's own-label weights here
+    if (CW && tiled) fill(at<u32>(ws, lay.IW), 4 * (size_t)L, 0, s);
   }
-  if (L <= PRIV_MAX && g->rpb && g->pos1) {
-    // column-blocked graph: move the labels with the bucket plan and count per label (the
-    // blocked edge pass needs no per-node offsets)
+  if (L <= PRIV_MAX && tiled && g->pos1) {
+    // tiled graph: move the labels with the bucket plan and count per label (the edge pass
+    // needs no per-node offsets)
     u32* HN = at<u32>(ws, lay.HN);
     u32* HD = at<u32>(ws, lay.HD);
     LT* tmp = reinterpret_cast<LT*>(loc);  // per-node offsets are not used on this path
@@ -609,9 +630,8 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
             rows, ctl);
       }
       // A partition out of the stored order (many label changes along it) would make the
-      // column blocks' run claims as many as the nodes: k_colscan_rows then picks staging
-      // through the row-major copy, whose per-node offsets come from the gated launches
-      // below (they return at once when the blocks are kept).
+      // tiles' run claims as many as the nodes: k_colscan_rows then picks staging at per-node
+      // offsets, which come from the gated launches below (they return at once otherwise).
       const bool dual = !CW;
       {
         StageMark mk(ctx, ST_COLSCAN, timed);
@@ -626,7 +646,6 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
           k_colscan<true, true><<<colscan_grid(L), CS_LABELS * CS_GROUPS, 0, s>>>(lay.W, L, HN, HD, N, D, nullptr, ctl,
                                                                              STAGE_ROWS);
         }
-        dual_rows = dual;
       }
     } else {
       // more labels than LDS holds beside a bucket: count in the caller's order
@@ -692,24 +711,25 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   }
   {
     StageMark mk(ctx, ST_GATHER, timed);
-    if (g->rpb) {
-      const int64_t span = (n + COL_BLOCKS - 1) / COL_BLOCKS;
-      const unsigned own_groups = (unsigned)((span + BT_ROWS - 1) / BT_ROWS);
-      const unsigned grid = COL_BLOCKS * (own_groups + g->far_tiles);
-      if (CW)
-        k_gather_blocked<LT, true><<<grid, BT_THREADS, 0, s>>>((int)n, (int)span, g->rpb, g->colb, g->rowb, g->far, own_groups,
-                                                               g->far_tiles, labx, start, D, at<u32>(ws, lay.cursor), ctl, CB,
-                                                               g->wb, CW, at<unsigned long long>(ws, lay.IW));
-      else
-        k_gather_blocked<LT, false><<<grid, BT_THREADS, 0, s>>>((int)n, (int)span, g->rpb, g->colb, g->rowb, g->far, own_groups,
-                                                                g->far_tiles, labx, start, D, at<u32>(ws, lay.cursor), ctl, CB,
-                                                                nullptr, nullptr, nullptr);
-      if (dual_rows) {
-        // the other choice: every entry staged at its row's offset, through the row-major copy
-        const unsigned gr = std::min(grid_for(n, GROWS, 1u << 30), (unsigned)(ctx->num_cus * 64));
-        k_gather<true, LT, false><<<gr, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, nullptr,
-                                                       nullptr, ctl);
+    if (tiled) {
+      const int T = (int)((n + TG_ROWS - 1) / TG_ROWS), S = g->slices;
+      LT* fl = at<LT>(ws, lay.fl);
+      if (g->far > 0) {
+        // about four workgroups per CU, of at least 4,096 entries
+        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((4 * ctx->num_cus + S - 1) / S, g->far / ((int64_t)S * 4096)));
+        k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << TS_SHIFT, s>>>((int)n, parts, g->fpt,
+                                                                                          g->fpt + (size_t)T * S, g->fcol, labx, fl);
       }
+      const unsigned grid = 8u * (unsigned)((T + 7) / 8);
+      unsigned long long* cur = at<unsigned long long>(ws, lay.cursor);
+      if (CW)
+        k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::BYTES, s>>>(
+            (int)n, S, g->rp, g->nrp, g->ncol, g->fpt, g->frow, fl, labx, start, D, cur, ctl, CB, g->nw, g->fw, CW,
+            at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc);
+      else
+        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::BYTES, s>>>(
+            (int)n, S, g->rp, g->nrp, g->ncol, g->fpt, g->frow, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr, nullptr,
+            nullptr, L, lay.chunk, PM, loc);
     } else {
       const unsigned grid = 8u * (unsigned)((((int64_t)n + GROWS - 1) / GROWS + 7) / 8);  // one workgroup per tile
       if (lay.priv && CW)
@@ -754,8 +774,8 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
       k_inv_sizes<<<grid_for(L, 256, 1024), 256, 0, s>>>(L, N, invN);
       int nb = 0;
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_groups_w<LT>, GBLOCK, lds) != hipSuccess || nb < 1) nb = 1;
-      // column-blocked graphs stage compactly: lengths and own-label counts in the cursors
-      const unsigned long long* cur64 = g->rpb ? at<unsigned long long>(ws, lay.cursor) : nullptr;
+      // tiled graphs stage compactly: lengths and own-label counts in the cursors
+      const unsigned long long* cur64 = tiled ? at<unsigned long long>(ws, lay.cursor) : nullptr;
       k_groups_w<LT><<<(unsigned)(ctx->num_cus * nb), GBLOCK, lds, s>>>(CB, CW, start, D, order, ctl, (u32)L, vis, wo,
                                                                         cur64, at<u32>(ws, lay.wq));
     }
@@ -763,14 +783,14 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
     {
       StageMark mk(ctx, ST_FINAL, timed);
       k_score_final_w<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, wo.SW, wo.IW, wo.PENW, g->total_w, pc, wparts, n, nnz, vis.ecap,
-                                               ctl, d_out, g->rpb ? 1u : 0u);
+                                               ctl, d_out, tiled ? 1u : 0u);
     }
     return;
   }
   {
     StageMark mk(ctx, ST_GROUPS, timed);
-    // column-blocked graphs stage compactly (see k_gather_blocked): lengths and own-label counts in the cursors
-    const unsigned long long* cur64 = g->rpb ? at<unsigned long long>(ws, lay.cursor) : nullptr;
+    // tiled graphs stage compactly (see k_tile_gather): lengths and own-label counts in the cursors
+    const unsigned long long* cur64 = tiled ? at<unsigned long long>(ws, lay.cursor) : nullptr;
     // Label spaces beyond the direct LDS table (16-bit labels): groups of degree sum below
     // GW_SPLIT are counted one per wave after the workgroup-per-group pass has taken the
     // others.  The choice depends on num_labels and the degree sums only, so a group takes
@@ -806,7 +826,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   }
   {
     StageMark mk(ctx, ST_FINAL, timed);
-    k_score_final<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, PEN, n, nnz, pc, parts, vis.ecap, ctl, d_out, g->rpb ? 1u : 0u);
+    k_score_final<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, PEN, n, nnz, pc, parts, vis.ecap, ctl, d_out, tiled ? 1u : 0u);
   }
 }
 
@@ -938,9 +958,9 @@ cq_status score_enqueue(cq_context* ctx, const cq_graph* g, const int32_t* label
     return fail(ctx, CQ_E_INVALID_ARG, "weighted scoring supports up to %u label ids", HASH_WORDS);
   if (pairs && pairs->capacity > 0 && (!pairs->ci || !pairs->cj || !pairs->count))
     return fail(ctx, CQ_E_INVALID_ARG, "pair table with null arrays");
-  const ScoreLayout lay = graph_score_layout(g, L);
-  if (!ws || ws_bytes < lay.total)
-    return fail(ctx, CQ_E_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, lay.total);
+  const ScoreLayout lay = graph_score_layout(g, L, ws_bytes);
+  if (!ws || ws_bytes < lay.min_total)
+    return fail(ctx, CQ_E_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, lay.min_total);
   if (reinterpret_cast<uintptr_t>(ws) % WS_ALIGN) return fail(ctx, CQ_E_INVALID_ARG, "workspace not 16-byte aligned");
   if (lay.small_wgs > 0)
     score_launch_small(ctx, g, labels, L, ws, lay, d_out, per_comm, pairs, timed);
@@ -1265,65 +1285,61 @@ void scan_u32(const u32* in, u32* out, long long n, u32* tiles, hipStream_t s) {
 
 constexpr int LP_SWEEPS = 10;
 constexpr int LP_SALTED_SWEEPS = 20;
-// Column blocks pay off while one block's labels (2 bytes per node) fit an XCD's L2, and
-// once all labels do not (below that the plain edge pass has more workgroups in flight).
+// Graphs kept as tiles by default: from where their labels outgrow half an L2 (below, the label
+// reads of the member rows stay in it), up to the ids the tile tables are made for.
 constexpr int64_t BLOCK_MAX_N = 16 << 20;
 constexpr int64_t BLOCK_MIN_N = 1 << 20;
+static_assert(BLOCK_MAX_N <= (int64_t)TG_MAX_SLICES << TS_SHIFT, "slices");
 
-// Splits the renumbered graph (g->owned_rp / owned_col) into COL_BLOCKS column blocks.
-cq_status build_column_blocks(cq_context* ctx, cq_graph* g) {
+// Builds the tiles of the renumbered graph (g->owned_rp / owned_col / owned_w).
+cq_status build_tiles(cq_context* ctx, cq_graph* g) {
   const int n = g->n;
   const int64_t nnz = g->nnz;
   hipStream_t s = ctx->stream;
-  const long long len = (long long)COL_BLOCKS * ((long long)n + 1);
-  u32 *cnt = nullptr, *tiles = nullptr;
+  const int T = (n + TG_ROWS - 1) / TG_ROWS, S = (n + TS_NODES - 1) >> TS_SHIFT;
+  const long long cells = (long long)T * S;
+  u32 *ncnt = nullptr, *fcnt = nullptr, *fstart = nullptr, *tiles = nullptr;
   hipError_t e = hipSuccess;
   auto alloc = [&](void** p, size_t bytes) {
-    if (e == hipSuccess) e = hipMalloc(p, std::max<size_t>(bytes, 4));
+    if (e == hipSuccess) e = hipMalloc(p, std::max<size_t>(bytes, 16));
   };
-  alloc((void**)&g->rpb, 4 * ((size_t)len + 1));
-  alloc((void**)&g->colb, 4 * (size_t)nnz);
-  alloc((void**)&g->rowb, 4 * (size_t)nnz);
-  if (g->owned_w) alloc((void**)&g->wb, 4 * (size_t)nnz);
-  alloc((void**)&cnt, 4 * (size_t)len);
-  alloc((void**)&tiles, 4 * ((size_t)((len + SCAN_TILE - 1) / SCAN_TILE) + 1));
-  cq_status st = CQ_OK;
-  if (e != hipSuccess) {
-    st = fail(ctx, CQ_E_DEVICE, "allocating column blocks: %s", hipGetErrorString(e));
-  } else {
-    const int span = (int)(((int64_t)n + COL_BLOCKS - 1) / COL_BLOCKS);
-    const unsigned gw = grid_for((int64_t)n * 64, 256, 65535);
-    k_blk_count<<<gw, 256, 0, s>>>(n, g->owned_rp, g->owned_col, span, cnt);
-    scan_u32(cnt, g->rpb, len, tiles, s);
-    k_blk_place<<<gw, 256, 0, s>>>(n, g->owned_rp, g->owned_col, span, g->rpb, g->colb, g->rowb, g->owned_w, g->wb);
+  g->slices = S;
+  alloc((void**)&g->nrp, 4 * ((size_t)n + 1));
+  alloc((void**)&g->fpt, 4 * ((size_t)cells + S));
+  alloc((void**)&ncnt, 4 * (size_t)n);
+  alloc((void**)&fcnt, 4 * (size_t)cells);
+  alloc((void**)&fstart, 4 * ((size_t)cells + 1));
+  alloc((void**)&tiles, 4 * ((size_t)((std::max<long long>(n, cells) + SCAN_TILE - 1) / SCAN_TILE) + 1));
+  u32 near = 0, far = 0;
+  if (e == hipSuccess) {
+    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, T, S, g->owned_rp, g->owned_col, ncnt, fcnt);
+    scan_u32(ncnt, g->nrp, n, tiles, s);
+    scan_u32(fcnt, fstart, cells, tiles, s);
+    k_tile_table<<<grid_for(cells + S, 256, 4096), 256, 0, s>>>(T, S, fstart, g->fpt);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(&near, g->nrp + n, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&far, fstart + cells, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  }
+  alloc((void**)&g->ncol, 2 * (size_t)near);
+  alloc((void**)&g->fcol, 2 * (size_t)far);
+  alloc((void**)&g->frow, 2 * (size_t)far);
+  if (g->owned_w) {
+    alloc((void**)&g->nw, 4 * (size_t)near);
+    alloc((void**)&g->fw, 4 * (size_t)far);
+  }
+  if (e == hipSuccess) {
+    k_tile_place<<<T, TG_THREADS, 0, s>>>(n, T, S, g->owned_rp, g->owned_col, g->owned_w, g->nrp, g->fpt, g->ncol, g->nw, g->fcol,
+                                          g->frow, g->fw);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    // far-entry ranges of every block: rows [0, s0) and [s1, n), s0..s1 being its span
-    g->far_tiles = 0;
-    const u32 ent = g->owned_w ? FT_ENT_W : FT_ENT;  // entries per far tile, as the gather kernel takes them
-    for (int y = 0; y < COL_BLOCKS && e == hipSuccess; ++y) {
-      const int64_t s0 = std::min<int64_t>(n, (int64_t)y * span), s1 = std::min<int64_t>(n, s0 + span);
-      const int64_t at_row[4] = {0, s0, s1, n};
-      for (int j = 0; j < 4 && e == hipSuccess; ++j)
-        e = hipMemcpy(&g->far.b[y][j], g->rpb + (size_t)y * ((size_t)n + 1) + at_row[j], 4, hipMemcpyDeviceToHost);
-      const u32 t = (g->far.b[y][1] - g->far.b[y][0] + ent - 1) / ent + (g->far.b[y][3] - g->far.b[y][2] + ent - 1) / ent;
-      g->far_tiles = std::max(g->far_tiles, (unsigned)t);
-    }
-    if (e != hipSuccess) st = fail(ctx, CQ_E_DEVICE, "building column blocks: %s", hipGetErrorString(e));
   }
-  if (cnt) (void)hipFree(cnt);
-  if (tiles) (void)hipFree(tiles);
-  if (st != CQ_OK) {
-    if (g->rpb) (void)hipFree(g->rpb);
-    if (g->colb) (void)hipFree(g->colb);
-    if (g->rowb) (void)hipFree(g->rowb);
-    if (g->wb) (void)hipFree(g->wb);
-    g->rpb = nullptr;
-    g->colb = nullptr;
-    g->rowb = nullptr;
-    g->wb = nullptr;
-  }
-  return st;
+  g->far = far;
+  for (u32* p : {ncnt, fcnt, fstart, tiles})
+    if (p) (void)hipFree(p);
+  if (e == hipSuccess && (int64_t)near + far == nnz) return CQ_OK;
+  g->free_tiles();
+  return fail(ctx, CQ_E_DEVICE, "building the graph's tiles: %s", hipGetErrorString(e));
 }
 
 // Builds the label permutation plan of a renumbered graph from newid (caller id ->
@@ -1342,7 +1358,7 @@ cq_status build_perm_plan(cq_context* ctx, cq_graph* g, const int32_t* newid, co
   alloc((void**)&g->pos1, 4 * (size_t)n);
   alloc((void**)&g->tgt, 2 * (size_t)n);
   alloc((void**)&g->pbstart, 4 * ((size_t)nb + 1));
-  if (g->rpb) {
+  if (g->nrp) {
     alloc((void**)&g->lrank, 2 * (size_t)n);
     alloc((void**)&g->spos, 4 * (size_t)n);
   } else if (((int64_t)n + SB_MASK) >> SB_SHIFT <= SB_MAX) {
@@ -1456,8 +1472,8 @@ cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, 
     k_new_degree<<<gn, 256, 0, s>>>(n, rp, g->owned_perm, cnt);
     scan_u32(cnt, reinterpret_cast<u32*>(g->owned_rp), n, tiles, s);
     k_relabel_rows<<<gw, 256, 0, s>>>(n, rp, col, g->owned_perm, newid, g->owned_rp, g->owned_col, g->w, g->owned_w);
-    if (blocks) st = build_column_blocks(ctx, g);
-    if (st == CQ_OK && (g->rpb || n >= BLOCK_MIN_N)) st = build_perm_plan(ctx, g, newid, rp);
+    if (blocks) st = build_tiles(ctx, g);
+    if (st == CQ_OK && (g->nrp || n >= BLOCK_MIN_N)) st = build_perm_plan(ctx, g, newid, rp);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (st == CQ_OK && e != hipSuccess) st = fail(ctx, CQ_E_DEVICE, "renumbering the graph: %s", hipGetErrorString(e));
@@ -1469,14 +1485,17 @@ cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, 
     g->col = g->owned_col;
     g->perm = g->owned_perm;
     if (g->owned_w) g->w = g->owned_w;
-    g->reordered = CQ_GRAPH_REORDER | (g->rpb ? 0u : CQ_GRAPH_NO_BLOCKS);
+    g->reordered = CQ_GRAPH_REORDER | (g->nrp ? 0u : CQ_GRAPH_NO_BLOCKS);
     g->owned_bytes = (int64_t)(4 * ((size_t)n + 1) + 4 * (size_t)nnz + 4 * (size_t)n);
-    if (g->rpb) g->owned_bytes += (int64_t)(4 * ((size_t)COL_BLOCKS * ((size_t)n + 1) + 1) + 8 * (size_t)nnz);
+    if (g->nrp) {
+      const size_t T = ((size_t)n + TG_ROWS - 1) / TG_ROWS;
+      g->owned_bytes += (int64_t)(4 * ((size_t)n + 1) + 4 * (T + 1) * (size_t)g->slices + 2 * (size_t)(nnz - g->far) +
+                                  4 * (size_t)g->far + (g->owned_w ? 4 * (size_t)nnz : 0));
+    }
     if (g->pos1) g->owned_bytes += (int64_t)(10 * (size_t)n + 4 * ((size_t)g->perm_buckets + 1));
     if (g->lrank) g->owned_bytes += (int64_t)(6 * (size_t)n);
     if (g->sid) g->owned_bytes += (int64_t)(4 * (size_t)n);
     if (g->owned_w) g->owned_bytes += (int64_t)(4 * (size_t)nnz);
-    if (g->wb) g->owned_bytes += (int64_t)(4 * (size_t)nnz);
   }
   return st;
 }
@@ -2003,6 +2022,12 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 512, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 256, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
+  set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint16_t>), 2 << TS_SHIFT);
+  set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint32_t>), 4 << TS_SHIFT);
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::BYTES);
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::BYTES);
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::BYTES);
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::BYTES);
   set_big_lds(reinterpret_cast<const void*>(k_small_count), ss_lds(SS_MAX_N, SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_final), 4 * (size_t)ss_cells(SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_compare), 4 * (size_t)SC_MAX_CELLS + 24 * (size_t)SC_MAX_L + 64);
@@ -2242,7 +2267,7 @@ cq_status cq_score_partition_noalloc(cq_context* ctx, const cq_graph* g, const i
   ctx->err[0] = 0;
   if (!h_out || !g) return fail(ctx, CQ_E_INVALID_ARG, "null graph or result pointer");
   if (!ctx->scratch) return fail(ctx, CQ_E_DEVICE, "the scratch array's address on device %d is unknown", ctx->device);
-  const size_t need = graph_score_layout(g, std::max(num_labels, 1)).total;
+  const size_t need = graph_score_layout(g, std::max(num_labels, 1)).min_total;
   if (need > SCRATCH_BYTES)
     return fail(ctx, CQ_E_WORKSPACE, "this call needs %zu bytes of scratch; the library's array holds %zu "
                 "(score with a caller workspace instead)", need, SCRATCH_BYTES);
@@ -2508,7 +2533,10 @@ cq_status cq_server_submit_score(cq_server* srv, const cq_graph* g, const int32_
   r->n = g->n;
   r->L = num_labels;
   r->ha = h_labels;
-  r->ws_bytes = graph_score_layout(g, num_labels).total;
+  // the workspace with room for the tiles' far labels where the arena holds it
+  const ScoreLayout lay = graph_score_layout(g, num_labels);
+  const int64_t all = (int64_t)(cqsrv::aup(4 * (size_t)g->n) + cqsrv::aup(lay.total) + cqsrv::aup(sizeof(cq_score_result)));
+  r->ws_bytes = all <= srv->cfg.memory_budget ? lay.total : lay.min_total;
   // inside a grouped launch: the task's workspace and, at most, one group's interleaved
   // labels (8 bytes per node; batch_layout)
   r->group_ws = cqsrv::aup(score_layout(g->n, g->nnz, num_labels).total) + cqsrv::aup(8 * (size_t)g->n);
