@@ -273,12 +273,12 @@ __device__ __forceinline__ u32 wave_count(u32* s, u32 bin, bool on) {
     const u64 act = __ballot(on);
     if (act == 0) break;
     const int leader = __ffsll((long long)act) - 1;
-    const u32 lead_bin = __shfl(bin, leader, 64);
+    const u32 lead_bin = (u32)__builtin_amdgcn_readlane((int)bin, leader);
     const u64 grp = __ballot(on && bin == lead_bin);
     if (__popcll(grp) < 4) break;  // mixed bins: plain atomics below
     u32 b = 0;
     if (lane == (u32)leader) b = atomicAdd(&s[lead_bin], (u32)__popcll(grp));
-    b = __shfl(b, leader, 64);
+    b = (u32)__builtin_amdgcn_readlane((int)b, leader);
     if (on && bin == lead_bin) {
       old = b + (u32)__popcll(grp & ((1ull << lane) - 1ull));
       on = false;

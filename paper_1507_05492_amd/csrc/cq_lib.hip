@@ -1321,7 +1321,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g) {
     if (e == hipSuccess) e = hipMemcpyAsync(&far, fstart + cells, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
   }
-  alloc((void**)&g->ncol, 2 * (size_t)near);
+  alloc((void**)&g->ncol, 2 * (size_t)near + 16);  // read in 16-byte words
   alloc((void**)&g->fcol, 2 * (size_t)far);
   alloc((void**)&g->frow, 2 * (size_t)far);
   if (g->owned_w) {

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void k_rows_place(int n, const int32_t* __rest
 // its own number.
 constexpr int RG_UNROLL = 8;
 template <class LT, int NT, int NTV>
-__global__ __launch_bounds__(NT) void k_rows_groups(const uint2* __restrict__ rec, const int32_t* __restrict__ col,
+__global__ __launch_bounds__(NT, 8) void k_rows_groups(const uint2* __restrict__ rec, const int32_t* __restrict__ col,
                                                     const LT* __restrict__ labx, const u32* __restrict__ start,
                                                     const u32* __restrict__ order, u32* __restrict__ D,
                                                     Ctl* __restrict__ ctl, u32 Lv, ScoreVis vis, u32* __restrict__ wq) {

@@ -163,70 +163,91 @@ __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int parts, con
 //
 // STAGE_BLOCKS: consecutive rows with the same label form a run.  An entry whose neighbour has
 // the row's own label c only adds to 2|E_c^in| (and, weighted, its weight to 2 w_in(c)) and
-// is not staged; the others are counted per run and kept in an LDS buffer, each run adds
-// (own << 32) | others to community c's cursor with one atomic, which hands it consecutive
-// places in the segment, and the buffer is written out there run by run.  When the buffer
-// overflows (and for 32-bit labels) the tile's entries are walked a second time instead.
+// is not staged; the others are counted per run, each run adds (own << 32) | others to
+// community c's cursor with one atomic, which hands it consecutive places in the segment,
+// and they are written there run by run.  Until then far entries stay in registers and near
+// ones (few of them have another label) in an LDS buffer; what does not fit is read again.
 // Weighted: own-label weights are summed exactly per run and added to IWacc[c].
 //
 // STAGE_ROWS (a partition that does not follow the stored order, so that runs are hardly
 // longer than a row): every entry goes to its row's place, start + chunk prefix + per-node
-// offset, near entries first.
+// offset, near entries first.  The rows are put together in LDS and written from there by 16
+// lanes each: written one by one, the far entries' 2-byte stores were one L2 request each
+// (0.3 of 0.7 ms on the 10M-node graph).
 //
-// Rows of near entries are found through s_row8, the row of every eighth entry, and a short
-// walk.  Far entries come in one short run per slice: half-waves take a slice each.
-constexpr int TG_CHUNK = 16384;               // near entries per step of the row table
-constexpr int TG_BUF = 8192, TG_BUF_W = 4096; // entries of another label kept in LDS
-constexpr int TG_UNROLL = 8;
+// A tile is a chain of a few dependent loads, and two workgroups share a CU, so the pass is
+// bound by latency and by LDS work per entry: a thread loads eight near entries at once and
+// all of its far ones before the first is used, a wave's 512 near entries nearly always lie
+// in one run (one LDS read per entry, two atomics per wave), and a far entry's slice is found
+// through s_seg8, the slice of every eighth far entry, and a short walk.
+constexpr int TG_FAR = 8;                     // far entries per thread held in registers
+constexpr int TG_CHUNK = 16384;               // near entries per step of the row table (STAGE_ROWS)
+constexpr int TG_BUF = 4096, TG_BUF_W = 1536; // near entries of another label kept in LDS
 template <class LT, bool WT>
 struct TileLds {
   static constexpr int PER = 16 / (int)sizeof(LT);
   static constexpr int WIN = (TG_ROWS + 2 * TG_HALO + PER) / PER * 4;        // words of the label window
   static constexpr int BUF = sizeof(LT) == 2 ? (WT ? TG_BUF_W : TG_BUF) : 0; // (run << 16) | label
-  static constexpr int WORDS = WIN + (TG_ROWS + 4) + TG_CHUNK / 16 + 4 * (TG_ROWS + 4) + BUF + (WT ? BUF + 4 * TG_ROWS : 0) +
-                               2 * TG_MAX_SLICES;
+  static constexpr int ARR = TG_ROWS + 4;
+  static constexpr int SEG = 2 * (TG_MAX_SLICES + 2) + TG_FAR * TG_THREADS / 16;
+  // STAGE_ROWS puts the rows together in BUF, EXTRA and, when all far entries fit the
+  // registers, SEG: 19,072 entries, and two workgroups per CU
+  static constexpr int EXTRA = sizeof(LT) == 2 && !WT ? 3900 : 0;
+  static constexpr int WORDS = WIN + 6 * ARR + BUF + (WT ? BUF + 4 * TG_ROWS : EXTRA) + SEG;
   static constexpr size_t BYTES = 4 * (size_t)WORDS;
 };
+static_assert(TG_CHUNK / 16 + 2 <= TG_ROWS + 4, "the row table of STAGE_ROWS takes a row array");
+static_assert(TileLds<uint16_t, false>::BYTES + 128 <= 80 << 10, "two workgroups per CU");
 
 template <class LT, bool WT>
-__global__ __launch_bounds__(TG_THREADS) void k_tile_gather(int n, int S, const int32_t* __restrict__ rp,
-                                                            const u32* __restrict__ nrp, const uint16_t* __restrict__ ncol,
-                                                            const u32* __restrict__ fpt, const uint16_t* __restrict__ frow,
-                                                            const LT* __restrict__ fl, const LT* __restrict__ labx,
-                                                            const u32* __restrict__ start, const u32* __restrict__ D,
-                                                            unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl,
-                                                            LT* __restrict__ CB, const float* __restrict__ nw,
-                                                            const float* __restrict__ fw, float* __restrict__ CW,
-                                                            unsigned long long* __restrict__ IWacc, int L, int chunk,
-                                                            const u32* __restrict__ PM, const u32* __restrict__ loc) {
+__global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
+    int n, int S, const int32_t* __restrict__ rp, const u32* __restrict__ nrp, const uint16_t* __restrict__ ncol,
+    const u32* __restrict__ fpt, const uint16_t* __restrict__ frow, const LT* __restrict__ fl, const LT* __restrict__ labx,
+    const u32* __restrict__ start, const u32* __restrict__ D, unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl,
+    LT* __restrict__ CB, const float* __restrict__ nw, const float* __restrict__ fw, float* __restrict__ CW,
+    unsigned long long* __restrict__ IWacc, int L, int chunk, const u32* __restrict__ PM, const u32* __restrict__ loc) {
   using TL = TileLds<LT, WT>;
   constexpr u32 NOLAB = (u32)LabelT<LT>::SENTINEL;
+  constexpr int WAVES = TG_THREADS / 64;
   extern __shared__ __align__(16) u32 s_mem[];
   u32* s_win32 = s_mem;
   const LT* s_win = reinterpret_cast<const LT*>(s_win32);
-  u32* s_nr = s_win32 + TL::WIN;                                       // near row starts (tile-relative)
-  uint16_t* s_row8 = reinterpret_cast<uint16_t*>(s_nr + TG_ROWS + 4);  // row of every eighth near entry of a chunk
-  u32* s_a = s_nr + TG_ROWS + 4 + TG_CHUNK / 16;  // blocks: run of every row;         rows: place of the row's first entry
-  u32* s_b = s_a + TG_ROWS + 4;                   // blocks: first row of every run;   rows: next free place of the row's far entries
-  u32* s_cnt = s_b + TG_ROWS + 4;                 // blocks: staged entries per run, then the next free place of the run
-  u32* s_base = s_cnt + TG_ROWS + 4;              // blocks: place of the run's first staged entry
-  u32* s_buf = s_base + TG_ROWS + 4;
+  u32* s_nr = s_win32 + TL::WIN;   // near row starts (tile-relative); later the places of the runs
+  u32* s_a = s_nr + TL::ARR;       // run (and 16-bit label) of every row
+  u32* s_b = s_a + TL::ARR;        // first row of every run
+  u32* s_cnt = s_b + TL::ARR;      // staged far entries per run (those in registers)
+  u32* s_more = s_cnt + TL::ARR;   // the other staged entries per run, then the next free place after the former
+  u32* s_base = s_more + TL::ARR;  // first near entry of every run
+  u32* s_place = s_nr;
+  u32* s_buf = s_base + TL::ARR;
   float* s_wbuf = reinterpret_cast<float*>(s_buf + TL::BUF);
   unsigned long long* s_ilo = reinterpret_cast<unsigned long long*>(s_buf + 2 * TL::BUF);  // WT: own-label weight sum per run
   unsigned long long* s_ihi = s_ilo + TG_ROWS;
-  u32* s_seg = s_buf + TL::BUF + (WT ? TL::BUF + 4 * TG_ROWS : 0);  // far entries: first and end per slice
-  __shared__ u32 s_wave[TG_THREADS / 64];
+  u32* s_pre = s_buf + TL::BUF + (WT ? TL::BUF + 4 * TG_ROWS : TL::EXTRA);  // far entries before each slice
+  u32* s_foff = s_pre + TG_MAX_SLICES + 2;                          // place of a slice's far entry j, minus j
+  uint16_t* s_seg8 = reinterpret_cast<uint16_t*>(s_foff + TG_MAX_SLICES + 2);
+  __shared__ u32 s_wave[WAVES];
   __shared__ u32 s_nbuf;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int T = (n + TG_ROWS - 1) / TG_ROWS;
   // each XCD (workgroup b runs on XCD b % 8) takes a contiguous eighth of the tiles
   const int per = (T + 7) / 8, t = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
   if ((int)(blockIdx.x / 8u) >= per || t >= T) return;
-  const bool by_rows = !WT && ctl->mode == STAGE_ROWS;
+  const bool by_rows = !WT && sizeof(LT) == 2 && ctl->mode == STAGE_ROWS;  // see k_colscan_rows
   const int r0 = t * TG_ROWS, rows = min(TG_ROWS, n - r0);
   const int w0 = tile_w0(r0), w1 = tile_w1(r0, n), roff = r0 - w0;
   const u32 nb = nrp[r0];
   const u32 ne = nrp[r0 + rows] - nb;
+  const u32 ng = (nb & 7u) + ne;  // near entries from the 16-byte word that holds the first one
+  const uint4* ncol8 = reinterpret_cast<const uint4*>(ncol + (nb & ~7u));
+  // the wave's first block of near entries (word i holds entries 8 i .. 8 i + 7 from nb & ~7)
+  uint4 ahead = make_uint4(0u, 0u, 0u, 0u);
+  if ((u32)(8 * tid) < ng) ahead = ncol8[tid];
+  u32 fa = 0, fe = 0;
+  if (tid < S) {
+    fa = fpt[(size_t)t * S + tid];
+    fe = fpt[((size_t)t + 1) * S + tid];
+  }
   {
     typedef u32 v4u __attribute__((ext_vector_type(4)));
     const v4u* src = reinterpret_cast<const v4u*>(labx + w0);  // w0 is a multiple of 1,024; the array is padded past n
@@ -234,97 +255,136 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_gather(int n, int S, const 
     for (int i = tid; i < (w1 - w0 + TL::PER - 1) / TL::PER; i += TG_THREADS) dst[i] = src[i];
     if (tid <= rows) s_nr[tid] = nrp[r0 + tid] - nb;
     if (tid == 0 && rows == TG_ROWS) s_nr[TG_ROWS] = ne;
-    for (int i = tid; i < S; i += TG_THREADS) {
-      s_seg[i] = fpt[(size_t)t * S + i];
-      s_seg[S + i] = fpt[((size_t)t + 1) * S + i];
-    }
     if (tid == 0) s_nbuf = 0;
   }
+  // far entries numbered slice by slice
+  u32 nf = 0;
+  {
+    const u32 cnt = fe - fa;
+    const u32 incl = wave_incl_scan(cnt);
+    if (lane == 63) s_wave[wv] = incl;
+    __syncthreads();
+    u32 before = 0;
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) {
+      const u32 k = s_wave[i];
+      if (i < wv) before += k;
+      nf += k;
+    }
+    const u32 pre = before + incl - cnt;
+    if (tid < S) {
+      s_pre[tid] = pre;
+      s_foff[tid] = fa - pre;
+      for (u32 g = (pre + 7u) / 8u; g * 8u < pre + cnt && g < (u32)(TG_FAR * TG_THREADS / 8); ++g) s_seg8[g] = (uint16_t)tid;
+    }
+    if (tid == 0) s_pre[S] = nf;
+  }
   __syncthreads();
-  // Calls f(row, label, weight) for every entry of the tile (lanes of a wave on neighbouring
-  // entries; f may use wave votes, which then see the calling lanes).  near_place: called
-  // with the entry's number in its row too.
-  auto for_near = [&](auto&& f) {
-    for (u32 c0 = 0; c0 < ne; c0 += TG_CHUNK) {
-      const u32 c1 = min(ne, c0 + (u32)TG_CHUNK);
-      __syncthreads();  // the previous chunk's row table is no longer read
-      if (tid < rows) {
-        const u32 a = max(s_nr[tid], c0), b = min(s_nr[tid + 1], c1);
-        for (u32 g = (a + 7u) / 8u; g * 8u < b; ++g) s_row8[g - c0 / 8u] = (uint16_t)tid;
-      }
-      __syncthreads();
-      for (u32 eb = c0 + tid; eb < c1; eb += TG_THREADS * TG_UNROLL) {
-        u32 off[TG_UNROLL], row[TG_UNROLL], x[TG_UNROLL];
-        float wt[TG_UNROLL];
+  // place of far entry j (slices without entries are walked over)
+  auto far_at = [&](u32 j) {
+    u32 s;
+    if (j < (u32)(TG_FAR * TG_THREADS)) {
+      s = s_seg8[j >> 3];
+    } else {  // beyond the table: last slice whose entries start at or before j
+      s = 0;
+      for (u32 st = TG_MAX_SLICES / 2; st > 0; st >>= 1)
+        if (s + st < (u32)S && s_pre[s + st] <= j) s += st;
+    }
+    while (s_pre[s + 1] <= j) ++s;
+    return s_foff[s] + j;
+  };
+  // the thread's far entries j = tid + 1024 k: row << 16 | label (16-bit labels), all loads in flight
+  u32 fat[TG_FAR], fr[TG_FAR], fx[TG_FAR];
 #pragma unroll
-        for (int k = 0; k < TG_UNROLL; ++k) {
-          const u32 e = min(eb + (u32)(k * TG_THREADS), c1 - 1u);  // in bounds; masked below
-          off[k] = ncol[nb + e];
-          wt[k] = WT ? nw[nb + e] : 0.0f;
-        }
-#pragma unroll
-        for (int k = 0; k < TG_UNROLL; ++k) {
-          const u32 e = min(eb + (u32)(k * TG_THREADS), c1 - 1u);
-          u32 r = s_row8[(e - c0) >> 3];
-          while (s_nr[r + 1] <= e) ++r;
-          row[k] = r;
-        }
-#pragma unroll
-        for (int k = 0; k < TG_UNROLL; ++k) x[k] = (u32)s_win[off[k]];
-#pragma unroll
-        for (int k = 0; k < TG_UNROLL; ++k) {
-          const u32 e = eb + (u32)(k * TG_THREADS);
-          if (e < c1) f(row[k], x[k], wt[k], e - s_nr[row[k]]);
-        }
-      }
+  for (int k = 0; k < TG_FAR; ++k) {
+    const u32 j = (u32)(tid + k * TG_THREADS);
+    fr[k] = 0;
+    fx[k] = 0;
+    if (j < nf) {
+      fat[k] = far_at(j);
+      fr[k] = frow[fat[k]];
+      fx[k] = (u32)fl[fat[k]];
+    }
+  }
+  // Walks the tile's near entries in wave blocks of 512: f(e, off) with e the number of the
+  // lane's first of eight entries (from nb & ~7) and off their window offsets, two per word.
+  auto near_blocks = [&](auto&& f) {
+    uint4 q = ahead;
+    for (u32 b = (u32)wv * 512u; b < ng; b += WAVES * 512u) {
+      const u32 next = b + WAVES * 512u + 8u * (u32)lane;
+      uint4 q1 = make_uint4(0u, 0u, 0u, 0u);
+      if (next < ng) q1 = ncol8[next / 8u];
+      f(b, b + 8u * (u32)lane, q);
+      q = q1;
     }
   };
-  auto for_far = [&](auto&& f) {
-    constexpr int HW = TG_THREADS / 32;
-    const u32 hl = (u32)tid & 31u;
-    for (int s = tid >> 5; s < S; s += 2 * HW) {  // two slices in flight
-      const int s2 = s + HW < S ? s + HW : s;
-      const u32 a = s_seg[s], b = s_seg[S + s];
-      const u32 a2 = s_seg[s2], b2 = s2 != s ? s_seg[S + s2] : a2;
-      const u32 len = max(b - a, b2 - a2);
-      for (u32 i = hl; i < len; i += 32) {
-        const bool in = a + i < b, in2 = a2 + i < b2;
-        u32 r = 0, x = 0, r2 = 0, x2 = 0;
-        float wa = 0.0f, wb = 0.0f;
-        if (in) {
-          r = frow[a + i];
-          x = (u32)fl[a + i];
-          if (WT) wa = fw[a + i];
-        }
-        if (in2) {
-          r2 = frow[a2 + i];
-          x2 = (u32)fl[a2 + i];
-          if (WT) wb = fw[a2 + i];
-        }
-        if (in) f(r, x, wa);
-        if (in2) f(r2, x2, wb);
-      }
-    }
+  auto off_of = [](const uint4& q, int k) {
+    const u32 w = k < 2 ? q.x : k < 4 ? q.y : k < 6 ? q.z : q.w;
+    return (k & 1) ? w >> 16 : w & 0xFFFFu;
   };
+  const u32 skip = nb & 7u;  // entry number of the tile's first near entry
   if (by_rows) {
+    // Entries are placed relative to the tile's first entry, row by row.  Per row: end of its
+    // near entries, and the place of near entry e minus e (one LDS read gives both); the next
+    // free place of its far entries; the row's place in its segment (SENT: not written, only
+    // with a label error, which voids the result).
+    uint2* s_row = reinterpret_cast<uint2*>(s_a);  // s_a and s_b
+    u32* s_far = s_cnt;
+    uint16_t* s_row8 = reinterpret_cast<uint16_t*>(s_more);
+    LT* s_out = reinterpret_cast<LT*>(s_buf);
+    const u32 cap = (u32)(TL::BUF + TL::EXTRA + (nf <= (u32)(TG_FAR * TG_THREADS) ? TL::SEG : 0)) * (4 / sizeof(LT));
     if (tid < rows) {
       const int u = r0 + tid;
       const u32 c = (u32)s_win[roff + tid], lu = loc[u];
+      const u32 a = s_nr[tid], b = s_nr[tid + 1], at = (u32)(rp[u] - rp[r0]);
       u32 base = SENT;
       if (c != NOLAB && lu != SENT) base = start[c] + PM[(size_t)(u / chunk) * L + c] + lu;
-      s_a[tid] = base;
-      s_b[tid] = s_nr[tid + 1] - s_nr[tid];  // far entries follow the near ones
+      s_row[tid] = make_uint2(b + skip, at - a - skip);
+      s_far[tid] = at + b - a;
+      s_base[tid] = base;
     }
-    // (for_near's first barrier comes before the first use)
-    for_near([&](u32 r, u32 x, float, u32 i) {
-      const u32 base = s_a[r];
-      if (base != SENT) CB[base + i] = (LT)x;
-    });
-    __syncthreads();  // a tile without near entries passes no barrier above
-    for_far([&](u32 r, u32 x, float) {
-      const u32 base = s_a[r];
-      if (base != SENT) CB[base + atomicAdd(&s_b[r], 1u)] = (LT)x;
-    });
+    auto put = [&](u32 r, u32 at, u32 x) {
+      if (at < cap) s_out[at] = (LT)x;
+      else if (s_base[r] != SENT) CB[s_base[r] + (at - (s_row[r].y + s_nr[r] + skip))] = (LT)x;
+    };
+    for (u32 c0 = 0; c0 < ng; c0 += TG_CHUNK) {
+      const u32 c1 = min(ng, c0 + (u32)TG_CHUNK);
+      __syncthreads();  // the far entries are in registers; the previous chunk's row table is no longer read
+      if (tid < rows) {
+        const u32 a = max(s_nr[tid] + skip, c0), b = min(s_nr[tid + 1] + skip, c1);
+        const u32 lo = s_nr[tid] == 0 ? c0 : a;  // the first group starts before the tile's first entry
+        if (a < b)
+          for (u32 g = (lo + 7u) / 8u; g * 8u < b; ++g) s_row8[g - c0 / 8u] = (uint16_t)tid;
+      }
+      __syncthreads();
+      for (u32 e0 = c0 + 8u * (u32)tid; e0 < c1; e0 += 8u * TG_THREADS) {
+        const uint4 q = c0 == 0 && e0 == 8u * (u32)tid ? ahead : ncol8[e0 / 8u];
+        u32 r = s_row8[(e0 - c0) / 8u];
+        uint2 row = s_row[r];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const u32 e = e0 + (u32)k;
+          if (e >= skip && e < c1) {
+            while (row.x <= e) row = s_row[++r];
+            put(r, row.y + e, (u32)s_win[off_of(q, k)]);
+          }
+        }
+      }
+    }
+    __syncthreads();  // (a tile without near entries passes no barrier above)
+#pragma unroll
+    for (int k = 0; k < TG_FAR; ++k)
+      if ((u32)(tid + k * TG_THREADS) < nf) put(fr[k], atomicAdd(&s_far[fr[k]], 1u), fx[k]);
+    for (u32 j = (u32)(tid + TG_FAR * TG_THREADS); j < nf; j += TG_THREADS) {
+      const u32 at = far_at(j), r = frow[at];
+      put(r, atomicAdd(&s_far[r], 1u), (u32)fl[at]);
+    }
+    __syncthreads();
+    for (int r = tid >> 4; r < rows; r += TG_THREADS / 16) {
+      const u32 base = s_base[r], at = s_row[r].y + s_nr[r] + skip, end = min(s_far[r], cap);
+      if (base == SENT) continue;
+      for (u32 i = at + ((u32)tid & 15u); i < end; i += 16) CB[base + (i - at)] = s_out[i];
+    }
     return;
   }
   // runs of rows with equal labels
@@ -337,17 +397,21 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_gather(int n, int S, const 
     __syncthreads();
     u32 before = 0;
 #pragma unroll
-    for (int i = 0; i < TG_THREADS / 64; ++i) {
+    for (int i = 0; i < WAVES; ++i) {
       const u32 k = s_wave[i];
       if (i < wv) before += k;
       nruns += k;
     }
     const u32 run = before + (u32)__popcll(m & (~0ull >> (63 - lane))) - 1u;  // runs that start at or before this row
-    if (tid < rows) s_a[tid] = run;
-    if (head) s_b[run] = (u32)tid;
+    if (tid < rows) s_a[tid] = sizeof(LT) == 2 ? (run << 16) | c : run;
+    if (head) {
+      s_b[run] = (u32)tid;
+      s_base[run] = s_nr[tid] + skip;
+    }
     if (tid == 0) s_b[nruns] = (u32)rows;
     if (tid < rows) {
       s_cnt[tid] = 0;
+      s_more[tid] = 0;
       if (WT) {
         s_ilo[tid] = 0ull;
         s_ihi[tid] = 0ull;
@@ -355,6 +419,17 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_gather(int n, int S, const 
     }
     __syncthreads();
   }
+  // run of near entry e: the last one whose rows' near entries start at or before e (runs
+  // without near entries start where the next one does)
+  u32 top = 0;
+  if (nruns > 1) top = 1u << (31 - __clz((int)(nruns - 1)));
+  auto run_of = [&](u32 e) {
+    u32 l = 0;
+    for (u32 st = top; st > 0; st >>= 1)
+      if (l + st < nruns && s_base[l + st] <= e) l += st;
+    return l;
+  };
+  auto label_of = [&](u32 run) { return (u32)s_win[roff + s_b[run]]; };
   // WT: a thread sums the own-label weights of its current run and adds them to the run's LDS
   // sum when the run changes (64-bit atomics, the low word's carry added to the high word)
   u32 wrun = SENT;
@@ -366,50 +441,97 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_gather(int n, int S, const 
       if (hi) atomicAdd(&s_ihi[wrun], hi);
     }
   };
-  const u64 below = (1ull << lane) - 1ull;
-  auto stage = [&](u32 r, u32 x, float w) {
-    const u32 run = s_a[r];
-    const bool inter = x != (u32)s_win[roff + r];
-    if (WT && !inter) {
-      if (run != wrun) {
-        wflush();
-        wrun = run;
-        wacc = WeightSum();
-      }
-      u64 vlo, vhi;
-      WeightSum::split(w, vlo, vhi);
-      wacc.add(vlo, vhi);
+  auto own_weight = [&](u32 run, float w) {
+    if (run != wrun) {
+      wflush();
+      wrun = run;
+      wacc = WeightSum();
     }
-    const u64 m = __ballot(inter);
-    if (m == 0) return;
-    // slots once per wave, counts once per wave for the first lane's run
-    const int lead = __ffsll((long long)m) - 1;
-    const u32 rl = __shfl(run, lead, 64);
-    const u64 ms = __ballot(inter && run == rl);
-    u32 slot0 = 0;
-    if (lane == lead) {
-      slot0 = atomicAdd(&s_nbuf, (u32)__popcll(m));
-      atomicAdd(&s_cnt[rl], (u32)__popcll(ms));
-    }
-    slot0 = __shfl(slot0, lead, 64);
-    if (inter) {
-      const u32 slot = slot0 + (u32)__popcll(m & below);
-      if (slot < (u32)TL::BUF) {
-        s_buf[slot] = (run << 16) | x;
-        if (WT) s_wbuf[slot] = w;
-      }
-      if (run != rl) atomicAdd(&s_cnt[run], 1u);
-    }
+    u64 vlo, vhi;
+    WeightSum::split(w, vlo, vhi);
+    wacc.add(vlo, vhi);
   };
-  for_near([&](u32 r, u32 x, float w, u32) { stage(r, x, w); });
-  for_far([&](u32 r, u32 x, float w) { stage(r, x, w); });
+  // calls f(k, run, own label) for the lane's near entries of block b that exist
+  auto with_runs = [&](u32 b, u32 e0, auto&& f) {
+    const u32 q0 = run_of(max(b, skip)), q1 = run_of(min(b + 512u, ng) - 1u);
+    u32 run = q0;
+    if (q0 != q1 && e0 < ng) run = run_of(max(e0, skip));
+    u32 c = label_of(run);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const u32 e = e0 + (u32)k;
+      if (e < skip || e >= ng) continue;
+      if (q0 != q1 && run + 1 < nruns && s_base[run + 1] <= e) {
+        do ++run;
+        while (run + 1 < nruns && s_base[run + 1] <= e);
+        c = label_of(run);
+      }
+      f(k, run, c);
+    }
+    return q0 == q1 ? q0 : SENT;
+  };
+  near_blocks([&](u32 b, u32 e0, const uint4& q) {
+    u32 inter = 0;          // bit k: the lane's entry k has another label
+    u32 rk[8];              // its run (blocks of several runs only)
+    const u32 one = with_runs(b, e0, [&](int k, u32 run, u32 c) {
+      const u32 x = (u32)s_win[off_of(q, k)];
+      rk[k] = run;
+      if (x != c) inter |= 1u << k;
+      else if (WT) own_weight(run, nw[(nb & ~7u) + e0 + (u32)k]);
+    });
+    const u32 cnt = (u32)__popc(inter);
+    const u32 incl = wave_incl_scan(cnt);
+    const u32 total = (u32)__builtin_amdgcn_readlane((int)incl, 63);
+    if (total == 0) return;
+    u32 slot = 0;
+    if (lane == 0) {
+      slot = atomicAdd(&s_nbuf, total);
+      if (one != SENT) atomicAdd(&s_more[one], total);
+    }
+    slot = (u32)__builtin_amdgcn_readfirstlane((int)slot) + incl - cnt;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (!((inter >> k) & 1u)) continue;
+      if (one == SENT) atomicAdd(&s_more[rk[k]], 1u);
+      if (slot < (u32)TL::BUF) {
+        s_buf[slot] = (rk[k] << 16) | (u32)s_win[off_of(q, k)];
+        if (WT) s_wbuf[slot] = nw[(nb & ~7u) + e0 + (u32)k];
+      }
+      ++slot;
+    }
+  });
+  auto of_row = [&](u32 r, u32& run, u32& c) {
+    const u32 q = s_a[r];
+    run = sizeof(LT) == 2 ? q >> 16 : q;
+    c = sizeof(LT) == 2 ? q & 0xFFFFu : (u32)s_win[roff + r];
+  };
+  // far entries: fr becomes the run (SENT: own label), and the entry's rank among the run's
+  // staged entries is known at once
+  u32 rank[TG_FAR];
+#pragma unroll
+  for (int k = 0; k < TG_FAR; ++k) {
+    const bool in = (u32)(tid + k * TG_THREADS) < nf;
+    u32 run = 0, c = 0;
+    of_row(fr[k], run, c);  // row 0 where there is no entry
+    const bool inter = in && fx[k] != c;
+    if (WT && in && !inter) own_weight(run, fw[fat[k]]);
+    fr[k] = inter ? run : SENT;
+    rank[k] = wave_count<2>(s_cnt, run, inter);
+  }
+  for (u32 j = (u32)(tid + TG_FAR * TG_THREADS); j < nf; j += TG_THREADS) {
+    const u32 at = far_at(j);
+    u32 run, c;
+    of_row(frow[at], run, c);
+    if ((u32)fl[at] != c) atomicAdd(&s_more[run], 1u);
+    else if (WT) own_weight(run, fw[at]);
+  }
   if (WT) wflush();
   __syncthreads();
   // one claim per run
   if ((u32)tid < nruns) {
     const u32 ra = s_b[tid], rb = s_b[tid + 1];
     const u32 c = (u32)s_win[roff + ra];
-    const u32 tot = (u32)(rp[r0 + rb] - rp[r0 + ra]), inter = s_cnt[tid];
+    const u32 tot = (u32)(rp[r0 + rb] - rp[r0 + ra]), inter = s_cnt[tid] + s_more[tid];
     u32 base = SENT;
     if (c != NOLAB && tot > 0) {
       const unsigned long long old = atomicAdd(&cur64[c], ((unsigned long long)(tot - inter) << 32) | inter);
@@ -425,42 +547,42 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_gather(int n, int S, const 
         }
       }
     }
-    s_base[tid] = base;
-    s_cnt[tid] = 0;
+    s_place[tid] = base;
+    s_more[tid] = s_cnt[tid];
   }
   __syncthreads();
+  auto put = [&](u32 run, u32 at, u32 x, float w) {
+    const u32 base = s_place[run];
+    if (base == SENT) return;
+    CB[base + at] = (LT)x;
+    if (WT) CW[base + at] = w;
+  };
+#pragma unroll
+  for (int k = 0; k < TG_FAR; ++k)
+    if (fr[k] != SENT) put(fr[k], rank[k], fx[k], WT ? fw[fat[k]] : 0.0f);
+  for (u32 j = (u32)(tid + TG_FAR * TG_THREADS); j < nf; j += TG_THREADS) {
+    const u32 at = far_at(j), x = (u32)fl[at];
+    u32 run, c;
+    of_row(frow[at], run, c);
+    if (x != c) put(run, atomicAdd(&s_more[run], 1u), x, WT ? fw[at] : 0.0f);
+  }
   const u32 nbuf = s_nbuf;
   if (nbuf <= (u32)TL::BUF) {
-    // write the buffer out: each wave takes consecutive places per run (coalesced)
-    for (u32 k = tid; k < nbuf; k += TG_THREADS) {
-      const u32 ent = s_buf[k];
-      const u32 run = ent >> 16;
-      const u64 act = __ballot(true);
-      const int lead = __ffsll((long long)act) - 1;
-      const u32 rl = __shfl(run, lead, 64);
-      const u64 ms = __ballot(run == rl);
-      u32 p0 = 0;
-      if (lane == lead) p0 = atomicAdd(&s_cnt[rl], (u32)__popcll(ms));
-      p0 = __shfl(p0, lead, 64);
-      const u32 rank = run == rl ? p0 + (u32)__popcll(ms & below) : atomicAdd(&s_cnt[run], 1u);
-      const u32 base = s_base[run];
-      if (base != SENT) {
-        CB[base + rank] = (LT)(ent & 0xFFFFu);
-        if (WT) CW[base + rank] = s_wbuf[k];
-      }
+    // each wave takes consecutive places per run (coalesced)
+    for (u32 k0 = 0; k0 < nbuf; k0 += TG_THREADS) {
+      const u32 k = k0 + (u32)tid;
+      const u32 ent = k < nbuf ? s_buf[k] : 0u;
+      const u32 at = wave_count<2>(s_more, ent >> 16, k < nbuf);
+      if (k < nbuf) put(ent >> 16, at, ent & 0xFFFFu, WT ? s_wbuf[k] : 0.0f);
     }
   } else {
-    // buffer overflow (or 32-bit labels): walk the tile's entries again
-    auto direct = [&](u32 r, u32 x, float w) {
-      const u32 run = s_a[r], base = s_base[run];
-      if (x != (u32)s_win[roff + r] && base != SENT) {
-        const u32 rank = atomicAdd(&s_cnt[run], 1u);
-        CB[base + rank] = (LT)x;
-        if (WT) CW[base + rank] = w;
-      }
-    };
-    for_near([&](u32 r, u32 x, float w, u32) { direct(r, x, w); });
-    for_far([&](u32 r, u32 x, float w) { direct(r, x, w); });
+    // more than the buffer holds (or 32-bit labels): walk the near entries again
+    near_blocks([&](u32 b, u32 e0, const uint4& q) {
+      (void)with_runs(b, e0, [&](int k, u32 run, u32 c) {
+        const u32 x = (u32)s_win[off_of(q, k)];
+        if (x != c) put(run, atomicAdd(&s_more[run], 1u), x, WT ? nw[(nb & ~7u) + e0 + (u32)k] : 0.0f);
+      });
+    });
   }
 }
 
