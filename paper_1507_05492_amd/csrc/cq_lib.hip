@@ -68,6 +68,7 @@ struct cq_graph {
   float *nw = nullptr, *fw = nullptr;                          // their weights
   int64_t far = 0;                 // far entries
   int slices = 0;
+  bool blocked = false;            // runs may be staged compactly through the tiles (n <= 2^24); else by rows only
   u32* deg_in = nullptr;           // label permutation plan (caller order -> stored order): degrees,
   u32* pos1 = nullptr;             // bucket slots and their stored ids; null when not built
   uint16_t* tgt = nullptr;         // offset of the slot's stored id in its bucket
@@ -270,7 +271,9 @@ struct ScoreLayout {
   size_t CW, SW, IW, PENW, INVN;  // weighted graphs only (0 otherwise)
   bool rows;  // scored by member rows (cq_rows.hpp): rec and bad in place of the staged entries
   size_t rec, bad;
-  bool tiled;   // scored through the graph's tiles (cq_tiles.hpp); fl: its far entries' labels
+  // scored through the graph's tiles (cq_tiles.hpp): staging chosen by the partition, or by
+  // rows always; fl: the far entries' labels
+  bool tiled, tile_rows;
   size_t fl, min_total;
   int small_wgs;  // > 0: scored in two launches (cq_small.hpp) by that many counting workgroups
   size_t slots;
@@ -340,14 +343,15 @@ constexpr int64_t SMALL_MAX_CELLS = 256 << 10;
 // labels as well (total), else its row-major copy.  Member rows and small graphs take the
 // workspace of the staged path (which they fit unless the graph has hardly any edges).
 ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_MAX) {
-  const bool perm = g->nrp && g->pos1 && L <= PRIV_MAX;
+  const bool perm = g->blocked && g->pos1 && L <= PRIV_MAX;
   ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
   s.min_total = s.total;
-  if (g->nrp) {
+  if (g->nrp && (g->blocked || s.small)) {
     ScoreLayout t = s;
     Carve c;
     c.off = s.total;
-    t.tiled = true;
+    t.tiled = g->blocked;
+    t.tile_rows = !g->blocked;
     t.fl = c.take((s.small ? 2 : 4) * (size_t)g->far);
     t.total = c.off;
     if (t.total <= have) return t;
@@ -711,7 +715,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   }
   {
     StageMark mk(ctx, ST_GATHER, timed);
-    if (tiled) {
+    if (tiled || lay.tile_rows) {
       const int T = (int)((n + TG_ROWS - 1) / TG_ROWS), S = g->slices;
       LT* fl = at<LT>(ws, lay.fl);
       if (g->far > 0) {
@@ -723,13 +727,13 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
       const unsigned grid = 8u * (unsigned)((T + 7) / 8);
       unsigned long long* cur = at<unsigned long long>(ws, lay.cursor);
       if (CW)
-        k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::BYTES, s>>>(
+        k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(S), s>>>(
             (int)n, S, g->rp, g->nrp, g->ncol, g->fpt, g->frow, fl, labx, start, D, cur, ctl, CB, g->nw, g->fw, CW,
-            at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc);
+            at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc, 0);
       else
-        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::BYTES, s>>>(
+        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(S), s>>>(
             (int)n, S, g->rp, g->nrp, g->ncol, g->fpt, g->frow, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr, nullptr,
-            nullptr, L, lay.chunk, PM, loc);
+            nullptr, L, lay.chunk, PM, loc, lay.tile_rows ? 1 : 0);
     } else {
       const unsigned grid = 8u * (unsigned)((((int64_t)n + GROWS - 1) / GROWS + 7) / 8);  // one workgroup per tile
       if (lay.priv && CW)
@@ -1289,7 +1293,9 @@ constexpr int LP_SALTED_SWEEPS = 20;
 // reads of the member rows stay in it), up to the ids the tile tables are made for.
 constexpr int64_t BLOCK_MAX_N = 16 << 20;
 constexpr int64_t BLOCK_MIN_N = 1 << 20;
-static_assert(BLOCK_MAX_N <= (int64_t)TG_MAX_SLICES << TS_SHIFT, "slices");
+// Larger graphs are tiled as well (unless CQ_GRAPH_NO_BLOCKS), but always staged by rows.
+constexpr int64_t TILE_MAX_N = (int64_t)TG_MAX_SLICES << TS_SHIFT;
+static_assert(BLOCK_MAX_N <= TILE_MAX_N, "slices");
 
 // Builds the tiles of the renumbered graph (g->owned_rp / owned_col / owned_w).
 cq_status build_tiles(cq_context* ctx, cq_graph* g) {
@@ -1358,7 +1364,7 @@ cq_status build_perm_plan(cq_context* ctx, cq_graph* g, const int32_t* newid, co
   alloc((void**)&g->pos1, 4 * (size_t)n);
   alloc((void**)&g->tgt, 2 * (size_t)n);
   alloc((void**)&g->pbstart, 4 * ((size_t)nb + 1));
-  if (g->nrp) {
+  if (g->blocked) {
     alloc((void**)&g->lrank, 2 * (size_t)n);
     alloc((void**)&g->spos, 4 * (size_t)n);
   } else if (((int64_t)n + SB_MASK) >> SB_SHIFT <= SB_MAX) {
@@ -1402,7 +1408,7 @@ cq_status build_perm_plan(cq_context* ctx, cq_graph* g, const int32_t* newid, co
 }
 
 // Builds the renumbered copy of a graph (see CQ_GRAPH_REORDER in cq.h).
-cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, const int32_t* col, bool blocks) {
+cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, const int32_t* col, bool blocks, bool tiled) {
   const int n = g->n;
   const int64_t nnz = g->nnz;
   hipStream_t s = ctx->stream;
@@ -1472,8 +1478,9 @@ cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, 
     k_new_degree<<<gn, 256, 0, s>>>(n, rp, g->owned_perm, cnt);
     scan_u32(cnt, reinterpret_cast<u32*>(g->owned_rp), n, tiles, s);
     k_relabel_rows<<<gw, 256, 0, s>>>(n, rp, col, g->owned_perm, newid, g->owned_rp, g->owned_col, g->w, g->owned_w);
-    if (blocks) st = build_tiles(ctx, g);
-    if (st == CQ_OK && (g->nrp || n >= BLOCK_MIN_N)) st = build_perm_plan(ctx, g, newid, rp);
+    g->blocked = blocks;
+    if (blocks || tiled) st = build_tiles(ctx, g);
+    if (st == CQ_OK && (blocks || n >= BLOCK_MIN_N)) st = build_perm_plan(ctx, g, newid, rp);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (st == CQ_OK && e != hipSuccess) st = fail(ctx, CQ_E_DEVICE, "renumbering the graph: %s", hipGetErrorString(e));
@@ -1485,7 +1492,7 @@ cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, 
     g->col = g->owned_col;
     g->perm = g->owned_perm;
     if (g->owned_w) g->w = g->owned_w;
-    g->reordered = CQ_GRAPH_REORDER | (g->nrp ? 0u : CQ_GRAPH_NO_BLOCKS);
+    g->reordered = CQ_GRAPH_REORDER | (g->blocked ? 0u : CQ_GRAPH_NO_BLOCKS);
     g->owned_bytes = (int64_t)(4 * ((size_t)n + 1) + 4 * (size_t)nnz + 4 * (size_t)n);
     if (g->nrp) {
       const size_t T = ((size_t)n + TG_ROWS - 1) / TG_ROWS;
@@ -2024,10 +2031,10 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint16_t>), 2 << TS_SHIFT);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint32_t>), 4 << TS_SHIFT);
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::BYTES);
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::BYTES);
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::BYTES);
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::BYTES);
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_MAX_SLICES));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_MAX_SLICES));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::bytes(TG_MAX_SLICES));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::bytes(TG_MAX_SLICES));
   set_big_lds(reinterpret_cast<const void*>(k_small_count), ss_lds(SS_MAX_N, SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_final), 4 * (size_t)ss_cells(SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_compare), 4 * (size_t)SC_MAX_CELLS + 24 * (size_t)SC_MAX_L + 64);
@@ -2175,7 +2182,8 @@ cq_status graph_load(cq_context* ctx, int32_t n, int64_t nnz, const int32_t* d_r
   if ((flags & CQ_GRAPH_REORDER) && nnz > 0) {
     const bool blocks = (flags & CQ_GRAPH_BLOCKS) ? n <= BLOCK_MAX_N
                         : !(flags & CQ_GRAPH_NO_BLOCKS) && n >= BLOCK_MIN_N && n <= BLOCK_MAX_N;
-    cq_status st = build_locality_order(ctx, g, d_row_ptr, d_col_idx, blocks);
+    const bool tiles = !(flags & CQ_GRAPH_NO_BLOCKS) && n > BLOCK_MAX_N && n <= TILE_MAX_N && !d_weights;
+    cq_status st = build_locality_order(ctx, g, d_row_ptr, d_col_idx, blocks, tiles);
     if (st != CQ_OK) {
       delete g;
       return st;

@@ -26,7 +26,7 @@ constexpr int TG_ROWS = 1024;        // rows per tile, one per thread
 constexpr int TG_HALO = 4096;        // ids of the window before and after the tile's rows
 constexpr int TS_SHIFT = 15;
 constexpr int TS_NODES = 1 << TS_SHIFT;  // ids per slice: 64 KB of 16-bit labels, 128 KB of 32-bit ones
-constexpr int TG_MAX_SLICES = 512;   // n up to 2^24
+constexpr int TG_MAX_SLICES = 4096;  // n up to 2^27 (12-bit slice numbers, 16 KB of counters at load time)
 static_assert(TG_ROWS == TG_THREADS, "one row per thread");
 static_assert(TG_ROWS + 2 * TG_HALO <= 65536, "16-bit window offsets");
 
@@ -189,15 +189,17 @@ struct TileLds {
   static constexpr int WIN = (TG_ROWS + 2 * TG_HALO + PER) / PER * 4;        // words of the label window
   static constexpr int BUF = sizeof(LT) == 2 ? (WT ? TG_BUF_W : TG_BUF) : 0; // (run << 16) | label
   static constexpr int ARR = TG_ROWS + 4;
-  static constexpr int SEG = 2 * (TG_MAX_SLICES + 2) + TG_FAR * TG_THREADS / 16;
-  // STAGE_ROWS puts the rows together in BUF, EXTRA and, when all far entries fit the
-  // registers, SEG: 19,072 entries, and two workgroups per CU
-  static constexpr int EXTRA = sizeof(LT) == 2 && !WT ? 3900 : 0;
-  static constexpr int WORDS = WIN + 6 * ARR + BUF + (WT ? BUF + 4 * TG_ROWS : EXTRA) + SEG;
-  static constexpr size_t BYTES = 4 * (size_t)WORDS;
+  static constexpr int BASE = WIN + 7 * ARR + BUF + (WT ? BUF + 4 * TG_ROWS : 0);
+  static constexpr int seg(int S) { return 2 * (S + 2) + TG_FAR * TG_THREADS / 16; }  // the far entries' tables
+  // 16-bit labels, unweighted: STAGE_ROWS puts the rows together in BUF and what follows it, so
+  // the workgroup takes all that leaves room for two per CU
+  static constexpr int FULL = ((80 << 10) - 640) / 4;
+  static constexpr int words(int S) {
+    return sizeof(LT) == 2 && !WT && BASE + seg(S) < FULL ? FULL : BASE + seg(S);
+  }
+  static constexpr size_t bytes(int S) { return 4 * (size_t)words(S); }
 };
 static_assert(TG_CHUNK / 16 + 2 <= TG_ROWS + 4, "the row table of STAGE_ROWS takes a row array");
-static_assert(TileLds<uint16_t, false>::BYTES + 128 <= 80 << 10, "two workgroups per CU");
 
 template <class LT, bool WT>
 __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
@@ -205,7 +207,8 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     const u32* __restrict__ fpt, const uint16_t* __restrict__ frow, const LT* __restrict__ fl, const LT* __restrict__ labx,
     const u32* __restrict__ start, const u32* __restrict__ D, unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl,
     LT* __restrict__ CB, const float* __restrict__ nw, const float* __restrict__ fw, float* __restrict__ CW,
-    unsigned long long* __restrict__ IWacc, int L, int chunk, const u32* __restrict__ PM, const u32* __restrict__ loc) {
+    unsigned long long* __restrict__ IWacc, int L, int chunk, const u32* __restrict__ PM, const u32* __restrict__ loc,
+    int always_rows) {
   using TL = TileLds<LT, WT>;
   constexpr u32 NOLAB = (u32)LabelT<LT>::SENTINEL;
   constexpr int WAVES = TG_THREADS / 64;
@@ -218,14 +221,15 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   u32* s_cnt = s_b + TL::ARR;      // staged far entries per run (those in registers)
   u32* s_more = s_cnt + TL::ARR;   // the other staged entries per run, then the next free place after the former
   u32* s_base = s_more + TL::ARR;  // first near entry of every run
+  u32* s_first = s_base + TL::ARR; // first stored entry of every run
   u32* s_place = s_nr;
-  u32* s_buf = s_base + TL::ARR;
+  u32* s_buf = s_first + TL::ARR;
   float* s_wbuf = reinterpret_cast<float*>(s_buf + TL::BUF);
   unsigned long long* s_ilo = reinterpret_cast<unsigned long long*>(s_buf + 2 * TL::BUF);  // WT: own-label weight sum per run
   unsigned long long* s_ihi = s_ilo + TG_ROWS;
-  u32* s_pre = s_buf + TL::BUF + (WT ? TL::BUF + 4 * TG_ROWS : TL::EXTRA);  // far entries before each slice
-  u32* s_foff = s_pre + TG_MAX_SLICES + 2;                          // place of a slice's far entry j, minus j
-  uint16_t* s_seg8 = reinterpret_cast<uint16_t*>(s_foff + TG_MAX_SLICES + 2);
+  u32* s_pre = s_mem + TL::words(S) - TL::seg(S);  // far entries before each slice
+  u32* s_foff = s_pre + S + 2;                     // place of a slice's far entry j, minus j
+  uint16_t* s_seg8 = reinterpret_cast<uint16_t*>(s_foff + S + 2);
   __shared__ u32 s_wave[WAVES];
   __shared__ u32 s_nbuf;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -233,9 +237,35 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   // each XCD (workgroup b runs on XCD b % 8) takes a contiguous eighth of the tiles
   const int per = (T + 7) / 8, t = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
   if ((int)(blockIdx.x / 8u) >= per || t >= T) return;
-  const bool by_rows = !WT && sizeof(LT) == 2 && ctl->mode == STAGE_ROWS;  // see k_colscan_rows
+  const bool by_rows = !WT && sizeof(LT) == 2 && (always_rows || ctl->mode == STAGE_ROWS);  // see k_colscan_rows
   const int r0 = t * TG_ROWS, rows = min(TG_ROWS, n - r0);
   const int w0 = tile_w0(r0), w1 = tile_w1(r0, n), roff = r0 - w0;
+  // Every load that depends on no other is issued first, then those that need the tile's first
+  // near entry or the row's label; the LDS writes wait for all of them at once.
+  constexpr int SPT = TG_MAX_SLICES / TG_THREADS;
+  const int spt = (S + TG_THREADS - 1) / TG_THREADS;
+  const int my_row = r0 + min(tid, rows - 1);
+  typedef u32 v4u __attribute__((ext_vector_type(4)));
+  constexpr int WV = TL::WIN / 4;                                // 16-byte words of the window
+  constexpr int WPT = (WV + TG_THREADS - 1) / TG_THREADS;
+  const int nwin = (w1 - w0 + TL::PER - 1) / TL::PER;
+  const v4u* win = reinterpret_cast<const v4u*>(labx + w0);  // w0 is a multiple of 1,024; the array is padded past n
+  v4u wreg[WPT];
+#pragma unroll
+  for (int i = 0; i < WPT; ++i) wreg[i] = win[min(tid + i * TG_THREADS, nwin - 1)];
+  const u32 own = (u32)labx[my_row];
+  const u32 row_n = nrp[my_row];
+  const int row_e = rp[my_row];
+  const u32 lu = by_rows ? loc[my_row] : 0u;
+  // the thread's slices (consecutive): far entries [fa, fe) of each
+  u32 fa[SPT], fe[SPT];
+#pragma unroll
+  for (int i = 0; i < SPT; ++i) {
+    const int s = tid * spt + i;
+    const bool in = i < spt && s < S;
+    fa[i] = in ? fpt[(size_t)t * S + s] : 0u;
+    fe[i] = in ? fpt[((size_t)t + 1) * S + s] : 0u;
+  }
   const u32 nb = nrp[r0];
   const u32 ne = nrp[r0 + rows] - nb;
   const u32 ng = (nb & 7u) + ne;  // near entries from the 16-byte word that holds the first one
@@ -243,39 +273,46 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   // the wave's first block of near entries (word i holds entries 8 i .. 8 i + 7 from nb & ~7)
   uint4 ahead = make_uint4(0u, 0u, 0u, 0u);
   if ((u32)(8 * tid) < ng) ahead = ncol8[tid];
-  u32 fa = 0, fe = 0;
-  if (tid < S) {
-    fa = fpt[(size_t)t * S + tid];
-    fe = fpt[((size_t)t + 1) * S + tid];
-  }
+  // STAGE_ROWS: the row's place in its segment (SENT: not written, only with a label error,
+  // which voids the result)
+  u32 row_place = SENT;
+  if (by_rows && own != NOLAB && lu != SENT) row_place = start[own] + PM[(size_t)(my_row / chunk) * L + own] + lu;
   {
-    typedef u32 v4u __attribute__((ext_vector_type(4)));
-    const v4u* src = reinterpret_cast<const v4u*>(labx + w0);  // w0 is a multiple of 1,024; the array is padded past n
     v4u* dst = reinterpret_cast<v4u*>(s_win32);
-    for (int i = tid; i < (w1 - w0 + TL::PER - 1) / TL::PER; i += TG_THREADS) dst[i] = src[i];
-    if (tid <= rows) s_nr[tid] = nrp[r0 + tid] - nb;
-    if (tid == 0 && rows == TG_ROWS) s_nr[TG_ROWS] = ne;
-    if (tid == 0) s_nbuf = 0;
+#pragma unroll
+    for (int i = 0; i < WPT; ++i)
+      if (tid + i * TG_THREADS < nwin) dst[tid + i * TG_THREADS] = wreg[i];
+    if (tid < rows) s_nr[tid] = row_n - nb;
+    if (tid == 0) {
+      s_nr[rows] = ne;
+      s_nbuf = 0;
+    }
   }
   // far entries numbered slice by slice
   u32 nf = 0;
   {
-    const u32 cnt = fe - fa;
+    u32 cnt = 0;
+#pragma unroll
+    for (int i = 0; i < SPT; ++i) cnt += fe[i] - fa[i];
     const u32 incl = wave_incl_scan(cnt);
     if (lane == 63) s_wave[wv] = incl;
     __syncthreads();
-    u32 before = 0;
+    u32 pre = incl - cnt;
 #pragma unroll
     for (int i = 0; i < WAVES; ++i) {
       const u32 k = s_wave[i];
-      if (i < wv) before += k;
+      if (i < wv) pre += k;
       nf += k;
     }
-    const u32 pre = before + incl - cnt;
-    if (tid < S) {
-      s_pre[tid] = pre;
-      s_foff[tid] = fa - pre;
-      for (u32 g = (pre + 7u) / 8u; g * 8u < pre + cnt && g < (u32)(TG_FAR * TG_THREADS / 8); ++g) s_seg8[g] = (uint16_t)tid;
+#pragma unroll
+    for (int i = 0; i < SPT; ++i) {
+      const int s = tid * spt + i;
+      if (i >= spt || s >= S) break;
+      const u32 c = fe[i] - fa[i];
+      s_pre[s] = pre;
+      s_foff[s] = fa[i] - pre;
+      for (u32 g = (pre + 7u) / 8u; g * 8u < pre + c && g < (u32)(TG_FAR * TG_THREADS / 8); ++g) s_seg8[g] = (uint16_t)s;
+      pre += c;
     }
     if (tid == 0) s_pre[S] = nf;
   }
@@ -326,22 +363,19 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   if (by_rows) {
     // Entries are placed relative to the tile's first entry, row by row.  Per row: end of its
     // near entries, and the place of near entry e minus e (one LDS read gives both); the next
-    // free place of its far entries; the row's place in its segment (SENT: not written, only
-    // with a label error, which voids the result).
+    // free place of its far entries; the row's place in its segment.
     uint2* s_row = reinterpret_cast<uint2*>(s_a);  // s_a and s_b
     u32* s_far = s_cnt;
     uint16_t* s_row8 = reinterpret_cast<uint16_t*>(s_more);
     LT* s_out = reinterpret_cast<LT*>(s_buf);
-    const u32 cap = (u32)(TL::BUF + TL::EXTRA + (nf <= (u32)(TG_FAR * TG_THREADS) ? TL::SEG : 0)) * (4 / sizeof(LT));
+    // entries put together in LDS (beyond: written straight away); the far tables' space too
+    // once all far entries are in registers
+    const u32 cap = ((u32)(s_pre - s_buf) + (nf <= (u32)(TG_FAR * TG_THREADS) ? (u32)TL::seg(S) : 0u)) * (4 / sizeof(LT));
     if (tid < rows) {
-      const int u = r0 + tid;
-      const u32 c = (u32)s_win[roff + tid], lu = loc[u];
-      const u32 a = s_nr[tid], b = s_nr[tid + 1], at = (u32)(rp[u] - rp[r0]);
-      u32 base = SENT;
-      if (c != NOLAB && lu != SENT) base = start[c] + PM[(size_t)(u / chunk) * L + c] + lu;
+      const u32 a = s_nr[tid], b = s_nr[tid + 1], at = (u32)(row_e - rp[r0]);
       s_row[tid] = make_uint2(b + skip, at - a - skip);
       s_far[tid] = at + b - a;
-      s_base[tid] = base;
+      s_base[tid] = row_place;
     }
     auto put = [&](u32 r, u32 at, u32 x) {
       if (at < cap) s_out[at] = (LT)x;
@@ -390,7 +424,7 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   // runs of rows with equal labels
   u32 nruns = 0;
   {
-    const u32 c = tid < rows ? (u32)s_win[roff + tid] : 0u;
+    const u32 c = own;
     const bool head = tid < rows && (tid == 0 || c != (u32)s_win[roff + tid - 1]);
     const u64 m = __ballot(head);
     if (lane == 0) s_wave[wv] = (u32)__popcll(m);
@@ -406,9 +440,13 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     if (tid < rows) s_a[tid] = sizeof(LT) == 2 ? (run << 16) | c : run;
     if (head) {
       s_b[run] = (u32)tid;
+      s_first[run] = (u32)row_e;
       s_base[run] = s_nr[tid] + skip;
     }
-    if (tid == 0) s_b[nruns] = (u32)rows;
+    if (tid == 0) {
+      s_b[nruns] = (u32)rows;
+      s_first[nruns] = (u32)rp[r0 + rows];
+    }
     if (tid < rows) {
       s_cnt[tid] = 0;
       s_more[tid] = 0;
@@ -529,9 +567,9 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   __syncthreads();
   // one claim per run
   if ((u32)tid < nruns) {
-    const u32 ra = s_b[tid], rb = s_b[tid + 1];
+    const u32 ra = s_b[tid];
     const u32 c = (u32)s_win[roff + ra];
-    const u32 tot = (u32)(rp[r0 + rb] - rp[r0 + ra]), inter = s_cnt[tid] + s_more[tid];
+    const u32 tot = s_first[tid + 1] - s_first[tid], inter = s_cnt[tid] + s_more[tid];
     u32 base = SENT;
     if (c != NOLAB && tot > 0) {
       const unsigned long long old = atomicAdd(&cur64[c], ((unsigned long long)(tot - inter) << 32) | inter);
