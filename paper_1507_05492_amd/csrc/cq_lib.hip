@@ -62,10 +62,11 @@ struct cq_graph {
   int32_t* owned_rp = nullptr;    // device memory owned by the handle (CQ_GRAPH_REORDER)
   int32_t* owned_col = nullptr;
   int32_t* owned_perm = nullptr;
-  u32* nrp = nullptr;              // tiles (cq_tiles.hpp; owned, null when the graph has none): near row starts,
-  u32* fpt = nullptr;              // far entries' first places per tile and slice,
-  uint16_t *ncol = nullptr, *fcol = nullptr, *frow = nullptr;  // near entries; far entries' columns and rows
-  float *nw = nullptr, *fw = nullptr;                          // their weights
+  Tile* tiles = nullptr;           // tiles (cq_tiles.hpp; owned, null when the graph has none), their entries' table
+  uint16_t *eidx = nullptr, *fcol = nullptr;        // places, far entries by slice with the slices' first ones,
+  u32 *fadr = nullptr, *fslice = nullptr;           // and by tile
+  int ntiles = 0, fmax = 0;        // tiles; most far entries of one
+  int64_t groups = 0;              // groups of eidx
   int64_t far = 0;                 // far entries
   int slices = 0;
   bool blocked = false;            // runs may be staged compactly through the tiles (n <= 2^24); else by rows only
@@ -95,11 +96,11 @@ struct cq_graph {
     if (owned_w) (void)hipFree(owned_w);
   }
   void free_tiles() {
-    for (void* p : {(void*)nrp, (void*)fpt, (void*)ncol, (void*)fcol, (void*)frow, (void*)nw, (void*)fw})
+    for (void* p : {(void*)tiles, (void*)eidx, (void*)fcol, (void*)fadr, (void*)fslice})
       if (p) (void)hipFree(p);
-    nrp = fpt = nullptr;
-    ncol = fcol = frow = nullptr;
-    nw = fw = nullptr;
+    tiles = nullptr;
+    eidx = fcol = nullptr;
+    fadr = fslice = nullptr;
   }
 };
 
@@ -346,7 +347,7 @@ ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_
   const bool perm = g->blocked && g->pos1 && L <= PRIV_MAX;
   ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
   s.min_total = s.total;
-  if (g->nrp && (g->blocked || s.small)) {
+  if (g->tiles && (g->blocked || s.small)) {
     ScoreLayout t = s;
     Carve c;
     c.off = s.total;
@@ -716,23 +717,23 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   {
     StageMark mk(ctx, ST_GATHER, timed);
     if (tiled || lay.tile_rows) {
-      const int T = (int)((n + TG_ROWS - 1) / TG_ROWS), S = g->slices;
+      const int T = g->ntiles, S = g->slices;
       LT* fl = at<LT>(ws, lay.fl);
       if (g->far > 0) {
         // about four workgroups per CU, of at least 4,096 entries
         const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((4 * ctx->num_cus + S - 1) / S, g->far / ((int64_t)S * 4096)));
-        k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << TS_SHIFT, s>>>((int)n, parts, g->fpt,
-                                                                                          g->fpt + (size_t)T * S, g->fcol, labx, fl);
+        k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << TS_SHIFT, s>>>((int)n, parts, g->fslice,
+                                                                                          g->fcol, labx, fl);
       }
       const unsigned grid = 8u * (unsigned)((T + 7) / 8);
       unsigned long long* cur = at<unsigned long long>(ws, lay.cursor);
       if (CW)
-        k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(S), s>>>(
-            (int)n, S, g->rp, g->nrp, g->ncol, g->fpt, g->frow, fl, labx, start, D, cur, ctl, CB, g->nw, g->fw, CW,
+        k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(g->fmax), s>>>(
+            (int)n, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, g->w, CW,
             at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc, 0);
       else
-        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(S), s>>>(
-            (int)n, S, g->rp, g->nrp, g->ncol, g->fpt, g->frow, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr, nullptr,
+        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(g->fmax), s>>>(
+            (int)n, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr,
             nullptr, L, lay.chunk, PM, loc, lay.tile_rows ? 1 : 0);
     } else {
       const unsigned grid = 8u * (unsigned)((((int64_t)n + GROWS - 1) / GROWS + 7) / 8);  // one workgroup per tile
@@ -1297,55 +1298,88 @@ constexpr int64_t BLOCK_MIN_N = 1 << 20;
 constexpr int64_t TILE_MAX_N = (int64_t)TG_MAX_SLICES << TS_SHIFT;
 static_assert(BLOCK_MAX_N <= TILE_MAX_N, "slices");
 
-// Builds the tiles of the renumbered graph (g->owned_rp / owned_col / owned_w).
-cq_status build_tiles(cq_context* ctx, cq_graph* g) {
+// Builds the tiles of the renumbered graph (g->owned_rp / owned_col), of at most `ent` entries;
+// *most = the most far entries of one.  When that is over `limit`, no tiles are left.
+cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* most) {
   const int n = g->n;
-  const int64_t nnz = g->nnz;
   hipStream_t s = ctx->stream;
-  const int T = (n + TG_ROWS - 1) / TG_ROWS, S = (n + TS_NODES - 1) >> TS_SHIFT;
-  const long long cells = (long long)T * S;
-  u32 *ncnt = nullptr, *fcnt = nullptr, *fstart = nullptr, *tiles = nullptr;
+  const int blocks = (n + TG_ROWS - 1) / TG_ROWS, S = (n + TS_NODES - 1) >> TS_SHIFT;
+  u32 *bcnt = nullptr, *bfirst = nullptr, *fcnt = nullptr, *fstart = nullptr, *tmp = nullptr, *cnt = nullptr;
+  u32 *group0 = nullptr, *nfar = nullptr, *far0 = nullptr, *fmax = nullptr;
   hipError_t e = hipSuccess;
   auto alloc = [&](void** p, size_t bytes) {
     if (e == hipSuccess) e = hipMalloc(p, std::max<size_t>(bytes, 16));
   };
+  auto read = [&](u32* to, const u32* from) {
+    if (e == hipSuccess) e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(to, from, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+  };
+  auto scan_tmp = [](long long m) { return 4 * ((size_t)((m + SCAN_TILE - 1) / SCAN_TILE) + 1); };
   g->slices = S;
-  alloc((void**)&g->nrp, 4 * ((size_t)n + 1));
-  alloc((void**)&g->fpt, 4 * ((size_t)cells + S));
-  alloc((void**)&ncnt, 4 * (size_t)n);
+  *most = 0;
+  u32 T = 0, far = 0, groups = 0;
+  alloc((void**)&bcnt, 4 * (size_t)blocks);
+  alloc((void**)&bfirst, 4 * ((size_t)blocks + 1));
+  alloc((void**)&tmp, scan_tmp(blocks));
+  alloc((void**)&fmax, 16);
+  if (e == hipSuccess) {
+    k_tile_blocks<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, ent, g->owned_rp, bcnt);
+    scan_u32(bcnt, bfirst, blocks, tmp, s);
+    read(&T, bfirst + blocks);
+  }
+  const long long cells = (long long)T * S;
+  if (tmp) (void)hipFree(tmp);
+  tmp = nullptr;
+  alloc((void**)&tmp, scan_tmp(std::max<long long>(cells, T)));
+  alloc((void**)&g->tiles, sizeof(Tile) * (size_t)T);
+  alloc((void**)&g->fslice, 4 * ((size_t)S + 1));
+  alloc((void**)&cnt, 4 * (size_t)T);
+  alloc((void**)&group0, 4 * ((size_t)T + 1));
+  alloc((void**)&nfar, 4 * (size_t)T);
+  alloc((void**)&far0, 4 * ((size_t)T + 1));
   alloc((void**)&fcnt, 4 * (size_t)cells);
   alloc((void**)&fstart, 4 * ((size_t)cells + 1));
-  alloc((void**)&tiles, 4 * ((size_t)((std::max<long long>(n, cells) + SCAN_TILE - 1) / SCAN_TILE) + 1));
-  u32 near = 0, far = 0;
   if (e == hipSuccess) {
-    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, T, S, g->owned_rp, g->owned_col, ncnt, fcnt);
-    scan_u32(ncnt, g->nrp, n, tiles, s);
-    scan_u32(fcnt, fstart, cells, tiles, s);
-    k_tile_table<<<grid_for(cells + S, 256, 4096), 256, 0, s>>>(T, S, fstart, g->fpt);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&near, g->nrp + n, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&far, fstart + cells, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    k_tile_list<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, ent, g->owned_rp, bfirst, g->tiles, cnt);
+    scan_u32(cnt, group0, T, tmp, s);
+    fill(fmax, 1, 0, s);
+    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, g->tiles, g->owned_col, fcnt, nfar, fmax);
+    scan_u32(fcnt, fstart, cells, tmp, s);
+    scan_u32(nfar, far0, T, tmp, s);
+    k_tile_slices<<<(S + 256) / 256, 256, 0, s>>>((int)T, S, fstart, g->fslice);
+    read(&far, fstart + cells);
+    read(&groups, group0 + T);
+    read(most, fmax);
   }
-  alloc((void**)&g->ncol, 2 * (size_t)near + 16);  // read in 16-byte words
-  alloc((void**)&g->fcol, 2 * (size_t)far);
-  alloc((void**)&g->frow, 2 * (size_t)far);
-  if (g->owned_w) {
-    alloc((void**)&g->nw, 4 * (size_t)near);
-    alloc((void**)&g->fw, 4 * (size_t)far);
+  const bool keep = e == hipSuccess && *most <= limit;
+  if (keep) {
+    alloc((void**)&g->eidx, 2 * (size_t)groups * TG_GROUP);
+    alloc((void**)&g->fcol, 2 * (size_t)far + 16);  // read in 16-byte words
+    alloc((void**)&g->fadr, 4 * (size_t)far);
+    if (e == hipSuccess) {
+      fill(reinterpret_cast<u32*>(g->eidx), (size_t)groups * TG_GROUP / 2, 0, s);  // places past a tile's entries are read too
+      k_tile_place<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, g->tiles, group0, far0, g->owned_col, fcnt, fstart, g->eidx, g->fcol,
+                                            g->fadr);
+      e = hipGetLastError();
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
   }
-  if (e == hipSuccess) {
-    k_tile_place<<<T, TG_THREADS, 0, s>>>(n, T, S, g->owned_rp, g->owned_col, g->owned_w, g->nrp, g->fpt, g->ncol, g->nw, g->fcol,
-                                          g->frow, g->fw);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-  }
+  g->ntiles = (int)T;
   g->far = far;
-  for (u32* p : {ncnt, fcnt, fstart, tiles})
+  g->fmax = (int)*most;
+  g->groups = groups;
+  for (u32* p : {bcnt, bfirst, fcnt, fstart, tmp, cnt, group0, nfar, far0, fmax})
     if (p) (void)hipFree(p);
-  if (e == hipSuccess && (int64_t)near + far == nnz) return CQ_OK;
-  g->free_tiles();
+  if (!keep || e != hipSuccess) g->free_tiles();
+  if (e == hipSuccess) return CQ_OK;
   return fail(ctx, CQ_E_DEVICE, "building the graph's tiles: %s", hipGetErrorString(e));
+}
+
+cq_status build_tiles(cq_context* ctx, cq_graph* g) {
+  u32 most = 0;
+  const cq_status st = build_tiles(ctx, g, TG_ENT, TG_FAR_MAX, &most);
+  return st != CQ_OK || most <= (u32)TG_FAR_MAX ? st : build_tiles(ctx, g, TG_ENT_FAR, TG_ENT_FAR, &most);
 }
 
 // Builds the label permutation plan of a renumbered graph from newid (caller id ->
@@ -1494,11 +1528,9 @@ cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, 
     if (g->owned_w) g->w = g->owned_w;
     g->reordered = CQ_GRAPH_REORDER | (g->blocked ? 0u : CQ_GRAPH_NO_BLOCKS);
     g->owned_bytes = (int64_t)(4 * ((size_t)n + 1) + 4 * (size_t)nnz + 4 * (size_t)n);
-    if (g->nrp) {
-      const size_t T = ((size_t)n + TG_ROWS - 1) / TG_ROWS;
-      g->owned_bytes += (int64_t)(4 * ((size_t)n + 1) + 4 * (T + 1) * (size_t)g->slices + 2 * (size_t)(nnz - g->far) +
-                                  4 * (size_t)g->far + (g->owned_w ? 4 * (size_t)nnz : 0));
-    }
+    if (g->tiles)
+      g->owned_bytes += (int64_t)(sizeof(Tile) * (size_t)g->ntiles + 4 * ((size_t)g->slices + 1) +
+                                  2 * (size_t)g->groups * TG_GROUP + 6 * (size_t)g->far);
     if (g->pos1) g->owned_bytes += (int64_t)(10 * (size_t)n + 4 * ((size_t)g->perm_buckets + 1));
     if (g->lrank) g->owned_bytes += (int64_t)(6 * (size_t)n);
     if (g->sid) g->owned_bytes += (int64_t)(4 * (size_t)n);
@@ -2031,10 +2063,10 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint16_t>), 2 << TS_SHIFT);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint32_t>), 4 << TS_SHIFT);
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_MAX_SLICES));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_MAX_SLICES));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::bytes(TG_MAX_SLICES));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::bytes(TG_MAX_SLICES));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_ENT_FAR));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_ENT_FAR));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::bytes(TG_ENT_FAR));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::bytes(TG_ENT_FAR));
   set_big_lds(reinterpret_cast<const void*>(k_small_count), ss_lds(SS_MAX_N, SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_final), 4 * (size_t)ss_cells(SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_compare), 4 * (size_t)SC_MAX_CELLS + 24 * (size_t)SC_MAX_L + 64);

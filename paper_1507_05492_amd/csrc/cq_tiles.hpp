@@ -4,128 +4,201 @@
 // communities, mostly) join random places.  Reading those neighbours' labels one by one is
 // what an edge pass spends its time on: an L2 serves a random read per channel and cycle
 // (265 G/s for the chip), and only if the labels fit it (77 G/s over 20 MB).  So the graph is
-// also kept as tiles of TG_ROWS consecutive rows, and each tile's entries in two parts:
-//   near  the neighbour lies in the tile's window of ids (TG_HALO before and after its rows):
-//         16-bit offsets in the window, row by row;
-//   far   all others, sorted by slice (TS_NODES consecutive ids) of the neighbour, then by
-//         tile: the 16-bit place of the neighbour in its slice, and the row's number in its
-//         tile (16 bits).
+// also kept as tiles: the entries of TG_ROWS consecutive rows (a block of rows with many
+// entries is cut into several tiles).  An entry is near when its neighbour lies in the block's
+// window of ids (TG_HALO before and after its rows), else far.  Per graph:
+//   eidx  one 16-bit word per entry, in row order: the place of the neighbour's label in the
+//         tile's table, which holds the window's labels, then the tile's far labels;
+//   fcol  the far entries sorted by slice (TS_NODES consecutive ids) of the neighbour, then by
+//         tile: the 16-bit place of the neighbour in its slice;
+//   fadr  for every tile, the numbers of its far entries in that order.
+//
 // A call takes two passes.  k_far_labels holds one slice's labels in LDS, walks the slice's far
 // entries in order and writes their labels out in order: no random read leaves LDS.
-// k_tile_gather then takes one tile per workgroup, with the window's labels in LDS: near
-// entries read theirs there, far entries read consecutive words of the first pass.  Both
-// passes stream: about 4 bytes per near entry and 8 per far entry, labels and staging aside.
-//
-// Measured on the 10M-node graph (199M entries, 30 % of them far): see k_tile_gather.
+// k_tile_gather then takes one tile per workgroup, puts its table together in LDS from the
+// window and the far labels (one short run per slice), and finds every neighbour's label there.
+// Both passes stream: 2 bytes per entry and 10 per far entry, labels and staging aside.
 #pragma once
 
 namespace cq {
 
 constexpr int TG_THREADS = 1024;
-constexpr int TG_ROWS = 1024;        // rows per tile, one per thread
-constexpr int TG_HALO = 4096;        // ids of the window before and after the tile's rows
+constexpr int TG_WAVES = TG_THREADS / 64;
+constexpr int TG_ROWS = 1024;        // rows per block, one per thread
+constexpr int TG_HALO = 3584;        // ids of the window before and after the block's rows
+constexpr int TG_WIN = TG_ROWS + 2 * TG_HALO;  // table places of the window (8,192); far labels follow
+constexpr int TG_GROUP = 512;        // entries per wave and step: 8 per lane
+constexpr int TG_STEPS = 3;          // steps per wave at most
+constexpr int TG_ENT = TG_WAVES * TG_GROUP * TG_STEPS;  // entries per tile at most: 24,576
+// A graph with a tile of more far entries than this is cut into tiles of at most TG_ENT_FAR
+// entries instead, so that two workgroups of 16-bit labels (one of 32-bit ones) fit a CU's LDS.
+constexpr int TG_FAR_MAX = 12288;
+constexpr int TG_ENT_FAR = 16384;
 constexpr int TS_SHIFT = 15;
 constexpr int TS_NODES = 1 << TS_SHIFT;  // ids per slice: 64 KB of 16-bit labels, 128 KB of 32-bit ones
-constexpr int TG_MAX_SLICES = 4096;  // n up to 2^27 (12-bit slice numbers, 16 KB of counters at load time)
+constexpr int TG_MAX_SLICES = 4096;  // n up to 2^27 (32 KB of counters at load time)
 static_assert(TG_ROWS == TG_THREADS, "one row per thread");
-static_assert(TG_ROWS + 2 * TG_HALO <= 65536, "16-bit window offsets");
+static_assert(2 * (TG_WIN + TG_ENT_FAR) <= 65536 && TG_FAR_MAX <= TG_ENT_FAR, "16-bit table places, in units of 2 bytes");
 
-// First id of the window of the tile starting at row r0, and one past its last.
-__host__ __device__ __forceinline__ int tile_w0(int r0) { return r0 > TG_HALO ? r0 - TG_HALO : 0; }
-__host__ __device__ __forceinline__ int tile_w1(int r0, int n) {
-  return n - r0 > TG_ROWS + TG_HALO ? r0 + TG_ROWS + TG_HALO : n;
+struct Tile {
+  int b0;       // first row of its block
+  int r0, r1;   // rows with entries in the tile
+  u32 e0, ne;   // first stored entry, entries
+  u32 g0;       // first group of eidx
+  u32 f0, nf;   // first word of fadr, far entries
+};
+
+// First id of the window of the block starting at row b0, and one past its last.
+__host__ __device__ __forceinline__ int tile_w0(int b0) { return b0 > TG_HALO ? b0 - TG_HALO : 0; }
+__host__ __device__ __forceinline__ int tile_w1(int b0, int n) {
+  return n - b0 > TG_ROWS + TG_HALO ? b0 + TG_ROWS + TG_HALO : n;
+}
+// Place of a tile's entry i in eidx, from the tile's first word: a lane's 16-byte word holds
+// entries 64 apart, so that a wave's k-th entries are consecutive.
+__device__ __forceinline__ u32 tile_word(u32 i) {
+  return (i & ~(u32)(TG_GROUP - 1)) + (i & 63u) * 8u + ((i >> 6) & 7u);
 }
 
 // ---- load time -------------------------------------------------------------------
-// One workgroup per tile: near entries per row (ncnt), far entries per slice
-// (fcnt[slice * T + tile]).
-__global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, const int32_t* __restrict__ rp,
-                                                           const int32_t* __restrict__ col, u32* __restrict__ ncnt,
-                                                           u32* __restrict__ fcnt) {
-  __shared__ u32 s_far[TG_MAX_SLICES];
-  __shared__ u32 s_near[TG_ROWS];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int r0 = (int)blockIdx.x * TG_ROWS, rows = min(TG_ROWS, n - r0);
-  const int w0 = tile_w0(r0), w1 = tile_w1(r0, n);
-  for (int i = tid; i < S; i += TG_THREADS) s_far[i] = 0;
-  s_near[tid] = 0;
-  __syncthreads();
-  for (int r = wv; r < rows; r += TG_THREADS / 64) {  // one wave per row
-    const int a = rp[r0 + r], b = rp[r0 + r + 1];
-    u32 near = 0;
-    for (int e = a + lane; e < b; e += 64) {
-      const int v = col[e];
-      if (v >= w0 && v < w1) ++near;
-      else atomicAdd(&s_far[v >> TS_SHIFT], 1u);
-    }
-    if (near) atomicAdd(&s_near[r], near);
-  }
-  __syncthreads();
-  if (tid < rows) ncnt[r0 + tid] = s_near[tid];
-  for (int i = tid; i < S; i += TG_THREADS) fcnt[(size_t)i * T + blockIdx.x] = s_far[i];
+// Tiles of at most `ent` entries per block of rows (at least one), and the tiles themselves
+// once their numbers are known.
+__global__ __launch_bounds__(256) void k_tile_blocks(int n, int blocks, u32 ent, const int32_t* __restrict__ rp,
+                                                     u32* __restrict__ cnt) {
+  const int b = blockIdx.x * 256 + threadIdx.x;
+  if (b >= blocks) return;
+  const u32 ne = (u32)(rp[min(n, (b + 1) * TG_ROWS)] - rp[b * TG_ROWS]);
+  cnt[b] = max(1u, (ne + ent - 1u) / ent);
 }
 
-// fpt[tile * S + slice] = first far entry of (slice, tile) for tiles 0..T (T: the slice's end).
-__global__ __launch_bounds__(256) void k_tile_table(int T, int S, const u32* __restrict__ fstart, u32* __restrict__ fpt) {
-  const size_t total = ((size_t)T + 1) * S;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-    const size_t t = i / S, s = i - t * S;
-    fpt[i] = fstart[s * T + t];  // the next slice's start ends this one
-  }
-}
-
-// One workgroup per tile: writes its entries (and weights) to their places.
-__global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, const int32_t* __restrict__ rp,
-                                                           const int32_t* __restrict__ col, const float* __restrict__ w,
-                                                           const u32* __restrict__ nrp, const u32* __restrict__ fpt,
-                                                           uint16_t* __restrict__ ncol, float* __restrict__ nw,
-                                                           uint16_t* __restrict__ fcol, uint16_t* __restrict__ frow,
-                                                           float* __restrict__ fw) {
-  __shared__ u32 s_far[TG_MAX_SLICES];
-  __shared__ u32 s_near[TG_ROWS];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int r0 = (int)blockIdx.x * TG_ROWS, rows = min(TG_ROWS, n - r0);
-  const int w0 = tile_w0(r0), w1 = tile_w1(r0, n);
-  for (int i = tid; i < S; i += TG_THREADS) s_far[i] = fpt[(size_t)blockIdx.x * S + i];
-  if (tid < rows) s_near[tid] = nrp[r0 + tid];
-  __syncthreads();
-  for (int r = wv; r < rows; r += TG_THREADS / 64) {
-    const int a = rp[r0 + r], b = rp[r0 + r + 1];
-    for (int e = a + lane; e < b; e += 64) {
-      const int v = col[e];
-      if (v >= w0 && v < w1) {
-        const u32 at = atomicAdd(&s_near[r], 1u);
-        ncol[at] = (uint16_t)(v - w0);
-        if (w) nw[at] = w[e];
-      } else {
-        const u32 at = atomicAdd(&s_far[v >> TS_SHIFT], 1u);
-        fcol[at] = (uint16_t)(v & (TS_NODES - 1));
-        frow[at] = (uint16_t)r;
-        if (w) fw[at] = w[e];
+__global__ __launch_bounds__(256) void k_tile_list(int n, int blocks, u32 ent, const int32_t* __restrict__ rp,
+                                                   const u32* __restrict__ first, Tile* __restrict__ tiles,
+                                                   u32* __restrict__ groups) {
+  const int b = blockIdx.x * 256 + threadIdx.x;
+  if (b >= blocks) return;
+  const int b0 = b * TG_ROWS, b1 = min(n, b0 + TG_ROWS);
+  const u32 E0 = (u32)rp[b0], E1 = (u32)rp[b1];
+  for (u32 t = first[b], k = 0; t < first[b + 1]; ++t, ++k) {
+    const u32 a = E0 + k * ent, z = min(E1, a + ent);
+    // rows [r0, r1): all rows of the block for a single tile, else those with entries in [a, z)
+    int r0 = b0, r1 = b1;
+    if (first[b + 1] - first[b] > 1) {
+      int lo = b0, hi = b1 - 1;  // last row starting at or before a
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if ((u32)rp[mid] <= a) lo = mid; else hi = mid - 1;
       }
+      r0 = lo;
+      hi = b1 - 1;  // last row starting before z
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if ((u32)rp[mid] < z) lo = mid; else hi = mid - 1;
+      }
+      r1 = lo + 1;
     }
+    tiles[t] = Tile{b0, r0, r1, a, z - a, 0u, 0u, 0u};
+    groups[t] = (z - a + TG_GROUP - 1u) / TG_GROUP;
+  }
+}
+
+// One workgroup per tile: far entries per slice (fcnt[slice * T + tile]), in all, and the most
+// of any tile.
+__global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, const Tile* __restrict__ tiles,
+                                                           const int32_t* __restrict__ col, u32* __restrict__ fcnt,
+                                                           u32* __restrict__ nfar, u32* __restrict__ fmax) {
+  __shared__ u32 s_far[TG_MAX_SLICES];
+  __shared__ u32 s_all;
+  const Tile t = tiles[blockIdx.x];
+  const int w0 = tile_w0(t.b0), w1 = tile_w1(t.b0, n);
+  for (int i = threadIdx.x; i < S; i += TG_THREADS) s_far[i] = 0;
+  if (threadIdx.x == 0) s_all = 0;
+  __syncthreads();
+  u32 mine = 0;
+  for (u32 i = threadIdx.x; i < t.ne; i += TG_THREADS) {
+    const int v = col[t.e0 + i];
+    if (v >= w0 && v < w1) continue;
+    ++mine;
+    atomicAdd(&s_far[v >> TS_SHIFT], 1u);
+  }
+  if (mine) atomicAdd(&s_all, mine);
+  __syncthreads();
+  for (int i = threadIdx.x; i < S; i += TG_THREADS) fcnt[(size_t)i * T + blockIdx.x] = s_far[i];
+  if (threadIdx.x == 0) {
+    nfar[blockIdx.x] = s_all;
+    atomicMax(fmax, s_all);
+  }
+}
+
+// first[slice] = the slice's first far entry (slice S: their number).
+__global__ __launch_bounds__(256) void k_tile_slices(int T, int S, const u32* __restrict__ fstart, u32* __restrict__ first) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i <= S) first[i] = fstart[(size_t)i * T];
+}
+
+// One workgroup per tile: writes its entries' table places and its far entries.
+__global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, Tile* __restrict__ tiles,
+                                                           const u32* __restrict__ group0, const u32* __restrict__ far0,
+                                                           const int32_t* __restrict__ col, const u32* __restrict__ fcnt,
+                                                           const u32* __restrict__ fstart, uint16_t* __restrict__ eidx,
+                                                           uint16_t* __restrict__ fcol, u32* __restrict__ fadr) {
+  __shared__ u32 s_pre[TG_MAX_SLICES];  // far entries of the tile before the slice
+  __shared__ u32 s_cnt[TG_MAX_SLICES];
+  const int tid = threadIdx.x;
+  const Tile t = tiles[blockIdx.x];
+  const int w0 = tile_w0(t.b0), w1 = tile_w1(t.b0, n);
+  for (int i = tid; i < S; i += TG_THREADS) {
+    s_pre[i] = fcnt[(size_t)i * T + blockIdx.x];
+    s_cnt[i] = 0;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    u32 run = 0;
+    for (int i = 0; i < S; ++i) {
+      const u32 c = s_pre[i];
+      s_pre[i] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  const u32 g0 = group0[blockIdx.x], f0 = far0[blockIdx.x];
+  uint16_t* out = eidx + (size_t)g0 * TG_GROUP;
+  for (u32 i = tid; i < t.ne; i += TG_THREADS) {
+    const int v = col[t.e0 + i];
+    u32 at = (u32)(v - w0);
+    if (v < w0 || v >= w1) {
+      const int s = v >> TS_SHIFT;
+      const u32 k = atomicAdd(&s_cnt[s], 1u), j = s_pre[s] + k, g = fstart[(size_t)s * T + blockIdx.x] + k;
+      fcol[g] = (uint16_t)(v & (TS_NODES - 1));
+      fadr[f0 + j] = g;
+      at = (u32)TG_WIN + j;
+    }
+    out[tile_word(i)] = (uint16_t)(2u * at);
+  }
+  if (tid == 0) {
+    tiles[blockIdx.x].g0 = g0;
+    tiles[blockIdx.x].f0 = f0;
+    tiles[blockIdx.x].nf = far0[blockIdx.x + 1] - f0;
   }
 }
 
 // ---- pass 1 ------------------------------------------------------------------------
 // Labels of the far entries in their order.  Workgroup (slice, part): the slice's labels in
-// LDS, then its share of the slice's entries (first[slice] up to end[slice]), eight per
+// LDS, then its share of the slice's entries (from first[slice] up to first[slice + 1]), eight per
 // thread and step.
 constexpr int FL_THREADS = 1024;
 template <class LT>
 __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int parts, const u32* __restrict__ first,
-                                                           const u32* __restrict__ end, const uint16_t* __restrict__ fcol, const LT* __restrict__ labx,
+                                                           const uint16_t* __restrict__ fcol, const LT* __restrict__ labx,
                                                            LT* __restrict__ fl) {
   extern __shared__ __align__(16) u32 s_slice[];
   const LT* lab = reinterpret_cast<const LT*>(s_slice);
   const int tid = threadIdx.x;
   const int slice = (int)blockIdx.x / parts, part = (int)blockIdx.x % parts;
-  const u32 a = first[slice], b = end[slice];
-  // parts cut at multiples of 8 entries; the first and last also take the unaligned ends
+  const u32 a = first[slice], b = first[slice + 1];
+  // parts cut at multiples of 8 entries; the first part also takes the unaligned ends
   const u32 v0 = (a + 7u) / 8u, v1 = max(v0, b / 8u);  // whole groups of 8 inside [a, b)
   const u32 per = (v1 - v0 + (u32)parts - 1u) / (u32)parts;
   const u32 g0 = min(v1, v0 + (u32)part * per), g1 = min(v1, g0 + per);
-  const bool ends = part == 0;  // the few entries outside the whole groups
+  const bool ends = part == 0;
   if (g0 == g1 && !ends) return;
   {
     constexpr int PER = 16 / (int)sizeof(LT);
@@ -161,466 +234,330 @@ __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int parts, con
 // ---- pass 2 ------------------------------------------------------------------------
 // One tile per workgroup, in one of two stagings (ctl->mode, chosen by k_colscan_rows).
 //
-// STAGE_BLOCKS: consecutive rows with the same label form a run.  An entry whose neighbour has
-// the row's own label c only adds to 2|E_c^in| (and, weighted, its weight to 2 w_in(c)) and
-// is not staged; the others are counted per run, each run adds (own << 32) | others to
-// community c's cursor with one atomic, which hands it consecutive places in the segment,
-// and they are written there run by run.  Until then far entries stay in registers and near
-// ones (few of them have another label) in an LDS buffer; what does not fit is read again.
-// Weighted: own-label weights are summed exactly per run and added to IWacc[c].
+// STAGE_BLOCKS: consecutive rows (with entries) of the same label form a run.  An entry whose
+// neighbour has the row's own label c only adds to 2|E_c^in| (and, weighted, its weight to
+// 2 w_in(c)) and is not staged.  The others are numbered through the tile; a run's count is
+// the difference of two numbers, each run adds (own << 32) | others to community c's cursor
+// with one atomic, which hands it consecutive places in the segment, and a second walk over
+// the entries writes them there.  Weighted: own-label weights are summed exactly per run and
+// added to IWacc[c].
 //
 // STAGE_ROWS (a partition that does not follow the stored order, so that runs are hardly
-// longer than a row): every entry goes to its row's place, start + chunk prefix + per-node
-// offset, near entries first.  The rows are put together in LDS and written from there by 16
-// lanes each: written one by one, the far entries' 2-byte stores were one L2 request each
-// (0.3 of 0.7 ms on the 10M-node graph).
+// longer than a row): every row is a run, and every entry goes to its row's place, start +
+// chunk prefix + per-node offset + its number in the row.
 //
-// A tile is a chain of a few dependent loads, and two workgroups share a CU, so the pass is
-// bound by latency and by LDS work per entry: a thread loads eight near entries at once and
-// all of its far ones before the first is used, a wave's 512 near entries nearly always lie
-// in one run (one LDS read per entry, two atomics per wave), and a far entry's slice is found
-// through s_seg8, the slice of every eighth far entry, and a short walk.
-constexpr int TG_FAR = 8;                     // far entries per thread held in registers
-constexpr int TG_CHUNK = 16384;               // near entries per step of the row table (STAGE_ROWS)
-constexpr int TG_BUF = 4096, TG_BUF_W = 1536; // near entries of another label kept in LDS
+// The pass is bound by instructions (one of a wave takes a SIMD 4 cycles), so the work per 64
+// consecutive entries is kept to a few: a lane takes their places from 16-byte loads, one bit
+// per entry says where a run starts, and an entry's run and its number among the staged ones
+// are counts of bits below its lane.  What a wave needs for each of its (up to 24) vectors is
+// held in its lanes and read as scalars.
 template <class LT, bool WT>
 struct TileLds {
   static constexpr int PER = 16 / (int)sizeof(LT);
-  static constexpr int WIN = (TG_ROWS + 2 * TG_HALO + PER) / PER * 4;        // words of the label window
-  static constexpr int BUF = sizeof(LT) == 2 ? (WT ? TG_BUF_W : TG_BUF) : 0; // (run << 16) | label
   static constexpr int ARR = TG_ROWS + 4;
-  static constexpr int BASE = WIN + 7 * ARR + BUF + (WT ? BUF + 4 * TG_ROWS : 0);
-  static constexpr int seg(int S) { return 2 * (S + 2) + TG_FAR * TG_THREADS / 16; }  // the far entries' tables
-  // 16-bit labels, unweighted: STAGE_ROWS puts the rows together in BUF and what follows it, so
-  // the workgroup takes all that leaves room for two per CU
-  static constexpr int FULL = ((80 << 10) - 640) / 4;
-  static constexpr int words(int S) {
-    return sizeof(LT) == 2 && !WT && BASE + seg(S) < FULL ? FULL : BASE + seg(S);
-  }
-  static constexpr size_t bytes(int S) { return 4 * (size_t)words(S); }
+  static constexpr int VEC = TG_ENT / 64;
+  // label table (window, up to fmax far labels); run starts and staged entries (a bit per
+  // entry); run and number of every vector's first entry; per run first entry, label, place
+  static constexpr int table(int fmax) { return (TG_WIN + fmax + PER) / PER * 4; }
+  static constexpr int words(int fmax) { return table(fmax) + 4 * VEC + VEC + VEC + 3 * ARR + (WT ? 4 * TG_ROWS : 0); }
+  static constexpr size_t bytes(int fmax) { return 4 * (size_t)words(fmax); }
 };
-static_assert(TG_CHUNK / 16 + 2 <= TG_ROWS + 4, "the row table of STAGE_ROWS takes a row array");
 
 template <class LT, bool WT>
 __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
-    int n, int S, const int32_t* __restrict__ rp, const u32* __restrict__ nrp, const uint16_t* __restrict__ ncol,
-    const u32* __restrict__ fpt, const uint16_t* __restrict__ frow, const LT* __restrict__ fl, const LT* __restrict__ labx,
-    const u32* __restrict__ start, const u32* __restrict__ D, unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl,
-    LT* __restrict__ CB, const float* __restrict__ nw, const float* __restrict__ fw, float* __restrict__ CW,
-    unsigned long long* __restrict__ IWacc, int L, int chunk, const u32* __restrict__ PM, const u32* __restrict__ loc,
-    int always_rows) {
+    int n, int T, int fmax, const Tile* __restrict__ tiles, const int32_t* __restrict__ rp, const uint16_t* __restrict__ eidx,
+    const u32* __restrict__ fadr, const LT* __restrict__ fl, const LT* __restrict__ labx, const u32* __restrict__ start,
+    const u32* __restrict__ D, unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl, LT* __restrict__ CB,
+    const float* __restrict__ w, float* __restrict__ CW, unsigned long long* __restrict__ IWacc, int L, int chunk,
+    const u32* __restrict__ PM, const u32* __restrict__ loc, int always_rows) {
   using TL = TileLds<LT, WT>;
   constexpr u32 NOLAB = (u32)LabelT<LT>::SENTINEL;
-  constexpr int WAVES = TG_THREADS / 64;
+  constexpr u32 NOWHERE = 0x80000000u;  // places are below 2^31, and less an entry's number above -TG_ENT
   extern __shared__ __align__(16) u32 s_mem[];
-  u32* s_win32 = s_mem;
-  const LT* s_win = reinterpret_cast<const LT*>(s_win32);
-  u32* s_nr = s_win32 + TL::WIN;   // near row starts (tile-relative); later the places of the runs
-  u32* s_a = s_nr + TL::ARR;       // run (and 16-bit label) of every row
-  u32* s_b = s_a + TL::ARR;        // first row of every run
-  u32* s_cnt = s_b + TL::ARR;      // staged far entries per run (those in registers)
-  u32* s_more = s_cnt + TL::ARR;   // the other staged entries per run, then the next free place after the former
-  u32* s_base = s_more + TL::ARR;  // first near entry of every run
-  u32* s_first = s_base + TL::ARR; // first stored entry of every run
-  u32* s_place = s_nr;
-  u32* s_buf = s_first + TL::ARR;
-  float* s_wbuf = reinterpret_cast<float*>(s_buf + TL::BUF);
-  unsigned long long* s_ilo = reinterpret_cast<unsigned long long*>(s_buf + 2 * TL::BUF);  // WT: own-label weight sum per run
+  LT* s_tab = reinterpret_cast<LT*>(s_mem);
+  u32* s_bits = s_mem + TL::table(fmax);  // 64 per vector: bit i - 1 for a run that starts at its entry i > 0
+  unsigned long long* s_neq = reinterpret_cast<unsigned long long*>(s_bits + 2 * TL::VEC);
+  u32* s_vrun = s_bits + 4 * TL::VEC;
+  u32* s_vpre = s_vrun + TL::VEC;
+  u32* s_first = s_vpre + TL::VEC;
+  u32* s_lab = s_first + TL::ARR;
+  u32* s_to = s_lab + TL::ARR;
+  unsigned long long* s_ilo = reinterpret_cast<unsigned long long*>(s_to + TL::ARR);  // WT: own-label weight sum
   unsigned long long* s_ihi = s_ilo + TG_ROWS;
-  u32* s_pre = s_mem + TL::words(S) - TL::seg(S);  // far entries before each slice
-  u32* s_foff = s_pre + S + 2;                     // place of a slice's far entry j, minus j
-  uint16_t* s_seg8 = reinterpret_cast<uint16_t*>(s_foff + S + 2);
-  __shared__ u32 s_wave[WAVES];
-  __shared__ u32 s_nbuf;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int T = (n + TG_ROWS - 1) / TG_ROWS;
+  __shared__ u32 s_last[TG_WAVES], s_heads[TG_WAVES], s_staged[TG_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // each XCD (workgroup b runs on XCD b % 8) takes a contiguous eighth of the tiles
   const int per = (T + 7) / 8, t = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
   if ((int)(blockIdx.x / 8u) >= per || t >= T) return;
   const bool by_rows = !WT && sizeof(LT) == 2 && (always_rows || ctl->mode == STAGE_ROWS);  // see k_colscan_rows
-  const int r0 = t * TG_ROWS, rows = min(TG_ROWS, n - r0);
-  const int w0 = tile_w0(r0), w1 = tile_w1(r0, n), roff = r0 - w0;
-  // Every load that depends on no other is issued first, then those that need the tile's first
-  // near entry or the row's label; the LDS writes wait for all of them at once.
-  constexpr int SPT = TG_MAX_SLICES / TG_THREADS;
-  const int spt = (S + TG_THREADS - 1) / TG_THREADS;
-  const int my_row = r0 + min(tid, rows - 1);
-  typedef u32 v4u __attribute__((ext_vector_type(4)));
-  constexpr int WV = TL::WIN / 4;                                // 16-byte words of the window
-  constexpr int WPT = (WV + TG_THREADS - 1) / TG_THREADS;
-  const int nwin = (w1 - w0 + TL::PER - 1) / TL::PER;
-  const v4u* win = reinterpret_cast<const v4u*>(labx + w0);  // w0 is a multiple of 1,024; the array is padded past n
-  v4u wreg[WPT];
+  const Tile tile = tiles[t];
+  const u32 ne = tile.ne;
+  if (ne == 0) return;
+  const int rows = tile.r1 - tile.r0;
+  const int w0 = tile_w0(tile.b0), w1 = tile_w1(tile.b0, n);
+  // a wave takes `steps` consecutive groups
+  const u32 ng = (ne + TG_GROUP - 1u) / TG_GROUP, steps = (ng + TG_WAVES - 1u) / TG_WAVES, gw = (u32)wv * steps;
+  // every load that depends on no other first
+  const int my_row = tile.r0 + min(tid, rows - 1);
+  const uint4* ew = reinterpret_cast<const uint4*>(eidx) + (size_t)tile.g0 * (TG_GROUP / 8) + lane;
+  constexpr int FU = 8;
+  u32 fa[FU];
 #pragma unroll
-  for (int i = 0; i < WPT; ++i) wreg[i] = win[min(tid + i * TG_THREADS, nwin - 1)];
+  for (int k = 0; k < FU; ++k) fa[k] = (u32)(tid + k * TG_THREADS) < tile.nf ? fadr[tile.f0 + (u32)(tid + k * TG_THREADS)] : 0u;
+  uint4 q[TG_STEPS];
+#pragma unroll
+  for (int i = 0; i < TG_STEPS; ++i)
+    q[i] = (u32)i < steps && gw + i < ng ? ew[(gw + i) * (u32)(TG_GROUP / 8)] : make_uint4(0u, 0u, 0u, 0u);
   const u32 own = (u32)labx[my_row];
-  const u32 row_n = nrp[my_row];
-  const int row_e = rp[my_row];
+  const u32 ra = (u32)rp[my_row], rb = (u32)rp[my_row + 1];
   const u32 lu = by_rows ? loc[my_row] : 0u;
-  // the thread's slices (consecutive): far entries [fa, fe) of each
-  u32 fa[SPT], fe[SPT];
-#pragma unroll
-  for (int i = 0; i < SPT; ++i) {
-    const int s = tid * spt + i;
-    const bool in = i < spt && s < S;
-    fa[i] = in ? fpt[(size_t)t * S + s] : 0u;
-    fe[i] = in ? fpt[((size_t)t + 1) * S + s] : 0u;
-  }
-  const u32 nb = nrp[r0];
-  const u32 ne = nrp[r0 + rows] - nb;
-  const u32 ng = (nb & 7u) + ne;  // near entries from the 16-byte word that holds the first one
-  const uint4* ncol8 = reinterpret_cast<const uint4*>(ncol + (nb & ~7u));
-  // the wave's first block of near entries (word i holds entries 8 i .. 8 i + 7 from nb & ~7)
-  uint4 ahead = make_uint4(0u, 0u, 0u, 0u);
-  if ((u32)(8 * tid) < ng) ahead = ncol8[tid];
-  // STAGE_ROWS: the row's place in its segment (SENT: not written, only with a label error,
-  // which voids the result)
-  u32 row_place = SENT;
-  if (by_rows && own != NOLAB && lu != SENT) row_place = start[own] + PM[(size_t)(my_row / chunk) * L + own] + lu;
+  typedef u32 v4u __attribute__((ext_vector_type(4)));
   {
-    v4u* dst = reinterpret_cast<v4u*>(s_win32);
-#pragma unroll
-    for (int i = 0; i < WPT; ++i)
-      if (tid + i * TG_THREADS < nwin) dst[tid + i * TG_THREADS] = wreg[i];
-    if (tid < rows) s_nr[tid] = row_n - nb;
-    if (tid == 0) {
-      s_nr[rows] = ne;
-      s_nbuf = 0;
-    }
+    const v4u* src = reinterpret_cast<const v4u*>(labx + w0);  // w0 is a multiple of 512; the array is padded past n
+    v4u* dst = reinterpret_cast<v4u*>(s_mem);
+    for (int i = tid; i < (w1 - w0 + TL::PER - 1) / TL::PER; i += TG_THREADS) dst[i] = src[i];
   }
-  // far entries numbered slice by slice
-  u32 nf = 0;
+  if (tid < 2 * TL::VEC) s_bits[tid] = 0;
+  // the row's entries in the tile: [a, b)
+  const u32 a = max(ra, tile.e0) - tile.e0, b = min(max(rb, tile.e0) - tile.e0, ne);
+  const bool has = tid < rows && a < b;
+  const u64 hasm = __ballot(has);
+  // the label of the wave's last row with entries
+  if (hasm ? lane == 63 - __clzll((long long)hasm) : lane == 0) s_last[wv] = hasm ? own : SENT;
+#pragma unroll
+  for (int k = 0; k < FU; ++k)
+    if ((u32)(tid + k * TG_THREADS) < tile.nf) s_tab[TG_WIN + tid + k * TG_THREADS] = fl[fa[k]];
+  for (u32 j = tid + FU * TG_THREADS; j < tile.nf; j += TG_THREADS) s_tab[TG_WIN + j] = fl[fadr[tile.f0 + j]];
+  // STAGE_ROWS: the place of the row's entry e, less e
+  u32 row_to = NOWHERE;  // only with a label error, which voids the result
+  if (by_rows && own != NOLAB && lu != SENT)
+    row_to = start[own] + PM[(size_t)(my_row / chunk) * L + own] + lu + (tile.e0 - ra);
+  __syncthreads();
+  // runs
+  const u64 below = (1ull << lane) - 1ull;
+  u32 prev = SENT;
   {
-    u32 cnt = 0;
+    const u64 pm = hasm & below;
+    const u32 in_wave = (u32)__shfl((int)own, pm ? 63 - __clzll((long long)pm) : 0, 64);
+    for (int i = 0; i < wv; ++i) prev = s_last[i] != SENT ? s_last[i] : prev;
+    if (pm) prev = in_wave;
+  }
+  const bool head = has && (by_rows || own != prev || prev == SENT);
+  const u64 headm = __ballot(head);
+  if (lane == 0) s_heads[wv] = (u32)__popcll(headm);
+  __syncthreads();
+  u32 nruns = 0, run = (u32)__popcll(headm & (below | (1ull << lane))) - 1u;
 #pragma unroll
-    for (int i = 0; i < SPT; ++i) cnt += fe[i] - fa[i];
-    const u32 incl = wave_incl_scan(cnt);
-    if (lane == 63) s_wave[wv] = incl;
-    __syncthreads();
-    u32 pre = incl - cnt;
-#pragma unroll
-    for (int i = 0; i < WAVES; ++i) {
-      const u32 k = s_wave[i];
-      if (i < wv) pre += k;
-      nf += k;
-    }
-#pragma unroll
-    for (int i = 0; i < SPT; ++i) {
-      const int s = tid * spt + i;
-      if (i >= spt || s >= S) break;
-      const u32 c = fe[i] - fa[i];
-      s_pre[s] = pre;
-      s_foff[s] = fa[i] - pre;
-      for (u32 g = (pre + 7u) / 8u; g * 8u < pre + c && g < (u32)(TG_FAR * TG_THREADS / 8); ++g) s_seg8[g] = (uint16_t)s;
-      pre += c;
-    }
-    if (tid == 0) s_pre[S] = nf;
+  for (int i = 0; i < TG_WAVES; ++i) {
+    const u32 k = s_heads[i];
+    if (i < wv) run += k;
+    nruns += k;
+  }
+  if (head) {
+    s_first[run] = a;
+    s_lab[run] = own;
+    if (by_rows) s_to[run] = row_to;
+    if (a & 63u) atomicOr(&s_bits[2u * (a >> 6) + (((a & 63u) - 1u) >> 5)], 1u << (((a & 63u) - 1u) & 31u));
+  }
+  if (tid == 0) s_first[nruns] = ne;
+  if (has)
+    for (u32 v = (a + 63u) / 64u; v * 64u < b; ++v) s_vrun[v] = run;
+  if (WT && tid < rows) {
+    s_ilo[tid] = 0ull;
+    s_ihi[tid] = 0ull;
   }
   __syncthreads();
-  // place of far entry j (slices without entries are walked over)
-  auto far_at = [&](u32 j) {
-    u32 s;
-    if (j < (u32)(TG_FAR * TG_THREADS)) {
-      s = s_seg8[j >> 3];
-    } else {  // beyond the table: last slice whose entries start at or before j
-      s = 0;
-      for (u32 st = TG_MAX_SLICES / 2; st > 0; st >>= 1)
-        if (s + st < (u32)S && s_pre[s + st] <= j) s += st;
-    }
-    while (s_pre[s + 1] <= j) ++s;
-    return s_foff[s] + j;
+  // lane l: the wave's vector l
+  const u32 v0 = gw * (TG_GROUP / 64);
+  const bool have = (u32)lane < steps * (TG_GROUP / 64) && (v0 + lane) * 64u < ne;
+  const u32 vl = v0 + (have ? (u32)lane : 0u);
+  const u32 vbl = have ? s_bits[2u * vl] : 0u, vbh = have ? s_bits[2u * vl + 1u] : 0u, vr = have ? s_vrun[vl] : 0u;
+  const u64 multi = __ballot((vbl | vbh) != 0u);
+  auto of = [](u32 x, int i) { return (u32)__builtin_amdgcn_readlane((int)x, i); };
+  auto below_in = [](u32 lo, u32 hi, u32 base) {  // base + set bits below the lane
+    return (u32)__builtin_amdgcn_mbcnt_hi((int)hi, __builtin_amdgcn_mbcnt_lo((int)lo, (int)base));
   };
-  // the thread's far entries j = tid + 1024 k: row << 16 | label (16-bit labels), all loads in flight
-  u32 fat[TG_FAR], fr[TG_FAR], fx[TG_FAR];
-#pragma unroll
-  for (int k = 0; k < TG_FAR; ++k) {
-    const u32 j = (u32)(tid + k * TG_THREADS);
-    fr[k] = 0;
-    fx[k] = 0;
-    if (j < nf) {
-      fat[k] = far_at(j);
-      fr[k] = frow[fat[k]];
-      fx[k] = (u32)fl[fat[k]];
-    }
-  }
-  // Walks the tile's near entries in wave blocks of 512: f(e, off) with e the number of the
-  // lane's first of eight entries (from nb & ~7) and off their window offsets, two per word.
-  auto near_blocks = [&](auto&& f) {
-    uint4 q = ahead;
-    for (u32 b = (u32)wv * 512u; b < ng; b += WAVES * 512u) {
-      const u32 next = b + WAVES * 512u + 8u * (u32)lane;
-      uint4 q1 = make_uint4(0u, 0u, 0u, 0u);
-      if (next < ng) q1 = ncol8[next / 8u];
-      f(b, b + 8u * (u32)lane, q);
-      q = q1;
-    }
+  auto half = [](const uint4& v, int k) {
+    const u32 x = k < 2 ? v.x : k < 4 ? v.y : k < 6 ? v.z : v.w;
+    return (k & 1) ? x >> 16 : x & 0xFFFFu;
   };
-  auto off_of = [](const uint4& q, int k) {
-    const u32 w = k < 2 ? q.x : k < 4 ? q.y : k < 6 ? q.z : q.w;
-    return (k & 1) ? w >> 16 : w & 0xFFFFu;
+  auto label = [&](const uint4& v, int k) {
+    return (u32) * reinterpret_cast<const LT*>(reinterpret_cast<const char*>(s_mem) + half(v, k) * (sizeof(LT) / 2));
   };
-  const u32 skip = nb & 7u;  // entry number of the tile's first near entry
   if (by_rows) {
-    // Entries are placed relative to the tile's first entry, row by row.  Per row: end of its
-    // near entries, and the place of near entry e minus e (one LDS read gives both); the next
-    // free place of its far entries; the row's place in its segment.
-    uint2* s_row = reinterpret_cast<uint2*>(s_a);  // s_a and s_b
-    u32* s_far = s_cnt;
-    uint16_t* s_row8 = reinterpret_cast<uint16_t*>(s_more);
-    LT* s_out = reinterpret_cast<LT*>(s_buf);
-    // entries put together in LDS (beyond: written straight away); the far tables' space too
-    // once all far entries are in registers
-    const u32 cap = ((u32)(s_pre - s_buf) + (nf <= (u32)(TG_FAR * TG_THREADS) ? (u32)TL::seg(S) : 0u)) * (4 / sizeof(LT));
-    if (tid < rows) {
-      const u32 a = s_nr[tid], b = s_nr[tid + 1], at = (u32)(row_e - rp[r0]);
-      s_row[tid] = make_uint2(b + skip, at - a - skip);
-      s_far[tid] = at + b - a;
-      s_base[tid] = row_place;
-    }
-    auto put = [&](u32 r, u32 at, u32 x) {
-      if (at < cap) s_out[at] = (LT)x;
-      else if (s_base[r] != SENT) CB[s_base[r] + (at - (s_row[r].y + s_nr[r] + skip))] = (LT)x;
-    };
-    for (u32 c0 = 0; c0 < ng; c0 += TG_CHUNK) {
-      const u32 c1 = min(ng, c0 + (u32)TG_CHUNK);
-      __syncthreads();  // the far entries are in registers; the previous chunk's row table is no longer read
-      if (tid < rows) {
-        const u32 a = max(s_nr[tid] + skip, c0), b = min(s_nr[tid + 1] + skip, c1);
-        const u32 lo = s_nr[tid] == 0 ? c0 : a;  // the first group starts before the tile's first entry
-        if (a < b)
-          for (u32 g = (lo + 7u) / 8u; g * 8u < b; ++g) s_row8[g - c0 / 8u] = (uint16_t)tid;
-      }
-      __syncthreads();
-      for (u32 e0 = c0 + 8u * (u32)tid; e0 < c1; e0 += 8u * TG_THREADS) {
-        const uint4 q = c0 == 0 && e0 == 8u * (u32)tid ? ahead : ncol8[e0 / 8u];
-        u32 r = s_row8[(e0 - c0) / 8u];
-        uint2 row = s_row[r];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const u32 e = e0 + (u32)k;
-          if (e >= skip && e < c1) {
-            while (row.x <= e) row = s_row[++r];
-            put(r, row.y + e, (u32)s_win[off_of(q, k)]);
-          }
-        }
-      }
-    }
-    __syncthreads();  // (a tile without near entries passes no barrier above)
+    for (int i = 0; i < TG_STEPS; ++i) {
+      if ((u32)i >= steps || gw + i >= ng) break;
+      u32 to[8], x[8];
 #pragma unroll
-    for (int k = 0; k < TG_FAR; ++k)
-      if ((u32)(tid + k * TG_THREADS) < nf) put(fr[k], atomicAdd(&s_far[fr[k]], 1u), fx[k]);
-    for (u32 j = (u32)(tid + TG_FAR * TG_THREADS); j < nf; j += TG_THREADS) {
-      const u32 at = far_at(j), r = frow[at];
-      put(r, atomicAdd(&s_far[r], 1u), (u32)fl[at]);
-    }
-    __syncthreads();
-    for (int r = tid >> 4; r < rows; r += TG_THREADS / 16) {
-      const u32 base = s_base[r], at = s_row[r].y + s_nr[r] + skip, end = min(s_far[r], cap);
-      if (base == SENT) continue;
-      for (u32 i = at + ((u32)tid & 15u); i < end; i += 16) CB[base + (i - at)] = s_out[i];
+      for (int k = 0; k < 8; ++k) {
+        const int v = 8 * i + k;
+        to[k] = s_to[below_in(of(vbl, v), of(vbh, v), of(vr, v))];
+        x[k] = label(q[i], k);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const u32 e = (gw + i) * TG_GROUP + (u32)(64 * k + lane);
+        if (to[k] != NOWHERE && e < ne) CB[to[k] + e] = (LT)x[k];
+      }
     }
     return;
   }
-  // runs of rows with equal labels
-  u32 nruns = 0;
-  {
-    const u32 c = own;
-    const bool head = tid < rows && (tid == 0 || c != (u32)s_win[roff + tid - 1]);
-    const u64 m = __ballot(head);
-    if (lane == 0) s_wave[wv] = (u32)__popcll(m);
-    __syncthreads();
-    u32 before = 0;
-#pragma unroll
-    for (int i = 0; i < WAVES; ++i) {
-      const u32 k = s_wave[i];
-      if (i < wv) before += k;
-      nruns += k;
-    }
-    const u32 run = before + (u32)__popcll(m & (~0ull >> (63 - lane))) - 1u;  // runs that start at or before this row
-    if (tid < rows) s_a[tid] = sizeof(LT) == 2 ? (run << 16) | c : run;
-    if (head) {
-      s_b[run] = (u32)tid;
-      s_first[run] = (u32)row_e;
-      s_base[run] = s_nr[tid] + skip;
-    }
-    if (tid == 0) {
-      s_b[nruns] = (u32)rows;
-      s_first[nruns] = (u32)rp[r0 + rows];
-    }
-    if (tid < rows) {
-      s_cnt[tid] = 0;
-      s_more[tid] = 0;
-      if (WT) {
-        s_ilo[tid] = 0ull;
-        s_ihi[tid] = 0ull;
-      }
-    }
-    __syncthreads();
-  }
-  // run of near entry e: the last one whose rows' near entries start at or before e (runs
-  // without near entries start where the next one does)
-  u32 top = 0;
-  if (nruns > 1) top = 1u << (31 - __clz((int)(nruns - 1)));
-  auto run_of = [&](u32 e) {
-    u32 l = 0;
-    for (u32 st = top; st > 0; st >>= 1)
-      if (l + st < nruns && s_base[l + st] <= e) l += st;
-    return l;
-  };
-  auto label_of = [&](u32 run) { return (u32)s_win[roff + s_b[run]]; };
-  // WT: a thread sums the own-label weights of its current run and adds them to the run's LDS
-  // sum when the run changes (64-bit atomics, the low word's carry added to the high word)
-  u32 wrun = SENT;
+  // first walk: which entries are staged
+  const u32 vc = have ? s_lab[vr] : 0u;
+  u32 nlo = 0, nhi = 0;  // lane l: the staged entries of vector l
+  u32 wrun = SENT;       // WT: the run whose own-label weights wacc sums
   WeightSum wacc;
   auto wflush = [&]() {
-    if (wrun != SENT) {
-      const unsigned long long old = atomicAdd(&s_ilo[wrun], (unsigned long long)wacc.lo);
-      const unsigned long long hi = wacc.hi + (old + wacc.lo < old ? 1ull : 0ull);
+    if (wrun == SENT) return;
+    const u128 sum = wave_sum_u128(wacc.value());
+    if (lane == 0) {
+      const unsigned long long lo = (unsigned long long)sum, old = atomicAdd(&s_ilo[wrun], lo);
+      const unsigned long long hi = (unsigned long long)(sum >> 64) + (old + lo < old ? 1ull : 0ull);
       if (hi) atomicAdd(&s_ihi[wrun], hi);
     }
+    wacc = WeightSum();
   };
-  auto own_weight = [&](u32 run, float w) {
-    if (run != wrun) {
-      wflush();
-      wrun = run;
-      wacc = WeightSum();
+#pragma unroll
+  for (int i = 0; i < TG_STEPS; ++i) {
+    if ((u32)i >= steps || gw + i >= ng) break;
+    const u32 e0 = (gw + i) * TG_GROUP;
+    u32 x[8];
+    u64 m[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = label(q[i], k);
+    if ((multi >> (8 * i)) & 0xFFull) {
+      u32 c[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) c[k] = s_lab[below_in(of(vbl, 8 * i + k), of(vbh, 8 * i + k), of(vr, 8 * i + k))];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) m[k] = __ballot(x[k] != c[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) m[k] = __ballot(x[k] != of(vc, 8 * i + k));
     }
-    u64 vlo, vhi;
-    WeightSum::split(w, vlo, vhi);
-    wacc.add(vlo, vhi);
-  };
-  // calls f(k, run, own label) for the lane's near entries of block b that exist
-  auto with_runs = [&](u32 b, u32 e0, auto&& f) {
-    const u32 q0 = run_of(max(b, skip)), q1 = run_of(min(b + 512u, ng) - 1u);
-    u32 run = q0;
-    if (q0 != q1 && e0 < ng) run = run_of(max(e0, skip));
-    u32 c = label_of(run);
+    if (ne - e0 < (u32)TG_GROUP) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const u32 left = ne - e0 > 64u * k ? ne - e0 - 64u * k : 0u;
+        if (left < 64u) m[k] &= (1ull << left) - 1ull;
+      }
+    }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const u32 e = e0 + (u32)k;
-      if (e < skip || e >= ng) continue;
-      if (q0 != q1 && run + 1 < nruns && s_base[run + 1] <= e) {
-        do ++run;
-        while (run + 1 < nruns && s_base[run + 1] <= e);
-        c = label_of(run);
-      }
-      f(k, run, c);
+      const bool it = __builtin_amdgcn_inverse_ballot_w64(1ull << (8 * i + k));
+      nlo = it ? (u32)m[k] : nlo;
+      nhi = it ? (u32)(m[k] >> 32) : nhi;
     }
-    return q0 == q1 ? q0 : SENT;
-  };
-  near_blocks([&](u32 b, u32 e0, const uint4& q) {
-    u32 inter = 0;          // bit k: the lane's entry k has another label
-    u32 rk[8];              // its run (blocks of several runs only)
-    const u32 one = with_runs(b, e0, [&](int k, u32 run, u32 c) {
-      const u32 x = (u32)s_win[off_of(q, k)];
-      rk[k] = run;
-      if (x != c) inter |= 1u << k;
-      else if (WT) own_weight(run, nw[(nb & ~7u) + e0 + (u32)k]);
-    });
-    const u32 cnt = (u32)__popc(inter);
-    const u32 incl = wave_incl_scan(cnt);
-    const u32 total = (u32)__builtin_amdgcn_readlane((int)incl, 63);
-    if (total == 0) return;
-    u32 slot = 0;
-    if (lane == 0) {
-      slot = atomicAdd(&s_nbuf, total);
-      if (one != SENT) atomicAdd(&s_more[one], total);
-    }
-    slot = (u32)__builtin_amdgcn_readfirstlane((int)slot) + incl - cnt;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (!((inter >> k) & 1u)) continue;
-      if (one == SENT) atomicAdd(&s_more[rk[k]], 1u);
-      if (slot < (u32)TL::BUF) {
-        s_buf[slot] = (rk[k] << 16) | (u32)s_win[off_of(q, k)];
-        if (WT) s_wbuf[slot] = nw[(nb & ~7u) + e0 + (u32)k];
-      }
-      ++slot;
-    }
-  });
-  auto of_row = [&](u32 r, u32& run, u32& c) {
-    const u32 q = s_a[r];
-    run = sizeof(LT) == 2 ? q >> 16 : q;
-    c = sizeof(LT) == 2 ? q & 0xFFFFu : (u32)s_win[roff + r];
-  };
-  // far entries: fr becomes the run (SENT: own label), and the entry's rank among the run's
-  // staged entries is known at once
-  u32 rank[TG_FAR];
-#pragma unroll
-  for (int k = 0; k < TG_FAR; ++k) {
-    const bool in = (u32)(tid + k * TG_THREADS) < nf;
-    u32 run = 0, c = 0;
-    of_row(fr[k], run, c);  // row 0 where there is no entry
-    const bool inter = in && fx[k] != c;
-    if (WT && in && !inter) own_weight(run, fw[fat[k]]);
-    fr[k] = inter ? run : SENT;
-    rank[k] = wave_count<2>(s_cnt, run, inter);
+    if (sizeof(LT) == 2)  // the labels take the places' registers
+      q[i] = make_uint4(x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16);
   }
-  for (u32 j = (u32)(tid + TG_FAR * TG_THREADS); j < nf; j += TG_THREADS) {
-    const u32 at = far_at(j);
-    u32 run, c;
-    of_row(frow[at], run, c);
-    if ((u32)fl[at] != c) atomicAdd(&s_more[run], 1u);
-    else if (WT) own_weight(run, fw[at]);
-  }
-  if (WT) wflush();
-  __syncthreads();
-  // one claim per run
-  if ((u32)tid < nruns) {
-    const u32 ra = s_b[tid];
-    const u32 c = (u32)s_win[roff + ra];
-    const u32 tot = s_first[tid + 1] - s_first[tid], inter = s_cnt[tid] + s_more[tid];
-    u32 base = SENT;
-    if (c != NOLAB && tot > 0) {
-      const unsigned long long old = atomicAdd(&cur64[c], ((unsigned long long)(tot - inter) << 32) | inter);
-      const u32 lo = (u32)old;
-      if (lo + inter <= D[c]) base = start[c] + lo;  // < 2^31, so never the SENT marker
-      else atomicOr(&ctl->flags, F_SEGMENT);  // never expected: the tile's counts disagree with the degrees
-      if (WT) {
-        const unsigned long long ilo = s_ilo[tid], ihi = s_ihi[tid];
-        if (ilo | ihi) {
-          const unsigned long long was = atomicAdd(&IWacc[2 * (size_t)c], ilo);
-          const unsigned long long h = ihi + (was + ilo < was ? 1ull : 0ull);
-          if (h) atomicAdd(&IWacc[2 * (size_t)c + 1], h);
+  if constexpr (WT) {
+    // own-label weights, the runs of a vector one after another
+    constexpr int U = 4;
+    const int nv = (int)min(steps * (u32)(TG_GROUP / 64), v0 * 64u < ne ? (ne - v0 * 64u + 63u) / 64u : 0u);
+    for (int vb = 0; vb < nv; vb += U) {
+      float wt[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) wt[k] = w[tile.e0 + min((v0 + (u32)(vb + k)) * 64u + (u32)lane, ne - 1u)];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int v = vb + k;
+        if (v >= nv) break;
+        u64 vlo, vhi;
+        WeightSum::split(wt[k], vlo, vhi);
+        const u64 neq = ((u64)of(nhi, v) << 32) | of(nlo, v);
+        const bool mine = !((neq >> lane) & 1ull) && (v0 + (u32)v) * 64u + (u32)lane < ne;
+        u64 bits = ((u64)of(vbh, v) << 32) | of(vbl, v);
+        u32 r = of(vr, v);
+        int lo = 0;
+        while (true) {
+          const int hi = bits ? __ffsll((unsigned long long)bits) : 64;
+          if (r != wrun) {
+            wflush();
+            wrun = r;
+          }
+          if (mine && lane >= lo && lane < hi) wacc.add(vlo, vhi);
+          if (!bits) break;
+          bits &= bits - 1ull;
+          lo = hi;
+          ++r;
         }
       }
     }
-    s_place[tid] = base;
-    s_more[tid] = s_cnt[tid];
+  }
+  if (WT) wflush();
+  u32 vp;
+  {
+    const u32 cnt = (u32)(__popc(nlo) + __popc(nhi)), incl = wave_incl_scan(cnt);
+    vp = incl - cnt;
+    if (have) {
+      s_neq[vl] = ((u64)nhi << 32) | nlo;
+      s_vpre[vl] = vp;
+    }
+    if (lane == 63) s_staged[wv] = incl;
   }
   __syncthreads();
-  auto put = [&](u32 run, u32 at, u32 x, float w) {
-    const u32 base = s_place[run];
-    if (base == SENT) return;
-    CB[base + at] = (LT)x;
-    if (WT) CW[base + at] = w;
-  };
-#pragma unroll
-  for (int k = 0; k < TG_FAR; ++k)
-    if (fr[k] != SENT) put(fr[k], rank[k], fx[k], WT ? fw[fat[k]] : 0.0f);
-  for (u32 j = (u32)(tid + TG_FAR * TG_THREADS); j < nf; j += TG_THREADS) {
-    const u32 at = far_at(j), x = (u32)fl[at];
-    u32 run, c;
-    of_row(frow[at], run, c);
-    if (x != c) put(run, atomicAdd(&s_more[run], 1u), x, WT ? fw[at] : 0.0f);
-  }
-  const u32 nbuf = s_nbuf;
-  if (nbuf <= (u32)TL::BUF) {
-    // each wave takes consecutive places per run (coalesced)
-    for (u32 k0 = 0; k0 < nbuf; k0 += TG_THREADS) {
-      const u32 k = k0 + (u32)tid;
-      const u32 ent = k < nbuf ? s_buf[k] : 0u;
-      const u32 at = wave_count<2>(s_more, ent >> 16, k < nbuf);
-      if (k < nbuf) put(ent >> 16, at, ent & 0xFFFFu, WT ? s_wbuf[k] : 0.0f);
+  // number of the first staged entry of every wave
+  const u32 wincl = wave_incl_scan(lane < TG_WAVES ? s_staged[lane] : 0u);
+  vp += wv ? of(wincl, wv - 1) : 0u;
+  // one claim per run
+  {
+    // staged entries before entry e of the tile
+    const bool mine = (u32)tid < nruns;
+    auto before = [&](u32 e) {
+      const u32 v = min(e, ne - 1u) >> 6, wave = v / (steps * (TG_GROUP / 64));
+      const u32 base = (u32)__shfl((int)wincl, wave ? (int)wave - 1 : 0, 64);
+      return (wave ? base : 0u) + s_vpre[v] +
+             (e >= ne ? (u32)__popcll(s_neq[v]) : (u32)__popcll(s_neq[v] & ((1ull << (e & 63u)) - 1ull)));
+    };
+    const u32 f = mine ? s_first[tid] : 0u, z = mine ? s_first[tid + 1] : 0u;
+    const u32 p = before(f), inter = before(z) - p;
+    if (mine) {
+      const u32 c = s_lab[tid], tot = z - f;
+      u32 to = NOWHERE;
+      if (c != NOLAB) {
+        const unsigned long long old = atomicAdd(&cur64[c], ((unsigned long long)(tot - inter) << 32) | inter);
+        const u32 lo = (u32)old;
+        if (lo + inter <= D[c]) to = start[c] + lo - p;
+        else atomicOr(&ctl->flags, F_SEGMENT);  // never expected: the tile's counts disagree with the degrees
+        if (WT) {
+          const unsigned long long ilo = s_ilo[tid], ihi = s_ihi[tid];
+          if (ilo | ihi) {
+            const unsigned long long was = atomicAdd(&IWacc[2 * (size_t)c], ilo);
+            const unsigned long long h = ihi + (was + ilo < was ? 1ull : 0ull);
+            if (h) atomicAdd(&IWacc[2 * (size_t)c + 1], h);
+          }
+        }
+      }
+      s_to[tid] = to;
     }
-  } else {
-    // more than the buffer holds (or 32-bit labels): walk the near entries again
-    near_blocks([&](u32 b, u32 e0, const uint4& q) {
-      (void)with_runs(b, e0, [&](int k, u32 run, u32 c) {
-        const u32 x = (u32)s_win[off_of(q, k)];
-        if (x != c) put(run, atomicAdd(&s_more[run], 1u), x, WT ? nw[(nb & ~7u) + e0 + (u32)k] : 0.0f);
-      });
-    });
+  }
+  __syncthreads();
+  // second walk: their labels (and weights) to their places
+  const u32 vt = have ? s_to[vr] : NOWHERE;
+#pragma unroll
+  for (int i = 0; i < TG_STEPS; ++i) {
+    if ((u32)i >= steps || gw + i >= ng) break;
+    const u32 e0 = (gw + i) * TG_GROUP;
+    u32 to[8];
+    if ((multi >> (8 * i)) & 0xFFull) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) to[k] = s_to[below_in(of(vbl, 8 * i + k), of(vbh, 8 * i + k), of(vr, 8 * i + k))];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) to[k] = of(vt, 8 * i + k);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const u32 lo = of(nlo, 8 * i + k), hi = of(nhi, 8 * i + k);
+      const u32 at = below_in(lo, hi, to[k] + of(vp, 8 * i + k));
+      if (__builtin_amdgcn_inverse_ballot_w64(((u64)hi << 32) | lo) && to[k] != NOWHERE) {
+        CB[at] = (LT)(sizeof(LT) == 2 ? half(q[i], k) : label(q[i], k));
+        if (WT) CW[at] = w[tile.e0 + e0 + (u32)(64 * k + lane)];
+      }
+    }
   }
 }
 
