@@ -1377,9 +1377,10 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
 }
 
 cq_status build_tiles(cq_context* ctx, cq_graph* g) {
+  const u32 limit = g->owned_w ? TG_ENT_W : TG_ENT;
   u32 most = 0;
-  const cq_status st = build_tiles(ctx, g, TG_ENT, TG_FAR_MAX, &most);
-  return st != CQ_OK || most <= (u32)TG_FAR_MAX ? st : build_tiles(ctx, g, TG_ENT_FAR, TG_ENT_FAR, &most);
+  const cq_status st = build_tiles(ctx, g, TG_ENT, limit, &most);
+  return st != CQ_OK || most <= limit ? st : build_tiles(ctx, g, TG_ENT_W, limit, &most);
 }
 
 // Builds the label permutation plan of a renumbered graph from newid (caller id ->
@@ -2063,10 +2064,10 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint16_t>), 2 << TS_SHIFT);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint32_t>), 4 << TS_SHIFT);
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_ENT_FAR));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_ENT_FAR));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::bytes(TG_ENT_FAR));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::bytes(TG_ENT_FAR));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_ENT));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_ENT_W));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::bytes(TG_ENT));
+  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::bytes(TG_ENT_W));
   set_big_lds(reinterpret_cast<const void*>(k_small_count), ss_lds(SS_MAX_N, SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_final), 4 * (size_t)ss_cells(SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_compare), 4 * (size_t)SC_MAX_CELLS + 24 * (size_t)SC_MAX_L + 64);

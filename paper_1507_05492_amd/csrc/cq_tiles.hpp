@@ -30,15 +30,14 @@ constexpr int TG_WIN = TG_ROWS + 2 * TG_HALO;  // table places of the window (8,
 constexpr int TG_GROUP = 512;        // entries per wave and step: 8 per lane
 constexpr int TG_STEPS = 3;          // steps per wave at most
 constexpr int TG_ENT = TG_WAVES * TG_GROUP * TG_STEPS;  // entries per tile at most: 24,576
-// A graph with a tile of more far entries than this is cut into tiles of at most TG_ENT_FAR
-// entries instead, so that two workgroups of 16-bit labels (one of 32-bit ones) fit a CU's LDS.
-constexpr int TG_FAR_MAX = 12288;
-constexpr int TG_ENT_FAR = 16384;
+// A weighted graph with a tile of more far entries than this is cut into tiles of at most so many
+// entries instead: 32-bit labels and the runs' weight sums then still fit a CU's LDS.
+constexpr int TG_ENT_W = 16384;
 constexpr int TS_SHIFT = 15;
 constexpr int TS_NODES = 1 << TS_SHIFT;  // ids per slice: 64 KB of 16-bit labels, 128 KB of 32-bit ones
 constexpr int TG_MAX_SLICES = 4096;  // n up to 2^27 (32 KB of counters at load time)
 static_assert(TG_ROWS == TG_THREADS, "one row per thread");
-static_assert(2 * (TG_WIN + TG_ENT_FAR) <= 65536 && TG_FAR_MAX <= TG_ENT_FAR, "16-bit table places, in units of 2 bytes");
+static_assert(2 * (TG_WIN + TG_ENT) <= 65536, "16-bit table places, in units of 2 bytes");
 
 struct Tile {
   int b0;       // first row of its block
@@ -100,8 +99,8 @@ __global__ __launch_bounds__(256) void k_tile_list(int n, int blocks, u32 ent, c
   }
 }
 
-// One workgroup per tile: far entries per slice (fcnt[slice * T + tile]), in all, and the most
-// of any tile.
+// One workgroup per tile: far entries per slice (fcnt[slice * T + tile]), in all, and the
+// most of any tile.
 __global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, const Tile* __restrict__ tiles,
                                                            const int32_t* __restrict__ col, u32* __restrict__ fcnt,
                                                            u32* __restrict__ nfar, u32* __restrict__ fmax) {
@@ -254,12 +253,14 @@ __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int parts, con
 template <class LT, bool WT>
 struct TileLds {
   static constexpr int PER = 16 / (int)sizeof(LT);
-  static constexpr int ARR = TG_ROWS + 4;
+  static constexpr int ARR = TG_ROWS + 8;
   static constexpr int VEC = TG_ENT / 64;
   // label table (window, up to fmax far labels); run starts and staged entries (a bit per
-  // entry); run and number of every vector's first entry; per run first entry, label, place
-  static constexpr int table(int fmax) { return (TG_WIN + fmax + PER) / PER * 4; }
-  static constexpr int words(int fmax) { return table(fmax) + 4 * VEC + VEC + VEC + 3 * ARR + (WT ? 4 * TG_ROWS : 0); }
+  // entry); per run place, label and first entry; run and number of every vector's first entry
+  static constexpr int table(int fmax) { return (TG_WIN + fmax + PER - 1) / PER * 4; }
+  static constexpr int words(int fmax) {
+    return table(fmax) + 4 * VEC + ARR + ARR * (int)sizeof(LT) / 4 + ARR / 2 + VEC + (WT ? 4 * TG_ROWS : 0);
+  }
   static constexpr size_t bytes(int fmax) { return 4 * (size_t)words(fmax); }
 };
 
@@ -277,16 +278,20 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   LT* s_tab = reinterpret_cast<LT*>(s_mem);
   u32* s_bits = s_mem + TL::table(fmax);  // 64 per vector: bit i - 1 for a run that starts at its entry i > 0
   unsigned long long* s_neq = reinterpret_cast<unsigned long long*>(s_bits + 2 * TL::VEC);
-  u32* s_vrun = s_bits + 4 * TL::VEC;
-  u32* s_vpre = s_vrun + TL::VEC;
-  u32* s_first = s_vpre + TL::VEC;
-  u32* s_lab = s_first + TL::ARR;
-  u32* s_to = s_lab + TL::ARR;
-  unsigned long long* s_ilo = reinterpret_cast<unsigned long long*>(s_to + TL::ARR);  // WT: own-label weight sum
+  u32* s_to = s_bits + 4 * TL::VEC;
+  LT* s_lab = reinterpret_cast<LT*>(s_to + TL::ARR);
+  uint16_t* s_first = reinterpret_cast<uint16_t*>(s_lab + TL::ARR);
+  uint16_t* s_vrun = s_first + TL::ARR;
+  uint16_t* s_vpre = s_vrun + TL::VEC;
+  unsigned long long* s_ilo = reinterpret_cast<unsigned long long*>(s_vpre + TL::VEC);  // WT: own-label weight sum
   unsigned long long* s_ihi = s_ilo + TG_ROWS;
   __shared__ u32 s_last[TG_WAVES], s_heads[TG_WAVES], s_staged[TG_WAVES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto of = [](u32 x, int i) { return (u32)__builtin_amdgcn_readlane((int)x, i); };
+  auto below_in = [](u32 lo, u32 hi, u32 base) {  // base + set bits below the lane
+    return (u32)__builtin_amdgcn_mbcnt_hi((int)hi, __builtin_amdgcn_mbcnt_lo((int)lo, (int)base));
+  };
   // each XCD (workgroup b runs on XCD b % 8) takes a contiguous eighth of the tiles
   const int per = (T + 7) / 8, t = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
   if ((int)(blockIdx.x / 8u) >= per || t >= T) return;
@@ -300,23 +305,25 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   const u32 ng = (ne + TG_GROUP - 1u) / TG_GROUP, steps = (ng + TG_WAVES - 1u) / TG_WAVES, gw = (u32)wv * steps;
   // every load that depends on no other first
   const int my_row = tile.r0 + min(tid, rows - 1);
-  const uint4* ew = reinterpret_cast<const uint4*>(eidx) + (size_t)tile.g0 * (TG_GROUP / 8) + lane;
+  const uint4* ew = reinterpret_cast<const uint4*>(eidx) + (size_t)tile.g0 * (TG_GROUP / 8);
+  const u32* fp = fadr + tile.f0;
   constexpr int FU = 8;
   u32 fa[FU];
 #pragma unroll
-  for (int k = 0; k < FU; ++k) fa[k] = (u32)(tid + k * TG_THREADS) < tile.nf ? fadr[tile.f0 + (u32)(tid + k * TG_THREADS)] : 0u;
+  for (int k = 0; k < FU; ++k) fa[k] = (u32)(tid + k * TG_THREADS) < tile.nf ? fp[(u32)(tid + k * TG_THREADS)] : 0u;
   uint4 q[TG_STEPS];
 #pragma unroll
   for (int i = 0; i < TG_STEPS; ++i)
-    q[i] = (u32)i < steps && gw + i < ng ? ew[(gw + i) * (u32)(TG_GROUP / 8)] : make_uint4(0u, 0u, 0u, 0u);
-  const u32 own = (u32)labx[my_row];
-  const u32 ra = (u32)rp[my_row], rb = (u32)rp[my_row + 1];
-  const u32 lu = by_rows ? loc[my_row] : 0u;
+    q[i] = (u32)i < steps && gw + i < ng ? ew[(gw + i) * (u32)(TG_GROUP / 8) + lane] : make_uint4(0u, 0u, 0u, 0u);
+  const u32 own = (u32)labx[(u32)my_row];
+  const u32 ra = (u32)rp[(u32)my_row], rb = (u32)rp[(u32)my_row + 1u];
+  const u32 lu = by_rows ? loc[(u32)my_row] : 0u;
   typedef u32 v4u __attribute__((ext_vector_type(4)));
   {
     const v4u* src = reinterpret_cast<const v4u*>(labx + w0);  // w0 is a multiple of 512; the array is padded past n
     v4u* dst = reinterpret_cast<v4u*>(s_mem);
-    for (int i = tid; i < (w1 - w0 + TL::PER - 1) / TL::PER; i += TG_THREADS) dst[i] = src[i];
+    const u32 words = (u32)(w1 - w0 + TL::PER - 1) / TL::PER;
+    for (u32 i = tid; i < words; i += TG_THREADS) dst[i] = src[i];
   }
   if (tid < 2 * TL::VEC) s_bits[tid] = 0;
   // the row's entries in the tile: [a, b)
@@ -325,44 +332,48 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   const u64 hasm = __ballot(has);
   // the label of the wave's last row with entries
   if (hasm ? lane == 63 - __clzll((long long)hasm) : lane == 0) s_last[wv] = hasm ? own : SENT;
+  {
+    LT x[FU];
 #pragma unroll
-  for (int k = 0; k < FU; ++k)
-    if ((u32)(tid + k * TG_THREADS) < tile.nf) s_tab[TG_WIN + tid + k * TG_THREADS] = fl[fa[k]];
-  for (u32 j = tid + FU * TG_THREADS; j < tile.nf; j += TG_THREADS) s_tab[TG_WIN + j] = fl[fadr[tile.f0 + j]];
+    for (int k = 0; k < FU; ++k)
+      if ((u32)(tid + k * TG_THREADS) < tile.nf) x[k] = fl[fa[k]];
+#pragma unroll
+    for (int k = 0; k < FU; ++k)
+      if ((u32)(tid + k * TG_THREADS) < tile.nf) s_tab[TG_WIN + tid + k * TG_THREADS] = x[k];
+    for (u32 j = tid + FU * TG_THREADS; j < tile.nf; j += TG_THREADS) s_tab[TG_WIN + j] = fl[fp[j]];
+  }
   // STAGE_ROWS: the place of the row's entry e, less e
   u32 row_to = NOWHERE;  // only with a label error, which voids the result
   if (by_rows && own != NOLAB && lu != SENT)
     row_to = start[own] + PM[(size_t)(my_row / chunk) * L + own] + lu + (tile.e0 - ra);
   __syncthreads();
   // runs
-  const u64 below = (1ull << lane) - 1ull;
   u32 prev = SENT;
   {
-    const u64 pm = hasm & below;
+    const u64 pm = hasm & ((1ull << lane) - 1ull);
     const u32 in_wave = (u32)__shfl((int)own, pm ? 63 - __clzll((long long)pm) : 0, 64);
-    for (int i = 0; i < wv; ++i) prev = s_last[i] != SENT ? s_last[i] : prev;
+    const u32 last = s_last[lane & (TG_WAVES - 1)];
+    const u64 lm = __ballot(last != SENT) & ((1ull << wv) - 1ull);
+    if (lm) prev = of(last, 63 - __clzll((long long)lm));
     if (pm) prev = in_wave;
   }
   const bool head = has && (by_rows || own != prev || prev == SENT);
   const u64 headm = __ballot(head);
   if (lane == 0) s_heads[wv] = (u32)__popcll(headm);
   __syncthreads();
-  u32 nruns = 0, run = (u32)__popcll(headm & (below | (1ull << lane))) - 1u;
-#pragma unroll
-  for (int i = 0; i < TG_WAVES; ++i) {
-    const u32 k = s_heads[i];
-    if (i < wv) run += k;
-    nruns += k;
-  }
+  const u32 hincl = wave_incl_scan(lane < TG_WAVES ? s_heads[lane] : 0u);
+  const u32 nruns = of(hincl, TG_WAVES - 1);
+  // the row's run: heads up to and with the row, less 1
+  const u32 run = below_in((u32)headm, (u32)(headm >> 32), (wv ? of(hincl, wv - 1) : 0u) + (head ? 1u : 0u)) - 1u;
   if (head) {
-    s_first[run] = a;
-    s_lab[run] = own;
+    s_first[run] = (uint16_t)a;
+    s_lab[run] = (LT)own;
     if (by_rows) s_to[run] = row_to;
     if (a & 63u) atomicOr(&s_bits[2u * (a >> 6) + (((a & 63u) - 1u) >> 5)], 1u << (((a & 63u) - 1u) & 31u));
   }
-  if (tid == 0) s_first[nruns] = ne;
+  if (tid == 0) s_first[nruns] = (uint16_t)ne;
   if (has)
-    for (u32 v = (a + 63u) / 64u; v * 64u < b; ++v) s_vrun[v] = run;
+    for (u32 v = (a + 63u) / 64u; v * 64u < b; ++v) s_vrun[v] = (uint16_t)run;
   if (WT && tid < rows) {
     s_ilo[tid] = 0ull;
     s_ihi[tid] = 0ull;
@@ -374,10 +385,6 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   const u32 vl = v0 + (have ? (u32)lane : 0u);
   const u32 vbl = have ? s_bits[2u * vl] : 0u, vbh = have ? s_bits[2u * vl + 1u] : 0u, vr = have ? s_vrun[vl] : 0u;
   const u64 multi = __ballot((vbl | vbh) != 0u);
-  auto of = [](u32 x, int i) { return (u32)__builtin_amdgcn_readlane((int)x, i); };
-  auto below_in = [](u32 lo, u32 hi, u32 base) {  // base + set bits below the lane
-    return (u32)__builtin_amdgcn_mbcnt_hi((int)hi, __builtin_amdgcn_mbcnt_lo((int)lo, (int)base));
-  };
   auto half = [](const uint4& v, int k) {
     const u32 x = k < 2 ? v.x : k < 4 ? v.y : k < 6 ? v.z : v.w;
     return (k & 1) ? x >> 16 : x & 0xFFFFu;
@@ -404,8 +411,11 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     }
     return;
   }
+  // what the claims need of their communities
+  const u32 c = (u32)tid < nruns ? (u32)s_lab[tid] : NOLAB;
+  const u32 dc = c != NOLAB ? D[c] : 0u, sc = c != NOLAB ? start[c] : 0u;
   // first walk: which entries are staged
-  const u32 vc = have ? s_lab[vr] : 0u;
+  const u32 vc = have ? (u32)s_lab[vr] : 0u;
   u32 nlo = 0, nhi = 0;  // lane l: the staged entries of vector l
   u32 wrun = SENT;       // WT: the run whose own-label weights wacc sums
   WeightSum wacc;
@@ -430,7 +440,7 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     if ((multi >> (8 * i)) & 0xFFull) {
       u32 c[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) c[k] = s_lab[below_in(of(vbl, 8 * i + k), of(vbh, 8 * i + k), of(vr, 8 * i + k))];
+      for (int k = 0; k < 8; ++k) c[k] = (u32)s_lab[below_in(of(vbl, 8 * i + k), of(vbh, 8 * i + k), of(vr, 8 * i + k))];
 #pragma unroll
       for (int k = 0; k < 8; ++k) m[k] = __ballot(x[k] != c[k]);
     } else {
@@ -494,7 +504,7 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     vp = incl - cnt;
     if (have) {
       s_neq[vl] = ((u64)nhi << 32) | nlo;
-      s_vpre[vl] = vp;
+      s_vpre[vl] = (uint16_t)vp;
     }
     if (lane == 63) s_staged[wv] = incl;
   }
@@ -512,15 +522,15 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
       return (wave ? base : 0u) + s_vpre[v] +
              (e >= ne ? (u32)__popcll(s_neq[v]) : (u32)__popcll(s_neq[v] & ((1ull << (e & 63u)) - 1ull)));
     };
-    const u32 f = mine ? s_first[tid] : 0u, z = mine ? s_first[tid + 1] : 0u;
+    const u32 f = mine ? (u32)s_first[tid] : 0u, z = mine ? (u32)s_first[tid + 1] : 0u;
     const u32 p = before(f), inter = before(z) - p;
     if (mine) {
-      const u32 c = s_lab[tid], tot = z - f;
+      const u32 tot = z - f;
       u32 to = NOWHERE;
       if (c != NOLAB) {
         const unsigned long long old = atomicAdd(&cur64[c], ((unsigned long long)(tot - inter) << 32) | inter);
         const u32 lo = (u32)old;
-        if (lo + inter <= D[c]) to = start[c] + lo - p;
+        if (lo + inter <= dc) to = sc + lo - p;
         else atomicOr(&ctl->flags, F_SEGMENT);  // never expected: the tile's counts disagree with the degrees
         if (WT) {
           const unsigned long long ilo = s_ilo[tid], ihi = s_ihi[tid];
