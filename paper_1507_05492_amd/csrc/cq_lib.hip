@@ -565,17 +565,26 @@ cq_status map_flags(cq_context* ctx, u32 flags) {
 // and room for 8 bytes per node, the move takes the two streaming passes of
 // k_perm_split / k_perm_place; otherwise the bucket plan's scatter and per-bucket pass.
 template <class LT>
-void stage_labels(const cq_graph* g, const int32_t* labels, int32_t L, LT* tmp, LT* labx, Ctl* ctl, void* scratch,
+void stage_labels(const cq_graph* g, int num_cus, const int32_t* labels, int32_t L, LT* tmp, LT* labx, Ctl* ctl, void* scratch,
                   size_t scratch_bytes, hipStream_t s) {
   const int n = g->n;
-  const int nsb = (int)(((int64_t)n + SB_MASK) >> SB_SHIFT);
-  const size_t stage_bytes = 8 * ((size_t)nsb << SB_SHIFT);
+  // a super-bucket per CU at least: with fewer, its one workgroup takes longer than the parts of
+  // a large super-bucket side by side
+  const int nsl = (int)(((int64_t)n + (1 << SBL_SHIFT) - 1) >> SBL_SHIFT);
+  const bool lds = sizeof(LT) == 2 && nsl >= num_cus && nsl <= SB_MAX;
+  const int shift = lds ? SBL_SHIFT : SB_SHIFT;
+  const int nsb = (int)(((int64_t)n + (1 << shift) - 1) >> shift);
+  const size_t stage_bytes = 8 * ((size_t)nsb << shift);
   if (g->sid && nsb <= SB_MAX && stage_bytes + 4 * (size_t)SB_MAX <= scratch_bytes) {
     auto* stage = static_cast<unsigned long long*>(scratch);
     u32* gcur = reinterpret_cast<u32*>(static_cast<char*>(scratch) + stage_bytes);
     fill(gcur, (size_t)nsb, 0, s);
-    k_perm_split<LT><<<(unsigned)(((int64_t)n + PS_NODES - 1) / PS_NODES), 1024, 0, s>>>(n, labels, g->sid, L, nsb, gcur,
-                                                                                        stage, ctl);
+    k_perm_split<LT><<<(unsigned)(((int64_t)n + PS_NODES - 1) / PS_NODES), 1024, 0, s>>>(n, labels, g->sid, L, nsb, shift,
+                                                                                        gcur, stage, ctl);
+    if (lds) {
+      k_perm_place_lds<<<(unsigned)nsb, 1024, (size_t)2 << SBL_SHIFT, s>>>(n, stage, reinterpret_cast<uint16_t*>(labx));
+      return;
+    }
     const unsigned groups = (unsigned)((nsb + 7) / 8);
     k_perm_place<LT><<<8u * PP_PARTS * groups, 1024, 0, s>>>(n, nsb, stage, labx);
     return;
@@ -676,7 +685,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
       // move the labels to the stored order first (streaming), then count in that order;
       // without a plan the first range's launch reads them and writes labx
       if (g->pos1)
-        stage_labels<LT>(g, labels, L, reinterpret_cast<LT*>(loc), labx, ctl, CB, sizeof(LT) * (size_t)nnz, s);
+        stage_labels<LT>(g, ctx->num_cus, labels, L, reinterpret_cast<LT*>(loc), labx, ctl, CB, sizeof(LT) * (size_t)nnz, s);
       for (int64_t lb = 0; lb < L; lb += PRIV_MAX) {
         const int lr = (int)std::min<int64_t>(PRIV_MAX, L - lb);
         const size_t shm = 2 * (size_t)lr * 4;
@@ -698,7 +707,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
     {
       StageMark mk(ctx, ST_NODE, timed);
       if (g->pos1) {
-        stage_labels<LT>(g, labels, L, reinterpret_cast<LT*>(loc), labx, ctl, CB, sizeof(LT) * (size_t)nnz, s);
+        stage_labels<LT>(g, ctx->num_cus, labels, L, reinterpret_cast<LT*>(loc), labx, ctl, CB, sizeof(LT) * (size_t)nnz, s);
         k_node_global<true, LT, true><<<grid_for(n, 256, 8192), 256, 0, s>>>((int)n, labels, g->perm, g->rp, L, SZ, loc, labx,
                                                                             ctl);
       } else {
@@ -2050,6 +2059,7 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_node_priv<true, uint32_t, true>), 2 * PRIV_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_node_priv<false, uint32_t>), PRIV_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_hist_priv), PRIV_MAX * 4);
+  set_big_lds(reinterpret_cast<const void*>(k_perm_place_lds), 2 << SBL_SHIFT);
   set_big_lds(reinterpret_cast<const void*>(k_perm_plan), 8 * (size_t)PERM_MAX_BUCKETS);
   set_big_lds(reinterpret_cast<const void*>(k_perm_apply_count), ((size_t)1 << PERM_SHIFT) * 2 + 8 * (size_t)APPLY_COUNT_MAX_L);
   set_big_lds(reinterpret_cast<const void*>(k_groups<ScoreVis, uint16_t, GBLOCK_WIDE>), gl);
