@@ -840,58 +840,75 @@ __device__ __forceinline__ void node_priv_body(int n, const int32_t* __restrict_
   const long long u1 = min((long long)n, u0 + chunk);
   const int lane = threadIdx.x & 63;
   u32 bad = 0;
-  for (long long ub = u0; ub < u1; ub += blockDim.x) {  // uniform trip count per wave
-    const long long u = ub + threadIdx.x;
-    const bool in = u < u1;
-    int c;
-    if (STAGED) {
-      const u32 x = in ? (u32)labx[u * lst] : 0u;
-      c = x == (u32)LabelT<LT>::SENTINEL ? -1 : (int)x;
-    } else {
-      c = in ? labels[perm ? perm[u] : u] : 0;
-    }
-    const bool valid = in && (u32)c < (u32)L;
-    if (first && in && !valid) {
-      bad = 1;
-      loc[u] = SENT;
-      if (labx && !STAGED) labx[u * lst] = LabelT<LT>::SENTINEL;
-    }
-    const int cl = c - lbase;
-    const bool here = valid && (u32)cl < (u32)LR;
-    const u32 w = here ? (WEIGHTED ? (u32)(rp[u + 1] - rp[u]) : 1u) : 0u;
-    // Lanes with equal labels (common when the graph is stored in a locality order)
-    // add to the LDS histogram through one leader lane; each lane's offset is the
-    // leader's old value plus the weights of the group's lower lanes.
-    bool pending = here;
-    u32 old = 0;
-    for (int round = 0; round < 4; ++round) {
-      const u64 act = __ballot(pending);
-      if (act == 0) break;
-      const int leader = __ffsll((long long)act) - 1;
-      const int lc = __shfl(cl, leader, 64);
-      const bool mine = pending && cl == lc;
-      const u64 grp = __ballot(mine);
-      if (__popcll(grp) < 4) break;  // mixed labels: plain atomics below
-      const u32 pw = mine ? w : 0u;
-      const u32 incl = wave_incl_scan(pw);
-      const u32 tot = __shfl(incl, 63, 64);
-      u32 b = 0;
-      if (lane == leader) {
-        if (WEIGHTED) atomicAdd(&hn[lc], (u32)__popcll(grp));
-        b = atomicAdd(&hd[lc], tot);
+  // A wide label space leaves room for one workgroup of LDS histograms per CU, so the loads of
+  // NPV nodes per thread are issued before the first is counted (40M nodes, 16,384 labels a
+  // launch: 229 -> 179 us).  Labels read through perm or for a batch gain nothing from it.
+  constexpr int NPV = STAGED ? 4 : 1;
+  for (long long ua = u0; ua < u1; ua += (long long)NPV * blockDim.x) {
+    int cs[NPV];
+    u32 ws[NPV];
+#pragma unroll
+    for (int k = 0; k < NPV; ++k) {
+      const long long u = ua + (long long)k * blockDim.x + threadIdx.x;
+      const bool in = u < u1;
+      if (STAGED) {
+        const u32 x = in ? (u32)labx[u * lst] : 0u;
+        cs[k] = x == (u32)LabelT<LT>::SENTINEL ? -1 : (int)x;
+      } else {
+        cs[k] = in ? labels[perm ? perm[u] : u] : 0;
       }
-      b = __shfl(b, leader, 64);
-      if (mine) {
-        old = b + incl - pw;
-        pending = false;
+      ws[k] = WEIGHTED ? (in ? (u32)(rp[u + 1] - rp[u]) : 0u) : 1u;
+    }
+#pragma unroll
+    for (int k = 0; k < NPV; ++k) {
+      const long long ub = ua + (long long)k * blockDim.x;
+      if (ub >= u1) break;  // uniform
+      const long long u = ub + threadIdx.x;
+      const bool in = u < u1;
+      const int c = cs[k];
+      const bool valid = in && (u32)c < (u32)L;
+      if (first && in && !valid) {
+        bad = 1;
+        loc[u] = SENT;
+        if (labx && !STAGED) labx[u * lst] = LabelT<LT>::SENTINEL;
       }
+      const int cl = c - lbase;
+      const bool here = valid && (u32)cl < (u32)LR;
+      const u32 w = here ? ws[k] : 0u;
+      // Lanes with equal labels (common when the graph is stored in a locality order)
+      // add to the LDS histogram through one leader lane; each lane's offset is the
+      // leader's old value plus the weights of the group's lower lanes.
+      bool pending = here;
+      u32 old = 0;
+      for (int round = 0; round < 4; ++round) {
+        const u64 act = __ballot(pending);
+        if (act == 0) break;
+        const int leader = __ffsll((long long)act) - 1;
+        const int lc = __shfl(cl, leader, 64);
+        const bool mine = pending && cl == lc;
+        const u64 grp = __ballot(mine);
+        if (__popcll(grp) < 4) break;  // mixed labels: plain atomics below
+        const u32 pw = mine ? w : 0u;
+        const u32 incl = wave_incl_scan(pw);
+        const u32 tot = __shfl(incl, 63, 64);
+        u32 b = 0;
+        if (lane == leader) {
+          if (WEIGHTED) atomicAdd(&hn[lc], (u32)__popcll(grp));
+          b = atomicAdd(&hd[lc], tot);
+        }
+        b = __shfl(b, leader, 64);
+        if (mine) {
+          old = b + incl - pw;
+          pending = false;
+        }
+      }
+      if (pending) {
+        if (WEIGHTED) atomicAdd(&hn[cl], 1u);
+        old = atomicAdd(&hd[cl], w);
+      }
+      if (here) loc[u] = old;
+      if (first && valid && labx && !STAGED) labx[u * lst] = (LT)c;
     }
-    if (pending) {
-      if (WEIGHTED) atomicAdd(&hn[cl], 1u);
-      old = atomicAdd(&hd[cl], w);
-    }
-    if (here) loc[u] = old;
-    if (first && valid && labx && !STAGED) labx[u * lst] = (LT)c;
   }
   if (bad) s_bad = 1;
   __syncthreads();
