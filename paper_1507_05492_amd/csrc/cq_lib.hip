@@ -68,7 +68,7 @@ struct cq_graph {
   int ntiles = 0, fmax = 0;        // tiles; most far entries of one
   int64_t groups = 0;              // groups of eidx
   int64_t far = 0;                 // far entries
-  int slices = 0;
+  int slices = 0, sshift = TS_SHIFT;  // slices, of 2^sshift ids
   bool blocked = false;            // runs may be staged compactly through the tiles (n <= 2^24); else by rows only
   u32* deg_in = nullptr;           // label permutation plan (caller order -> stored order): degrees,
   u32* pos1 = nullptr;             // bucket slots and their stored ids; null when not built
@@ -731,7 +731,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
       if (g->far > 0) {
         // about four workgroups per CU, of at least 4,096 entries
         const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((4 * ctx->num_cus + S - 1) / S, g->far / ((int64_t)S * 4096)));
-        k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << TS_SHIFT, s>>>((int)n, parts, g->fslice,
+        k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << g->sshift, s>>>((int)n, g->sshift, parts, g->fslice,
                                                                                           g->fcol, labx, fl);
       }
       const unsigned grid = 8u * (unsigned)((T + 7) / 8);
@@ -1304,15 +1304,16 @@ constexpr int LP_SALTED_SWEEPS = 20;
 constexpr int64_t BLOCK_MAX_N = 16 << 20;
 constexpr int64_t BLOCK_MIN_N = 1 << 20;
 // Larger graphs are tiled as well (unless CQ_GRAPH_NO_BLOCKS), but always staged by rows.
-constexpr int64_t TILE_MAX_N = (int64_t)TG_MAX_SLICES << TS_SHIFT;
-static_assert(BLOCK_MAX_N <= TILE_MAX_N, "slices");
+constexpr int64_t TILE_MAX_N = (int64_t)TG_MAX_SLICES << TS_SHIFT_LARGE;
+static_assert(BLOCK_MAX_N <= (int64_t)TG_MAX_SLICES << TS_SHIFT, "slices");
 
 // Builds the tiles of the renumbered graph (g->owned_rp / owned_col), of at most `ent` entries;
 // *most = the most far entries of one.  When that is over `limit`, no tiles are left.
 cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* most) {
   const int n = g->n;
   hipStream_t s = ctx->stream;
-  const int blocks = (n + TG_ROWS - 1) / TG_ROWS, S = (n + TS_NODES - 1) >> TS_SHIFT;
+  const int blocks = (n + TG_ROWS - 1) / TG_ROWS, shift = n > BLOCK_MAX_N ? TS_SHIFT_LARGE : TS_SHIFT;
+  const int S = (int)(((int64_t)n + (1 << shift) - 1) >> shift);
   u32 *bcnt = nullptr, *bfirst = nullptr, *fcnt = nullptr, *fstart = nullptr, *tmp = nullptr, *cnt = nullptr;
   u32 *group0 = nullptr, *nfar = nullptr, *far0 = nullptr, *fmax = nullptr;
   hipError_t e = hipSuccess;
@@ -1326,6 +1327,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
   };
   auto scan_tmp = [](long long m) { return 4 * ((size_t)((m + SCAN_TILE - 1) / SCAN_TILE) + 1); };
   g->slices = S;
+  g->sshift = shift;
   *most = 0;
   u32 T = 0, far = 0, groups = 0;
   alloc((void**)&bcnt, 4 * (size_t)blocks);
@@ -1353,7 +1355,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
     k_tile_list<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, ent, g->owned_rp, bfirst, g->tiles, cnt);
     scan_u32(cnt, group0, T, tmp, s);
     fill(fmax, 1, 0, s);
-    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, g->tiles, g->owned_col, fcnt, nfar, fmax);
+    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, shift, g->tiles, g->owned_col, fcnt, nfar, fmax);
     scan_u32(fcnt, fstart, cells, tmp, s);
     scan_u32(nfar, far0, T, tmp, s);
     k_tile_slices<<<(S + 256) / 256, 256, 0, s>>>((int)T, S, fstart, g->fslice);
@@ -1368,7 +1370,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
     alloc((void**)&g->fadr, 4 * (size_t)far);
     if (e == hipSuccess) {
       fill(reinterpret_cast<u32*>(g->eidx), (size_t)groups * TG_GROUP / 2, 0, s);  // places past a tile's entries are read too
-      k_tile_place<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, g->tiles, group0, far0, g->owned_col, fcnt, fstart, g->eidx, g->fcol,
+      k_tile_place<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, shift, g->tiles, group0, far0, g->owned_col, fcnt, fstart, g->eidx, g->fcol,
                                             g->fadr);
       e = hipGetLastError();
       if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -2072,7 +2074,7 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 512, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 256, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
-  set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint16_t>), 2 << TS_SHIFT);
+  set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint16_t>), 2 << TS_SHIFT_LARGE);
   set_big_lds(reinterpret_cast<const void*>(k_far_labels<uint32_t>), 4 << TS_SHIFT);
   set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_ENT));
   set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_ENT_W));

@@ -9,7 +9,7 @@
 // window of ids (TG_HALO before and after its rows), else far.  Per graph:
 //   eidx  one 16-bit word per entry, in row order: the place of the neighbour's label in the
 //         tile's table, which holds the window's labels, then the tile's far labels;
-//   fcol  the far entries sorted by slice (TS_NODES consecutive ids) of the neighbour, then by
+//   fcol  the far entries sorted by slice (2^shift consecutive ids) of the neighbour, then by
 //         tile: the 16-bit place of the neighbour in its slice;
 //   fadr  for every tile, the numbers of its far entries in that order.
 //
@@ -33,9 +33,13 @@ constexpr int TG_ENT = TG_WAVES * TG_GROUP * TG_STEPS;  // entries per tile at m
 // A weighted graph with a tile of more far entries than this is cut into tiles of at most so many
 // entries instead: 32-bit labels and the runs' weight sums then still fit a CU's LDS.
 constexpr int TG_ENT_W = 16384;
+// Slices of 2^15 ids: 64 KB of 16-bit labels (two workgroups a CU), 128 KB of 32-bit ones.  Graphs
+// whose tiles only ever serve 16-bit labels (more than 2^24 nodes) have slices of 2^16: a tile's
+// far labels then are half as many, twice as long runs.  40M nodes: edge pass 1045 -> 934 us and
+// far labels 141 -> 143; 10M nodes: 244 -> 238, but 52 -> 64.
 constexpr int TS_SHIFT = 15;
-constexpr int TS_NODES = 1 << TS_SHIFT;  // ids per slice: 64 KB of 16-bit labels, 128 KB of 32-bit ones
-constexpr int TG_MAX_SLICES = 4096;  // n up to 2^27 (32 KB of counters at load time)
+constexpr int TS_SHIFT_LARGE = 16;
+constexpr int TG_MAX_SLICES = 2048;  // n up to 2^27 (16 KB of counters at load time)
 static_assert(TG_ROWS == TG_THREADS, "one row per thread");
 static_assert(2 * (TG_WIN + TG_ENT) <= 65536, "16-bit table places, in units of 2 bytes");
 
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(256) void k_tile_list(int n, int blocks, u32 ent, c
 
 // One workgroup per tile: far entries per slice (fcnt[slice * T + tile]), in all, and the
 // most of any tile.
-__global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, const Tile* __restrict__ tiles,
+__global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, int shift, const Tile* __restrict__ tiles,
                                                            const int32_t* __restrict__ col, u32* __restrict__ fcnt,
                                                            u32* __restrict__ nfar, u32* __restrict__ fmax) {
   __shared__ u32 s_far[TG_MAX_SLICES];
@@ -116,7 +120,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, 
     const int v = col[t.e0 + i];
     if (v >= w0 && v < w1) continue;
     ++mine;
-    atomicAdd(&s_far[v >> TS_SHIFT], 1u);
+    atomicAdd(&s_far[v >> shift], 1u);
   }
   if (mine) atomicAdd(&s_all, mine);
   __syncthreads();
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(256) void k_tile_slices(int T, int S, const u32* __
 }
 
 // One workgroup per tile: writes its entries' table places and its far entries.
-__global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, Tile* __restrict__ tiles,
+__global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, int shift, Tile* __restrict__ tiles,
                                                            const u32* __restrict__ group0, const u32* __restrict__ far0,
                                                            const int32_t* __restrict__ col, const u32* __restrict__ fcnt,
                                                            const u32* __restrict__ fstart, uint16_t* __restrict__ eidx,
@@ -164,9 +168,9 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, 
     const int v = col[t.e0 + i];
     u32 at = (u32)(v - w0);
     if (v < w0 || v >= w1) {
-      const int s = v >> TS_SHIFT;
+      const int s = v >> shift;
       const u32 k = atomicAdd(&s_cnt[s], 1u), j = s_pre[s] + k, g = fstart[(size_t)s * T + blockIdx.x] + k;
-      fcol[g] = (uint16_t)(v & (TS_NODES - 1));
+      fcol[g] = (uint16_t)(v & ((1 << shift) - 1));
       fadr[f0 + j] = g;
       at = (u32)TG_WIN + j;
     }
@@ -185,7 +189,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, 
 // thread and step.
 constexpr int FL_THREADS = 1024;
 template <class LT>
-__global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int parts, const u32* __restrict__ first,
+__global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int shift, int parts, const u32* __restrict__ first,
                                                            const uint16_t* __restrict__ fcol, const LT* __restrict__ labx,
                                                            LT* __restrict__ fl) {
   extern __shared__ __align__(16) u32 s_slice[];
@@ -201,8 +205,8 @@ __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int parts, con
   if (g0 == g1 && !ends) return;
   {
     constexpr int PER = 16 / (int)sizeof(LT);
-    const long long id0 = (long long)slice << TS_SHIFT;
-    const int cnt = (int)min((long long)TS_NODES, (long long)n - id0);
+    const long long id0 = (long long)slice << shift;
+    const int cnt = (int)min(1ll << shift, (long long)n - id0);
     typedef u32 v4u __attribute__((ext_vector_type(4)));
     const v4u* src = reinterpret_cast<const v4u*>(labx + id0);  // 16-byte aligned; padded past n (workspace array)
     v4u* dst = reinterpret_cast<v4u*>(s_slice);
