@@ -28,7 +28,7 @@ METRIC = "GEdges/s scoring full metric set at 10M/100M nodes; served p50/p99 lat
 HBM_PEAK_GBS = 8000.0
 WEIGHTED_MAX_LABELS = 32768  # label ids a weighted score can take (its direct LDS table)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_l10m.json")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1507_05492_amd", "csrc", f) for f in ("cq_kernels.hpp", "cq_device.hpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1507_05492_amd", "csrc", f) for f in ("cq_kernels.hpp", "cq_tiles.hpp", "cq_device.hpp")]
 
 
 def kernel_source_hash() -> str:
@@ -44,14 +44,14 @@ def algorithmic_bytes(n: int, nnz: int) -> int:
     return 4 * nnz + 8 * n
 
 
-def kernel_names(L: int, blocked: bool) -> dict:
+def kernel_names(L: int, blocked: bool, tiled: bool | None = None) -> dict:
     """Profiler names of the unweighted kernels of each stage (namespace dropped)."""
     lt = "unsigned short" if L <= 65535 else "unsigned int"
     priv = "true" if L <= 131072 else "false"  # LDS-private node histograms (in label ranges)
-    return {"edge_gather": f"k_gather_blocked<{lt}, false>" if blocked else f"k_gather<{priv}, {lt}, false>",
+    return {"edge_gather": f"k_tile_gather<{lt}, false>" if (blocked if tiled is None else tiled) else f"k_gather<{priv}, {lt}, false>",
             "group_count": f"k_groups<ScoreVis, {lt}>",
             "node_pass": f"k_node_scatter<{lt}>" if blocked else f"k_node_priv<true, {lt}, true>",
-            "final_reduce": "k_score_final1", "column_scan": "k_colscan", "scan_order": "k_scan_order"}
+            "final_reduce": "k_score_final", "column_scan": "k_colscan", "scan_order": "k_scan_order"}
 
 
 def traffic_for(kernel: str):
@@ -188,7 +188,7 @@ def main() -> int:
     log(f"{ms_async:.3f} ms/step back to back without waiting for each result")
     log(f"{ms_per_step:.3f} ms/step, {gedges:.1f} GEdges/s; {dom} {dom_ms:.3f} ms; stages (all timed) " +
         ", ".join(f"{k}={v:.3f}ms" for k, v in stage_avg.items()))
-    blocked = graph.stats["reordered"] == cq.CQ_GRAPH_REORDER  # renumbered and stored in column blocks
+    blocked = graph.stats["reordered"] == cq.CQ_GRAPH_REORDER  # renumbered and stored in tiles
     kernel_of = kernel_names(L, blocked)
     abytes = algorithmic_bytes(n, nnz)
     achieved = abytes / (dom_ms * 1e-3) / 1e9
@@ -390,10 +390,10 @@ def big_graph_leg(args, ctx, cq, factory, log) -> dict:
     del cws, pert
     graph.close()
     out = {"workload": "lfr_s100m", "n": n, "nnz": nnz, "communities": L, "seed": args.seed,
-           "max_degree": g.stats["max_degree"], "graph_order": "locality (no column blocks above 2^24 nodes)",
+           "max_degree": g.stats["max_degree"], "graph_order": "locality (tiles, staged by rows above 2^24 nodes)",
            "graph_load_ms": round(load_ms, 1), "ms_per_step": round(ms, 4),
            "GEdges_per_s": round(nnz / (ms * 1e-3) / 1e9, 2),
-           "roofline": {"bound": "hbm", "kernel": kernel_names(L, blocked).get(dom, dom), "stage": dom,
+           "roofline": {"bound": "hbm", "kernel": kernel_names(L, blocked, True).get(dom, dom), "stage": dom,
                         "avg_ms": round(dom_ms, 4), "achieved": round(abytes / (dom_ms * 1e-3) / 1e9, 1),
                         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(abytes / (dom_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                         "algorithmic_bytes": abytes, "step_frac": round(abytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)},

@@ -93,16 +93,16 @@ cq_status cq_context_stage_times(const cq_context* ctx, double* total_ms, int64_
 /* Name of stage id s (static storage), or "" if s is not a stage id. */
 const char* cq_stage_name(int32_t s);
 
-/* ---- staging choice on column-blocked graphs -------------------------------- */
+/* ---- staging choice on tiled graphs --------------------------------------- */
 
-/* A column-blocked graph stores nodes so that communities found at load time are runs of
+/* A tiled graph stores nodes so that communities found at load time are runs of
  * consecutive ids, and stages neighbour labels with one claim per run of equal labels.  A
  * partition that does not follow that order (say, a perturbed or unrelated one) breaks
  * the runs, and the claims grow to one per node.  Each unweighted call on such a graph
  * (with up to 12,224 label ids) therefore counts, on the device, the label changes between
- * consecutive stored nodes; when they reach change_fraction * n the call stages through
- * the graph's row-major copy with per-node offsets instead (cq_score_result.staging says
- * which).  Default 1/16; <= 0 always takes the row-major copy, >= 1 never does.  The
+ * consecutive stored nodes; when they reach change_fraction * n the call stages every
+ * entry at per-node offsets instead (cq_score_result.staging says
+ * which).  Default 1/16; <= 0 always takes per-node offsets, >= 1 never does.  The
  * results are the same either way. */
 cq_status cq_context_set_row_staging(cq_context* ctx, double change_fraction);
 
@@ -111,8 +111,8 @@ cq_status cq_context_set_row_staging(cq_context* ctx, double change_fraction);
 /* Flags for cq_graph_load. */
 #define CQ_VALIDATE_GRAPH 1u  /* also check symmetry (rows must be sorted), no self-loops, no repeated entries */
 #define CQ_GRAPH_REORDER 2u   /* store the graph in a locality order (see cq_graph_load) */
-#define CQ_GRAPH_NO_BLOCKS 4u /* with CQ_GRAPH_REORDER: never build column blocks (see cq_graph_load) */
-#define CQ_GRAPH_BLOCKS 8u    /* with CQ_GRAPH_REORDER: build column blocks for any n <= 2^24 */
+#define CQ_GRAPH_NO_BLOCKS 4u /* with CQ_GRAPH_REORDER: never build tiles (see cq_graph_load) */
+#define CQ_GRAPH_BLOCKS 8u    /* with CQ_GRAPH_REORDER: build tiles for any n <= 2^24 */
 
 typedef struct {
   int64_t n;           /* |V| */
@@ -121,7 +121,7 @@ typedef struct {
   int64_t max_degree;
   uint32_t validated;  /* CQ_VALIDATE_GRAPH if the full check ran and passed */
   uint32_t reordered;  /* CQ_GRAPH_REORDER if the graph is stored in a locality order, plus
-                          CQ_GRAPH_NO_BLOCKS if it is stored without column blocks */
+                          CQ_GRAPH_NO_BLOCKS if it is never staged by runs of labels */
   int64_t owned_bytes; /* device memory the graph handle allocated (0 without CQ_GRAPH_REORDER) */
   uint32_t weighted;   /* 1 for a graph registered with cq_graph_load_weighted */
   uint32_t pad;
@@ -148,13 +148,15 @@ typedef struct {
  * so that the neighbours of a row mostly have nearby ids.  Labels passed to scoring
  * calls keep the caller's node numbering; every result is identical with and without
  * the flag.  The borrowed arrays are not read after the load returns.
- * When 2^20 <= n <= 2^24 the copy is also kept as 8 column blocks, one per XCD of the
- * device (the edge pass then reads each neighbour label from one XCD's L2; below 2^20
- * nodes one L2 holds all labels anyway), with a plan that moves labels from the
- * caller's order to the stored one: a further 4(8(n+1)+1) + 8 nnz + 16n + 4(n/32768 + 2)
- * bytes.  CQ_GRAPH_NO_BLOCKS never builds them, CQ_GRAPH_BLOCKS builds them for any
- * n <= 2^24 (both flags at once: CQ_E_INVALID_ARG).  owned_bytes in cq_graph_stats
- * reports the total.
+ * When 2^20 <= n <= 2^27 the copy is also kept as tiles (the edge pass then finds every
+ * neighbour label in LDS; below 2^20 nodes one L2 holds all labels anyway): 2 bytes per
+ * entry, rounded up to 512 entries a tile, 6 bytes per entry whose neighbour's id is far
+ * from the row's, and 32 bytes per tile.  A plan that moves labels from the caller's order
+ * to the stored one comes with them.  CQ_GRAPH_NO_BLOCKS never builds tiles, CQ_GRAPH_BLOCKS
+ * builds them for any n <= 2^24 (both flags at once: CQ_E_INVALID_ARG).  owned_bytes in
+ * cq_graph_stats reports the total.  A tiled graph's workspace has room for the far entries'
+ * labels (2 bytes each, 4 with more than 65,535 label ids); a call with a workspace that
+ * lacks just that room is scored through the row-major copy.
  */
 cq_status cq_graph_load(cq_context* ctx, int32_t n, int64_t nnz, const int32_t* d_row_ptr,
                         const int32_t* d_col_idx, uint32_t flags, cq_graph** out);
@@ -212,9 +214,9 @@ typedef struct {
 } cq_score_result;
 
 /* cq_score_result.staging.  The results do not depend on it. */
-#define CQ_STAGING_ROWS_ONLY 0u  /* the graph's row-major storage (no column blocks; batched calls) */
-#define CQ_STAGING_BLOCKS 1u     /* column blocks, compact staging with one claim per run of equal labels */
-#define CQ_STAGING_ROWS 2u       /* a column-blocked graph staged through its row-major copy: the partition
+#define CQ_STAGING_ROWS_ONLY 0u  /* the graph's row-major storage (no tiles; batched calls) */
+#define CQ_STAGING_BLOCKS 1u     /* tiles, compact staging with one claim per run of equal labels */
+#define CQ_STAGING_ROWS 2u       /* a tiled graph staged at per-node offsets: the partition
                                     does not follow the stored order (see cq_context_set_row_staging) */
 
 /* Optional per-label outputs: DEVICE arrays of length num_labels, each may be NULL.

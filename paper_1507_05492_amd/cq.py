@@ -473,7 +473,7 @@ class Graph:
 
     def __init__(self, ctx: Context, row_ptr, col_idx, validate: bool = False, reorder: bool = False,
                  blocks: bool | None = None, weights=None):
-        """reorder: store in a locality order; blocks (with reorder): None = column blocks
+        """reorder: store in a locality order; blocks (with reorder): None = tiles
         when the library's size rule says so, True = always (n <= 2^24), False = never.
         weights: float32 per stored entry (an edge-weighted graph), or None."""
         self.ctx = ctx

@@ -3,9 +3,9 @@
 // per-row quantities the final pass combines into VI, NMI, F, NVD, RI, ARI and JI
 // (Eqs. (1)-(7)).
 //
-// At most 65,535 labels on each side: the ground-truth labels are cut into bands: runs of consecutive label ids holding about
-// T nodes (and at most CB_ROWS labels); the band sizes and their places follow from the
-// label sizes alone.  A pass over chunks of nodes writes every node as one 32-bit word
+// At most 65,535 labels on each side: the ground-truth labels are cut into bands, runs of
+// consecutive label ids holding about T nodes (and at most CB_ROWS labels); the band sizes and
+// their places follow from the label sizes alone.  A pass over chunks of nodes writes every node as one 32-bit word
 // (label - first label of its band) << 16 | detected label into its band's range: a
 // chunk counts its nodes per band in LDS, claims a run of places in each band with one
 // atomic, lays its words out in LDS band by band, and writes them in that order, so the

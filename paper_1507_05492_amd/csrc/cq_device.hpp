@@ -26,11 +26,11 @@ struct Ctl {
   u32 flags;
   u32 K;          // non-empty communities (filled by the scan kernel)
   u32 kbig;       // groups whose segment holds at least GW_SPLIT entries (they come first in the order)
-  u32 dense_rows;  // node pass of column-blocked graphs: buckets that wrote histogram rows
+  u32 dense_rows;  // node pass of tiled graphs: buckets that wrote histogram rows
   unsigned long long export_count;
   u32 done, done2;  // workgroups that have finished a pass whose last workgroup goes on alone
-  u32 changes;    // column-blocked node pass: label changes between consecutive stored ids
-  u32 mode;       // column-blocked graphs: STAGE_BLOCKS or STAGE_ROWS, chosen from `changes`
+  u32 changes;    // tiled graphs' node pass: label changes between consecutive stored ids
+  u32 mode;       // tiled graphs: STAGE_BLOCKS or STAGE_ROWS, chosen from `changes`
   unsigned long long pad1[3];
 };
 
@@ -67,11 +67,10 @@ __device__ __forceinline__ unsigned long long* wq_sum(u32* wq, u32 q) {
   return reinterpret_cast<unsigned long long*>(wq + (WQ_QUEUES + q) * WQ_LINE);
 }
 
-// How a call on a column-blocked graph stages the neighbour labels (Ctl::mode; also
-// reported in the result): through the column blocks with run claims, or through the
-// graph's row-major copy with per-node offsets when the partition does not follow the
+// How a call on a tiled graph stages the neighbour labels (Ctl::mode; also reported in the
+// result): with run claims, or at per-node offsets when the partition does not follow the
 // stored order (short runs of equal labels make run claims as many as the nodes).
-constexpr u32 STAGE_ROWS_ONLY = 0;  // the graph has no column blocks
+constexpr u32 STAGE_ROWS_ONLY = 0;  // the graph has no tiles
 constexpr u32 STAGE_BLOCKS = 1;
 constexpr u32 STAGE_ROWS = 2;
 

@@ -1122,9 +1122,10 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_colscan(int W, int L,
 // Node pass of a tiled graph: adds the histogram rows of the dense buckets (rows[0,
 // ctl->dense_rows), written by k_perm_apply_count) to N and D, and clears the 64-bit run
 // cursors.  Integer sums, so the order of the row list does not matter.
-// It also chooses how the call stages neighbour labels (Ctl::mode): through the row-major
-// copy when the stored-order labels change at least `rows_from` times (a partition that
-// does not follow the stored order), else through the column blocks.
+// It also chooses how the call stages neighbour labels (Ctl::mode): at per-node offsets when
+// the stored-order labels change at least `rows_from` times (a partition that does not follow
+// the stored order), else by runs.  10M nodes, labels changing at every second node: 855 us a
+// call by rows, 1,466 us by runs (an atomic per run); the ground truth: 734 by rows, 572 by runs.
 __global__ __launch_bounds__(256) void k_colscan_rows(int L, const u32* __restrict__ HN, const u32* __restrict__ HD,
                                                       const u32* __restrict__ rows, Ctl* __restrict__ ctl,
                                                       u32* __restrict__ N, u32* __restrict__ D,

@@ -30,8 +30,8 @@ using namespace cq;
 
 struct cq_context {
   int device = 0;
-  // column-blocked graphs: a partition whose labels change between at least this fraction
-  // of consecutive stored nodes is staged through the graph's row-major copy
+  // tiled graphs: a partition whose labels change between at least this fraction of
+  // consecutive stored nodes is staged at per-node offsets
   double row_staging_from = 1.0 / 16.0;
   void* scratch = nullptr;  // device address of the library's scratch array on this device
   hipStream_t stream = nullptr;
@@ -73,10 +73,10 @@ struct cq_graph {
   u32* deg_in = nullptr;           // label permutation plan (caller order -> stored order): degrees,
   u32* pos1 = nullptr;             // bucket slots and their stored ids; null when not built
   uint16_t* tgt = nullptr;         // offset of the slot's stored id in its bucket
-  uint16_t* lrank = nullptr;       // column-blocked graphs: node numbers and slots of the plan's chunks
+  uint16_t* lrank = nullptr;       // tiled graphs: node numbers and slots of the plan's chunks
   u32* spos = nullptr;
   u32* pbstart = nullptr;          // first slot of every bucket (nb + 1)
-  u32* sid = nullptr;              // graphs without column blocks: stored id of every caller node (k_perm_split)
+  u32* sid = nullptr;              // graphs not staged by runs: stored id of every caller node (k_perm_split)
   int perm_buckets = 0;
   const float* w = nullptr;        // edge weights in the stored entry order (borrowed or owned_w); null: unweighted
   float* owned_w = nullptr;
@@ -253,7 +253,7 @@ int pick_chunk(int64_t n, int64_t max_chunk = 65536, int64_t min_chunk = 1024) {
 constexpr int64_t RANGE_CHUNK_MAX = 1 << 18;
 // Workgroups of a scoring node pass over several label ranges: the CUs of the GPU
 constexpr int64_t RANGE_WGS = 256;
-// The caller-order node pass of column-blocked graphs (k_node_perm) is bound by its
+// The caller-order node pass of tiled graphs (k_node_perm) is bound by its
 // scattered label stores and gains from more, smaller workgroups; its column scan only
 // needs totals, so the extra histogram rows cost little.
 constexpr int64_t PERM_CHUNK_MAX = 16384;
@@ -329,7 +329,7 @@ ScoreLayout score_layout(int64_t n, int64_t nnz, int64_t L, bool weighted = fals
 // histogram rows (W x L per task) few.  Never larger than the single-call layout.
 ScoreLayout batch_task_layout(int64_t n, int64_t nnz, int64_t L) { return score_layout(n, nnz, L, false, 65536, 4096); }
 
-// Nodes up to which a graph without column blocks is scored by member rows: their 16-bit
+// Nodes up to which a graph without tiles is scored by member rows: their 16-bit
 // labels fill one XCD's 4 MB L2.
 constexpr int64_t ROWS_MAX_N = 2 << 20;
 
