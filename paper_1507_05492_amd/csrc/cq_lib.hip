@@ -1307,9 +1307,10 @@ constexpr int64_t BLOCK_MIN_N = 1 << 20;
 constexpr int64_t TILE_MAX_N = (int64_t)TG_MAX_SLICES << TS_SHIFT_LARGE;
 static_assert(BLOCK_MAX_N <= (int64_t)TG_MAX_SLICES << TS_SHIFT, "slices");
 
-// Builds the tiles of the renumbered graph (g->owned_rp / owned_col), of at most `ent` entries;
-// *most = the most far entries of one.  When that is over `limit`, no tiles are left.
-cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* most) {
+// Builds the tiles of the renumbered graph (g->owned_rp / owned_col) of at most (*ents)[b] entries
+// in block b (null: TG_ENT everywhere); *most = the most far entries of one.  When that is over
+// `limit`, no tiles are left and *ents is allocated and set for a second try.
+cq_status build_tiles(cq_context* ctx, cq_graph* g, u32** ents, u32 limit, u32* most) {
   const int n = g->n;
   hipStream_t s = ctx->stream;
   const int blocks = (n + TG_ROWS - 1) / TG_ROWS, shift = n > BLOCK_MAX_N ? TS_SHIFT_LARGE : TS_SHIFT;
@@ -1335,7 +1336,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
   alloc((void**)&tmp, scan_tmp(blocks));
   alloc((void**)&fmax, 16);
   if (e == hipSuccess) {
-    k_tile_blocks<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, ent, g->owned_rp, bcnt);
+    k_tile_blocks<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, *ents, g->owned_rp, bcnt);
     scan_u32(bcnt, bfirst, blocks, tmp, s);
     read(&T, bfirst + blocks);
   }
@@ -1352,7 +1353,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
   alloc((void**)&fcnt, 4 * (size_t)cells);
   alloc((void**)&fstart, 4 * ((size_t)cells + 1));
   if (e == hipSuccess) {
-    k_tile_list<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, ent, g->owned_rp, bfirst, g->tiles, cnt);
+    k_tile_list<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, *ents, g->owned_rp, bfirst, g->tiles, cnt);
     scan_u32(cnt, group0, T, tmp, s);
     fill(fmax, 1, 0, s);
     k_tile_count<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, shift, g->tiles, g->owned_col, fcnt, nfar, fmax);
@@ -1376,6 +1377,14 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
       if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
   }
+  if (e == hipSuccess && !keep && !*ents) {
+    alloc((void**)ents, 4 * (size_t)blocks);
+    if (e == hipSuccess) {
+      k_tile_ents<<<(blocks + 255) / 256, 256, 0, s>>>(blocks, bfirst, nfar, limit, *ents);
+      e = hipGetLastError();
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
+  }
   g->ntiles = (int)T;
   g->far = far;
   g->fmax = (int)*most;
@@ -1389,9 +1398,11 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32 ent, u32 limit, u32* mos
 
 cq_status build_tiles(cq_context* ctx, cq_graph* g) {
   const u32 limit = g->owned_w ? TG_ENT_W : TG_ENT;
-  u32 most = 0;
-  const cq_status st = build_tiles(ctx, g, TG_ENT, limit, &most);
-  return st != CQ_OK || most <= limit ? st : build_tiles(ctx, g, TG_ENT_W, limit, &most);
+  u32 most = 0, *ents = nullptr;
+  cq_status st = build_tiles(ctx, g, &ents, limit, &most);
+  if (st == CQ_OK && most > limit) st = build_tiles(ctx, g, &ents, limit, &most);
+  if (ents) (void)hipFree(ents);
+  return st;
 }
 
 // Builds the label permutation plan of a renumbered graph from newid (caller id ->

@@ -30,8 +30,10 @@ constexpr int TG_WIN = TG_ROWS + 2 * TG_HALO;  // table places of the window (8,
 constexpr int TG_GROUP = 512;        // entries per wave and step: 8 per lane
 constexpr int TG_STEPS = 3;          // steps per wave at most
 constexpr int TG_ENT = TG_WAVES * TG_GROUP * TG_STEPS;  // entries per tile at most: 24,576
-// A weighted graph with a tile of more far entries than this is cut into tiles of at most so many
-// entries instead: 32-bit labels and the runs' weight sums then still fit a CU's LDS.
+// A weighted graph's blocks with a tile of more far entries than this are cut into tiles of at
+// most so many entries: two workgroups with 16-bit labels and the runs' weight sums still fit a
+// CU's LDS then, and one with 32-bit labels (a launch has the LDS of its largest tile).
+// 10M nodes, 200M weighted entries: 601 us; with every block cut so 820, with column blocks 852.
 constexpr int TG_ENT_W = 16384;
 // Slices of 2^15 ids: 64 KB of 16-bit labels (two workgroups a CU), 128 KB of 32-bit ones.  Graphs
 // whose tiles only ever serve 16-bit labels (more than 2^24 nodes) have slices of 2^16: a tile's
@@ -63,21 +65,23 @@ __device__ __forceinline__ u32 tile_word(u32 i) {
 }
 
 // ---- load time -------------------------------------------------------------------
-// Tiles of at most `ent` entries per block of rows (at least one), and the tiles themselves
-// once their numbers are known.
-__global__ __launch_bounds__(256) void k_tile_blocks(int n, int blocks, u32 ent, const int32_t* __restrict__ rp,
+// Tiles per block of rows (at least one), and the tiles themselves once their numbers are known;
+// a tile of block b has at most ents[b] entries (no ents: TG_ENT).
+__global__ __launch_bounds__(256) void k_tile_blocks(int n, int blocks, const u32* __restrict__ ents, const int32_t* __restrict__ rp,
                                                      u32* __restrict__ cnt) {
   const int b = blockIdx.x * 256 + threadIdx.x;
   if (b >= blocks) return;
+  const u32 ent = ents ? ents[b] : (u32)TG_ENT;
   const u32 ne = (u32)(rp[min(n, (b + 1) * TG_ROWS)] - rp[b * TG_ROWS]);
   cnt[b] = max(1u, (ne + ent - 1u) / ent);
 }
 
-__global__ __launch_bounds__(256) void k_tile_list(int n, int blocks, u32 ent, const int32_t* __restrict__ rp,
+__global__ __launch_bounds__(256) void k_tile_list(int n, int blocks, const u32* __restrict__ ents, const int32_t* __restrict__ rp,
                                                    const u32* __restrict__ first, Tile* __restrict__ tiles,
                                                    u32* __restrict__ groups) {
   const int b = blockIdx.x * 256 + threadIdx.x;
   if (b >= blocks) return;
+  const u32 ent = ents ? ents[b] : (u32)TG_ENT;
   const int b0 = b * TG_ROWS, b1 = min(n, b0 + TG_ROWS);
   const u32 E0 = (u32)rp[b0], E1 = (u32)rp[b1];
   for (u32 t = first[b], k = 0; t < first[b + 1]; ++t, ++k) {
@@ -101,6 +105,16 @@ __global__ __launch_bounds__(256) void k_tile_list(int n, int blocks, u32 ent, c
     tiles[t] = Tile{b0, r0, r1, a, z - a, 0u, 0u, 0u};
     groups[t] = (z - a + TG_GROUP - 1u) / TG_GROUP;
   }
+}
+
+// ents[b] for tiles cut without it, whose far entries are counted in nfar.
+__global__ __launch_bounds__(256) void k_tile_ents(int blocks, const u32* __restrict__ first, const u32* __restrict__ nfar,
+                                                   u32 limit, u32* __restrict__ ents) {
+  const int b = blockIdx.x * 256 + threadIdx.x;
+  if (b >= blocks) return;
+  u32 most = 0;
+  for (u32 t = first[b]; t < first[b + 1]; ++t) most = max(most, nfar[t]);
+  ents[b] = most > limit ? (u32)TG_ENT_W : (u32)TG_ENT;
 }
 
 // One workgroup per tile: far entries per slice (fcnt[slice * T + tile]), in all, and the
@@ -426,18 +440,6 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   // first walk: which entries are staged
   const u32 vc = have ? (u32)s_lab[vr] : 0u;
   u32 nlo = 0, nhi = 0;  // lane l: the staged entries of vector l
-  u32 wrun = SENT;       // WT: the run whose own-label weights wacc sums
-  WeightSum wacc;
-  auto wflush = [&]() {
-    if (wrun == SENT) return;
-    const u128 sum = wave_sum_u128(wacc.value());
-    if (lane == 0) {
-      const unsigned long long lo = (unsigned long long)sum, old = atomicAdd(&s_ilo[wrun], lo);
-      const unsigned long long hi = (unsigned long long)(sum >> 64) + (old + lo < old ? 1ull : 0ull);
-      if (hi) atomicAdd(&s_ihi[wrun], hi);
-    }
-    wacc = WeightSum();
-  };
 #pragma unroll
   for (int i = 0; i < TG_STEPS; ++i) {
     if ((u32)i >= steps || gw + i >= ng) break;
@@ -472,41 +474,6 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     if (sizeof(LT) == 2)  // the labels take the places' registers
       q[i] = make_uint4(x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16);
   }
-  if constexpr (WT) {
-    // own-label weights, the runs of a vector one after another
-    constexpr int U = 4;
-    const int nv = (int)min(steps * (u32)(TG_GROUP / 64), v0 * 64u < ne ? (ne - v0 * 64u + 63u) / 64u : 0u);
-    for (int vb = 0; vb < nv; vb += U) {
-      float wt[U];
-#pragma unroll
-      for (int k = 0; k < U; ++k) wt[k] = w[tile.e0 + min((v0 + (u32)(vb + k)) * 64u + (u32)lane, ne - 1u)];
-#pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const int v = vb + k;
-        if (v >= nv) break;
-        u64 vlo, vhi;
-        WeightSum::split(wt[k], vlo, vhi);
-        const u64 neq = ((u64)of(nhi, v) << 32) | of(nlo, v);
-        const bool mine = !((neq >> lane) & 1ull) && (v0 + (u32)v) * 64u + (u32)lane < ne;
-        u64 bits = ((u64)of(vbh, v) << 32) | of(vbl, v);
-        u32 r = of(vr, v);
-        int lo = 0;
-        while (true) {
-          const int hi = bits ? __ffsll((unsigned long long)bits) : 64;
-          if (r != wrun) {
-            wflush();
-            wrun = r;
-          }
-          if (mine && lane >= lo && lane < hi) wacc.add(vlo, vhi);
-          if (!bits) break;
-          bits &= bits - 1ull;
-          lo = hi;
-          ++r;
-        }
-      }
-    }
-  }
-  if (WT) wflush();
   u32 vp;
   {
     const u32 cnt = (u32)(__popc(nlo) + __popc(nhi)), incl = wave_incl_scan(cnt);
@@ -541,14 +508,6 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
         const u32 lo = (u32)old;
         if (lo + inter <= dc) to = sc + lo - p;
         else atomicOr(&ctl->flags, F_SEGMENT);  // never expected: the tile's counts disagree with the degrees
-        if (WT) {
-          const unsigned long long ilo = s_ilo[tid], ihi = s_ihi[tid];
-          if (ilo | ihi) {
-            const unsigned long long was = atomicAdd(&IWacc[2 * (size_t)c], ilo);
-            const unsigned long long h = ihi + (was + ilo < was ? 1ull : 0ull);
-            if (h) atomicAdd(&IWacc[2 * (size_t)c + 1], h);
-          }
-        }
       }
       s_to[tid] = to;
     }
@@ -574,7 +533,66 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
       const u32 at = below_in(lo, hi, to[k] + of(vp, 8 * i + k));
       if (__builtin_amdgcn_inverse_ballot_w64(((u64)hi << 32) | lo) && to[k] != NOWHERE) {
         CB[at] = (LT)(sizeof(LT) == 2 ? half(q[i], k) : label(q[i], k));
-        if (WT) CW[at] = w[tile.e0 + e0 + (u32)(64 * k + lane)];
+      }
+    }
+  }
+  if constexpr (WT) {
+    // every weight once: a staged entry's to its place, an own-label entry's into its run's sum,
+    // the runs of a vector one after another
+    u32 wrun = SENT;  // the run whose own-label weights wacc sums
+    WeightSum wacc;
+    auto wflush = [&]() {
+      if (wrun == SENT) return;
+      const u128 sum = wave_sum_u128(wacc.value());
+      if (lane == 0) {
+        const unsigned long long lo = (unsigned long long)sum, old = atomicAdd(&s_ilo[wrun], lo);
+        const unsigned long long hi = (unsigned long long)(sum >> 64) + (old + lo < old ? 1ull : 0ull);
+        if (hi) atomicAdd(&s_ihi[wrun], hi);
+      }
+      wacc = WeightSum();
+    };
+    constexpr int U = 8;  // loads in flight
+    const int nv = (int)min(steps * (u32)(TG_GROUP / 64), v0 * 64u < ne ? (ne - v0 * 64u + 63u) / 64u : 0u);
+    for (int vb = 0; vb < nv; vb += U) {
+      float wt[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) wt[k] = w[tile.e0 + min((v0 + (u32)(vb + k)) * 64u + (u32)lane, ne - 1u)];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int v = vb + k;
+        if (v >= nv) break;
+        const u32 slo = of(nlo, v), shi = of(nhi, v), bl = of(vbl, v), bh = of(vbh, v);
+        u32 r = of(vr, v);
+        const u32 to = (bl | bh) ? s_to[below_in(bl, bh, r)] : of(vt, v);
+        const bool staged = __builtin_amdgcn_inverse_ballot_w64(((u64)shi << 32) | slo);
+        if (staged && to != NOWHERE) CW[below_in(slo, shi, to + of(vp, v))] = wt[k];
+        u64 vlo, vhi;
+        WeightSum::split(wt[k], vlo, vhi);
+        const bool mine = !staged && (v0 + (u32)v) * 64u + (u32)lane < ne;
+        u64 bits = ((u64)bh << 32) | bl;
+        int lo = 0;
+        while (true) {
+          const int hi = bits ? __ffsll((unsigned long long)bits) : 64;
+          if (r != wrun) {
+            wflush();
+            wrun = r;
+          }
+          if (mine && lane >= lo && lane < hi) wacc.add(vlo, vhi);
+          if (!bits) break;
+          bits &= bits - 1ull;
+          lo = hi;
+          ++r;
+        }
+      }
+    }
+    wflush();
+    __syncthreads();
+    if (c != NOLAB) {  // a run's thread
+      const unsigned long long ilo = s_ilo[tid], ihi = s_ihi[tid];
+      if (ilo | ihi) {
+        const unsigned long long was = atomicAdd(&IWacc[2 * (size_t)c], ilo);
+        const unsigned long long h = ihi + (was + ilo < was ? 1ull : 0ull);
+        if (h) atomicAdd(&IWacc[2 * (size_t)c + 1], h);
       }
     }
   }

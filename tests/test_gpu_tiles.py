@@ -46,8 +46,8 @@ GRAPHS = {
     "n1023": (1023, 4000, 1000), "n1024": (1024, 4000, 1000), "n1025": (1025, 4000, 1000),
     # one slice less an id, whole, one more; far entries on both sides of the window
     "n32767": (32767, 150000, 60000), "n32768": (32768, 150000, 60000), "n32769": (32769, 150000, 60000),
-    # blocks of more than 24,576 entries (several tiles), and of 16,384 far ones
-    "dense": (12000, 100000, 250000),
+    # blocks of more than 24,576 entries (several tiles), and of more than 16,384 far ones each
+    "dense": (12000, 100000, 250000), "far": (60000, 100, 900000),
     # a row of more than a tile's entries, and rows without entries
     "hub": (60000, 100000, 20000, 50000, 3000),
     "sparse": (20000, 300, 50, 0, 9000),
@@ -87,7 +87,7 @@ def test_tiles(cq, ctx, name, width):
     G.close()
 
 
-@pytest.mark.parametrize("name", ["n1025", "n32769", "dense", "hub", "sparse"])
+@pytest.mark.parametrize("name", ["n1025", "n32769", "dense", "far", "hub", "sparse"])
 @pytest.mark.parametrize("width", [7, 9000])
 def test_tiles_weighted(cq, ctx, name, width):
     n = GRAPHS[name][0]
