@@ -31,7 +31,9 @@ struct Ctl {
   u32 done, done2;  // workgroups that have finished a pass whose last workgroup goes on alone
   u32 changes;    // tiled graphs' node pass: label changes between consecutive stored ids
   u32 mode;       // tiled graphs: STAGE_BLOCKS or STAGE_ROWS, chosen from `changes`
-  unsigned long long pad1[3];
+  u32 parts;      // member rows: parts of the communities that several workgroups share (kbig of them)
+  u32 pad0;
+  unsigned long long pad1[2];
 };
 
 // ---- work queues of the persistent per-community kernels ----------------------

@@ -1218,12 +1218,13 @@ __device__ __forceinline__ void load_labels(int c0, int L, const u32* __restrict
 }
 
 template <int PER>
-__device__ void scan_order_per(int L, const u32* __restrict__ N, const u32* __restrict__ D, u32* __restrict__ start,
-                               u32* __restrict__ order, Ctl* __restrict__ ctl) {
+__device__ u32 scan_order_per(int L, const u32* __restrict__ N, const u32* __restrict__ D, u32* __restrict__ start,
+                               u32* __restrict__ order, Ctl* __restrict__ ctl, int big_bucket) {
   __shared__ u32 s_wtot[16];
   __shared__ u32 s_carry;
   __shared__ u32 s_bcnt[64];
   __shared__ u32 s_boff[64];
+  __shared__ u32 s_big;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (tid < 64) s_bcnt[tid] = 0;
   if (tid == 0) s_carry = 0;
@@ -1258,7 +1259,7 @@ __device__ void scan_order_per(int L, const u32* __restrict__ N, const u32* __re
     const u32 incl = wave_incl_scan(cnt);
     if (tid <= 32) s_boff[32 - tid] = incl - cnt;
     if (tid == 32) ctl->K = incl;
-    if (tid == 32 - (GW_SPLIT_BUCKET - 1)) ctl->kbig = incl - cnt;  // groups in buckets >= GW_SPLIT_BUCKET
+    if (tid == 33 - big_bucket) ctl->kbig = s_big = incl - cnt;
   }
   __syncthreads();
   for (int base = 0; base < L; base += 1024 * PER) {
@@ -1270,13 +1271,16 @@ __device__ void scan_order_per(int L, const u32* __restrict__ N, const u32* __re
       if (nn[k] > 0) order[atomicAdd(&s_boff[size_bucket(d[k])], 1u)] = (u32)(c0 + k);
     }
   }
+  return s_big;
 }
 
-__device__ __forceinline__ void scan_order_body(int L, const u32* __restrict__ N, const u32* __restrict__ D,
-                                                u32* __restrict__ start, u32* __restrict__ order, Ctl* __restrict__ ctl) {
-  if (L <= 1024) scan_order_per<1>(L, N, D, start, order, ctl);
-  else if (L <= 4096) scan_order_per<4>(L, N, D, start, order, ctl);
-  else scan_order_per<16>(L, N, D, start, order, ctl);
+// Returns ctl->kbig, the groups in buckets >= big_bucket (1 to 33), which come first in the order.
+__device__ __forceinline__ u32 scan_order_body(int L, const u32* __restrict__ N, const u32* __restrict__ D,
+                                               u32* __restrict__ start, u32* __restrict__ order, Ctl* __restrict__ ctl,
+                                               int big_bucket = GW_SPLIT_BUCKET) {
+  if (L <= 1024) return scan_order_per<1>(L, N, D, start, order, ctl, big_bucket);
+  if (L <= 4096) return scan_order_per<4>(L, N, D, start, order, ctl, big_bucket);
+  return scan_order_per<16>(L, N, D, start, order, ctl, big_bucket);
 }
 
 __global__ __launch_bounds__(1024) void k_scan_order(int L, const u32* __restrict__ N, const u32* __restrict__ D,
@@ -1849,12 +1853,14 @@ struct ScoreVis {
     u32 g;
     double denom;
   };
-  __device__ void begin(State& st, u32 g) {
+  __device__ void begin(State& st, u32 g) { begin_n(st, g, N[g]); }
+  // the same with |g| = ng already loaded
+  __device__ void begin_n(State& st, u32 g, u32 ng) {
     st.pen = Frac96Sum();
     st.acc = 0.0;
     st.np = 0;
     st.g = g;
-    st.denom = twom * (double)N[g];
+    st.denom = twom * (double)ng;
     if (threadIdx.x == 0) I[g] = 0;  // overwritten by the thread that meets label g
   }
   // k_groups_wave: lane 0 of the group's wave clears I[g]

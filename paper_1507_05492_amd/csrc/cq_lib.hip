@@ -272,6 +272,9 @@ struct ScoreLayout {
   size_t CW, SW, IW, PENW, INVN;  // weighted graphs only (0 otherwise)
   bool rows;  // scored by member rows (cq_rows.hpp): rec and bad in place of the staged entries
   size_t rec, bad;
+  int split;      // log2 of the nodes from which a community is counted in parts
+  u32 part, max_parts;  // nodes per part, parts at most
+  size_t pitems, ptable;
   // scored through the graph's tiles (cq_tiles.hpp): staging chosen by the partition, or by
   // rows always; fl: the far entries' labels
   bool tiled, tile_rows;
@@ -386,6 +389,16 @@ ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_
   r.bad = c.take(4 * (size_t)r.W);
   r.labx = c.take(2 * (size_t)g->n);
   r.rec = c.take(8 * (size_t)g->n);
+  // A community of two chunks' nodes or more (1/128 of the graph; 2,048 nodes at least) is cut into
+  // parts of half a chunk, so that a part is at most 1/512 of the graph or 512 nodes.  2M nodes and
+  // 40M entries: one community 46 ms when one workgroup walked it, 0.30 in parts; a community of
+  // half the nodes among 1,000 24 and 0.31 (staged: 15 and 9.5); smaller ones not measurably.
+  r.split = 1;
+  while (1 << r.split < 2 * r.chunk) ++r.split;
+  r.part = (u32)r.chunk / 2;
+  r.max_parts = (u32)(g->n / r.part + (g->n >> r.split));
+  r.pitems = c.take(4 * (size_t)r.max_parts);
+  r.ptable = c.take(4 * (size_t)(g->n >> r.split) * rg_row_words((u32)L));
   r.parts = c.take(sizeof(ScorePart) * r.G);
   r.res = c.take(sizeof(ScoreResultDev));
   return c.off <= s.total ? r : s;
@@ -861,10 +874,10 @@ int rows_threads(cq_context* ctx, int32_t L) {
 template <int NT_, int NTV_>
 struct RowsTag {  // one shape of k_rows_groups
   static constexpr int NT = NT_, NTV = NTV_;
-  static unsigned grid(cq_context* ctx, int32_t L, size_t lds) {
+  static unsigned grid(cq_context* ctx, int32_t L, u32 parts, size_t lds) {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_rows_groups<uint16_t, NT, NTV>, NT, lds) != hipSuccess || nb < 1) nb = 1;
-    const int64_t cap = ((int64_t)L + 7) / 8 * 8;  // a multiple of the queues (static first items)
+    const int64_t cap = ((int64_t)L + parts + 7) / 8 * 8;  // a multiple of the queues (static first items)
     return (unsigned)std::min<int64_t>((int64_t)ctx->num_cus * nb / 8 * 8, cap);
   }
 };
@@ -910,6 +923,8 @@ void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels
   u32* bad = at<u32>(ws, lay.bad);
   uint16_t* labx = at<uint16_t>(ws, lay.labx);
   uint2* rec = at<uint2>(ws, lay.rec);
+  u32* pitems = at<u32>(ws, lay.pitems);
+  u32* ptable = at<u32>(ws, lay.ptable);
   ScoreVis vis;
   vis.N = N;
   vis.twom = (double)g->nnz;
@@ -926,9 +941,10 @@ void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels
   const bool small = L <= (int32_t)SMALL_L_MAX;
   auto groups = [&](auto tag, bool launch) -> unsigned {
     using T = decltype(tag);
-    const unsigned grid = T::grid(ctx, L, lds);
+    const unsigned grid = T::grid(ctx, L, lay.max_parts, lds);
     if (launch)
-      k_rows_groups<uint16_t, T::NT, T::NTV><<<grid, T::NT, lds, s>>>(rec, g->col, labx, start, order, D, ctl, (u32)L, vis, wq);
+      k_rows_groups<uint16_t, T::NT, T::NTV><<<grid, T::NT, lds, s>>>(rec, g->col, labx, start, order, D, ctl, (u32)L, vis, wq,
+                                                                    pitems, lay.part, ptable);
     return grid;
   };
   auto pick = [&](bool launch) -> unsigned {
@@ -944,11 +960,13 @@ void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels
   }
   {
     StageMark mk(ctx, ST_ORDER, timed);
-    k_rows_scan<<<colscan_grid(L), CS_LABELS * CS_GROUPS, 0, s>>>(lay.W, L, HN, N, start, order, bad, ctl);
+    k_rows_scan<<<colscan_grid(L), CS_LABELS * CS_GROUPS, 0, s>>>(lay.W, L, HN, N, start, order, pitems,
+                                                                              lay.split, lay.part, bad, ctl);
   }
   {
     StageMark mk(ctx, ST_SCATTER, timed);
-    k_rows_place<uint16_t><<<grid_for(n, 256, 8192), 256, 0, s>>>(n, g->rp, L, lay.chunk, HN, start, loc, labx, rec);
+    k_rows_place<uint16_t><<<grid_for(n, 256, 8192), 256, 0, s>>>(n, g->rp, L, lay.chunk, HN, start, loc, labx, rec,
+                                                                 ptable, ctl);
   }
   {
     StageMark mk(ctx, ST_GROUPS, timed);
