@@ -335,6 +335,12 @@ ScoreLayout batch_task_layout(int64_t n, int64_t nnz, int64_t L) { return score_
 // Nodes up to which a graph without tiles is scored by member rows: their 16-bit
 // labels fill one XCD's 4 MB L2.
 constexpr int64_t ROWS_MAX_N = 2 << 20;
+// Tiny communities under wide tables (one or two nodes among 12,000 label ids and more) are not:
+// a community then costs its dependent round trips, of which member rows have two more.  12,000
+// label ids over 20,000 nodes: 188 us (168 staged); at 16,000 label ids the two meet near 160
+// entries a community (379 and 352 us at 54 entries, 419 and 423 at 172); 6,000 label ids over
+// 20,000 nodes 102 (104).
+constexpr int64_t ROWS_TINY_MIN_L = 8192, ROWS_TINY_NNZ = 160;
 
 // Small graphs (cq_small.hpp): entries, entries per counting workgroup, and table cells that
 // the finishing workgroup adds up.
@@ -364,6 +370,7 @@ ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_
     return s;
   }
   if (g->w || L > DIRECT_MAX || g->n > ROWS_MAX_N) return s;
+  if (L > ROWS_TINY_MIN_L && g->nnz < ROWS_TINY_NNZ * L) return s;
   ScoreLayout r = s;
   Carve c;
   if (g->n <= SS_MAX_N && L <= SS_MAX_L && g->nnz <= SMALL_MAX_NNZ) {
@@ -860,13 +867,17 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   }
 }
 
-// Threads per workgroup of the member-row group pass: enough that the workgroups a CU holds
-// beside their tables fill its 2,048 threads, and that few communities spread over the chip
-// (399 communities: 1,024 threads each).
-int rows_threads(cq_context* ctx, int32_t L) {
+// Threads per workgroup of the member-row group pass.  Few communities spread over the chip
+// (399 communities: 1,024 threads each); up to 4,096 label ids, the workgroups that a CU holds
+// beside their tables fill its 2,048 threads.  Larger tables leave a CU two to five workgroups,
+// and the threads beyond 256 wait through a small community's chain of round trips: 20,000
+// nodes and 12,000 label ids 194 us with 256 threads, 203 with 512, 266 with 1,024; 1M nodes
+// and 16,000 label ids of 2,100 entries 663, 609 and 644.
+int rows_threads(cq_context* ctx, int64_t nnz, int32_t L) {
+  if (L > (int32_t)SMALL_L_MAX) return nnz / L < 2048 ? 256 : 512;
   const int64_t tables = std::min<int64_t>(16, (int64_t)(150 << 10) / (4 * (int64_t)L + 2048));  // workgroups per CU by LDS
   const int64_t want = std::max<int64_t>(2048 / std::max<int64_t>(tables, 1), (int64_t)ctx->num_cus * 2048 / L);
-  int nt = L <= (int32_t)SMALL_L_MAX ? 128 : 256;
+  int nt = 128;
   while (nt < 1024 && nt < want) nt *= 2;
   return nt;
 }
@@ -937,7 +948,7 @@ void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels
   vis.ecap = pairs ? pairs->capacity : 0;
   vis.ctl = ctl;
   const size_t lds = (size_t)std::max<u32>(((u32)L + 3u) & ~3u, 128u) * 4;
-  const int nt = rows_threads(ctx, L);
+  const int nt = rows_threads(ctx, g->nnz, L);
   const bool small = L <= (int32_t)SMALL_L_MAX;
   auto groups = [&](auto tag, bool launch) -> unsigned {
     using T = decltype(tag);
@@ -950,8 +961,7 @@ void score_launch_rows(cq_context* ctx, const cq_graph* g, const int32_t* labels
   auto pick = [&](bool launch) -> unsigned {
     if (small) return nt == 128 ? groups(RowsTag<128, GBLOCK_SMALL>{}, launch) : nt == 256 ? groups(RowsTag<256, GBLOCK_SMALL>{}, launch)
                     : nt == 512 ? groups(RowsTag<512, GBLOCK_SMALL>{}, launch) : groups(RowsTag<1024, GBLOCK_SMALL>{}, launch);
-    return nt == 256 ? groups(RowsTag<256, GBLOCK_DIRECT>{}, launch) : nt == 512 ? groups(RowsTag<512, GBLOCK_DIRECT>{}, launch)
-                     : groups(RowsTag<1024, GBLOCK_DIRECT>{}, launch);
+    return nt == 256 ? groups(RowsTag<256, GBLOCK_DIRECT>{}, launch) : groups(RowsTag<512, GBLOCK_DIRECT>{}, launch);
   };
   {
     StageMark mk(ctx, ST_NODE, timed);
@@ -2107,7 +2117,6 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_groups<ScoreVis, uint32_t, GBLOCK_WIDE>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<CmpVis, uint16_t>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<CmpVis, uint32_t>), gl);
-  set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 1024, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 512, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_groups<uint16_t, 256, GBLOCK_DIRECT>), DIRECT_MAX * 4);
   set_big_lds(reinterpret_cast<const void*>(k_rows_node<uint16_t>), DIRECT_MAX * 4);
