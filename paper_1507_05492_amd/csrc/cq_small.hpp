@@ -11,8 +11,12 @@ namespace cq {
 // nodes.  Second launch: one workgroup adds the tables up and finishes the call.
 // The tables are added in the workspace's slots: SS_WORDS(L) words per workgroup, the last
 // one its label error flag.
+// The finishing workgroup reads up to 32 tables of L x (L + 1) cells, so the line to member rows
+// lies at a number of label ids: 16,384 nodes and 390,000 entries 39 us with 2 label ids (49 by
+// member rows), 45 with 40 (45), 47 with 48 (45), 69 with 100 (42), 102 with 160 (42); 4,000
+// nodes and 32,000 entries 28 with 2 (48), 36 with 48 (40).
 constexpr int SS_MAX_N = 16384;   // nodes (32 KB of labels in LDS)
-constexpr int SS_MAX_L = 160;     // label ids (103 KB of counters in LDS)
+constexpr int SS_MAX_L = 48;      // label ids
 constexpr int SS_MAX_WG = 32;
 constexpr int SS_THREADS = 512;
 constexpr int SS_UNROLL = 4;

@@ -40,3 +40,16 @@ def test_tiny_communities(cq, ctx, n, m, L, path):  # noqa: F811
     lab = rng.integers(0, L, n).astype(np.int32)
     run_score(cq, ctx, rp, ci, lab, L, f"{n} nodes, {m} edges, {L} ids")
     assert route(cq, ctx, rp, ci, lab, L) == path
+
+
+@pytest.mark.parametrize("n,m,L,path", [
+    (1000, 7000, 48, "small"), (1000, 7000, 49, "rows"),
+    (16384, 190000, 48, "small"), (16384, 190000, 49, "rows"), (16384, 190000, 160, "rows"),
+    (16385, 190000, 48, "rows"), (16000, 210000, 48, "rows"),  # a node, or 20,000 entries, too many
+])
+def test_small_graphs(cq, ctx, n, m, L, path):  # noqa: F811
+    rng = np.random.default_rng(m)
+    rp, ci = csr_from_edges(n, rng.integers(0, n, (m, 2)))
+    lab = rng.integers(0, L, n).astype(np.int32)
+    run_score(cq, ctx, rp, ci, lab, L, f"{n} nodes, {m} edges, {L} ids")
+    assert route(cq, ctx, rp, ci, lab, L) == path
