@@ -151,12 +151,15 @@ typedef struct {
  * When 2^20 <= n <= 2^27 the copy is also kept as tiles (the edge pass then finds every
  * neighbour label in LDS; below 2^20 nodes one L2 holds all labels anyway): 2 bytes per
  * entry, rounded up to 512 entries a tile, 6 bytes per entry whose neighbour's id is far
- * from the row's, and 32 bytes per tile.  A plan that moves labels from the caller's order
+ * from the row's, 32 bytes per tile, and 4 bytes per 2^15 (2^16 beyond 2^24 nodes) ids for
+ * every 2n far entries.  A plan that moves labels from the caller's order
  * to the stored one comes with them.  CQ_GRAPH_NO_BLOCKS never builds tiles, CQ_GRAPH_BLOCKS
  * builds them for any n <= 2^24 (both flags at once: CQ_E_INVALID_ARG).  owned_bytes in
  * cq_graph_stats reports the total.  A tiled graph's workspace has room for the far entries'
- * labels (2 bytes each, 4 with more than 65,535 label ids); a call with a workspace that
- * lacks just that room is scored through the row-major copy.
+ * labels (2 bytes each, 4 with more than 65,535 label ids).  A call with a workspace that
+ * lacks just that room is served as well: up to 2^24 nodes a part of the far labels at a
+ * time (or, up to 2^21 nodes and 16,384 label ids, without them), beyond through the
+ * row-major copy, which takes about twice as long.
  */
 cq_status cq_graph_load(cq_context* ctx, int32_t n, int64_t nnz, const int32_t* d_row_ptr,
                         const int32_t* d_col_idx, uint32_t flags, cq_graph** out);

@@ -1334,14 +1334,17 @@ __device__ __forceinline__ void gather_rows(long long r0, int n, const int32_t* 
 // workgroup b runs on XCD b % 8 and takes tile (b % 8) * ceil(tiles / 8) + b / 8: each
 // XCD walks its own eighth of the rows in order, so the labels that neighbouring rows
 // share stay in its L2 (the 100M-node graph's edge pass: 7.63 -> 7.40 ms).  A smaller
-// grid takes the tiles in turn (grid-stride).
+// grid takes the tiles in turn (grid-stride).  With a gate nothing is done unless its mode is
+// STAGE_ROWS.
 template <bool PRIV, class LT, bool WT>
 __global__ __launch_bounds__(GROWS) void k_gather(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                   const LT* __restrict__ labx, int L, int chunk, const u32* __restrict__ PM,
                                                   const u32* __restrict__ start, const u32* __restrict__ loc,
-                                                  LT* __restrict__ CB, const float* __restrict__ w, float* __restrict__ CW) {
+                                                  LT* __restrict__ CB, const float* __restrict__ w, float* __restrict__ CW,
+                                                  const Ctl* __restrict__ gate = nullptr) {
   __shared__ int s_rs[GROWS + 1];
   __shared__ u32 s_base[GROWS];
+  if (gate && gate->mode != STAGE_ROWS) return;
   const long long tiles = ((long long)n + GROWS - 1) / GROWS;
   const long long per = (tiles + 7) / 8;
   if (gridDim.x >= 8 * per) {

@@ -68,6 +68,8 @@ struct cq_graph {
   int ntiles = 0, fmax = 0;        // tiles; most far entries of one
   int64_t groups = 0;              // groups of eidx
   int64_t far = 0;                 // far entries
+  std::vector<u32> ctile, cfar;    // per chunk of tiles: its first tile and far entry (and the ends)
+  u32 cmost = 0;                   // most far entries of a chunk
   int slices = 0, sshift = TS_SHIFT;  // slices, of 2^sshift ids
   bool blocked = false;            // runs may be staged compactly through the tiles (n <= 2^24); else by rows only
   u32* deg_in = nullptr;           // label permutation plan (caller order -> stored order): degrees,
@@ -278,7 +280,8 @@ struct ScoreLayout {
   // scored through the graph's tiles (cq_tiles.hpp): staging chosen by the partition, or by
   // rows always; fl: the far entries' labels
   bool tiled, tile_rows;
-  size_t fl, min_total;
+  bool rounds;  // fl has no room of its own: it is filled for some chunks of tiles at a time
+  size_t fl, fl_bytes, min_total;
   int small_wgs;  // > 0: scored in two launches (cq_small.hpp) by that many counting workgroups
   size_t slots;
 };
@@ -347,27 +350,10 @@ constexpr int64_t ROWS_TINY_MIN_L = 8192, ROWS_TINY_NNZ = 160;
 constexpr int64_t SMALL_MAX_NNZ = 400000;
 constexpr int64_t SMALL_WG_NNZ = 2048;
 
-// The layout of one scoring call on graph g with `have` bytes of workspace.  min_total is the
-// least a call takes; a tiled graph uses its tiles when there is room for the far entries'
-// labels as well (total), else its row-major copy.  Member rows and small graphs take the
-// workspace of the staged path (which they fit unless the graph has hardly any edges).
-ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_MAX) {
-  const bool perm = g->blocked && g->pos1 && L <= PRIV_MAX;
-  ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
-  s.min_total = s.total;
-  if (g->tiles && (g->blocked || s.small)) {
-    ScoreLayout t = s;
-    Carve c;
-    c.off = s.total;
-    t.tiled = g->blocked;
-    t.tile_rows = !g->blocked;
-    t.fl = c.take((s.small ? 2 : 4) * (size_t)g->far);
-    t.total = c.off;
-    if (t.total <= have) return t;
-    s = score_layout(g->n, g->nnz, L, g->w != nullptr, 65536);
-    s.min_total = t.min_total;
-    return s;
-  }
+// The layout s of the staged path, or that of a small graph or of member rows where those serve
+// the call.  They take the workspace of the staged path (which they fit unless the graph has hardly
+// any edges).
+ScoreLayout unstaged_layout(const cq_graph* g, int64_t L, const ScoreLayout& s) {
   if (g->w || L > DIRECT_MAX || g->n > ROWS_MAX_N) return s;
   if (L > ROWS_TINY_MIN_L && g->nnz < ROWS_TINY_NNZ * L) return s;
   ScoreLayout r = s;
@@ -408,6 +394,41 @@ ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_
   r.parts = c.take(sizeof(ScorePart) * r.G);
   r.res = c.take(sizeof(ScoreResultDev));
   return c.off <= s.total ? r : s;
+}
+
+// The layout of one scoring call on graph g with `have` bytes of workspace.  min_total is the
+// least a call takes; total has room for a tiled graph's far labels as well.  Without that room a
+// graph of few enough nodes is scored by member rows (1.1M nodes, 22M entries: 136 us with the
+// room, 120 without, 178 in turns); else the far labels take turns, chunk by chunk, in the arrays of
+// per-node offsets and node counts, which staging by runs leaves unused, and the row-major copy
+// serves staging by rows (10M nodes, 200M entries, a partition along the stored order: 537 us with
+// the room, 608 in turns, 1,477 through the row-major copy).  Graphs that are always staged by
+// rows, and those whose chunks do not fit (a few thousand nodes with thousands of neighbours
+// each), take the row-major copy without that room.
+ScoreLayout graph_score_layout(const cq_graph* g, int64_t L, size_t have = SIZE_MAX) {
+  const bool perm = g->blocked && g->pos1 && L <= PRIV_MAX;
+  ScoreLayout s = score_layout(g->n, g->nnz, L, g->w != nullptr, perm ? PERM_CHUNK_MAX : 65536);
+  s.min_total = s.total;
+  if (!g->tiles || !(g->blocked || s.small)) return unstaged_layout(g, L, s);
+  ScoreLayout t = s;
+  Carve c;
+  c.off = s.total;
+  t.tiled = g->blocked;
+  t.tile_rows = !g->blocked;
+  t.fl = c.take((s.small ? 2 : 4) * (size_t)g->far);
+  t.total = c.off;
+  if (t.total <= have) return t;
+  t = unstaged_layout(g, L, s);
+  if (t.rows || t.small_wgs > 0) return t;
+  s.fl = s.loc;
+  s.fl_bytes = s.priv ? s.HD - s.loc : 4 * (size_t)g->n;
+  if (g->blocked && (s.small ? 2 : 4) * ((size_t)g->cmost + 8) <= s.fl_bytes) {
+    s.tiled = s.rounds = true;
+    return s;
+  }
+  t = score_layout(g->n, g->nnz, L, g->w != nullptr, 65536);
+  t.min_total = s.min_total;
+  return t;
 }
 
 struct CmpLayout {
@@ -636,6 +657,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   ScorePart* parts = at<ScorePart>(ws, lay.parts);
   const u32* PM = nullptr;
   const bool tiled = lay.tiled;
+  bool dual = false;  // tiled graph whose staging is chosen on the device
   {
     StageMark mk(ctx, ST_SETUP, timed);
     // the control block and the work queues in one launch
@@ -668,7 +690,7 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
       // A partition out of the stored order (many label changes along it) would make the
       // tiles' run claims as many as the nodes: k_colscan_rows then picks staging at per-node
       // offsets, which come from the gated launches below (they return at once otherwise).
-      const bool dual = !CW;
+      dual = !CW;
       {
         StageMark mk(ctx, ST_COLSCAN, timed);
         const double f = ctx->row_staging_from;
@@ -748,24 +770,47 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   {
     StageMark mk(ctx, ST_GATHER, timed);
     if (tiled || lay.tile_rows) {
-      const int T = g->ntiles, S = g->slices;
-      LT* fl = at<LT>(ws, lay.fl);
-      if (g->far > 0) {
-        // about four workgroups per CU, of at least 4,096 entries
-        const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((4 * ctx->num_cus + S - 1) / S, g->far / ((int64_t)S * 4096)));
-        k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << g->sshift, s>>>((int)n, g->sshift, parts, g->fslice,
-                                                                                          g->fcol, labx, fl);
-      }
-      const unsigned grid = 8u * (unsigned)((T + 7) / 8);
+      const int S = g->slices, C = (int)g->ctile.size() - 1;
       unsigned long long* cur = at<unsigned long long>(ws, lay.cursor);
-      if (CW)
-        k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(g->fmax), s>>>(
-            (int)n, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, g->w, CW,
-            at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc, 0);
-      else
-        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(g->fmax), s>>>(
-            (int)n, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr,
-            nullptr, L, lay.chunk, PM, loc, lay.tile_rows ? 1 : 0);
+      // both passes over the tiles of chunks [c0, c1), whose far labels start at place `base` of fl's order
+      auto pass = [&](int c0, int c1, u32 base, int rows) {
+        LT* fl = reinterpret_cast<LT*>(reinterpret_cast<uintptr_t>(at<LT>(ws, lay.fl)) - sizeof(LT) * (uintptr_t)base);
+        const int64_t far = g->cfar[c1] - g->cfar[c0];
+        const int t0 = (int)g->ctile[c0], T = (int)g->ctile[c1] - t0, nc = c1 - c0;
+        if (far > 0) {
+          // about four workgroups per CU, of at least 4,096 entries
+          int parts = (int)std::max<int64_t>(1, std::min<int64_t>((4 * ctx->num_cus + S - 1) / S, far / ((int64_t)S * 4096)));
+          if (2 * parts > nc) parts = (parts + nc - 1) / nc * nc;  // equal shares
+          k_far_labels<LT><<<(unsigned)(S * parts), FL_THREADS, sizeof(LT) << g->sshift, s>>>(
+              (int)n, g->sshift, S, c0, c1, parts, g->fslice, g->fcol, labx, fl, rows == TG_RUNS_ONLY ? ctl : nullptr);
+        }
+        const unsigned grid = 8u * (unsigned)((T + 7) / 8);
+        if (CW)
+          k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(g->fmax), s>>>(
+              (int)n, t0, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, g->w, CW,
+              at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc, rows);
+        else
+          k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(g->fmax), s>>>(
+              (int)n, t0, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr,
+              nullptr, L, lay.chunk, PM, loc, rows);
+      };
+      if (!lay.rounds) {
+        pass(0, C, 0, lay.tile_rows ? TG_BY_ROWS : TG_BY_MODE);
+      } else {
+        const size_t room = lay.fl_bytes / sizeof(LT);
+        for (int c0 = 0, c1; c0 < C; c0 = c1) {
+          const u32 base = g->cfar[c0] & ~7u;  // k_far_labels writes aligned groups of 8
+          for (c1 = c0 + 1; c1 < C && g->cfar[c1 + 1] - base <= room; ++c1) {
+          }
+          pass(c0, c1, base, TG_RUNS_ONLY);
+        }
+        if (dual) {
+          // the other choice, whose offsets are in loc: through the row-major copy
+          const unsigned gr = std::min(grid_for(n, GROWS, 1u << 30), (unsigned)(ctx->num_cus * 64));
+          k_gather<true, LT, false><<<gr, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, nullptr,
+                                                         nullptr, ctl);
+        }
+      }
     } else {
       const unsigned grid = 8u * (unsigned)((((int64_t)n + GROWS - 1) / GROWS + 7) / 8);  // one workgroup per tile
       if (lay.priv && CW)
@@ -1346,7 +1391,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32** ents, u32 limit, u32* 
   const int blocks = (n + TG_ROWS - 1) / TG_ROWS, shift = n > BLOCK_MAX_N ? TS_SHIFT_LARGE : TS_SHIFT;
   const int S = (int)(((int64_t)n + (1 << shift) - 1) >> shift);
   u32 *bcnt = nullptr, *bfirst = nullptr, *fcnt = nullptr, *fstart = nullptr, *tmp = nullptr, *cnt = nullptr;
-  u32 *group0 = nullptr, *nfar = nullptr, *far0 = nullptr, *fmax = nullptr;
+  u32 *group0 = nullptr, *nfar = nullptr, *far0 = nullptr, *fmax = nullptr, *cfirst = nullptr, *cof = nullptr;
   hipError_t e = hipSuccess;
   auto alloc = [&](void** p, size_t bytes) {
     if (e == hipSuccess) e = hipMalloc(p, std::max<size_t>(bytes, 16));
@@ -1375,7 +1420,6 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32** ents, u32 limit, u32* 
   tmp = nullptr;
   alloc((void**)&tmp, scan_tmp(std::max<long long>(cells, T)));
   alloc((void**)&g->tiles, sizeof(Tile) * (size_t)T);
-  alloc((void**)&g->fslice, 4 * ((size_t)S + 1));
   alloc((void**)&cnt, 4 * (size_t)T);
   alloc((void**)&group0, 4 * ((size_t)T + 1));
   alloc((void**)&nfar, 4 * (size_t)T);
@@ -1386,13 +1430,50 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32** ents, u32 limit, u32* 
     k_tile_list<<<(blocks + 255) / 256, 256, 0, s>>>(n, blocks, *ents, g->owned_rp, bfirst, g->tiles, cnt);
     scan_u32(cnt, group0, T, tmp, s);
     fill(fmax, 1, 0, s);
-    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, shift, g->tiles, g->owned_col, fcnt, nfar, fmax);
-    scan_u32(fcnt, fstart, cells, tmp, s);
+    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, S, shift, g->tiles, g->owned_col, TileChunks{}, nullptr, nfar, fmax);
     scan_u32(nfar, far0, T, tmp, s);
-    k_tile_slices<<<(S + 256) / 256, 256, 0, s>>>((int)T, S, fstart, g->fslice);
-    read(&far, fstart + cells);
+    read(&far, far0 + T);
     read(&groups, group0 + T);
     read(most, fmax);
+  }
+  // even chunks of tiles, of at most 2n - 8 far entries on graphs of 25,000 nodes and more; one chunk
+  // when every call has room for all far labels or none
+  std::vector<u32> of;
+  g->cmost = 0;
+  try {
+    of.assign(T, 0u);
+    g->ctile.assign(1, 0u);
+    g->cfar.assign(1, 0u);
+    if (e == hipSuccess) {
+      std::vector<u32> f((size_t)T + 1, 0u);
+      e = hipMemcpy(f.data(), far0, 4 * f.size(), hipMemcpyDeviceToHost);
+      const int64_t lim = std::max<int64_t>(2 * (int64_t)n - 8 - TG_ENT, n);
+      const u64 k = g->blocked ? ((u64)far + (u64)lim - 1u) / (u64)lim : 1u;
+      for (u32 t = 0; t < T; ++t) {
+        if (t > g->ctile.back() && (u64)f[t] * k >= (u64)g->ctile.size() * far) {
+          g->ctile.push_back(t);
+          g->cfar.push_back(f[t]);
+        }
+        of[t] = (u32)g->ctile.size() - 1u;
+      }
+    }
+    g->ctile.push_back(T);
+    g->cfar.push_back(far);
+  } catch (const std::bad_alloc&) {
+    if (e == hipSuccess) e = hipErrorOutOfMemory;
+  }
+  const int C = std::max(1, (int)g->ctile.size() - 1);
+  for (int c = 0; e == hipSuccess && c < C; ++c) g->cmost = std::max(g->cmost, g->cfar[c + 1] - g->cfar[c]);
+  alloc((void**)&g->fslice, 4 * ((size_t)C * S + 1));
+  alloc((void**)&cfirst, 4 * ((size_t)C + 1));
+  alloc((void**)&cof, 4 * (size_t)T);
+  const TileChunks chunks{cfirst, cof};
+  if (e == hipSuccess) e = hipMemcpy(cfirst, g->ctile.data(), 4 * ((size_t)C + 1), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(cof, of.data(), 4 * (size_t)T, hipMemcpyHostToDevice);
+  if (e == hipSuccess) {
+    k_tile_count<<<T, TG_THREADS, 0, s>>>(n, S, shift, g->tiles, g->owned_col, chunks, fcnt, nullptr, nullptr);
+    scan_u32(fcnt, fstart, cells, tmp, s);
+    k_tile_slices<<<(unsigned)((C * S + 256) / 256), 256, 0, s>>>(C, S, cfirst, fstart, g->fslice);
   }
   const bool keep = e == hipSuccess && *most <= limit;
   if (keep) {
@@ -1401,8 +1482,8 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32** ents, u32 limit, u32* 
     alloc((void**)&g->fadr, 4 * (size_t)far);
     if (e == hipSuccess) {
       fill(reinterpret_cast<u32*>(g->eidx), (size_t)groups * TG_GROUP / 2, 0, s);  // places past a tile's entries are read too
-      k_tile_place<<<T, TG_THREADS, 0, s>>>(n, (int)T, S, shift, g->tiles, group0, far0, g->owned_col, fcnt, fstart, g->eidx, g->fcol,
-                                            g->fadr);
+      k_tile_place<<<T, TG_THREADS, 0, s>>>(n, S, shift, g->tiles, group0, far0, g->owned_col, fcnt, fstart, chunks, g->eidx,
+                                            g->fcol, g->fadr);
       e = hipGetLastError();
       if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
@@ -1419,7 +1500,7 @@ cq_status build_tiles(cq_context* ctx, cq_graph* g, u32** ents, u32 limit, u32* 
   g->far = far;
   g->fmax = (int)*most;
   g->groups = groups;
-  for (u32* p : {bcnt, bfirst, fcnt, fstart, tmp, cnt, group0, nfar, far0, fmax})
+  for (u32* p : {bcnt, bfirst, fcnt, fstart, tmp, cnt, group0, nfar, far0, fmax, cfirst, cof})
     if (p) (void)hipFree(p);
   if (!keep || e != hipSuccess) g->free_tiles();
   if (e == hipErrorOutOfMemory && n > BLOCK_MAX_N) {  // such a graph is scored through its row-major copy as well
@@ -1587,7 +1668,7 @@ cq_status build_locality_order(cq_context* ctx, cq_graph* g, const int32_t* rp, 
     g->reordered = CQ_GRAPH_REORDER | (g->blocked ? 0u : CQ_GRAPH_NO_BLOCKS);
     g->owned_bytes = (int64_t)(4 * ((size_t)n + 1) + 4 * (size_t)nnz + 4 * (size_t)n);
     if (g->tiles)
-      g->owned_bytes += (int64_t)(sizeof(Tile) * (size_t)g->ntiles + 4 * ((size_t)g->slices + 1) +
+      g->owned_bytes += (int64_t)(sizeof(Tile) * (size_t)g->ntiles + 4 * ((g->ctile.size() - 1) * (size_t)g->slices + 1) +
                                   2 * (size_t)g->groups * TG_GROUP + 6 * (size_t)g->far);
     if (g->pos1) g->owned_bytes += (int64_t)(10 * (size_t)n + 4 * ((size_t)g->perm_buckets + 1));
     if (g->lrank) g->owned_bytes += (int64_t)(6 * (size_t)n);

@@ -9,8 +9,8 @@
 // window of ids (TG_HALO before and after its rows), else far.  Per graph:
 //   eidx  one 16-bit word per entry, in row order: the place of the neighbour's label in the
 //         tile's table, which holds the window's labels, then the tile's far labels;
-//   fcol  the far entries sorted by slice (2^shift consecutive ids) of the neighbour, then by
-//         tile: the 16-bit place of the neighbour in its slice;
+//   fcol  the far entries sorted by chunk (consecutive tiles), slice (2^shift consecutive ids) of
+//         the neighbour and tile: the 16-bit place of the neighbour in its slice;
 //   fadr  for every tile, the numbers of its far entries in that order.
 //
 // A call takes two passes.  k_far_labels holds one slice's labels in LDS, walks the slice's far
@@ -18,6 +18,8 @@
 // k_tile_gather then takes one tile per workgroup, puts its table together in LDS from the
 // window and the far labels (one short run per slice), and finds every neighbour's label there.
 // Both passes stream: 2 bytes per entry and 10 per far entry, labels and staging aside.
+// A chunk has at most twice as many far entries as the graph has nodes (or one tile): a call whose
+// workspace has no room for all far labels takes the two passes a few chunks at a time.
 #pragma once
 
 namespace cq {
@@ -117,11 +119,24 @@ __global__ __launch_bounds__(256) void k_tile_ents(int blocks, const u32* __rest
   ents[b] = most > limit ? (u32)TG_ENT_W : (u32)TG_ENT;
 }
 
-// One workgroup per tile: far entries per slice (fcnt[slice * T + tile]), in all, and the
-// most of any tile.
-__global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, int shift, const Tile* __restrict__ tiles,
-                                                           const int32_t* __restrict__ col, u32* __restrict__ fcnt,
-                                                           u32* __restrict__ nfar, u32* __restrict__ fmax) {
+// The chunks of tiles: chunk c is tiles [first[c], first[c + 1]), of[t] tile t's chunk.
+struct TileChunks {
+  const u32* first;
+  const u32* of;
+  // tile t's place among the counters by chunk, slice and tile: at(t, s) = base + s * stride
+  __device__ __forceinline__ void at(u32 t, int S, size_t& base, u32& stride) const {
+    const u32 c = of[t], a = first[c];
+    stride = first[c + 1] - a;
+    base = (size_t)a * (u32)S + (t - a);
+  }
+};
+
+// One workgroup per tile: far entries per slice (fcnt, by chunk, slice and tile; or null: the
+// chunks are not known yet), in all, and the most of any tile.
+__global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int S, int shift, const Tile* __restrict__ tiles,
+                                                           const int32_t* __restrict__ col, TileChunks chunks,
+                                                           u32* __restrict__ fcnt, u32* __restrict__ nfar,
+                                                           u32* __restrict__ fmax) {
   __shared__ u32 s_far[TG_MAX_SLICES];
   __shared__ u32 s_all;
   const Tile t = tiles[blockIdx.x];
@@ -138,32 +153,44 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_count(int n, int T, int S, 
   }
   if (mine) atomicAdd(&s_all, mine);
   __syncthreads();
-  for (int i = threadIdx.x; i < S; i += TG_THREADS) fcnt[(size_t)i * T + blockIdx.x] = s_far[i];
-  if (threadIdx.x == 0) {
+  if (fcnt) {
+    size_t base;
+    u32 stride;
+    chunks.at(blockIdx.x, S, base, stride);
+    for (int i = threadIdx.x; i < S; i += TG_THREADS) fcnt[base + (size_t)i * stride] = s_far[i];
+  } else if (threadIdx.x == 0) {
     nfar[blockIdx.x] = s_all;
     atomicMax(fmax, s_all);
   }
 }
 
-// first[slice] = the slice's first far entry (slice S: their number).
-__global__ __launch_bounds__(256) void k_tile_slices(int T, int S, const u32* __restrict__ fstart, u32* __restrict__ first) {
+// out[chunk * S + slice] = their first far entry (after the last: the number of far entries).
+__global__ __launch_bounds__(256) void k_tile_slices(int C, int S, const u32* __restrict__ first, const u32* __restrict__ fstart,
+                                                     u32* __restrict__ out) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i <= S) first[i] = fstart[(size_t)i * T];
+  if (i > C * S) return;
+  const int c = i / S, s = i % S;
+  const u32 a = first[c];
+  out[i] = fstart[(size_t)a * (u32)S + (c < C ? (size_t)s * (first[c + 1] - a) : 0)];
 }
 
 // One workgroup per tile: writes its entries' table places and its far entries.
-__global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, int shift, Tile* __restrict__ tiles,
+__global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int S, int shift, Tile* __restrict__ tiles,
                                                            const u32* __restrict__ group0, const u32* __restrict__ far0,
                                                            const int32_t* __restrict__ col, const u32* __restrict__ fcnt,
-                                                           const u32* __restrict__ fstart, uint16_t* __restrict__ eidx,
-                                                           uint16_t* __restrict__ fcol, u32* __restrict__ fadr) {
+                                                           const u32* __restrict__ fstart, TileChunks chunks,
+                                                           uint16_t* __restrict__ eidx, uint16_t* __restrict__ fcol,
+                                                           u32* __restrict__ fadr) {
   __shared__ u32 s_pre[TG_MAX_SLICES];  // far entries of the tile before the slice
   __shared__ u32 s_cnt[TG_MAX_SLICES];
   const int tid = threadIdx.x;
   const Tile t = tiles[blockIdx.x];
   const int w0 = tile_w0(t.b0), w1 = tile_w1(t.b0, n);
+  size_t base;
+  u32 stride;
+  chunks.at(blockIdx.x, S, base, stride);
   for (int i = tid; i < S; i += TG_THREADS) {
-    s_pre[i] = fcnt[(size_t)i * T + blockIdx.x];
+    s_pre[i] = fcnt[base + (size_t)i * stride];
     s_cnt[i] = 0;
   }
   __syncthreads();
@@ -183,7 +210,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, 
     u32 at = (u32)(v - w0);
     if (v < w0 || v >= w1) {
       const int s = v >> shift;
-      const u32 k = atomicAdd(&s_cnt[s], 1u), j = s_pre[s] + k, g = fstart[(size_t)s * T + blockIdx.x] + k;
+      const u32 k = atomicAdd(&s_cnt[s], 1u), j = s_pre[s] + k, g = fstart[base + (size_t)s * stride] + k;
       fcol[g] = (uint16_t)(v & ((1 << shift) - 1));
       fadr[f0 + j] = g;
       at = (u32)TG_WIN + j;
@@ -198,25 +225,25 @@ __global__ __launch_bounds__(TG_THREADS) void k_tile_place(int n, int T, int S, 
 }
 
 // ---- pass 1 ------------------------------------------------------------------------
-// Labels of the far entries in their order.  Workgroup (slice, part): the slice's labels in
-// LDS, then its share of the slice's entries (from first[slice] up to first[slice + 1]), eight per
-// thread and step.
+// Labels of the far entries of chunks [c0, c1) in their order.  Workgroup (slice, part): the
+// slice's labels in LDS, then its share of the slice's entries, eight per thread and step: some
+// of the chunks, or (parts >= chunks) one of parts / chunks shares of a chunk.  Returns at once
+// when the gate's mode is STAGE_ROWS.
 constexpr int FL_THREADS = 1024;
 template <class LT>
-__global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int shift, int parts, const u32* __restrict__ first,
-                                                           const uint16_t* __restrict__ fcol, const LT* __restrict__ labx,
-                                                           LT* __restrict__ fl) {
+__global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int shift, int S, int c0, int c1, int parts,
+                                                           const u32* __restrict__ first, const uint16_t* __restrict__ fcol,
+                                                           const LT* __restrict__ labx, LT* __restrict__ fl,
+                                                           const Ctl* __restrict__ gate) {
   extern __shared__ __align__(16) u32 s_slice[];
   const LT* lab = reinterpret_cast<const LT*>(s_slice);
+  if (gate && gate->mode == STAGE_ROWS) return;
   const int tid = threadIdx.x;
   const int slice = (int)blockIdx.x / parts, part = (int)blockIdx.x % parts;
-  const u32 a = first[slice], b = first[slice + 1];
-  // parts cut at multiples of 8 entries; the first part also takes the unaligned ends
-  const u32 v0 = (a + 7u) / 8u, v1 = max(v0, b / 8u);  // whole groups of 8 inside [a, b)
-  const u32 per = (v1 - v0 + (u32)parts - 1u) / (u32)parts;
-  const u32 g0 = min(v1, v0 + (u32)part * per), g1 = min(v1, g0 + per);
-  const bool ends = part == 0;
-  if (g0 == g1 && !ends) return;
+  const int nc = c1 - c0, sub = parts >= nc ? parts / nc : 1;  // parts = nc * sub, or fewer than nc
+  const int ca = parts >= nc ? c0 + part / sub : c0 + (int)((long long)part * nc / parts);
+  const int cb = parts >= nc ? ca + 1 : c0 + (int)((long long)(part + 1) * nc / parts);
+  const u32 share = parts >= nc ? (u32)(part % sub) : 0u;
   {
     constexpr int PER = 16 / (int)sizeof(LT);
     const long long id0 = (long long)slice << shift;
@@ -227,29 +254,40 @@ __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int shift, int
     for (int i = tid; i < (cnt + PER - 1) / PER; i += FL_THREADS) dst[i] = src[i];
   }
   __syncthreads();
-  if (ends) {
-    const u32 head = min(b, v0 * 8u), tail = max(head, v1 * 8u);
-    if (tid < 8 && a + tid < head) fl[a + tid] = lab[fcol[a + tid]];
-    if (tid >= 64 && tid < 72 && tail + (tid - 64) < b) fl[tail + (tid - 64)] = lab[fcol[tail + (tid - 64)]];
-  }
-  const uint4* src = reinterpret_cast<const uint4*>(fcol);
-  for (u32 g = g0 + tid; g < g1; g += FL_THREADS) {
-    const uint4 q = src[g];
-    const u32 c4[4] = {q.x, q.y, q.z, q.w};
-    u32 x[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = (u32)lab[(c4[k >> 1] >> (16 * (k & 1))) & 0xFFFFu];
-    if constexpr (sizeof(LT) == 2) {
-      reinterpret_cast<uint4*>(fl)[g] = make_uint4(x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16);
-    } else {
-      reinterpret_cast<uint4*>(fl)[2 * (size_t)g] = make_uint4(x[0], x[1], x[2], x[3]);
-      reinterpret_cast<uint4*>(fl)[2 * (size_t)g + 1] = make_uint4(x[4], x[5], x[6], x[7]);
+  u32 turn = 0;  // the thread that takes the next group of 8: every wave gets its share of all chunks together
+  for (int c = ca; c < cb; ++c) {
+    const u32 a = first[(size_t)c * S + slice], b = first[(size_t)c * S + slice + 1];
+    // shares cut at multiples of 8 entries; the first share also takes the unaligned ends
+    const u32 v0 = (a + 7u) / 8u, v1 = max(v0, b / 8u);  // whole groups of 8 inside [a, b)
+    const u32 per = (v1 - v0 + (u32)sub - 1u) / (u32)sub;
+    const u32 g0 = min(v1, v0 + share * per), g1 = min(v1, g0 + per);
+    if (share == 0) {
+      const u32 head = min(b, v0 * 8u), tail = max(head, v1 * 8u);
+      if (tid < 8 && a + tid < head) fl[a + tid] = lab[fcol[a + tid]];
+      if (tid >= 64 && tid < 72 && tail + (tid - 64) < b) fl[tail + (tid - 64)] = lab[fcol[tail + (tid - 64)]];
     }
+    const uint4* src = reinterpret_cast<const uint4*>(fcol);
+    for (u32 g = g0 + (((u32)tid - turn) & (FL_THREADS - 1u)); g < g1; g += FL_THREADS) {
+      const uint4 q = src[g];
+      const u32 c4[4] = {q.x, q.y, q.z, q.w};
+      u32 x[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = (u32)lab[(c4[k >> 1] >> (16 * (k & 1))) & 0xFFFFu];
+      if constexpr (sizeof(LT) == 2) {
+        reinterpret_cast<uint4*>(fl)[g] = make_uint4(x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16);
+      } else {
+        reinterpret_cast<uint4*>(fl)[2 * (size_t)g] = make_uint4(x[0], x[1], x[2], x[3]);
+        reinterpret_cast<uint4*>(fl)[2 * (size_t)g + 1] = make_uint4(x[4], x[5], x[6], x[7]);
+      }
+    }
+    turn = (turn + (g1 - g0)) & (FL_THREADS - 1u);
   }
 }
 
 // ---- pass 2 ------------------------------------------------------------------------
-// One tile per workgroup, in one of two stagings (ctl->mode, chosen by k_colscan_rows).
+// One tile per workgroup (T tiles from t0 on), in one of two stagings (ctl->mode, chosen by
+// k_colscan_rows; rows = TG_BY_ROWS: by rows in any case; TG_RUNS_ONLY: nothing is done when the
+// mode is STAGE_ROWS).
 //
 // STAGE_BLOCKS: consecutive rows (with entries) of the same label form a run.  An entry whose
 // neighbour has the row's own label c only adds to 2|E_c^in| (and, weighted, its weight to
@@ -273,6 +311,7 @@ __global__ __launch_bounds__(FL_THREADS) void k_far_labels(int n, int shift, int
 // per entry says where a run starts, and an entry's run and its number among the staged ones
 // are counts of bits below its lane.  What a wave needs for each of its (up to 24) vectors is
 // held in its lanes and read as scalars.
+enum { TG_BY_MODE = 0, TG_BY_ROWS = 1, TG_RUNS_ONLY = 2 };
 template <class LT, bool WT>
 struct TileLds {
   static constexpr int PER = 16 / (int)sizeof(LT);
@@ -289,11 +328,11 @@ struct TileLds {
 
 template <class LT, bool WT>
 __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
-    int n, int T, int fmax, const Tile* __restrict__ tiles, const int32_t* __restrict__ rp, const uint16_t* __restrict__ eidx,
+    int n, int t0, int T, int fmax, const Tile* __restrict__ tiles, const int32_t* __restrict__ rp, const uint16_t* __restrict__ eidx,
     const u32* __restrict__ fadr, const LT* __restrict__ fl, const LT* __restrict__ labx, const u32* __restrict__ start,
     const u32* __restrict__ D, unsigned long long* __restrict__ cur64, Ctl* __restrict__ ctl, LT* __restrict__ CB,
     const float* __restrict__ w, float* __restrict__ CW, unsigned long long* __restrict__ IWacc, int L, int chunk,
-    const u32* __restrict__ PM, const u32* __restrict__ loc, int always_rows) {
+    const u32* __restrict__ PM, const u32* __restrict__ loc, int rows) {
   using TL = TileLds<LT, WT>;
   constexpr u32 NOLAB = (u32)LabelT<LT>::SENTINEL;
   constexpr u32 NOWHERE = 0x80000000u;  // places are below 2^31, and less an entry's number above -TG_ENT
@@ -318,16 +357,17 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   // each XCD (workgroup b runs on XCD b % 8) takes a contiguous eighth of the tiles
   const int per = (T + 7) / 8, t = (int)(blockIdx.x % 8u) * per + (int)(blockIdx.x / 8u);
   if ((int)(blockIdx.x / 8u) >= per || t >= T) return;
-  const bool by_rows = !WT && sizeof(LT) == 2 && (always_rows || ctl->mode == STAGE_ROWS);  // see k_colscan_rows
-  const Tile tile = tiles[t];
+  const bool by_rows = !WT && sizeof(LT) == 2 && (rows == TG_BY_ROWS || ctl->mode == STAGE_ROWS);  // see k_colscan_rows
+  if (by_rows && rows == TG_RUNS_ONLY) return;
+  const Tile tile = tiles[t0 + t];
   const u32 ne = tile.ne;
   if (ne == 0) return;
-  const int rows = tile.r1 - tile.r0;
+  const int nrows = tile.r1 - tile.r0;
   const int w0 = tile_w0(tile.b0), w1 = tile_w1(tile.b0, n);
   // a wave takes `steps` consecutive groups
   const u32 ng = (ne + TG_GROUP - 1u) / TG_GROUP, steps = (ng + TG_WAVES - 1u) / TG_WAVES, gw = (u32)wv * steps;
   // every load that depends on no other first
-  const int my_row = tile.r0 + min(tid, rows - 1);
+  const int my_row = tile.r0 + min(tid, nrows - 1);
   const uint4* ew = reinterpret_cast<const uint4*>(eidx) + (size_t)tile.g0 * (TG_GROUP / 8);
   const u32* fp = fadr + tile.f0;
   constexpr int FU = 8;
@@ -351,7 +391,7 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   if (tid < 2 * TL::VEC) s_bits[tid] = 0;
   // the row's entries in the tile: [a, b)
   const u32 a = max(ra, tile.e0) - tile.e0, b = min(max(rb, tile.e0) - tile.e0, ne);
-  const bool has = tid < rows && a < b;
+  const bool has = tid < nrows && a < b;
   const u64 hasm = __ballot(has);
   // the label of the wave's last row with entries
   if (hasm ? lane == 63 - __clzll((long long)hasm) : lane == 0) s_last[wv] = hasm ? own : SENT;
@@ -397,7 +437,7 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
   if (tid == 0) s_first[nruns] = (uint16_t)ne;
   if (has)
     for (u32 v = (a + 63u) / 64u; v * 64u < b; ++v) s_vrun[v] = (uint16_t)run;
-  if (WT && tid < rows) {
+  if (WT && tid < nrows) {
     s_ilo[tid] = 0ull;
     s_ihi[tid] = 0ull;
   }
