@@ -2712,10 +2712,9 @@ cq_status cq_server_submit_score(cq_server* srv, const cq_graph* g, const int32_
   r->n = g->n;
   r->L = num_labels;
   r->ha = h_labels;
-  // the workspace with room for the tiles' far labels where the arena holds it
   const ScoreLayout lay = graph_score_layout(g, num_labels);
-  const int64_t all = (int64_t)(cqsrv::aup(4 * (size_t)g->n) + cqsrv::aup(lay.total) + cqsrv::aup(sizeof(cq_score_result)));
-  r->ws_bytes = all <= srv->cfg.memory_budget ? lay.total : lay.min_total;
+  r->ws_bytes = lay.min_total;
+  if (lay.total > lay.min_total) r->ws_more = lay.total;  // room for the tiles' far labels
   // inside a grouped launch: the task's workspace and, at most, one group's interleaved
   // labels (8 bytes per node; batch_layout)
   r->group_ws = cqsrv::aup(score_layout(g->n, g->nnz, num_labels).total) + cqsrv::aup(8 * (size_t)g->n);

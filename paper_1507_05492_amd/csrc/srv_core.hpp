@@ -34,7 +34,8 @@ struct Req {
   int32_t n = 0, L = 0, La = 0, Lb = 0;
   const int32_t* ha = nullptr;
   const int32_t* hb = nullptr;
-  size_t ws_bytes = 0;  // workspace when run alone
+  size_t ws_bytes = 0;  // workspace when run alone: the least one, or (set at admission) ws_more
+  size_t ws_more = 0;   // workspace with which it runs faster (0: none)
   size_t group_ws = 0;  // workspace inside a grouped launch (score requests)
   size_t foot = 0;      // device bytes when run alone (set by submit)
   bool small = false;   // may join a grouped launch
@@ -105,6 +106,11 @@ class Arena {
       }
     }
   }
+  size_t largest_free() const {
+    size_t most = 0;
+    for (const auto& kv : free_) most = std::max(most, kv.second);
+    return most;
+  }
   size_t in_use() const { return in_use_; }
   size_t peak() const { return peak_; }
   void reset_peak() { peak_ = in_use_; }
@@ -174,6 +180,7 @@ class Scheduler {
     r->t_submit = Clock::now();
     {
       std::lock_guard<std::mutex> lk(mu_);
+      max_foot_ = std::max(max_foot_, r->foot);
       if (stop_) {
         delete r;
         if (why) *why = "the server is shutting down";
@@ -296,6 +303,23 @@ class Scheduler {
     size_t off = 0, len = 0;
   };
 
+  // Whether the head may have `more` bytes in place of its footprint: the requests queued behind
+  // it, then any of the largest footprint seen, must find the room in the idle slots beside it
+  // that they find beside the smaller one.
+  bool leaves_room(const Req& head, size_t more) const {
+    Arena least = arena_, large = arena_;
+    size_t off;
+    if (!large.alloc(more, &off) || !least.alloc(head.foot, &off)) return false;
+    size_t idle = 0;
+    for (const Slot& sl : slots_) idle += sl.busy ? 0 : 1;
+    for (size_t i = 1; i < idle; ++i) {  // one is the head's
+      const size_t want = i < pending_.size() ? pending_[i]->foot : std::min(max_foot_, least.largest_free());
+      if (want == 0 || !least.alloc(want, &off)) break;
+      if (!large.alloc(want, &off)) return false;
+    }
+    return true;
+  }
+
   // Completions, then admissions into free slots in arrival order.  A small scoring
   // request at the head takes the small scoring requests queued behind it (up to
   // max_batch, as many as fit the arena) into one grouped launch; any other head waits
@@ -349,6 +373,13 @@ class Scheduler {
           grouped = take.size() > 1;
         }
         if (!grouped) {
+          if (head->ws_more > head->ws_bytes) {
+            const size_t more = head->foot - aup(head->ws_bytes) + aup(head->ws_more);
+            if (leaves_room(*head, more)) {
+              head->ws_bytes = head->ws_more;
+              head->foot = more;
+            }
+          }
           len = head->foot;
           if (!arena_.alloc(len, &off)) break;  // wait for memory (arrival order is kept)
         }
@@ -381,6 +412,7 @@ class Scheduler {
 
   Config cfg_;
   size_t cap_;  // usable arena bytes
+  size_t max_foot_ = 0;  // largest least footprint of the requests so far
   Executor* ex_;
   Arena arena_;
   std::vector<Slot> slots_;  // touched by the worker thread only
