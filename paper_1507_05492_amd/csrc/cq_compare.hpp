@@ -38,9 +38,11 @@ constexpr u32 CMP_BAD_B = 0xFFFFu;    // detected label outside [0, Lb)
 // (at most 80 KB of LDS each).
 struct CellsNarrow {  // 16-bit label spaces
   static constexpr int ROWS = CB_ROWS, SUB = 8, BBITS = 16;
+  static constexpr bool SHARED = false;  // one workgroup per band
 };
 struct CellsWide {  // label spaces beyond 16 bits: small communities, so more and shorter rows
   static constexpr int ROWS = 256, SUB = 2, BBITS = 24;
+  static constexpr bool SHARED = true;  // several for a large one
 };
 
 // A flag in LDS that other threads of the workgroup may set: read as a workgroup-scope
@@ -410,6 +412,19 @@ constexpr int BH_NPT = 8;             // nodes per thread and round in k_bin_his
 constexpr int BIN_A_MAX = 4096;       // ground-truth bins (block_excl_scan4, 16-bit bin numbers)
 constexpr int BIN_B_MAX = 512;        // detected bins
 constexpr int BIN_RB_MIN = 10, BIN_RB_MAX = 14;  // log2 of the detected labels per bin (LDS counters)
+// A bin of BIN_LARGE nodes or more (one with a giant community) is shared: its labels are counted
+// by slices of BIN_SLICE nodes, and its cells by up to 16 workgroups, each of which walks all of
+// the bin's words and takes the detected labels of one residue.  3M nodes, half of them in one of
+// 100,000 communities, against 1,000 unrelated ones: 71 ms with a workgroup per bin, 0.83 shared
+// (segments 1.26); a fifth in one, against 5,000: 32, 0.46 and 1.29.
+constexpr int BIN_LARGE_LOG2 = 16;
+constexpr u32 BIN_LARGE = 1u << BIN_LARGE_LOG2, BIN_SLICE = BIN_LARGE / 2;
+// log2 of the workgroups for the cells of a bin of sz nodes
+__host__ __device__ __forceinline__ u32 bin_classes(u32 sz) {
+  u32 lg = 0;
+  while (lg < 4 && (sz >> (BIN_LARGE_LOG2 + lg)) != 0) ++lg;
+  return lg;
+}
 
 // Nodes per bin: row blockIdx.x of H (nbA ground-truth bins, then nbB detected bins; nbB = 0
 // leaves the detected labels out).  Labels out of range are flagged and not counted.
@@ -444,20 +459,34 @@ __global__ __launch_bounds__(BH_THREADS) void k_bin_hist(int n, const int32_t* _
   if (threadIdx.x == 0 && s_bad) atomicOr(&ctl->flags, F_LABEL);
 }
 
+// What k_bin_totals prepares for large bins.
+struct LargeBins {
+  u32* slices;  // bin << 16 | slice, ctl->parts of them
+  u32 *A, *B;   // label sizes, and the ground-truth labels' outputs of k_cmp_cells: cleared for large bins
+  u64* RA11;
+  u32* RMAX;
+  double* RF;
+  u64* RXL;
+  int La, ra, Lb, rb;
+};
+
 // Bin sizes SZ (nbA + nbB) from the W rows of H; the last workgroup to finish (*done counts
 // them; it must be zero at launch) turns them into places: SA[0..nbA] for the ground-truth
-// bins, SB[0..nbB] for the detected ones, CUR (nbA + nbB) the claim cursors, BORD the
-// non-empty ground-truth bins by decreasing floor(log2 size), ctl->K their number.
+// bins, SB[0..nbB] for the detected ones, CUR (nbA + nbB) the claim cursors, BORD the work
+// of k_cmp_cells by decreasing floor(log2 size) of the ground-truth bins (see there), ctl->K its
+// items; and prepares the counting of large bins by slices.
 __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_bin_totals(int W, int nbA, int nbB, const u32* __restrict__ H,
                                                                       u32* __restrict__ SZ, u32* __restrict__ SA,
                                                                       u32* __restrict__ SB, u32* __restrict__ CUR,
                                                                       u32* __restrict__ BORD, u32* __restrict__ done,
-                                                                      Ctl* __restrict__ ctl) {
+                                                                      Ctl* __restrict__ ctl, LargeBins lb) {
   static_assert(CS_LABELS * CS_GROUPS == CP_THREADS, "block_excl_scan4");
   __shared__ u32 s_n[CS_GROUPS][CS_LABELS];
   __shared__ u32 s_v[BIN_A_MAX];
   __shared__ u32 s_w[CP_THREADS / 64];
   __shared__ u32 s_bcnt[33], s_boff[33];
+  __shared__ u32 s_slices, s_larges;
+  __shared__ uint16_t s_large[BIN_B_MAX];
   const int nb = nbA + nbB, tid = threadIdx.x;
   const int lane = tid % CS_LABELS, grp = tid / CS_LABELS;
   const int c = (int)blockIdx.x * CS_LABELS + lane;
@@ -475,11 +504,27 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_bin_totals(int W, int
   }
   if (!last_workgroup(done, gridDim.x)) return;
   if (tid < 33) s_bcnt[tid] = 0;
+  if (tid == 0) s_slices = s_larges = 0;
   for (int i = tid; i < nbA; i += CP_THREADS) s_v[i] = SZ[i];
   __syncthreads();
+  auto slices = [&](u32 bin, u32 sz) {
+    const u32 k = (sz + BIN_SLICE - 1u) / BIN_SLICE, at = atomicAdd(&s_slices, k);
+    for (u32 j = 0; j < k; ++j) lb.slices[at + j] = bin << 16 | j;
+  };
   for (int i = tid; i < nbA; i += CP_THREADS) {
     const u32 sz = s_v[i];
-    if (sz) atomicAdd(&s_bcnt[size_bucket(sz)], 1u);
+    if (sz) atomicAdd(&s_bcnt[size_bucket(sz)], 1u << bin_classes(sz));
+    if (sz >= BIN_LARGE) {
+      slices((u32)i, sz);
+      for (int r = i << lb.ra; r < min(lb.La, (i + 1) << lb.ra); ++r) {
+        lb.A[r] = 0;
+        lb.RA11[r] = 0;
+        lb.RMAX[r] = 0;
+        lb.RF[r] = 0.0;
+        lb.RXL[2 * (size_t)r] = 0;
+        lb.RXL[2 * (size_t)r + 1] = 0;
+      }
+    }
   }
   u32 total = block_excl_scan4(s_v, nbA, s_w);
   for (int i = tid; i < nbA; i += CP_THREADS) {
@@ -498,17 +543,34 @@ __global__ __launch_bounds__(CS_LABELS * CS_GROUPS) void k_bin_totals(int W, int
   __syncthreads();
   for (int i = tid; i < nbA; i += CP_THREADS) {
     const u32 sz = (i + 1 < nbA ? s_v[i + 1] : total) - s_v[i];
-    if (sz) BORD[atomicAdd(&s_boff[size_bucket(sz)], 1u)] = (u32)i;
+    if (!sz) continue;
+    const u32 lg = bin_classes(sz), at = atomicAdd(&s_boff[size_bucket(sz)], 1u << lg);
+    for (u32 res = 0; res < 1u << lg; ++res) BORD[at + res] = lg << 24 | res << 16 | (u32)i;
   }
   __syncthreads();
-  for (int i = tid; i < nbB; i += CP_THREADS) s_v[i] = SZ[nbA + i];
+  for (int i = tid; i < nbB; i += CP_THREADS) {
+    const u32 sz = SZ[nbA + i];
+    s_v[i] = sz;
+    if (sz >= BIN_LARGE) {
+      slices((u32)(nbA + i), sz);
+      s_large[atomicAdd(&s_larges, 1u)] = (uint16_t)i;
+    }
+  }
   __syncthreads();
+  // the whole workgroup clears a large detected bin's counters (up to 16,384)
+  for (u32 k = 0; k < s_larges; ++k) {
+    const int i = s_large[k];
+    for (int b = (i << lb.rb) + tid; b < min(lb.Lb, (i + 1) << lb.rb); b += CP_THREADS) lb.B[b] = 0;
+  }
   total = block_excl_scan4(s_v, nbB, s_w);
   for (int i = tid; i < nbB; i += CP_THREADS) {
     SB[i] = s_v[i];
     CUR[nbA + i] = s_v[i];
   }
-  if (tid == 0) SB[nbB] = total;
+  if (tid == 0) {
+    SB[nbB] = total;
+    ctl->parts = s_slices;
+  }
 }
 
 // Writes the nodes of one chunk (NPT * 1024 nodes) into their bins, as k_cmp_part does:
@@ -574,20 +636,35 @@ __global__ __launch_bounds__(CP_THREADS) void k_bin_part(int n, int chunks, cons
   }
 }
 
-// Label sizes from the partitioned words, one workgroup per bin: blocks [0, nbA) write A,
-// the others B.  Dynamic LDS: one counter per label of a bin.
+// Label sizes from the partitioned words, one workgroup per bin: blocks [0, nbA) write A, blocks
+// [nbA, nb) B; the blocks from nb on add the slices of large bins to the labels' cleared sizes.
+// Dynamic LDS: one counter per label of a bin.
 constexpr int BC_THREADS = 512;
 constexpr int BC_UNROLL = 4;
-__global__ __launch_bounds__(BC_THREADS) void k_bin_count(int La, int ra, int nbA, int Lb, int rb, const u32* __restrict__ SA,
-                                                          const u32* __restrict__ SB, const u32* __restrict__ E,
-                                                          const uint16_t* __restrict__ EB, u32* __restrict__ A,
-                                                          u32* __restrict__ B) {
+__global__ __launch_bounds__(BC_THREADS) void k_bin_count(int La, int ra, int nbA, int Lb, int rb, int nb,
+                                                          const u32* __restrict__ SA, const u32* __restrict__ SB,
+                                                          const u32* __restrict__ E, const uint16_t* __restrict__ EB,
+                                                          u32* __restrict__ A, u32* __restrict__ B,
+                                                          const u32* __restrict__ slices, const Ctl* __restrict__ ctl) {
   extern __shared__ u32 s_cnt[];
-  const bool side_a = (int)blockIdx.x < nbA;
-  const int bin = side_a ? (int)blockIdx.x : (int)blockIdx.x - nbA;
+  int bin = (int)blockIdx.x, slice = -1;
+  if (bin >= nb) {
+    const u32 i = blockIdx.x - (u32)nb;
+    if (i >= ctl->parts) return;
+    bin = (int)(slices[i] >> 16);
+    slice = (int)(slices[i] & 0xFFFFu);
+  }
+  const bool side_a = bin < nbA;
+  if (!side_a) bin -= nbA;
   const int r = side_a ? ra : rb;
   const int L = side_a ? La : Lb;
-  const u32 s0 = side_a ? SA[bin] : SB[bin], s1 = side_a ? SA[bin + 1] : SB[bin + 1];
+  u32 s0 = side_a ? SA[bin] : SB[bin], s1 = side_a ? SA[bin + 1] : SB[bin + 1];
+  if (slice >= 0) {
+    s0 += (u32)slice * BIN_SLICE;
+    s1 = min(s1, s0 + BIN_SLICE);
+  } else if (s1 - s0 >= BIN_LARGE) {
+    return;
+  }
   for (int i = threadIdx.x; i < (1 << r); i += BC_THREADS) s_cnt[i] = 0;
   __syncthreads();
   for (u32 e0 = s0; e0 < s1; e0 += BC_THREADS * BC_UNROLL) {  // uniform trip count
@@ -603,10 +680,15 @@ __global__ __launch_bounds__(BC_THREADS) void k_bin_count(int La, int ra, int nb
   __syncthreads();
   const int c0 = bin << r, c1 = min(L, c0 + (1 << r));
   u32* N = side_a ? A : B;
-  for (int c = c0 + threadIdx.x; c < c1; c += BC_THREADS) N[c] = s_cnt[c - c0];
+  for (int c = c0 + threadIdx.x; c < c1; c += BC_THREADS) {
+    const u32 x = s_cnt[c - c0];
+    if (slice < 0) N[c] = x;
+    else if (x) atomicAdd(&N[c], x);
+  }
 }
 
-// One band at a time per workgroup (bands by decreasing size from the work queues).
+// One item at a time per workgroup, from the work queues: a band, or (shared ones) lg << 24 |
+// res << 16 | band, the cells of a band whose detected labels are res modulo 2^lg.
 // A = |c_i|, B = |c'_j|; outputs per ground-truth label i: RA11 = Σ_j C(n_ij, 2),
 // RMAX = max_j n_ij, RF = max_j 2 n_ij / (|c_i| + |c'_j|) (Eq. (3)), RXL = Σ_j fix96 of
 // (n_ij / N) log n_ij; per detected label: COLMAX = max_i n_ij (cells of one node are left
@@ -621,7 +703,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
                                                           u32* __restrict__ RMAX, double* __restrict__ RF,
                                                           u64* __restrict__ RXL, int32_t* __restrict__ eci,
                                                           int32_t* __restrict__ ecj, int64_t* __restrict__ ecnt,
-                                                          long long ecap, u32* __restrict__ wq, int La, int ra) {
+                                                          long long ecap, u32* __restrict__ wq, int La, int ra, u32 Lb) {
   constexpr int CC_SUB = S::SUB;
   constexpr u32 BMASK = (1u << S::BBITS) - 1u;
   constexpr u32 BAD_B = BMASK;
@@ -631,7 +713,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
   __shared__ u32 s_hcnt[S::ROWS * CC_SUB];  // its count, spread over CC_SUB counters
   __shared__ u64 r_a11[S::ROWS], r_f[S::ROWS], r_xlo[S::ROWS], r_xhi[S::ROWS];
   __shared__ u32 r_max[S::ROWS], r_ai[S::ROWS];
-  __shared__ u32 s_item, s_over, s_sp, s_new, s_seen, s_est;
+  __shared__ u32 s_item, s_over, s_sp, s_new, s_seen, s_est, s_guess, s_bound;
   __shared__ u32 s_stack[CC_STACK];  // pending classes: residue << 5 | log2 of the modulus
   const int tid = threadIdx.x;
   const u32 K = ctl->K;  // non-empty bands
@@ -642,7 +724,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
     __syncthreads();
     const u32 item = s_item;
     if (item == 0xFFFFFFFFu) break;
-    const u32 band = BORD[item];
+    const u32 code = BORD[item], band = S::SHARED ? code & 0xFFFFu : code;
     const u32 base = SBS[band], len = SZB[band];
     // a band's labels: the listed ones, or (SBA null) the 2^ra labels of its number
     const u32 a0 = SBA ? SBA[band] : band << ra;
@@ -656,7 +738,7 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
       r_ai[r] = A[a0 + r];
     }
     if (tid == 0) {
-      s_stack[0] = 0;  // residue 0 mod 1: the whole band
+      s_stack[0] = S::SHARED ? ((code >> 16) & 0xFFu) << 5 | code >> 24 : 0u;
       s_sp = 1;
     }
     __syncthreads();
@@ -673,9 +755,11 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
         s_over = 0;
         s_new = 0;
         s_seen = 0;
+        s_bound = 0;
         s_est = len >> lg;  // the class's expected node count: a bound on its cells
       }
       __syncthreads();
+
       // each row's first detected label is taken from the band's first words, before the
       // counting threads would all meet it unset at once
       if ((u32)tid < len) {
@@ -717,13 +801,8 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
           const u32 e = e0 + (u32)tid + (u32)k * CC_THREADS;
           wv[k] = e < len ? E[base + e] : 0xFFFFFFFFu;  // b = BAD_B: skipped
         }
-#pragma unroll
-        for (int k = 0; k < CC_BATCH; ++k) {
-          const u32 w = wv[k];
-          const u32 b = w & BMASK;
-          if (b == BAD_B || (b & mask) != res) continue;
-          ++nseen;
-          const u32 r = w >> S::BBITS;
+        auto count = [&](u32 w) {
+          const u32 b = w & BMASK, r = w >> S::BBITS;
           u32 hb = s_hot[r];
           if (hb == EMPTY) {
             const u32 old = atomicCAS(&s_hot[r], EMPTY, b);
@@ -733,6 +812,33 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
             atomicAdd(&s_hcnt[r * CC_SUB + ((u32)tid & (CC_SUB - 1))], 1u);
           else
             insert(w, 1u);
+        };
+        if (!S::SHARED || lg == 0) {
+#pragma unroll
+          for (int k = 0; k < CC_BATCH; ++k) {
+            const u32 b = wv[k] & BMASK;
+            if (b == BAD_B || (!S::SHARED && (b & mask) != res)) continue;
+            ++nseen;
+            count(wv[k]);
+          }
+        } else {
+          // few words are the class's: every lane counts its next one, so a wave takes as many
+          // turns as its fullest lane has words
+          u32 hit = 0;
+#pragma unroll
+          for (int k = 0; k < CC_BATCH; ++k) {
+            const u32 b = wv[k] & BMASK;
+            hit |= (b != BAD_B && (b & mask) == res ? 1u : 0u) << k;
+          }
+          nseen += (u32)__popc(hit);
+          while (hit) {
+            const u32 k = (u32)__ffs((int)hit) - 1u;
+            hit &= hit - 1u;
+            u32 w = wv[0];
+#pragma unroll
+            for (int j = 1; j < CC_BATCH; ++j) w = k == (u32)j ? wv[j] : w;
+            count(w);
+          }
         }
         if (e0 == 0 && len > CC_THREADS * CC_BATCH) {
           // after the first batch: if new keys came at a rate that would overfill the table
@@ -743,14 +849,28 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
             atomicAdd(&s_seen, (u32)sn);
           }
           __syncthreads();
-          if (tid == 0 && s_seen > 0) {
-            const u64 est = (u64)s_new * (u64)(len >> lg) / s_seen;
-            if (est > CC_SLOTS * 5u / 8u) {
-              s_est = (u32)est;
-              s_over = 1;
-            }
+          if (tid == 0) {
+            const u64 est = s_seen ? (u64)s_new * (u64)(len >> lg) / s_seen : 0u;
+            s_guess = est > CC_SLOTS * 5u / 8u ? (u32)est : 0u;
           }
           __syncthreads();
+          if (s_guess) {
+            // the rate falls when most cells have been met: a row has no more of them than nodes,
+            // nor than detected labels (half of 3M nodes in one row, 1,000 detected labels: a
+            // thousand cells, where the rate of the first batch promises 360,000)
+            static_assert(S::ROWS <= CC_THREADS, "a row per thread");
+            const u32 most = wave_sum_u32((u32)tid < rows ? min((r_ai[tid] + mask) >> lg, (Lb + mask) >> lg) : 0u);
+            if ((tid & 63) == 0 && most) atomicAdd(&s_bound, most);
+            __syncthreads();
+            if (tid == 0) {
+              const u32 est = min(s_guess, s_bound);
+              if (est > CC_SLOTS * 5u / 8u) {
+                s_est = est;
+                s_over = 1;
+              }
+            }
+            __syncthreads();
+          }
         }
         if (lds_flag(&s_over)) break;  // the class is being split
       }
@@ -842,6 +962,15 @@ __global__ __launch_bounds__(CC_THREADS, 4) void k_cmp_cells(const u32* __restri
     }
     for (u32 r = tid; r < rows; r += CC_THREADS) {
       const size_t i = (size_t)a0 + r;
+      if (S::SHARED && (code >> 24)) {  // the other workgroups of the band add to the same rows
+        if (r_max[r] == 0) continue;
+        if (r_a11[r]) atomicAdd(&RA11[i], r_a11[r]);
+        atomicMax(&RMAX[i], r_max[r]);
+        atomicMax(reinterpret_cast<u64*>(&RF[i]), r_f[r]);
+        const u64 lo = r_xlo[r], old = atomicAdd(&RXL[2 * i], lo), hi = r_xhi[r] + (old + lo < old ? 1u : 0u);
+        if (hi) atomicAdd(&RXL[2 * i + 1], hi);
+        continue;
+      }
       RA11[i] = r_a11[r];
       RMAX[i] = r_max[r];
       RF[i] = __longlong_as_double((long long)r_f[r]);

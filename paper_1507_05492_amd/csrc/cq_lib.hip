@@ -441,6 +441,7 @@ struct CmpLayout {
   size_t HA, sbk, SBA, SZB, SBS, CUR, BORD, E;
   // wide path (a label space beyond 16 bits): log2 labels per bin, bins, histogram grid,
   // nodes per thread and chunks of the partition
+  size_t slices;
   bool wide, binsB;  // binsB: the detected labels' sizes come from bins too
   int ra, rb, nbA, nbB, Wh, npt, chunks;
   size_t SBB, EB;
@@ -476,6 +477,9 @@ bool wide_bins(int64_t n, int64_t La, int64_t Lb, CmpLayout* s) {
   s->nbB = s->binsB ? (int)((Lb + (1 << rb) - 1) >> rb) : 0;
   return s->nbA <= BIN_A_MAX && s->nbB <= BIN_B_MAX;
 }
+
+// Slices of the large bins of both sides at most.
+int64_t wide_slices(int64_t n) { return 2 * (n / BIN_SLICE + n / BIN_LARGE); }
 
 CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
   CmpLayout s{};
@@ -563,7 +567,8 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
   w.SBS = k.take(4 * ((size_t)w.nbA + 1));
   w.SBB = k.take(4 * ((size_t)w.nbB + 1));
   w.CUR = k.take(4 * (size_t)nb);
-  w.BORD = k.take(4 * (size_t)w.nbA);
+  w.BORD = k.take(4 * ((size_t)w.nbA + (size_t)(n / BIN_SLICE)));  // a large bin has a class per BIN_SLICE nodes at most
+  w.slices = k.take(4 * (size_t)wide_slices(n));
   w.E = k.take(4 * (size_t)n);
   w.EB = w.binsB ? k.take(2 * (size_t)n) : 0;
   w.parts = k.take(sizeof(CmpPart) * (w.Ga + w.Gb));
@@ -1208,6 +1213,8 @@ void compare_launch_wide(cq_context* ctx, int32_t n, const int32_t* la, int32_t 
   double* RF = at<double>(ws, lay.RF);
   u64* RXL = at<u64>(ws, lay.RXL);
   const int nb = lay.nbA + lay.nbB;
+  u32* slices = at<u32>(ws, lay.slices);
+  const LargeBins large{slices, A, B, RA11, RMAX, RF, RXL, La, lay.ra, Lb, lay.rb};
   {
     StageMark mk(ctx, ST_SETUP, timed);
     const int words = (int)(sizeof(Ctl) / 4) + (int)WQ_WORDS + Lb;
@@ -1218,7 +1225,7 @@ void compare_launch_wide(cq_context* ctx, int32_t n, const int32_t* la, int32_t 
     u32* H = at<u32>(ws, lay.HA);
     k_bin_hist<<<lay.Wh, BH_THREADS, (size_t)nb * 4, s>>>(n, la, La, lay.ra, lay.nbA, lb, Lb, lay.rb, lay.nbB, H, ctl);
     k_bin_totals<<<(nb + CS_LABELS - 1) / CS_LABELS, CS_LABELS * CS_GROUPS, 0, s>>>(lay.Wh, lay.nbA, lay.nbB, H, SZ, SA, SB,
-                                                                                 CUR, BORD, &ctl->done, ctl);
+                                                                                 CUR, BORD, &ctl->done, ctl, large);
   }
   {
     StageMark mk(ctx, ST_SCATTER, timed);
@@ -1236,14 +1243,15 @@ void compare_launch_wide(cq_context* ctx, int32_t n, const int32_t* la, int32_t 
     StageMark mk(ctx, ST_HIST_B, timed);
     if (!lay.binsB) label_totals(n, lb, Lb, lay.Wb, at<u32>(ws, lay.HB), B, ctl, s);
     const size_t shm = (size_t)4 << (lay.binsB ? std::max(lay.ra, lay.rb) : lay.ra);
-    k_bin_count<<<nb, BC_THREADS, shm, s>>>(La, lay.ra, lay.nbA, Lb, lay.rb, SA, SB, E, EB, A, B);
+    k_bin_count<<<(unsigned)(nb + wide_slices(n)), BC_THREADS, shm, s>>>(La, lay.ra, lay.nbA, Lb, lay.rb, nb, SA, SB, E, EB, A, B,
+                                                                        slices, ctl);
   }
   const long long ecap = cells ? cells->capacity : 0;
   {
     StageMark mk(ctx, ST_GROUPS, timed);
     k_cmp_cells<CellsWide><<<cells_grid<CellsWide>(ctx), CC_THREADS, 0, s>>>(
         E, SA, SZ, nullptr, BORD, ctl, A, B, (double)n, COLMAX, RA11, RMAX, RF, RXL, cells ? cells->ci : nullptr,
-        cells ? cells->cj : nullptr, cells ? cells->count : nullptr, ecap, wq, La, lay.ra);
+        cells ? cells->cj : nullptr, cells ? cells->count : nullptr, ecap, wq, La, lay.ra, (u32)Lb);
   }
   CmpPart* parts = at<CmpPart>(ws, lay.parts);
   {
@@ -1310,7 +1318,7 @@ void compare_launch_bands(cq_context* ctx, int32_t n, const int32_t* la, int32_t
     StageMark mk(ctx, ST_GROUPS, timed);
     k_cmp_cells<CellsNarrow><<<cells_grid<CellsNarrow>(ctx), CC_THREADS, 0, s>>>(
         E, SBS, SZB, SBA, BORD, ctl, A, B, (double)n, COLMAX, RA11, RMAX, RF, RXL, cells ? cells->ci : nullptr,
-        cells ? cells->cj : nullptr, cells ? cells->count : nullptr, ecap, wq, La, 0);
+        cells ? cells->cj : nullptr, cells ? cells->count : nullptr, ecap, wq, La, 0, (u32)Lb);
   }
   CmpPart* parts = at<CmpPart>(ws, lay.parts);
   {
