@@ -577,18 +577,21 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
     }
   }
   if constexpr (WT) {
-    // every weight once: a staged entry's to its place, an own-label entry's into its run's sum,
-    // the runs of a vector one after another
+    // every weight once: a staged entry's to its place, an own-label entry's into its run's sum.
+    // A vector inside one run adds in registers, reduced once per run; in a vector of several runs
+    // every lane adds to its run's words in LDS (a reduction per run took most of the pass where
+    // runs are short: 2M nodes, 40M entries and labels that change every few rows 195 us, now 164).
     u32 wrun = SENT;  // the run whose own-label weights wacc sums
     WeightSum wacc;
+    auto add_to_run = [&](u32 r, u64 lo, u64 hi) {
+      const u64 old = atomicAdd(&s_ilo[r], lo);
+      hi += old + lo < old ? 1ull : 0ull;
+      if (hi) atomicAdd(&s_ihi[r], hi);
+    };
     auto wflush = [&]() {
       if (wrun == SENT) return;
       const u128 sum = wave_sum_u128(wacc.value());
-      if (lane == 0) {
-        const unsigned long long lo = (unsigned long long)sum, old = atomicAdd(&s_ilo[wrun], lo);
-        const unsigned long long hi = (unsigned long long)(sum >> 64) + (old + lo < old ? 1ull : 0ull);
-        if (hi) atomicAdd(&s_ihi[wrun], hi);
-      }
+      if (lane == 0) add_to_run(wrun, (u64)sum, (u64)(sum >> 64));
       wacc = WeightSum();
     };
     constexpr int U = 8;  // loads in flight
@@ -602,26 +605,22 @@ __global__ __launch_bounds__(TG_THREADS, 8) void k_tile_gather(
         const int v = vb + k;
         if (v >= nv) break;
         const u32 slo = of(nlo, v), shi = of(nhi, v), bl = of(vbl, v), bh = of(vbh, v);
-        u32 r = of(vr, v);
-        const u32 to = (bl | bh) ? s_to[below_in(bl, bh, r)] : of(vt, v);
+        const bool several = (bl | bh) != 0u;  // uniform
+        const u32 r = several ? below_in(bl, bh, of(vr, v)) : of(vr, v);
+        const u32 to = several ? s_to[r] : of(vt, v);
         const bool staged = __builtin_amdgcn_inverse_ballot_w64(((u64)shi << 32) | slo);
         if (staged && to != NOWHERE) CW[below_in(slo, shi, to + of(vp, v))] = wt[k];
+        const bool mine = !staged && (v0 + (u32)v) * 64u + (u32)lane < ne;
         u64 vlo, vhi;
         WeightSum::split(wt[k], vlo, vhi);
-        const bool mine = !staged && (v0 + (u32)v) * 64u + (u32)lane < ne;
-        u64 bits = ((u64)bh << 32) | bl;
-        int lo = 0;
-        while (true) {
-          const int hi = bits ? __ffsll((unsigned long long)bits) : 64;
+        if (several) {
+          if (mine) add_to_run(r, vlo, vhi);
+        } else if (__ballot(mine)) {
           if (r != wrun) {
             wflush();
             wrun = r;
           }
-          if (mine && lane >= lo && lane < hi) wacc.add(vlo, vhi);
-          if (!bits) break;
-          bits &= bits - 1ull;
-          lo = hi;
-          ++r;
+          if (mine) wacc.add(vlo, vhi);
         }
       }
     }
