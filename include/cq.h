@@ -153,7 +153,9 @@ typedef struct {
  * entry, rounded up to 512 entries a tile, 6 bytes per entry whose neighbour's id is far
  * from the row's, 32 bytes per tile, and 4 bytes per 2^15 (2^16 beyond 2^24 nodes) ids for
  * every 2n far entries.  A plan that moves labels from the caller's order
- * to the stored one comes with them.  CQ_GRAPH_NO_BLOCKS never builds tiles, CQ_GRAPH_BLOCKS
+ * to the stored one comes with them.  Beyond 2^24 nodes a weighted graph has no tiles, an
+ * unweighted one none if the memory for them cannot be allocated, and calls with more than
+ * 65,535 label ids do not use them.  CQ_GRAPH_NO_BLOCKS never builds tiles, CQ_GRAPH_BLOCKS
  * builds them for any n <= 2^24 (both flags at once: CQ_E_INVALID_ARG).  owned_bytes in
  * cq_graph_stats reports the total.  A tiled graph's workspace has room for the far entries'
  * labels (2 bytes each, 4 with more than 65,535 label ids).  A call with a workspace that
@@ -217,7 +219,8 @@ typedef struct {
 } cq_score_result;
 
 /* cq_score_result.staging.  The results do not depend on it. */
-#define CQ_STAGING_ROWS_ONLY 0u  /* the graph's row-major storage (no tiles; batched calls) */
+#define CQ_STAGING_ROWS_ONLY 0u  /* rows as stored: graphs without tiles, batched calls, and graphs of more
+                                    than 2^24 nodes (whose tiles are staged at per-node offsets) */
 #define CQ_STAGING_BLOCKS 1u     /* tiles, compact staging with one claim per run of equal labels */
 #define CQ_STAGING_ROWS 2u       /* a tiled graph staged at per-node offsets: the partition
                                     does not follow the stored order (see cq_context_set_row_staging) */

@@ -1949,8 +1949,8 @@ struct ScoreVis {
 // (j, w) adds w to the weight sums and, for j != g, w |E_gj| / (2W |g| |j|) to the
 // penalty, truncated to a multiple of 2^-96 (term by term, so the sum is exact).  With
 // compact staging (tiled graphs) the segment holds only entries of other
-// labels (and far entries): the edge pass has already counted the own-label entries
-// (high word of the cursor) and summed their weights into IW[g], which both sums add.
+// labels: the edge pass has already counted the own-label entries (high word of the cursor)
+// and summed their weights into IW[g], which both sums add.
 struct WeightedOut {
   u64* SW;
   u64* IW;

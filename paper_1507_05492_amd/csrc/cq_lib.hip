@@ -270,7 +270,7 @@ unsigned colscan_grid(int64_t L) { return grid_for(L, CS_LABELS, 1u << 30); }
 struct ScoreLayout {
   bool priv, small;  // small: labels fit 16 bits (num_labels <= 65535)
   int chunk, W, G;
-  size_t ctl, wq, N, D, start, order, I, NP, PEN, SZ, cursor, loc, HN, HD, RL, labx, CB, parts, res, total;
+  size_t ctl, wq, N, D, start, order, I, NP, PEN, SZ, cursor, loc, HN, HD, RL, labx, CB, parts, total;
   size_t CW, SW, IW, PENW, INVN;  // weighted graphs only (0 otherwise)
   bool rows;  // scored by member rows (cq_rows.hpp): rec and bad in place of the staged entries
   size_t rec, bad;
@@ -318,7 +318,6 @@ ScoreLayout score_layout(int64_t n, int64_t nnz, int64_t L, bool weighted = fals
   s.labx = c.take(lt * n);
   s.CB = c.take(lt * nnz);
   s.parts = c.take(std::max(sizeof(ScorePart), sizeof(WScorePart)) * s.G);
-  s.res = c.take(sizeof(ScoreResultDev));
   if (weighted) {
     s.CW = c.take(4 * (size_t)nnz);
     s.SW = c.take(16 * (size_t)L);
@@ -392,7 +391,6 @@ ScoreLayout unstaged_layout(const cq_graph* g, int64_t L, const ScoreLayout& s) 
   r.pitems = c.take(4 * (size_t)r.max_parts);
   r.ptable = c.take(4 * (size_t)(g->n >> r.split) * rg_row_words((u32)L));
   r.parts = c.take(sizeof(ScorePart) * r.G);
-  r.res = c.take(sizeof(ScoreResultDev));
   return c.off <= s.total ? r : s;
 }
 
@@ -437,7 +435,7 @@ struct CmpLayout {
   int chunk, W, Wb, Ga, Gb;
   int Wa, rounds, Wc, nbmax;  // band path: histogram grid of A, rounds per chunk, chunks, bands at most
   u32 T;                      // band path: nodes per band aimed at
-  size_t ctl, wq, A, B, start, order, COLMAX, RA11, RMAX, RF, RXL, SZ, loc, HN, HB, CB, parts, res, total;
+  size_t ctl, wq, A, B, start, order, COLMAX, RA11, RMAX, RF, RXL, SZ, loc, HN, HB, CB, parts, total;
   size_t HA, sbk, SBA, SZB, SBS, CUR, BORD, E;
   // wide path (a label space beyond 16 bits): log2 labels per bin, bins, histogram grid,
   // nodes per thread and chunks of the partition
@@ -516,7 +514,6 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
     s.BORD = c.take(4 * (size_t)s.nbmax);
     s.E = c.take(4 * (size_t)n);
     s.parts = c.take(sizeof(CmpPart) * (s.Ga + s.Gb));
-    s.res = c.take(sizeof(CmpResultDev));
     s.total = c.off;
     return s;
   }
@@ -539,7 +536,6 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
   s.HB = s.privB ? c.take(4 * (size_t)s.Wb * Lb) : 0;
   s.CB = c.take((s.small ? 2 : 4) * n);
   s.parts = c.take(sizeof(CmpPart) * (s.Ga + s.Gb));
-  s.res = c.take(sizeof(CmpResultDev));
   s.total = c.off;
   // the wide path takes the same workspace (one that would need more stays on segments)
   CmpLayout w = s;
@@ -572,7 +568,6 @@ CmpLayout cmp_layout(int64_t n, int64_t La, int64_t Lb) {
   w.E = k.take(4 * (size_t)n);
   w.EB = w.binsB ? k.take(2 * (size_t)n) : 0;
   w.parts = k.take(sizeof(CmpPart) * (w.Ga + w.Gb));
-  w.res = k.take(sizeof(CmpResultDev));
   return k.off <= s.total ? w : s;
 }
 
@@ -658,7 +653,8 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   u32* loc = at<u32>(ws, lay.loc);
   LT* labx = at<LT>(ws, lay.labx);
   LT* CB = at<LT>(ws, lay.CB);
-  float* CW = g->w ? at<float>(ws, lay.CW) : nullptr;  // weights staged beside the labels
+  constexpr bool W = sizeof(LT) == 2;  // weighted graphs take label ids that fit 16 bits (the caller's check)
+  float* CW = W && g->w ? at<float>(ws, lay.CW) : nullptr;  // weights staged beside the labels
   ScorePart* parts = at<ScorePart>(ws, lay.parts);
   const u32* PM = nullptr;
   const bool tiled = lay.tiled;
@@ -790,14 +786,17 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
               (int)n, g->sshift, S, c0, c1, parts, g->fslice, g->fcol, labx, fl, rows == TG_RUNS_ONLY ? ctl : nullptr);
         }
         const unsigned grid = 8u * (unsigned)((T + 7) / 8);
-        if (CW)
-          k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(g->fmax), s>>>(
-              (int)n, t0, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, g->w, CW,
-              at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc, rows);
-        else
-          k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(g->fmax), s>>>(
-              (int)n, t0, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr,
-              nullptr, L, lay.chunk, PM, loc, rows);
+        if constexpr (W) {
+          if (CW) {
+            k_tile_gather<LT, true><<<grid, TG_THREADS, TileLds<LT, true>::bytes(g->fmax), s>>>(
+                (int)n, t0, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, g->w, CW,
+                at<unsigned long long>(ws, lay.IW), L, lay.chunk, PM, loc, rows);
+            return;
+          }
+        }
+        k_tile_gather<LT, false><<<grid, TG_THREADS, TileLds<LT, false>::bytes(g->fmax), s>>>(
+            (int)n, t0, T, g->fmax, g->tiles, g->rp, g->eidx, g->fadr, fl, labx, start, D, cur, ctl, CB, nullptr, nullptr,
+            nullptr, L, lay.chunk, PM, loc, rows);
       };
       if (!lay.rounds) {
         pass(0, C, 0, lay.tile_rows ? TG_BY_ROWS : TG_BY_MODE);
@@ -818,16 +817,16 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
       }
     } else {
       const unsigned grid = 8u * (unsigned)((((int64_t)n + GROWS - 1) / GROWS + 7) / 8);  // one workgroup per tile
-      if (lay.priv && CW)
-        k_gather<true, LT, true><<<grid, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, g->w, CW);
-      else if (lay.priv)
+      if (CW) {
+        if constexpr (W)
+          k_gather<true, LT, true><<<grid, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, g->w, CW);
+      } else if (lay.priv) {
         k_gather<true, LT, false><<<grid, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, nullptr,
                                                         nullptr);
-      else if (CW)
-        k_gather<false, LT, true><<<grid, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, g->w, CW);
-      else
+      } else {
         k_gather<false, LT, false><<<grid, GROWS, 0, s>>>((int)n, g->rp, g->col, labx, L, lay.chunk, PM, start, loc, CB, nullptr,
                                                          nullptr);
+      }
     }
   }
   ScoreVis vis;
@@ -848,28 +847,30 @@ void score_launch(cq_context* ctx, const cq_graph* g, const int32_t* labels, int
   if (per_comm) std::memcpy(&pc, per_comm, sizeof(pc));
   if (CW) {
     // weighted graph: direct tables only (L <= HASH_WORDS was checked by the caller)
-    WeightedOut wo;
-    wo.SW = at<u64>(ws, lay.SW);
-    wo.IW = at<u64>(ws, lay.IW);
-    wo.PENW = at<u64>(ws, lay.PENW);
-    double* invN = at<double>(ws, lay.INVN);
-    wo.invN = invN;
-    wo.twoW = 2.0 * g->total_w;
-    {
-      StageMark mk(ctx, ST_GROUPS, timed);
-      k_inv_sizes<<<grid_for(L, 256, 1024), 256, 0, s>>>(L, N, invN);
-      int nb = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_groups_w<LT>, GBLOCK, lds) != hipSuccess || nb < 1) nb = 1;
-      // tiled graphs stage compactly: lengths and own-label counts in the cursors
-      const unsigned long long* cur64 = tiled ? at<unsigned long long>(ws, lay.cursor) : nullptr;
-      k_groups_w<LT><<<(unsigned)(ctx->num_cus * nb), GBLOCK, lds, s>>>(CB, CW, start, D, order, ctl, (u32)L, vis, wo,
-                                                                        cur64, at<u32>(ws, lay.wq));
-    }
-    WScorePart* wparts = reinterpret_cast<WScorePart*>(parts);
-    {
-      StageMark mk(ctx, ST_FINAL, timed);
-      k_score_final_w<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, wo.SW, wo.IW, wo.PENW, g->total_w, pc, wparts, n, nnz, vis.ecap,
-                                               ctl, d_out, tiled ? 1u : 0u);
+    if constexpr (W) {
+      WeightedOut wo;
+      wo.SW = at<u64>(ws, lay.SW);
+      wo.IW = at<u64>(ws, lay.IW);
+      wo.PENW = at<u64>(ws, lay.PENW);
+      double* invN = at<double>(ws, lay.INVN);
+      wo.invN = invN;
+      wo.twoW = 2.0 * g->total_w;
+      {
+        StageMark mk(ctx, ST_GROUPS, timed);
+        k_inv_sizes<<<grid_for(L, 256, 1024), 256, 0, s>>>(L, N, invN);
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_groups_w<LT>, GBLOCK, lds) != hipSuccess || nb < 1) nb = 1;
+        // tiled graphs stage compactly: lengths and own-label counts in the cursors
+        const unsigned long long* cur64 = tiled ? at<unsigned long long>(ws, lay.cursor) : nullptr;
+        k_groups_w<LT><<<(unsigned)(ctx->num_cus * nb), GBLOCK, lds, s>>>(CB, CW, start, D, order, ctl, (u32)L, vis, wo,
+                                                                          cur64, at<u32>(ws, lay.wq));
+      }
+      WScorePart* wparts = reinterpret_cast<WScorePart*>(parts);
+      {
+        StageMark mk(ctx, ST_FINAL, timed);
+        k_score_final_w<<<lay.G, FBLOCK, 0, s>>>(L, N, D, I, NP, wo.SW, wo.IW, wo.PENW, g->total_w, pc, wparts, n, nnz, vis.ecap,
+                                                 ctl, d_out, tiled ? 1u : 0u);
+      }
     }
     return;
   }
@@ -2201,7 +2202,6 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_perm_apply_count), ((size_t)1 << PERM_SHIFT) * 2 + 8 * (size_t)APPLY_COUNT_MAX_L);
   set_big_lds(reinterpret_cast<const void*>(k_groups<ScoreVis, uint16_t, GBLOCK_WIDE>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups_w<uint16_t>), gl);
-  set_big_lds(reinterpret_cast<const void*>(k_groups_w<uint32_t>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<ScoreVis, uint32_t, GBLOCK_WIDE>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<CmpVis, uint16_t>), gl);
   set_big_lds(reinterpret_cast<const void*>(k_groups<CmpVis, uint32_t>), gl);
@@ -2213,7 +2213,6 @@ cq_status cq_context_create(int device, void* hip_stream, cq_context** out) {
   set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, false>), TileLds<uint16_t, false>::bytes(TG_ENT));
   set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint16_t, true>), TileLds<uint16_t, true>::bytes(TG_ENT_W));
   set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, false>), TileLds<uint32_t, false>::bytes(TG_ENT));
-  set_big_lds(reinterpret_cast<const void*>(k_tile_gather<uint32_t, true>), TileLds<uint32_t, true>::bytes(TG_ENT_W));
   set_big_lds(reinterpret_cast<const void*>(k_small_count), ss_lds(SS_MAX_N, SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_final), 4 * (size_t)ss_cells(SS_MAX_L));
   set_big_lds(reinterpret_cast<const void*>(k_small_compare), 4 * (size_t)SC_MAX_CELLS + 24 * (size_t)SC_MAX_L + 64);

@@ -34,7 +34,7 @@ constexpr int TG_STEPS = 3;          // steps per wave at most
 constexpr int TG_ENT = TG_WAVES * TG_GROUP * TG_STEPS;  // entries per tile at most: 24,576
 // A weighted graph's blocks with a tile of more far entries than this are cut into tiles of at
 // most so many entries: two workgroups with 16-bit labels and the runs' weight sums still fit a
-// CU's LDS then, and one with 32-bit labels (a launch has the LDS of its largest tile).
+// CU's LDS then (a launch has the LDS of its largest tile).
 // 10M nodes, 200M weighted entries: 601 us; with every block cut so 820, with column blocks 852.
 constexpr int TG_ENT_W = 16384;
 // Slices of 2^15 ids: 64 KB of 16-bit labels (two workgroups a CU), 128 KB of 32-bit ones.  Graphs
