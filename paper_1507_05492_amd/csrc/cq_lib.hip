@@ -1384,7 +1384,11 @@ void scan_u32(const u32* in, u32* out, long long n, u32* tiles, hipStream_t s) {
 constexpr int LP_SWEEPS = 10;
 constexpr int LP_SALTED_SWEEPS = 20;
 // Graphs kept as tiles by default: from where their labels outgrow half an L2 (below, the label
-// reads of the member rows stay in it), up to the ids the tile tables are made for.
+// reads of the member rows stay in it), up to the ids the tile tables are made for.  Up to 2^21
+// nodes member rows serve a graph as well, and which is faster depends on the call (tiles and
+// member rows, us): 1.05M nodes and 20 entries a node 133 and 114 with 1,000 label ids, 477 and 532
+// with 15,000; 2.09M nodes and 8 entries a node 216 and 181 with 5,000; 30 entries 220 and 306
+// with 1,000, 604 and 662 with 15,000.
 constexpr int64_t BLOCK_MAX_N = 16 << 20;
 constexpr int64_t BLOCK_MIN_N = 1 << 20;
 // Larger graphs are tiled as well (unless CQ_GRAPH_NO_BLOCKS), but always staged by rows.
