@@ -31,7 +31,8 @@ struct Ctl {
   u32 done, done2;  // workgroups that have finished a pass whose last workgroup goes on alone
   u32 changes;    // tiled graphs' node pass: label changes between consecutive stored ids
   u32 mode;       // tiled graphs: STAGE_BLOCKS or STAGE_ROWS, chosen from `changes`
-  u32 parts;      // member rows: parts of the communities that several workgroups share (kbig of them)
+  u32 parts;      // member rows: parts of the kbig communities that several workgroups share;
+                  // comparison by bins: slices of the large bins
   u32 pad0;
   unsigned long long pad1[2];
 };
